@@ -230,6 +230,15 @@ struct Stage {
   }
 };
 
+// f(0), f(1), ..., f(N-1) with the index as a compile-time constant
+template <int N, int I = 0, typename F>
+__device__ inline void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
 // XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs, so give
 // each XCD a contiguous run of tiles, walked in column-major groups of GROUP_M
 // tile rows (operand reuse in that XCD's L2).
@@ -269,7 +278,15 @@ __device__ inline void tile_of_block(int pid, int total, int tiles_m, int tiles_
   *tn = in / gsize;
 }
 
-template <int BM, int BN, int WM, int WN, bool A_TR, bool B_TR, bool ACCUM_F32, bool KTAIL>
+// What the epilogue does with the product, fixed at compile time: one straight run of instructions
+// per kind (with run-time switches between the strips the K = 1024 products lost 5 %).
+enum { EPI_PLAIN = 0,     // C = acc (+bias), bf16 or fp32
+       EPI_RES,           // C = acc (+bias) + residual
+       EPI_SWIGLU_FWD, EPI_SWIGLU_BWD,
+       EPI_ADD,           // fp32 C += acc
+       EPI_PARTIAL };     // acc -> this split's partial tile
+
+template <int BM, int BN, int WM, int WN, bool A_TR, bool B_TR, int EPI, bool KTAIL>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
   constexpr int NT = WM * WN * 64;
   constexpr int TM = BM / WM, TN_ = BN / WN;       // wave tile
@@ -324,7 +341,7 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
   Stage<BM, NT, A_TR, KTAIL> sa;
   Stage<BN, NT, B_TR, KTAIL> sb;
   sa.init(p.lda, p.M - m0, tid);
-  const bool swf = !B_TR && p.swf_a != nullptr;          // SwiGLU forward: N = 2F, a tile covers BN/2 columns of a
+  constexpr bool swf = EPI == EPI_SWIGLU_FWD;            // SwiGLU forward: N = 2F, a tile covers BN/2 columns of a
   if (swf) sb.init(p.ldb, BN, tid, TN_ / 2, p.N / 2, tn * (BN / 2));
   else sb.init(p.ldb, p.N - n0, tid);
   // slice base pointers (wave-uniform): first row of the tile at k = kbeg
@@ -462,11 +479,6 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
     } else {
       slice(no{}, no{}, no{}, k0, cur);
     }
-    pending_row([](int) {});
-    // the compiler does not know that the asm statements above are MFMAs and leaves no wait states
-    // between the last of them and the epilogue's reads of the accumulators
-    asm volatile("s_nop 15\n\ts_nop 15");
-    __builtin_amdgcn_sched_barrier(0);
   }
 
   {
@@ -478,93 +490,120 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
     float* stage = reinterpret_cast<float*>(smem_raw) + wave * (16 * SLD);
     constexpr int LPR = TN_ / 8;                          // lanes per output row (8 columns each)
     constexpr int RPI = 64 / LPR;                         // rows per store instruction
+    constexpr int TPS = 16 / RPI;                         // store instructions per strip
     static_assert(16 % RPI == 0, "a 16-row strip must be a whole number of store instructions");
     const int m_in = lane & 15, q4 = (lane >> 4) * 4;
     const int rcol = (lane % LPR) * 8, rrow = lane / LPR;
     const int gn = n0 + wn * TN_ + rcol;
+    // What the epilogue combines with the product -- the old C of a weight gradient, the residual,
+    // the saved g and u of the SwiGLU backward -- is requested two strips ahead, the first two
+    // strips before the held-back MFMAs: fetched in front of each store instead, a tile pays one
+    // memory latency per store instruction, 32 of them in a row (dW 22016x4096 over 777 rows 296 ->
+    // 247 us, over 8192 rows 1301 -> 1271 us; the 128-expert weight gradients of 8192 tokens 1610 ->
+    // 1220 us).  Addresses are clamped into the matrix, so that the requests carry no condition.
+    u32x4 pre[2][TPS][2];
+    auto request = [&](auto i_t) {
+      constexpr int i = decltype(i_t)::value;
+      if (i >= FM) return;
+#pragma unroll
+      for (int t = 0; t < TPS; ++t) {
+        const int gm = min(m0 + wm * TM + i * 16 + t * RPI + rrow, p.M - 1), gc = min(gn, p.N - 8);
+        if (EPI == EPI_ADD) {
+          const float* c = (const float*)p.C + c_off + (size_t)gm * p.ldc + gc;
+          pre[i & 1][t][0] = *reinterpret_cast<const u32x4*>(c);
+          pre[i & 1][t][1] = *reinterpret_cast<const u32x4*>(c + 4);
+        } else if (EPI == EPI_SWIGLU_BWD) {
+          const bf16_t* up = p.sw_up + (size_t)gm * (2 * p.N) + gc;
+          pre[i & 1][t][0] = *reinterpret_cast<const u32x4*>(up);
+          pre[i & 1][t][1] = *reinterpret_cast<const u32x4*>(up + p.N);
+        } else if (EPI == EPI_RES) {
+          pre[i & 1][t][0] = *reinterpret_cast<const u32x4*>(p.residual + (size_t)gm * p.ldc + gc);
+        }
+      }
+    };
+    request(std::integral_constant<int, 0>{});
+    request(std::integral_constant<int, 1>{});
+    pending_row([](int) {});
+    // the compiler does not know that the asm statements above are MFMAs and leaves no wait states
+    // between the last of them and the epilogue's reads of the accumulators
+    asm volatile("s_nop 15\n\ts_nop 15");
+    __builtin_amdgcn_sched_barrier(0);
+
     float bias[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) bias[e] = 0.f;
-    if (p.bias && gn < p.N) load16(p.bias + gn, bias);
+    if ((EPI == EPI_PLAIN || EPI == EPI_RES) && p.bias && gn < p.N) load16(p.bias + gn, bias);
+    // `full`: the tile lies inside C, so no store carries a condition (a conditional store makes the
+    // wait for the next strip's operands wait for the stores as well)
+    auto finish = [&](auto full_t) {
+      constexpr bool FULL = decltype(full_t)::value;
+      static_for<FM>([&](auto i_t) {
+        constexpr int i = decltype(i_t)::value;
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
-      // SwiGLU backward epilogue: the saved g and u of this strip are requested before the
-      // strip is transposed, so their latency is paid once per strip and not once per store
-      Vec16<bf16_t> sw_g[16 / RPI], sw_u[16 / RPI];
-      if (p.sw_up) {
+        for (int j = 0; j < FN; ++j)
+          *reinterpret_cast<f32x4*>(stage + m_in * SLD + j * 16 + q4) = acc[i][j];
+        if (EPI == EPI_SWIGLU_FWD) {
+          // SwiGLU forward: the strip holds g in its first TN_/2 columns and u in the others, of the
+          // same TN_/2 columns of a; a lane takes 8 of them
+          constexpr int HW = TN_ / 2, LPR2 = HW / 8, RPI2 = 64 / LPR2;
+          const int F = p.N / 2;
+          const int rcol2 = (lane % LPR2) * 8, rrow2 = lane / LPR2;
+          const int acol = tn * (BN / 2) + wn * HW + rcol2;
 #pragma unroll
-        for (int t = 0; t < 16 / RPI; ++t) {
-          const int gm = min(m0 + wm * TM + i * 16 + t * RPI + rrow, p.M - 1);
-          const bf16_t* up = p.sw_up + (size_t)gm * (2 * p.N) + min(gn, p.N - 8);
-          sw_g[t] = *reinterpret_cast<const Vec16<bf16_t>*>(up);
-          sw_u[t] = *reinterpret_cast<const Vec16<bf16_t>*>(up + p.N);
-        }
-      }
+          for (int t = 0; t < (16 + RPI2 - 1) / RPI2; ++t) {
+            const int row = t * RPI2 + rrow2;
+            const int gm = m0 + wm * TM + i * 16 + row;
+            if (row < 16 && gm < p.M) {
+              const f32x4 g0 = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol2);
+              const f32x4 g1 = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol2 + 4);
+              const f32x4 u0 = *reinterpret_cast<const f32x4*>(stage + row * SLD + HW + rcol2);
+              const f32x4 u1 = *reinterpret_cast<const f32x4*>(stage + row * SLD + HW + rcol2 + 4);
+              union { u32x4 v; bf16_t h[8]; } pg, pu, pa;
 #pragma unroll
-      for (int j = 0; j < FN; ++j)
-        *reinterpret_cast<f32x4*>(stage + m_in * SLD + j * 16 + q4) = acc[i][j];
-      if (!A_TR && !B_TR && !ACCUM_F32 && p.swf_a) {
-        // SwiGLU forward: the strip holds g in its first TN_/2 columns and u in the others, of the
-        // same TN_/2 columns of a; a lane takes 8 of them
-        constexpr int HW = TN_ / 2, LPR2 = HW / 8, RPI2 = 64 / LPR2;
-        const int F = p.N / 2;
-        const int rcol2 = (lane % LPR2) * 8, rrow2 = lane / LPR2;
-        const int acol = tn * (BN / 2) + wn * HW + rcol2;
-#pragma unroll
-        for (int t = 0; t < (16 + RPI2 - 1) / RPI2; ++t) {
-          const int row = t * RPI2 + rrow2;
-          const int gm = m0 + wm * TM + i * 16 + row;
-          if (row < 16 && gm < p.M) {
-            const f32x4 g0 = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol2);
-            const f32x4 g1 = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol2 + 4);
-            const f32x4 u0 = *reinterpret_cast<const f32x4*>(stage + row * SLD + HW + rcol2);
-            const f32x4 u1 = *reinterpret_cast<const f32x4*>(stage + row * SLD + HW + rcol2 + 4);
-            union { u32x4 v; bf16_t h[8]; } pg, pu, pa;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              pg.h[e] = Elt<bf16_t>::from_f(e < 4 ? g0[e] : g1[e - 4]);
-              pu.h[e] = Elt<bf16_t>::from_f(e < 4 ? u0[e] : u1[e - 4]);
-              const float g = (float)pg.h[e], u = (float)pu.h[e];
-              const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
-              pa.h[e] = Elt<bf16_t>::from_f(g * sig * u);
+              for (int e = 0; e < 8; ++e) {
+                pg.h[e] = Elt<bf16_t>::from_f(e < 4 ? g0[e] : g1[e - 4]);
+                pu.h[e] = Elt<bf16_t>::from_f(e < 4 ? u0[e] : u1[e - 4]);
+                const float g = (float)pg.h[e], u = (float)pu.h[e];
+                const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
+                pa.h[e] = Elt<bf16_t>::from_f(g * sig * u);
+              }
+              bf16_t* c = (bf16_t*)p.C + (size_t)gm * p.ldc + acol;
+              __builtin_nontemporal_store(pg.v, reinterpret_cast<u32x4*>(c));
+              __builtin_nontemporal_store(pu.v, reinterpret_cast<u32x4*>(c + F));
+              *reinterpret_cast<u32x4*>(p.swf_a + (size_t)gm * F + acol) = pa.v;
             }
-            bf16_t* c = (bf16_t*)p.C + (size_t)gm * p.ldc + acol;
-            __builtin_nontemporal_store(pg.v, reinterpret_cast<u32x4*>(c));
-            __builtin_nontemporal_store(pu.v, reinterpret_cast<u32x4*>(c + F));
-            *reinterpret_cast<u32x4*>(p.swf_a + (size_t)gm * F + acol) = pa.v;
           }
+          return;
         }
-        continue;
-      }
 #pragma unroll
-      for (int t = 0; t < 16 / RPI; ++t) {
-        const int row = t * RPI + rrow;
-        const int gm = m0 + wm * TM + i * 16 + row;
-        const f32x4 lo = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol);
-        const f32x4 hi = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol + 4);
-        if (gm < p.M && gn < p.N) {
+        for (int t = 0; t < TPS; ++t) {
+          const int row = t * RPI + rrow;
+          const int gm = m0 + wm * TM + i * 16 + row;
+          const f32x4 lo = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol);
+          const f32x4 hi = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol + 4);
+          if (!FULL && !(gm < p.M && gn < p.N)) continue;
           float out[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
           const size_t idx = (size_t)gm * p.ldc + gn;
-          if (ACCUM_F32) {
-            // weight gradient: fp32, added to C (or parked as this split's partial tile)
-            float* c = p.splits > 1 ? p.partial + ((size_t)split * p.M + gm) * p.N + gn
-                                    : (float*)p.C + c_off + idx;
-            f32x4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = {0.f, 0.f, 0.f, 0.f};
-            if (p.splits == 1) {
-              c0 = *reinterpret_cast<const f32x4*>(c);
-              c1 = *reinterpret_cast<const f32x4*>(c + 4);
+          if (EPI == EPI_ADD || EPI == EPI_PARTIAL) {
+            // weight gradient: fp32, added to C or parked as this split's partial tile
+            float* c = EPI == EPI_ADD ? (float*)p.C + c_off + idx : p.partial + ((size_t)split * p.M + gm) * p.N + gn;
+            if (EPI == EPI_ADD) {
+              union { u32x4 u; f32x4 f; } c0{pre[i & 1][t][0]}, c1{pre[i & 1][t][1]};
+#pragma unroll
+              for (int e = 0; e < 4; ++e) { out[e] += c0.f[e]; out[4 + e] += c1.f[e]; }
             }
-            *reinterpret_cast<f32x4*>(c) = f32x4{c0[0] + out[0], c0[1] + out[1], c0[2] + out[2], c0[3] + out[3]};
-            *reinterpret_cast<f32x4*>(c + 4) = f32x4{c1[0] + out[4], c1[1] + out[5], c1[2] + out[6], c1[3] + out[7]};
+            *reinterpret_cast<f32x4*>(c) = f32x4{out[0], out[1], out[2], out[3]};
+            *reinterpret_cast<f32x4*>(c + 4) = f32x4{out[4], out[5], out[6], out[7]};
             continue;
           }
-          if (p.sw_up) {
+          if (EPI == EPI_SWIGLU_BWD) {
             // out = dA of 8 columns of one row: d_up and the activation instead of C
             const size_t up_idx = (size_t)gm * (2 * p.N) + gn;
+            union { u32x4 u; bf16_t h[8]; } sg{pre[i & 1][t][0]}, su{pre[i & 1][t][1]};
             float dg[8], du[8], av[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-              const float g = (float)sw_g[t].v[e], u = (float)sw_u[t].v[e];
+              const float g = (float)sg.h[e], u = (float)su.h[e];
               const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
               const float sl = g * sig;                          // silu(g)
               av[e] = sl * u;
@@ -578,27 +617,28 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
           }
 #pragma unroll
           for (int e = 0; e < 8; ++e) out[e] += bias[e];
-          if (p.residual) {
-            float res[8];
-            load16(p.residual + idx, res);
+          if (EPI == EPI_RES) {
+            union { u32x4 u; bf16_t h[8]; } r{pre[i & 1][t][0]};
 #pragma unroll
-            for (int e = 0; e < 8; ++e) out[e] += res[e];
+            for (int e = 0; e < 8; ++e) out[e] += (float)r.h[e];
           }
           if (p.out_fp32) {
             float* c = (float*)p.C + idx;
             *reinterpret_cast<f32x4*>(c) = f32x4{out[0], out[1], out[2], out[3]};
             *reinterpret_cast<f32x4*>(c + 4) = f32x4{out[4], out[5], out[6], out[7]};
           } else {
-            {
-              union { u32x4 u; bf16_t h[8]; } pk;
+            union { u32x4 u; bf16_t h[8]; } pk;
 #pragma unroll
-              for (int e = 0; e < 8; ++e) pk.h[e] = Elt<bf16_t>::from_f(out[e]);
-              __builtin_nontemporal_store(pk.u, reinterpret_cast<u32x4*>((bf16_t*)p.C + idx));
-            }
+            for (int e = 0; e < 8; ++e) pk.h[e] = Elt<bf16_t>::from_f(out[e]);
+            __builtin_nontemporal_store(pk.u, reinterpret_cast<u32x4*>((bf16_t*)p.C + idx));
           }
         }
-      }
-    }
+        request(std::integral_constant<int, i + 2>{});
+      });
+    };
+    constexpr bool FETCHES = EPI == EPI_ADD || EPI == EPI_RES || EPI == EPI_SWIGLU_BWD;
+    if (FETCHES && m0 + BM <= p.M && n0 + BN <= p.N) finish(yes{});
+    else finish(no{});
   }
 }
 
@@ -660,12 +700,12 @@ Plan make_plan(int layout, int M, int N, int K) {
   return best;
 }
 
-template <int BM, int BN, int WM, int WN, bool A_TR, bool B_TR, bool ACC, bool KTAIL>
+template <int BM, int BN, int WM, int WN, bool A_TR, bool B_TR, int EPI, bool KTAIL>
 bm_status launch_k(const GemmParams& p, hipStream_t st) {
   constexpr size_t lds_pipe = (size_t)2 * (BM + BN) * BK * sizeof(bf16_t);
   constexpr size_t lds_epi = (size_t)WM * WN * 16 * (BN / WN + 4) * sizeof(float);
   constexpr size_t lds = lds_pipe > lds_epi ? lds_pipe : lds_epi;
-  auto kern = gemm_mfma_kernel<BM, BN, WM, WN, A_TR, B_TR, ACC, KTAIL>;
+  auto kern = gemm_mfma_kernel<BM, BN, WM, WN, A_TR, B_TR, EPI, KTAIL>;
   static bool attr_done = false;
   if (!attr_done) {
     BM_CHECK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
@@ -680,10 +720,25 @@ bm_status launch_k(const GemmParams& p, hipStream_t st) {
 }
 
 // the zero-filling variant only when a k range is not a whole number of slices
-template <int BM, int BN, int WM, int WN, bool A_TR, bool B_TR, bool ACC>
+template <int BM, int BN, bool A_TR, bool B_TR, int EPI>
 bm_status launch(const GemmParams& p, hipStream_t st) {
-  if (p.K % BK) return launch_k<BM, BN, WM, WN, A_TR, B_TR, ACC, true>(p, st);
-  return launch_k<BM, BN, WM, WN, A_TR, B_TR, ACC, false>(p, st);
+  if (p.K % BK) return launch_k<BM, BN, 2, 2, A_TR, B_TR, EPI, true>(p, st);
+  return launch_k<BM, BN, 2, 2, A_TR, B_TR, EPI, false>(p, st);
+}
+
+// the epilogue kinds of the weight gradient, and of the other two layouts
+template <int BM, int BN>
+bm_status launch_tn(const GemmParams& p, hipStream_t st) {
+  return p.splits > 1 ? launch<BM, BN, true, true, EPI_PARTIAL>(p, st) : launch<BM, BN, true, true, EPI_ADD>(p, st);
+}
+template <int BM, int BN>
+bm_status launch_rows(int layout, const GemmParams& p, hipStream_t st) {
+  if (layout == GEMM_NT) {
+    if (p.swf_a) return launch<BM, BN, false, false, EPI_SWIGLU_FWD>(p, st);
+    return p.residual ? launch<BM, BN, false, false, EPI_RES>(p, st) : launch<BM, BN, false, false, EPI_PLAIN>(p, st);
+  }
+  if (p.sw_up) return launch<BM, BN, false, true, EPI_SWIGLU_BWD>(p, st);
+  return p.residual ? launch<BM, BN, false, true, EPI_RES>(p, st) : launch<BM, BN, false, true, EPI_PLAIN>(p, st);
 }
 
 }  // namespace
@@ -739,15 +794,9 @@ bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, con
               (size_t)pl.splits * M * N * sizeof(float), scratch_bytes);
     return BM_ERR_WORKSPACE_TOO_SMALL;
   }
-  bm_status rc;
   const bool big = pl.bm == 256;
-  if (layout == GEMM_NT)
-    rc = big ? launch<256, 256, 2, 2, false, false, false>(p, st) : launch<128, 128, 2, 2, false, false, false>(p, st);
-  else if (layout == GEMM_NN)
-    rc = big ? launch<256, 256, 2, 2, false, true, false>(p, st) : launch<128, 128, 2, 2, false, true, false>(p, st);
-  else
-    rc = big ? launch<256, 256, 2, 2, true, true, true>(p, st) : launch<128, 128, 2, 2, true, true, true>(p, st);
-  BM_RETURN_IF(rc);
+  if (layout == GEMM_TN) BM_RETURN_IF(big ? (launch_tn<256, 256>(p, st)) : (launch_tn<128, 128>(p, st)));
+  else BM_RETURN_IF(big ? (launch_rows<256, 256>(layout, p, st)) : (launch_rows<128, 128>(layout, p, st)));
   if (layout == GEMM_TN && pl.splits > 1) {
     long n4 = ((long)M * N) / 4;
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3(cdiv(n4, 256)), dim3(256), 0, st,
@@ -833,7 +882,8 @@ bool gemm_mfma_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const vo
   p.second.M = M1; p.second.N = N1; p.second.lda = lda1; p.second.ldb = ldb1; p.second.ldc = ldc1;
   p.second.tiles_m = b.tiles_m; p.second.tiles_n = b.tiles_n; p.second.splits = b.splits;
   p.second.k_per_split = b.k_per_split; p.second.xcd_split = xb ? 1 : 0;
-  *rc = launch_k<256, 256, 2, 2, true, true, true, false>(p, st);
+  *rc = sp > 1 ? (launch_k<256, 256, 2, 2, true, true, EPI_PARTIAL, false>(p, st))
+               : (launch_k<256, 256, 2, 2, true, true, EPI_ADD, false>(p, st));
   if (*rc != BM_OK) return true;
   if (a.splits > 1)
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3(cdiv((long)M0 * N0 / 4, 256)), dim3(256), 0, st, p.partial, a.splits,
@@ -888,18 +938,16 @@ bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int 
   // wide enough: per flop a 128x256 tile writes and reads a quarter less LDS than two 128x128 ones
   if (layout != GEMM_TN && N >= 256) {
     p.tiles_n = cdiv(N, 256);
-    if (layout == GEMM_NT) return launch<128, 256, 2, 2, false, false, false>(p, st);
-    return launch<128, 256, 2, 2, false, true, false>(p, st);
+    return launch_rows<128, 256>(layout, p, st);
   }
-  if (layout == GEMM_NT) return launch<128, 128, 2, 2, false, false, false>(p, st);
-  if (layout == GEMM_NN) return launch<128, 128, 2, 2, false, true, false>(p, st);
+  if (layout != GEMM_TN) return launch_rows<128, 128>(layout, p, st);
   // weight gradient: rows are the contraction index, so the output tile is free; a group's
   // k range is short (a few slices), which makes the per-tile fixed cost count: large tiles
   if (M >= 256 && N >= 256) {
     p.tiles_m = cdiv(M, 256); p.tiles_n = cdiv(N, 256);
-    return launch_k<256, 256, 2, 2, true, true, true, false>(p, st);   // k ranges are whole slices
+    return launch_k<256, 256, 2, 2, true, true, EPI_ADD, false>(p, st);   // k ranges are whole slices
   }
-  return launch_k<128, 128, 2, 2, true, true, true, false>(p, st);
+  return launch_k<128, 128, 2, 2, true, true, EPI_ADD, false>(p, st);
 }
 
 }  // namespace bm
