@@ -53,6 +53,11 @@ size_t gemm_scratch_bytes(int layout, int M, int N, int K, int dtype) {
   return g > m ? g : m;
 }
 
+size_t gemm_scratch_need(int layout, int M, int N, int K, int dtype) {
+  if (layout == GEMM_TN) return gemm_scratch_bytes(layout, M, N, K, dtype);
+  return gemm_generic_scratch_bytes(M, N, K);
+}
+
 bm_status gemm(int layout, int dtype, int M, int N, int K, const void* A, int lda, const void* B,
                int ldb, void* C, int ldc, const GemmEpilogue& epi, void* scratch,
                size_t scratch_bytes, hipStream_t st) {
@@ -158,7 +163,7 @@ extern "C" bm_status bm_gemm(int32_t layout, int32_t dtype, int32_t M, int32_t N
   BM_ARG_CHECK(layout != GEMM_TN || !bias, "bm_gemm: bias is not defined for layout TN");
   const int a_cols = layout == GEMM_TN ? M : K, b_cols = layout == GEMM_NT ? K : N;
   BM_ARG_CHECK(lda >= a_cols && ldb >= b_cols && ldc >= N, "bm_gemm: leading dimension too small");
-  size_t need = gemm_scratch_bytes(layout, M, N, K, dtype);
+  size_t need = gemm_scratch_need(layout, M, N, K, dtype);
   if (need > scratch_bytes || (need && !scratch)) {
     set_error("bm_gemm needs %zu scratch bytes, got %zu", need, scratch_bytes);
     return BM_ERR_WORKSPACE_TOO_SMALL;

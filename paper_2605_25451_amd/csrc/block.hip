@@ -9,6 +9,8 @@
 // the two ungated branch outputs (their products with dy give the gate grads).
 #include "common.h"
 
+#include <algorithm>
+
 namespace bm {
 
 namespace {
@@ -82,10 +84,11 @@ struct FwdScratch {
   char *h, *a, *sc;
   float* logits;          // experts: [T, E]
   char *xp, *moe_ws;      // experts: [cap, d] routed inputs; layout scratch
-  size_t bytes;
+  char* gemm_ws;          // partial products of k ranges (few rows)
+  size_t gemm_ws_bytes, bytes;
 };
 
-FwdScratch layout_fwd(const Dims& m, void* base) {
+FwdScratch layout_fwd(const Dims& m, int dtype, void* base) {
   Arena a(base);
   FwdScratch s;
   const size_t T = m.T;
@@ -99,6 +102,8 @@ FwdScratch layout_fwd(const Dims& m, void* base) {
     s.xp = a.take<char>((size_t)m.cap * m.d * m.es);
     s.moe_ws = a.take<char>(moe_layout_scratch_bytes(m.T, m.E));
   }
+  s.gemm_ws_bytes = gemm_rows_scratch_bytes(m.T, m.d, dtype);
+  s.gemm_ws = a.take<char>(s.gemm_ws_bytes);
   s.bytes = a.off;
   return s;
 }
@@ -152,7 +157,7 @@ BwdScratch layout_bwd(const Dims& m, int dtype, void* base) {
   int widest = m.UP > m.QKV ? m.UP : m.QKV;
   if (6 * m.d > widest && m.ada) widest = 6 * m.d;
   s.colsum_ws = a.take<char>(colsum_scratch_bytes(m.T, widest));
-  s.gemm_ws_bytes = max_gemm_tn_scratch(m, dtype);
+  s.gemm_ws_bytes = std::max(max_gemm_tn_scratch(m, dtype), gemm_rows_scratch_bytes(m.T, m.d, dtype));
   s.gemm_ws = a.take<char>(s.gemm_ws_bytes);
   s.dyp = nullptr; s.xp = nullptr; s.dlogits = nullptr; s.dh2e = nullptr;
   if (m.E > 0) {
@@ -299,7 +304,7 @@ extern "C" bm_status bm_block_sizes(const bm_block_desc* desc, int32_t T, int32_
   BM_RETURN_IF(check_extent(*desc, T, S));
   Dims m = make_dims(*desc, T, S);
   *saved_bytes = layout_saved(m, nullptr).bytes;
-  size_t f = layout_fwd(m, nullptr).bytes, b = layout_bwd(m, desc->dtype, nullptr).bytes;
+  size_t f = layout_fwd(m, desc->dtype, nullptr).bytes, b = layout_bwd(m, desc->dtype, nullptr).bytes;
   *scratch_bytes = f > b ? f : b;
   return BM_OK;
 }
@@ -332,7 +337,7 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
   BM_ARG_CHECK(x != y, "y must not alias x");
   Dims m = make_dims(c, T, S);
   if (m.ada) NEED_PTR(cond);
-  FwdScratch ws = layout_fwd(m, scratch);
+  FwdScratch ws = layout_fwd(m, c.dtype, scratch);
   if (ws.bytes > scratch_bytes) {
     set_error("forward needs %zu scratch bytes, got %zu", ws.bytes, scratch_bytes);
     return BM_ERR_WORKSPACE_TOO_SMALL;
@@ -347,14 +352,14 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
     BM_RETURN_IF(silu_forward(dt, cond, ws.sc, (long)S * m.d, st));
     GemmEpilogue e; e.bias = w->b_ada; e.out_fp32 = 1;
     BM_RETURN_IF(gemm(GEMM_NT, dt, S, 6 * m.d, m.d, ws.sc, m.d, w->w_ada, m.d, sv.mod, 6 * m.d, e,
-                      nullptr, 0, st));
+                      ws.gemm_ws, ws.gemm_ws_bytes, st));
   }
   // attention half
   { ProfScope _p(PROF_NORM, 2.0 * T * m.d * (double)m.es, st); BM_RETURN_IF(norm_forward(norm_args(c, m, 1, w, sv.mod, ws.tok_seq), x, ws.h, sv.stats1, 1, st)); }
   {
     GemmEpilogue e; e.bias = c.linear_bias ? w->b_qkv : nullptr;
     BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.QKV, m.d, ws.h, m.d, w->w_qkv, m.d, sv.qkv, m.QKV, e,
-                      nullptr, 0, st));
+                      ws.gemm_ws, ws.gemm_ws_bytes, st));
   }
   if (c.rope)
     { ProfScope _p(PROF_ELEMENTWISE, 2.0 * T * (m.Hq + m.Hkv) * m.dh * (double)m.es, st); BM_RETURN_IF(rope_inplace(dt, sv.qkv, m.QKV, T, m.Hq + m.Hkv, m.dh, c.rope_base, cu_dev,
@@ -369,12 +374,12 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
     GemmEpilogue e; e.bias = c.linear_bias ? w->b_o : nullptr;
     if (m.ada) {
       BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.d, m.QD, sv.o, m.QD, w->w_o, m.QD, sv.attn, m.d, e,
-                        nullptr, 0, st));
+                        ws.gemm_ws, ws.gemm_ws_bytes, st));
       { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(gate_mul(dt, sv.attn, sv.mod + 2 * m.d, 6 * m.d, ws.tok_seq, x, sv.x1, T, m.d, st)); }
     } else {
       e.residual = x;
       BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.d, m.QD, sv.o, m.QD, w->w_o, m.QD, sv.x1, m.d, e,
-                        nullptr, 0, st));
+                        ws.gemm_ws, ws.gemm_ws_bytes, st));
     }
   }
   // MLP half
@@ -385,7 +390,7 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
     {
       GemmEpilogue e; e.out_fp32 = 1;
       BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.E, m.d, ws.h, m.d, w->w_router, m.d, ws.logits, m.E, e,
-                        nullptr, 0, st));
+                        ws.gemm_ws, ws.gemm_ws_bytes, st));
     }
     GemmGroups g;
     g.tile_group = sv.moe.tile_group; g.routed_rows = (long)T * m.k;
@@ -416,10 +421,10 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
         gemm_mfma_supported(GEMM_NT, dt, T, m.UP, m.d, m.d, m.d, m.UP, e)) {
       // the activation rides in the epilogue of the up projection: the pre-activations are not read again
       e.swiglu_fwd_a = ws.a;
-      BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.UP, m.d, ws.h, m.d, w->w_up, m.d, sv.up, m.UP, e, nullptr, 0, st));
+      BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.UP, m.d, ws.h, m.d, w->w_up, m.d, sv.up, m.UP, e, ws.gemm_ws, ws.gemm_ws_bytes, st));
     } else {
       BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.UP, m.d, ws.h, m.d, w->w_up, m.d, sv.up, m.UP, e,
-                        nullptr, 0, st));
+                        ws.gemm_ws, ws.gemm_ws_bytes, st));
       { ProfScope _p(PROF_ELEMENTWISE, (double)T * (m.UP + m.F) * (double)m.es, st); BM_RETURN_IF(act_forward(dt, c.act, sv.up, ws.a, T, m.F, st)); }
     }
   }
@@ -427,12 +432,12 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
     GemmEpilogue e; e.bias = c.linear_bias ? w->b_down : nullptr;
     if (m.ada) {
       BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.d, m.F, ws.a, m.F, w->w_down, m.F, sv.m, m.d, e,
-                        nullptr, 0, st));
+                        ws.gemm_ws, ws.gemm_ws_bytes, st));
       { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(gate_mul(dt, sv.m, sv.mod + 5 * m.d, 6 * m.d, ws.tok_seq, sv.x1, y, T, m.d, st)); }
     } else {
       e.residual = sv.x1;
       BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.d, m.F, ws.a, m.F, w->w_down, m.F, y, m.d, e,
-                        nullptr, 0, st));
+                        ws.gemm_ws, ws.gemm_ws_bytes, st));
     }
   }
   return BM_OK;
@@ -527,9 +532,9 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
       gemm_mfma_supported(GEMM_NN, dt, T, m.F, d, d, m.F, m.F, down_in)) {
     // SwiGLU backward rides in the epilogue of this GEMM: dA never goes to memory
     down_in.swiglu_up = sv.up; down_in.swiglu_dup = ws.dup; down_in.swiglu_a = ws.a;
-    BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.F, d, dm, d, w->w_down, m.F, ws.da, m.F, down_in, nullptr, 0, st));
+    BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.F, d, dm, d, w->w_down, m.F, ws.da, m.F, down_in, ws.gemm_ws, ws.gemm_ws_bytes, st));
   } else {
-    BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.F, d, dm, d, w->w_down, m.F, ws.da, m.F, none, nullptr, 0, st));
+    BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.F, d, dm, d, w->w_down, m.F, ws.da, m.F, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, (double)T * (2.0 * m.UP + 2.0 * m.F) * (double)m.es, st);
       BM_RETURN_IF(act_backward(dt, c.act, sv.up, ws.da, ws.dup, ws.a,
                                 c.linear_bias ? (float*)grads->b_up : nullptr, ws.colsum_ws, T, m.F, st)); }
@@ -543,7 +548,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
 
   // ---- up = h2 W_up^T + b_up,  h2 = N2(x1)
   NormArgs n2 = norm_args(c, m, 2, w, sv.mod, ws.tok_seq);
-  BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.UP, ws.dup, m.UP, w->w_up, d, ws.dh, d, none, nullptr, 0, st));
+  BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.UP, ws.dup, m.UP, w->w_up, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
   { ProfScope _p(PROF_NORM, 5.0 * T * m.d * (double)m.es, st);
     BM_RETURN_IF(norm_backward(n2, sv.x1, sv.stats2, ws.dh, dy, ws.dx1, ws.h, (float*)grads->norm2_g,
                                (float*)grads->norm2_b, fused_sums ? (float*)grads->b_down : nullptr,
@@ -566,7 +571,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   // the QKV projection at the end; dattn and the saved o stay untouched until then)
   if (c.linear_bias && !fused_sums)
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, dattn, d, T, d, (float*)grads->b_o, ws.colsum_ws, st)); }
-  BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.QD, d, dattn, d, w->w_o, m.QD, ws.d_o, m.QD, none, nullptr, 0, st));
+  BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.QD, d, dattn, d, w->w_o, m.QD, ws.d_o, m.QD, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
 
   // ---- attention
   AttnArgs at;
@@ -587,7 +592,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   NormArgs n1 = norm_args(c, m, 1, w, sv.mod, ws.tok_seq);
   if (c.linear_bias)
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, ws.dqkv, m.QKV, T, m.QKV, (float*)grads->b_qkv, ws.colsum_ws, st)); }
-  BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.QKV, ws.dqkv, m.QKV, w->w_qkv, d, ws.dh, d, none, nullptr, 0, st));
+  BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.QKV, ws.dqkv, m.QKV, w->w_qkv, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
   { ProfScope _p(PROF_NORM, 5.0 * T * m.d * (double)m.es, st);
     BM_RETURN_IF(norm_backward(n1, x, sv.stats1, ws.dh, ws.dx1, dx, ws.h, (float*)grads->norm1_g,
                                (float*)grads->norm1_b, nullptr, nullptr, ws.dmod, cu_dev, S,

@@ -140,7 +140,19 @@ struct GemmEpilogue {
   void* swiglu_fwd_a = nullptr;     // [M, N/2]
 };
 
+// gemm_scratch_bytes: what a product can make use of; NT and NN also run in less, TN and the generic
+// back end need gemm_scratch_need().  TN: grows with K only.
 size_t gemm_scratch_bytes(int layout, int M, int N, int K, int dtype);
+size_t gemm_scratch_need(int layout, int M, int N, int K, int dtype);
+// workspace of the NT / NN products of up to `rows` rows and N columns: their k ranges are split only
+// while splits x rows stays below SPLIT_ROWS_MAX (few rows leave the chip idle otherwise).  Grows with
+// `rows`, so that a buffer sized for the longest pack serves every shorter one.
+constexpr int SPLIT_ROWS_MAX = 4096;
+inline size_t gemm_rows_scratch_bytes(int rows, int N, int dtype) {
+  if (dtype != BM_DTYPE_BF16) return 0;
+  const long r = (long)rows * 16 < SPLIT_ROWS_MAX ? (long)rows * 16 : SPLIT_ROWS_MAX;
+  return (size_t)r * N * sizeof(float);
+}
 bm_status gemm(int layout, int dtype, int M, int N, int K, const void* A, int lda, const void* B,
                int ldb, void* C, int ldc, const GemmEpilogue& epi, void* scratch,
                size_t scratch_bytes, hipStream_t st);

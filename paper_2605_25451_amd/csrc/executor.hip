@@ -212,7 +212,7 @@ bm_status enc_fwd(bm_executor* ex, int u, hipStream_t st) {
   // encoder -> LLM projector
   GemmEpilogue none;
   return gemm(GEMM_NT, ex->cfg.enc.dtype, un.T, ex->cfg.llm.hidden, ex->cfg.enc.hidden, in, ex->cfg.enc.hidden,
-              ex->proj_in, ex->cfg.enc.hidden, s.feat, ex->cfg.llm.hidden, none, nullptr, 0, st);
+              ex->proj_in, ex->cfg.enc.hidden, s.feat, ex->cfg.llm.hidden, none, ex->scratch, ex->sz.scratch, st);
 }
 
 int rows_before(const bm_executor* ex, int m) {      // offset of microbatch m inside its unit's rows
@@ -267,7 +267,7 @@ bm_status gen_fwd(bm_executor* ex, int u, float* loss, hipStream_t st) {
     img += ex->mbs[m].n_images;
   }
   GemmEpilogue none;
-  BM_RETURN_IF(gemm(GEMM_NT, dt, un.S, dg, dl, g.hsel, dl, ex->proj_out, dl, g.cond, dg, none, nullptr, 0, st));
+  BM_RETURN_IF(gemm(GEMM_NT, dt, un.S, dg, dl, g.hsel, dl, ex->proj_out, dl, g.cond, dg, none, ex->scratch, ex->sz.scratch, st));
   const void* in = un.latents;
   for (int b = 0; b < ex->cfg.n_gen_blocks; ++b) {
     BM_RETURN_IF(bm_block_forward(&ex->cfg.gen, &ex->gen_w[b], in, un.gen_cu_dev, un.gen_cu_host, un.S, Tg, tpi,
@@ -297,7 +297,7 @@ bm_status gen_bwd(bm_executor* ex, int u, hipStream_t st) {
   GemmEpilogue none;
   // cond = hsel proj_out^T
   BM_RETURN_IF(gemm(GEMM_TN, dt, dg, dl, un.S, dcond, dg, g.hsel, dl, ex->g_proj_out, dl, none, ex->scratch, ex->sz.scratch, st));
-  BM_RETURN_IF(gemm(GEMM_NN, dt, un.S, dl, dg, dcond, dg, ex->proj_out, dl, g.dhsel, dl, none, nullptr, 0, st));
+  BM_RETURN_IF(gemm(GEMM_NN, dt, un.S, dl, dg, dcond, dg, ex->proj_out, dl, g.dhsel, dl, none, ex->scratch, ex->sz.scratch, st));
   int img = 0;
   for (int m = ex->unit_first(u); m <= ex->unit_last(u); ++m) {
     LlmSlot& ls = ex->llm_slots[ex->llm_slot_of[m]];
@@ -347,7 +347,7 @@ bm_status enc_bwd(bm_executor* ex, int u, hipStream_t st) {
   // feat = enc_out proj_in^T
   BM_RETURN_IF(gemm(GEMM_TN, dt, dl, de, un.T, s.dfeat, dl, s.act[n - 1], de, ex->g_proj_in, de, none, ex->scratch, ex->sz.scratch, st));
   char* dy = ex->ping[n & 1];
-  BM_RETURN_IF(gemm(GEMM_NN, dt, un.T, de, dl, s.dfeat, dl, ex->proj_in, de, dy, de, none, nullptr, 0, st));
+  BM_RETURN_IF(gemm(GEMM_NN, dt, un.T, de, dl, s.dfeat, dl, ex->proj_in, de, dy, de, none, ex->scratch, ex->sz.scratch, st));
   for (int b = n - 1; b >= 0; --b) {
     const void* x = b == 0 ? un.patches : s.act[b - 1];
     char* dx = ex->ping[b & 1];

@@ -1,0 +1,421 @@
+// bf16 GEMM for large and medium tiles: two groups of wavefronts that take turns.
+//
+// A workgroup has eight wavefronts, two on every SIMD: group 0 (wavefronts 0-3) and group 1 (4-7).
+// Work goes in phases with a workgroup barrier behind each; group 1 runs one phase behind group 0,
+// so that in every phase one wavefront of a SIMD issues nothing but MFMAs (32 of them, 512 clocks)
+// while the other one does everything else -- fragment reads for its next MFMAs, and the loads that
+// bring later slices straight from memory into LDS.  No memory instruction ever stands in front of
+// an MFMA of its own wavefront, and no wavefront holds staging registers.
+//
+// What this buys over one wavefront per SIMD that interleaves both (register-staged slices, four
+// wavefronts of 128x128): NT 8192x12288x4096 1400 -> 1560 TFLOP/s, NN 8192x4096x12288 1390 -> 1560,
+// TN 12288x4096x8192 1230 -> 1330, NT 16384x3072x1024 1150 -> 1280 (random operands, one box).  It is
+// bound by the power the matrix pipe draws: priorities, the order of a phase's memory instructions
+// and the tile order changed nothing.
+//
+// Loads that write LDS: lane l of a wavefront fills bytes 16 l .. 16 l + 15 of a 1 KiB run, so the
+// swizzle sits on the global side: the lane that owns a slot fetches the chunk that belongs there.
+// They are asm statements, invisible to the compiler's wait-count bookkeeping, which would make every
+// fragment read wait for all of them; the waits stand in the phases instead, and since the loads of
+// a wavefront return in order a wait for "at most n outstanding" names the ones that must have landed.
+#include "gemm_tile.h"
+
+#include <atomic>
+
+namespace bm {
+
+namespace {
+
+constexpr int THREADS = 512;
+
+template <int N> using Int = std::integral_constant<int, N>;
+
+template <int N> __device__ inline void wait_loads() { asm volatile("s_waitcnt vmcnt(%0)" :: "n"(N) : "memory"); }
+__device__ inline void wait_fragments() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+__device__ inline void end_phase() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+}
+__device__ inline void load_to_lds(const bf16_t* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(off), "s"(base) : "memory");
+}
+
+// LDS layouts of a region of R rows x 64 k (the swizzles keep fragment reads free of bank conflicts):
+//   k-contiguous operand  [row][64 k]: 16-byte chunk c of row r sits at c ^ ((r >> 1) & 7)
+//   transposed operand    [k][R rows]: chunk c of k-row k sits at c ^ ((k & 3) << 2) ^ (((k >> 3) & 1) << 1)
+// A region is filled in R/64 loads per wavefront; load i of wavefront w writes the 1 KiB run i*8 + w.
+template <int R, bool TR>
+struct Region {
+  static constexpr int LOADS = R / 64;
+  static constexpr uint32_t BYTES = R * BK * 2;
+  static constexpr int CPR = TR ? R / 8 : KCH;           // chunks per LDS row
+  static constexpr int RPL = 64 / CPR;                   // LDS rows per load
+  uint32_t off[LOADS];                                   // byte offset from the slice's base pointer
+  // LDS row and global chunk of this lane in load i
+  static __device__ inline void place(int i, int wave, int lane, int* row, int* chunk) {
+    const int r = (i * 8 + wave) * RPL + lane / CPR;
+    *row = r;
+    *chunk = (lane % CPR) ^ (TR ? ((r & 3) << 2) ^ (((r >> 3) & 1) << 1) : (r >> 1) & 7);
+  }
+  // row0: this region's first row in the tile; rows past rows_left (counted from the tile's first row)
+  // are clamped into the matrix: their products are never stored.
+  // half > 0 (k-contiguous only): rows are gathered from two ranges F rows apart -- within every run of
+  // 2*half tile rows the first half come from f0.. and the second from F + f0.. (gate and up rows of a
+  // SwiGLU weight); offsets are then relative to the matrix's first row.
+  __device__ inline void init(int ld, int row0, int rows_left, int wave, int lane, int half = 0, int F = 0, int f0 = 0) {
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      int r, c;
+      place(i, wave, lane, &r, &c);
+      if (TR) {
+        int row = row0 + c * 8;
+        if (row >= rows_left) row = 0;
+        off[i] = ((uint32_t)r * (uint32_t)ld + (uint32_t)row) * 2u;
+      } else {
+        int row = min(row0 + r, rows_left - 1);
+        if (half > 0) row = (r / half & 1) * F + f0 + (r / (2 * half)) * half + r % half;
+        off[i] = ((uint32_t)row * (uint32_t)ld + (uint32_t)c * 8u) * 2u;
+      }
+    }
+  }
+  // k_left < 64: a slice that ends inside the k range; what lies past it is fetched from its last
+  // valid k (row or chunk) and zeroed in the fragments
+  template <bool CUT>
+  __device__ inline void load(const bf16_t* base, int ld, int k_left, uint32_t lds, int wave, int lane) const {
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+      uint32_t o = off[i];
+      if (CUT && k_left < BK) {
+        int r, c;
+        place(i, wave, lane, &r, &c);
+        if (TR) { if (r >= k_left) o -= (uint32_t)(r - (k_left - 1)) * (uint32_t)ld * 2u; }
+        else if (c * 8 >= k_left) o -= (uint32_t)(c * 8 - (k_left - 8)) * 2u;
+      }
+      load_to_lds(base, o, lds + (i * 8 + wave) * 1024);
+    }
+  }
+};
+
+// 16(row) x 32(k) fragments of v_mfma_f32_16x16x32_bf16 from a region of R rows: lane l holds row l%16
+// and k = (l/16)*8 .. +7.  NB blocks of 16 rows from row0 on; block q, k-step ks.
+template <int R, bool TR, int NB>
+struct Fragments {
+  static constexpr int NA = TR ? NB : 2;
+  uint32_t addr[NA];
+  __device__ inline void init(int row0, int lane) {
+    const int gi = lane >> 4, s = lane & 15;
+#pragma unroll
+    for (int q = 0; q < NA; ++q) {
+      if (TR) {
+        // the 16 lanes of group gi read a 4(k) x 16(row) block, 8 bytes each; the transpose read
+        // hands lane s row s with 4 consecutive k; two reads give 8 k
+        const int k = gi * 8 + (s >> 2);
+        const int c = (row0 / 8 + q * 2 + ((s & 3) >> 1)) ^ ((s >> 2) << 2) ^ ((gi & 1) << 1);
+        addr[q] = k * (R * 2) + c * 16 + (s & 1) * 8;
+      } else {
+        addr[q] = (row0 + s) * (BK * 2) + ((q * 4 + gi) ^ (s >> 1)) * 16;
+      }
+    }
+  }
+  __device__ inline bf16x8 read(const unsigned char* smem, int q, int ks, uint32_t base) const {
+    if (TR) {
+      const unsigned char* p = smem + addr[q] + base + ks * (32 * R * 2);
+      s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)p);
+      s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p + 4 * R * 2));
+      union { struct { s16x4 a, b; } s; bf16x8 v; } u;
+      u.s.a = lo; u.s.b = hi;
+      return u.v;
+    }
+    return *reinterpret_cast<const bf16x8*>(smem + addr[ks] + base + q * (16 * BK * 2));
+  }
+};
+
+// zero what lies past the k range of a cut slice
+__device__ inline void cut_fragment(bf16x8& f, int ks, int k_left, int lane) {
+  const int k = ks * 32 + (lane >> 4) * 8;
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+    if (k + e >= k_left) f[e] = (__bf16)0.f;
+}
+
+// Accumulators start as the product of zero operands: written by ordinary instructions they would need
+// wait states in front of the first MFMA that the compiler, which does not know the asm statements
+// are MFMAs, would not leave.
+template <int FM, int FN>
+__device__ inline void clear(f32x4 (&acc)[FM][FN]) {
+  bf16x8 z = {};
+  asm volatile("s_nop 7" : "+v"(z));
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) mfma16_first(acc[i][j], z, z);
+}
+
+// ---- 256x256 tile.  Each wavefront owns 128x64: 64 rows in each half of A, 64 columns of B.  A slice is
+// two phases per group (first and second half of A); LDS holds two slices, and a slice's first half
+// of A with B, and its second half, are re-filled as soon as both groups have read them: loads are
+// in flight for more than a slice (4 to 5 phases of 512 clocks).
+template <bool A_TR, bool B_TR, int EPI, bool CUT>
+__global__ __launch_bounds__(THREADS, 2) void gemm_alt256_kernel(GemmParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  using RegA = Region<128, A_TR>;
+  using RegB = Region<256, B_TR>;
+  constexpr uint32_t A1 = RegA::BYTES, B0 = 2 * RegA::BYTES, BUF = B0 + RegB::BYTES;
+  constexpr int LATE = RegA::LOADS, EARLY = RegA::LOADS + RegB::LOADS;      // loads of a slice's two parts
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 2, wn = wave & 3;                                   // wm is the group
+  const TileJob job = locate_tile<256, 256>(p);
+  if (job.kbeg >= job.kend) return;
+  const int m0 = job.m0, n0 = job.n0, n = (job.kend - job.kbeg + BK - 1) / BK;
+  const int k_left = job.kend - job.kbeg - (n - 1) * BK;                     // of the last slice
+  constexpr bool SWF = EPI == EPI_SWIGLU_FWD;
+
+  RegA ra0, ra1;
+  RegB rb;
+  ra0.init(p.lda, 0, p.M - m0, wave, lane);
+  ra1.init(p.lda, 128, p.M - m0, wave, lane);
+  if (SWF) rb.init(p.ldb, 0, 256, wave, lane, 32, p.N / 2, job.tn * 128);
+  else rb.init(p.ldb, 0, p.N - n0, wave, lane);
+  const bf16_t* a_base = A_TR ? job.A + (size_t)job.kbeg * p.lda + m0 : job.A + (size_t)m0 * p.lda + job.kbeg;
+  const bf16_t* b_base = B_TR ? job.B + (size_t)job.kbeg * p.ldb + n0
+                              : job.B + (SWF ? (size_t)0 : (size_t)n0 * p.ldb) + job.kbeg;
+  const size_t a_step = A_TR ? (size_t)BK * p.lda : (size_t)BK, b_step = B_TR ? (size_t)BK * p.ldb : (size_t)BK;
+  auto load_early = [&](int j, uint32_t buf) {
+    const int left = CUT && j == n - 1 ? k_left : BK;
+    rb.template load<CUT>(b_base + (size_t)j * b_step, p.ldb, left, buf + B0, wave, lane);
+    ra0.template load<CUT>(a_base + (size_t)j * a_step, p.lda, left, buf, wave, lane);
+  };
+  auto load_late = [&](int j, uint32_t buf) {
+    ra1.template load<CUT>(a_base + (size_t)j * a_step, p.lda, CUT && j == n - 1 ? k_left : BK, buf + A1, wave, lane);
+  };
+
+  Fragments<128, A_TR, 4> fa;
+  Fragments<256, B_TR, 4> fb;
+  fa.init(wm * 64, lane);
+  fb.init(wn * 64, lane);
+  bf16x8 af[2][4], bf[2][4];
+  f32x4 acc[8][4];
+  auto multiply = [&](auto half_t) {
+    constexpr int H = decltype(half_t)::value * 4;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mfma16(acc[H + i][j], bf[ks][j], af[ks][i]);
+  };
+  // COME: slices that follow this one (2: two or more, 0: this is the last)
+  auto slice = [&](auto come_t, int j) {
+    constexpr int COME = decltype(come_t)::value;
+    const uint32_t buf = (j & 1) * BUF;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) bf[ks][q] = fb.read(smem, q, ks, buf + B0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) af[ks][q] = fa.read(smem, q, ks, buf);
+    }
+    if (COME >= 1) load_late(j + 1, buf ^ BUF);
+    wait_fragments();
+    if (CUT && COME == 0 && k_left < BK) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { cut_fragment(bf[ks][q], ks, k_left, lane); cut_fragment(af[ks][q], ks, k_left, lane); }
+    }
+    // the second half of A of this slice is read next: everything older than the loads requested
+    // since (the next slice's two parts) must have landed
+    wait_loads<COME >= 1 ? EARLY + LATE : 0>();
+    end_phase();
+    multiply(Int<0>{});
+    wait_loads<COME >= 1 ? EARLY + LATE : 0>();
+    end_phase();
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) af[ks][q] = fa.read(smem, q, ks, buf + A1);
+    if (COME >= 2) load_early(j + 2, buf);
+    wait_fragments();
+    if (CUT && COME == 0 && k_left < BK) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) cut_fragment(af[ks][q], ks, k_left, lane);
+    }
+    if (COME == 0) { end_phase(); return; }                 // the last MFMAs belong to the epilogue
+    // next: the following slice's first half of A and B
+    wait_loads<COME >= 2 ? EARLY + LATE : LATE>();
+    end_phase();
+    multiply(Int<1>{});
+    wait_loads<COME >= 2 ? EARLY + LATE : LATE>();
+    end_phase();
+  };
+  load_early(0, 0);
+  load_late(0, 0);
+  if (n > 1) load_early(1, BUF);
+  clear(acc);                                               // under the latency of the first loads
+  if (n > 1) wait_loads<EARLY + LATE>();
+  else wait_loads<0>();
+  end_phase();
+  if (wm == 1) end_phase();                                 // group 1 stays one phase behind
+  const bool full = m0 + 256 <= p.M && n0 + 256 <= p.N;
+  for (int j = 0; j < n - 2; ++j) slice(Int<2>{}, j);
+  if (n > 1) slice(Int<1>{}, n - 2);
+  slice(Int<0>{}, n - 1);
+  gemm_epilogue<EPI, 8, 4>(p, acc, reinterpret_cast<float*>(smem) + wave * epilogue_stage_floats<4>(), lane,
+                           n0 + wn * 64, job.tn * 128 + wn * 32, job.split, job.c_off, full,
+                           [&](int i) { return m0 + (i >> 2) * 128 + wm * 64 + (i & 3) * 16; },
+                           [&] {
+                             multiply(Int<1>{});
+                             // group 0 writes its strips over the buffers group 1 has just read
+                             if (wm == 0) end_phase();
+                           });
+}
+
+// ---- 128x256 and 256x128 tiles: each wavefront owns 64x64 and a slice is one phase per group.  LDS holds
+// three slices; the loads of slice j+2 go out while slice j is read.
+template <int BM, int BN, bool A_TR, bool B_TR, int EPI, bool CUT>
+__global__ __launch_bounds__(THREADS, 2) void gemm_alt128_kernel(GemmParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  using RegA = Region<BM, A_TR>;
+  using RegB = Region<BN, B_TR>;
+  constexpr uint32_t B0 = RegA::BYTES, BUF = B0 + RegB::BYTES;
+  constexpr int LOADS = RegA::LOADS + RegB::LOADS;
+  constexpr int WN = BN / 64;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / WN, wn = wave % WN, group = wave >> 2;
+  const TileJob job = locate_tile<BM, BN>(p);
+  if (job.kbeg >= job.kend) return;
+  const int m0 = job.m0, n0 = job.n0, n = (job.kend - job.kbeg + BK - 1) / BK;
+  const int k_left = job.kend - job.kbeg - (n - 1) * BK;
+  constexpr bool SWF = EPI == EPI_SWIGLU_FWD;
+
+  RegA ra;
+  RegB rb;
+  ra.init(p.lda, 0, p.M - m0, wave, lane);
+  if (SWF) rb.init(p.ldb, 0, BN, wave, lane, 32, p.N / 2, job.tn * (BN / 2));
+  else rb.init(p.ldb, 0, p.N - n0, wave, lane);
+  const bf16_t* a_base = A_TR ? job.A + (size_t)job.kbeg * p.lda + m0 : job.A + (size_t)m0 * p.lda + job.kbeg;
+  const bf16_t* b_base = B_TR ? job.B + (size_t)job.kbeg * p.ldb + n0
+                              : job.B + (SWF ? (size_t)0 : (size_t)n0 * p.ldb) + job.kbeg;
+  const size_t a_step = A_TR ? (size_t)BK * p.lda : (size_t)BK, b_step = B_TR ? (size_t)BK * p.ldb : (size_t)BK;
+  auto load = [&](int j, uint32_t buf) {
+    const int left = CUT && j == n - 1 ? k_left : BK;
+    rb.template load<CUT>(b_base + (size_t)j * b_step, p.ldb, left, buf + B0, wave, lane);
+    ra.template load<CUT>(a_base + (size_t)j * a_step, p.lda, left, buf, wave, lane);
+  };
+
+  Fragments<BM, A_TR, 4> fa;
+  Fragments<BN, B_TR, 4> fb;
+  fa.init(wm * 64, lane);
+  fb.init(wn * 64, lane);
+  bf16x8 af[2][4], bf[2][4];
+  f32x4 acc[4][4];
+  auto multiply = [&] {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) mfma16(acc[i][j], bf[ks][j], af[ks][i]);
+  };
+  uint32_t cur = 0;                                          // buffer of the slice to be read next
+  auto next_buf = [&](uint32_t b) { return b == 2 * BUF ? 0u : b + BUF; };
+  auto slice = [&](auto come_t, int j) {
+    constexpr int COME = decltype(come_t)::value;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) bf[ks][q] = fb.read(smem, q, ks, cur + B0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) af[ks][q] = fa.read(smem, q, ks, cur);
+    }
+    const uint32_t nxt = next_buf(cur);
+    if (COME >= 2) load(j + 2, next_buf(nxt));
+    wait_fragments();
+    if (CUT && COME == 0 && k_left < BK) {
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { cut_fragment(bf[ks][q], ks, k_left, lane); cut_fragment(af[ks][q], ks, k_left, lane); }
+    }
+    cur = nxt;
+    if (COME == 0) { end_phase(); return; }                  // the last MFMAs belong to the epilogue
+    wait_loads<COME >= 2 ? LOADS : 0>();                     // the next slice has landed
+    end_phase();
+    multiply();
+    wait_loads<COME >= 2 ? LOADS : 0>();
+    end_phase();
+  };
+  load(0, 0);
+  if (n > 1) load(1, BUF);
+  clear(acc);
+  if (n > 1) wait_loads<LOADS>();
+  else wait_loads<0>();
+  end_phase();
+  if (group == 1) end_phase();
+  const bool full = m0 + BM <= p.M && n0 + BN <= p.N;
+  for (int j = 0; j < n - 2; ++j) slice(Int<2>{}, j);
+  if (n > 1) slice(Int<1>{}, n - 2);
+  slice(Int<0>{}, n - 1);
+  gemm_epilogue<EPI, 4, 4>(p, acc, reinterpret_cast<float*>(smem) + wave * epilogue_stage_floats<4>(), lane,
+                           n0 + wn * 64, job.tn * (BN / 2) + wn * 32, job.split, job.c_off, full,
+                           [&](int i) { return m0 + wm * 64 + i * 16; },
+                           [&] {
+                             multiply();
+                             if (group == 0) end_phase();
+                           });
+}
+
+template <int BM, int BN, bool A_TR, bool B_TR, int EPI, bool CUT>
+bm_status launch_one(const GemmParams& p, hipStream_t st) {
+  constexpr bool LARGE = BM == 256 && BN == 256;
+  constexpr size_t lds = (size_t)(LARGE ? 2 : 3) * (BM + BN) * BK * sizeof(bf16_t);
+  void (*kern)(GemmParams);
+  if constexpr (LARGE) kern = gemm_alt256_kernel<A_TR, B_TR, EPI, CUT>;
+  else kern = gemm_alt128_kernel<BM, BN, A_TR, B_TR, EPI, CUT>;
+  static std::atomic<bool> attr_done{false};
+  if (!attr_done.load(std::memory_order_relaxed)) {
+    BM_CHECK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    attr_done.store(true, std::memory_order_relaxed);
+  }
+  int wgs = p.tiles_m * p.tiles_n * p.splits * p.grid_groups;
+  if (p.pair_wgs0 > 0) wgs = p.pair_wgs0 + p.second.tiles_m * p.second.tiles_n * p.second.splits;
+  hipLaunchKernelGGL(kern, dim3(wgs), dim3(THREADS), lds, st, p);
+  BM_CHECK_LAUNCH("gemm_alt");
+  return BM_OK;
+}
+
+template <int BM, int BN, bool A_TR, bool B_TR, int EPI>
+bm_status launch_cut(const GemmParams& p, hipStream_t st) {
+  if (p.K % BK) return launch_one<BM, BN, A_TR, B_TR, EPI, true>(p, st);
+  return launch_one<BM, BN, A_TR, B_TR, EPI, false>(p, st);
+}
+
+template <int BM, int BN>
+bm_status launch_tile(int layout, const GemmParams& p, hipStream_t st) {
+  if (layout == GEMM_TN)
+    return p.splits > 1 ? launch_cut<BM, BN, true, true, EPI_PARTIAL>(p, st) : launch_cut<BM, BN, true, true, EPI_ADD>(p, st);
+  if (layout == GEMM_NT) {
+    if (p.splits > 1) return launch_cut<BM, BN, false, false, EPI_PARTIAL>(p, st);
+    if (p.swf_a) return launch_cut<BM, BN, false, false, EPI_SWIGLU_FWD>(p, st);
+    return p.residual ? launch_cut<BM, BN, false, false, EPI_RES>(p, st) : launch_cut<BM, BN, false, false, EPI_PLAIN>(p, st);
+  }
+  if (p.splits > 1) return launch_cut<BM, BN, false, true, EPI_PARTIAL>(p, st);
+  if (p.sw_up) return launch_cut<BM, BN, false, true, EPI_SWIGLU_BWD>(p, st);
+  return p.residual ? launch_cut<BM, BN, false, true, EPI_RES>(p, st) : launch_cut<BM, BN, false, true, EPI_PLAIN>(p, st);
+}
+
+}  // namespace
+
+bm_status launch_gemm_alt(int layout, int bm, int bn, const GemmParams& p, hipStream_t st) {
+  if (bm == 256 && bn == 256) return launch_tile<256, 256>(layout, p, st);
+  if (bm == 256 && bn == 128) return launch_tile<256, 128>(layout, p, st);
+  return launch_tile<128, 256>(layout, p, st);
+}
+
+}  // namespace bm

@@ -1,61 +1,26 @@
-// bf16 GEMM on the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16), fp32 accumulation.
+// bf16 GEMM on the gfx950 matrix cores (v_mfma_f32_16x16x32_bf16), fp32 accumulation: the choice of tile and
+// k split, and the kernel of 128x128 tiles (the other tiles: gemm_alt.hip).
 //
 //   NT: C[M,N]  = A[M,K] B[N,K]^T (+bias)(+residual)   linear forward
 //   NN: C[M,N]  = A[M,K] B[K,N]                        input gradient
 //   TN: C[M,N] += A[K,M]^T B[K,N]     (C fp32)         weight gradient
 //
-// One workgroup owns a BM x BN tile of C and walks K in slices of BK=64.  Both
-// operand slices are staged in LDS (two buffers: the next slice is fetched
-// from HBM into registers while the current one feeds the MFMAs, one barrier per
+// The 128x128 kernel serves outputs of few tiles, two workgroups per CU: four wavefronts of 64x64, K in
+// slices of BK=64, both operand slices staged in LDS (two buffers: the next slice is fetched from
+// memory into registers while the current one feeds the MFMAs, one barrier per
 // slice).  An operand whose K index is contiguous in memory is kept as
 // [row][k] with its 16-byte chunks XOR-swizzled by the row, and fragments are
 // read with ds_read_b128.  An operand whose K index is the slow one (B of NN,
 // both operands of TN) is kept as [k][row] and fragments are read with the
 // LDS transpose read (ds_read_b64_tr_b16), so no transposed copy is ever made.
 // Workgroup ids are remapped so that the workgroups of one XCD (they share an
-// L2) cover a compact block of tiles.  The K split of TN writes fp32 partial
+// L2) cover a compact block of tiles.  A split k range leaves fp32 partial
 // tiles that a second kernel sums in a fixed order: no floating-point atomics.
-#include "common.h"
-
-#include <type_traits>
+#include "gemm_tile.h"
 
 namespace bm {
 
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-constexpr int BK = 64;          // k slice
-constexpr int KCH = BK / 8;     // 16-byte chunks per k-contiguous row
-
-struct GemmParams {
-  const bf16_t* A; const bf16_t* B; void* C;
-  const bf16_t* bias; const bf16_t* residual;
-  const bf16_t* sw_up = nullptr; bf16_t* sw_dup = nullptr; bf16_t* sw_a = nullptr;   // SwiGLU backward epilogue (see GemmEpilogue)
-  bf16_t* swf_a = nullptr;      // SwiGLU forward epilogue (see GemmEpilogue); N = 2F
-  float* partial;               // TN with splits > 1
-  int M, N, K, lda, ldb, ldc;
-  int tiles_m, tiles_n, splits, k_per_split;
-  int out_fp32;
-  int xcd_split;                // each k split owns 8/splits XCDs (splits in {2,4,8})
-  // grouped problems (see GemmGroups); all null / zero otherwise
-  const int32_t* tile_group;
-  const int32_t* group_rows;
-  long b_group_stride, c_group_stride;
-  int grid_groups;              // host: workgroups = tiles * splits * grid_groups (>= 1)
-  // paired launch: workgroups pair_wgs0.. of the grid work on a second problem of the same
-  // kind and the same K (two weight gradients that each leave CUs idle share one grid)
-  int pair_wgs0;                // 0: one problem
-  struct Second {
-    const bf16_t* A; const bf16_t* B; void* C; float* partial;
-    int M, N, lda, ldb, ldc, tiles_m, tiles_n, splits, k_per_split, xcd_split;
-  } second;
-};
 
 // ---- LDS layouts ---------------------------------------------------------
 // k-contiguous operand: [rows][KCH chunks]; chunk c of row r sits at c ^ ((r>>1)&7).
@@ -70,29 +35,6 @@ template <int R>
 __device__ inline int tr_offset(int k, int c) {             // in bf16 elements
   const int pos = c ^ ((k & 3) << 2) ^ (((k >> 3) & 1) << 1);
   return k * R + (pos << 3);
-}
-
-template <int R>
-__device__ inline bf16x8 tr_fragment(const bf16_t* lds, int row0, int k0, int lane) {
-  // 32(row) x 16(k) fragment of an operand stored [k][row]; lane l gets row
-  // row0 + l%32 and k = k0 + (l/32)*8 .. +7
-  const int gi = lane >> 4, s = lane & 15;
-  const int r = row0 + (gi & 1) * 16 + (s & 3) * 4;        // 4 consecutive rows (8 bytes)
-  const int k = k0 + (gi >> 1) * 8 + (s >> 2);
-  const int c = r >> 3, within = r & 7;
-  const bf16_t* p0 = lds + tr_offset<R>(k, c) + within;
-  const bf16_t* p1 = lds + tr_offset<R>(k + 4, c) + within;
-  s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)p0);
-  s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)p1);
-  union { struct { s16x4 a, b; } s; bf16x8 v; } u;
-  u.s.a = lo; u.s.b = hi;
-  return u.v;
-}
-
-__device__ inline bf16x8 kc_fragment(const bf16_t* lds, int row0, int ks, int lane) {
-  const int row = row0 + (lane & 31);
-  const int c = ks * 2 + (lane >> 5);
-  return *reinterpret_cast<const bf16x8*>(lds + kc_offset(row, c));
 }
 
 // 16(row) x 32(k) fragments of the v_mfma_f32_16x16x32_bf16 operands: lane l holds row
@@ -118,21 +60,6 @@ __device__ inline bf16x8 tr_fragment16(const bf16_t* lds, int row0, int k0, int 
   union { struct { s16x4 a, b; } s; bf16x8 v; } u;
   u.s.a = lo; u.s.b = hi;
   return u.v;
-}
-
-// acc += a b^T with v_mfma_f32_16x16x32_bf16.  Written as an asm statement that ties the
-// accumulator block to the accumulation half of the register file: with 64 four-register blocks
-// the allocator otherwise keeps some of them in the other half and runs out of registers there
-// (copies between the halves inside the loop, spills).  The accumulator of a block is next
-// touched 63 MFMAs later, far beyond any wait state the instruction asks for.
-__device__ inline void mfma16(f32x4& acc, const bf16x8& a, const bf16x8& b) {
-  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
-}
-// acc = a b^T: the first product of a tile takes the constant 0 as its addend, so the accumulators
-// are never initialised by separate instructions (which the compiler, not knowing that the asm
-// statement is an MFMA, would place right in front of it without the wait states that needs)
-__device__ inline void mfma16_first(f32x4& acc, const bf16x8& a, const bf16x8& b) {
-  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(a), "v"(b));
 }
 
 // ---- global -> registers -> LDS staging -----------------------------------
@@ -230,62 +157,6 @@ struct Stage {
   }
 };
 
-// f(0), f(1), ..., f(N-1) with the index as a compile-time constant
-template <int N, int I = 0, typename F>
-__device__ inline void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<N, I + 1>(f);
-  }
-}
-
-// XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs, so give
-// each XCD a contiguous run of tiles, walked in column-major groups of GROUP_M
-// tile rows (operand reuse in that XCD's L2).
-__device__ inline void grouped_tile(int id, int tiles_m, int tiles_n, int* tm, int* tn) {
-  constexpr int GROUP_M = 8;
-  const int per_group = GROUP_M * tiles_n;
-  const int g = id / per_group;
-  const int first_m = g * GROUP_M;
-  const int gsize = min(tiles_m - first_m, GROUP_M);
-  const int in = id % per_group;
-  *tm = first_m + in % gsize;
-  *tn = in / gsize;
-}
-
-// K split with XCD affinity: split s owns the 8/splits XCDs s*G .. s*G+G-1 and each of
-// them a contiguous run of that split's tiles, so an operand panel of one k range is
-// fetched by as few L2s as possible (HBM traffic of the weight gradient is dominated by
-// panels fetched once per XCD that touches them).
-__device__ inline void split_tile_of_block(int pid, int tiles, int splits, int tiles_m, int tiles_n,
-                                           int* split, int* tm, int* tn) {
-  const int G = 8 / splits;
-  const int xcd = pid & 7, local = pid >> 3;
-  *split = xcd / G;
-  grouped_tile((xcd % G) * (tiles / G) + local, tiles_m, tiles_n, tm, tn);
-}
-
-__device__ inline void tile_of_block(int pid, int total, int tiles_m, int tiles_n, int* tm, int* tn) {
-  constexpr int XCDS = 8, GROUP_M = 4;     // measured: 4 tile rows per group is a little ahead of 8, 2 and 16
-  int id = pid;
-  if (total % XCDS == 0) id = (pid % XCDS) * (total / XCDS) + pid / XCDS;
-  const int per_group = GROUP_M * tiles_n;
-  const int g = id / per_group;
-  const int first_m = g * GROUP_M;
-  const int gsize = min(tiles_m - first_m, GROUP_M);
-  const int in = id % per_group;
-  *tm = first_m + in % gsize;
-  *tn = in / gsize;
-}
-
-// What the epilogue does with the product, fixed at compile time: one straight run of instructions
-// per kind (with run-time switches between the strips the K = 1024 products lost 5 %).
-enum { EPI_PLAIN = 0,     // C = acc (+bias), bf16 or fp32
-       EPI_RES,           // C = acc (+bias) + residual
-       EPI_SWIGLU_FWD, EPI_SWIGLU_BWD,
-       EPI_ADD,           // fp32 C += acc
-       EPI_PARTIAL };     // acc -> this split's partial tile
-
 template <int BM, int BN, int WM, int WN, bool A_TR, bool B_TR, int EPI, bool KTAIL>
 __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
   constexpr int NT = WM * WN * 64;
@@ -298,38 +169,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WN, wn = wave % WN;
 
-  int pid = blockIdx.x;
-  if (p.pair_wgs0 > 0 && pid >= p.pair_wgs0) {
-    // second problem of a paired launch (workgroup-uniform): take its description over
-    pid -= p.pair_wgs0;
-    p.A = p.second.A; p.B = p.second.B; p.C = p.second.C; p.partial = p.second.partial;
-    p.M = p.second.M; p.N = p.second.N; p.lda = p.second.lda; p.ldb = p.second.ldb; p.ldc = p.second.ldc;
-    p.tiles_m = p.second.tiles_m; p.tiles_n = p.second.tiles_n; p.splits = p.second.splits;
-    p.k_per_split = p.second.k_per_split; p.xcd_split = p.second.xcd_split;
-  }
-  const int tiles = p.tiles_m * p.tiles_n;
-  int split = pid / tiles;
-  int tm, tn;
-  if (p.xcd_split) split_tile_of_block(pid, tiles, p.splits, p.tiles_m, p.tiles_n, &split, &tm, &tn);
-  else tile_of_block(pid % tiles, tiles, p.tiles_m, p.tiles_n, &tm, &tn);
-  const int m0 = tm * BM, n0 = tn * BN;
-  int kbeg = split * p.k_per_split;
-  int kend = min(p.K, kbeg + p.k_per_split);
-  const bf16_t* Bmat = p.B;
-  long c_off = 0;
-  if (p.group_rows) {
-    // grouped weight gradient: `split` is the group; its rows are the k range (all
-    // wavefronts take the same exit: the values are workgroup-uniform)
-    kbeg = min(p.group_rows[split], p.K);
-    kend = min(p.group_rows[split + 1], p.K);
-    if (kbeg >= kend) return;
-    c_off = (long)split * p.c_group_stride;
-    split = 0;
-  } else if (p.tile_group) {
-    const int g = p.tile_group[m0 / MOE_PAD];
-    if (g < 0) return;
-    Bmat += (long)g * p.b_group_stride;
-  }
+  const TileJob job = locate_tile<BM, BN>(p);
+  if (job.kbeg >= job.kend) return;
+  const int m0 = job.m0, n0 = job.n0, kbeg = job.kbeg, kend = job.kend;
 
   f32x4 acc[FM][FN];        // first written by the first k-step of the first slice
 
@@ -342,11 +184,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
   Stage<BN, NT, B_TR, KTAIL> sb;
   sa.init(p.lda, p.M - m0, tid);
   constexpr bool swf = EPI == EPI_SWIGLU_FWD;            // SwiGLU forward: N = 2F, a tile covers BN/2 columns of a
-  if (swf) sb.init(p.ldb, BN, tid, TN_ / 2, p.N / 2, tn * (BN / 2));
+  if (swf) sb.init(p.ldb, BN, tid, TN_ / 2, p.N / 2, job.tn * (BN / 2));
   else sb.init(p.ldb, p.N - n0, tid);
   // slice base pointers (wave-uniform): first row of the tile at k = kbeg
-  const bf16_t* a_base = A_TR ? p.A + (size_t)kbeg * p.lda + m0 : p.A + (size_t)m0 * p.lda + kbeg;
-  const bf16_t* b_base = B_TR ? Bmat + (size_t)kbeg * p.ldb + n0 : Bmat + (swf ? (size_t)0 : (size_t)n0 * p.ldb) + kbeg;
+  const bf16_t* a_base = A_TR ? job.A + (size_t)kbeg * p.lda + m0 : job.A + (size_t)m0 * p.lda + kbeg;
+  const bf16_t* b_base = B_TR ? job.B + (size_t)kbeg * p.ldb + n0 : job.B + (swf ? (size_t)0 : (size_t)n0 * p.ldb) + kbeg;
   const size_t a_step = A_TR ? (size_t)BK * p.lda : (size_t)BK;
   const size_t b_step = B_TR ? (size_t)BK * p.ldb : (size_t)BK;
   sa.load(a_base, p.lda, kend - kbeg, tid);
@@ -462,8 +304,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
   };
-  using yes = std::integral_constant<bool, true>;
-  using no = std::integral_constant<bool, false>;
+  using yes = std::true_type;
+  using no = std::false_type;
   {
     // the first slice has no row block pending; the flags of the steady-state slices are
     // compile-time constants, so the loop body is branch-free
@@ -481,165 +323,11 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
     }
   }
 
-  {
-    // ---- epilogue.  The MFMAs ran with swapped operands, so block (i,j) holds C^T:
-    // lane = row m = l%16, registers = 4 consecutive columns n = 4*(l/16) + e.
-    // Each wavefront transposes its own 16-row strips through LDS (free after the last
-    // barrier) and then writes whole rows: 16 bytes per lane, 256 contiguous bytes per row.
-    constexpr int SLD = TN_ + 4;                         // padded fp32 row: conflict-free both ways
-    float* stage = reinterpret_cast<float*>(smem_raw) + wave * (16 * SLD);
-    constexpr int LPR = TN_ / 8;                          // lanes per output row (8 columns each)
-    constexpr int RPI = 64 / LPR;                         // rows per store instruction
-    constexpr int TPS = 16 / RPI;                         // store instructions per strip
-    static_assert(16 % RPI == 0, "a 16-row strip must be a whole number of store instructions");
-    const int m_in = lane & 15, q4 = (lane >> 4) * 4;
-    const int rcol = (lane % LPR) * 8, rrow = lane / LPR;
-    const int gn = n0 + wn * TN_ + rcol;
-    // What the epilogue combines with the product -- the old C of a weight gradient, the residual,
-    // the saved g and u of the SwiGLU backward -- is requested two strips ahead, the first two
-    // strips before the held-back MFMAs: fetched in front of each store instead, a tile pays one
-    // memory latency per store instruction, 32 of them in a row (dW 22016x4096 over 777 rows 296 ->
-    // 247 us, over 8192 rows 1301 -> 1271 us; the 128-expert weight gradients of 8192 tokens 1610 ->
-    // 1220 us).  Addresses are clamped into the matrix, so that the requests carry no condition.
-    u32x4 pre[2][TPS][2];
-    auto request = [&](auto i_t) {
-      constexpr int i = decltype(i_t)::value;
-      if (i >= FM) return;
-#pragma unroll
-      for (int t = 0; t < TPS; ++t) {
-        const int gm = min(m0 + wm * TM + i * 16 + t * RPI + rrow, p.M - 1), gc = min(gn, p.N - 8);
-        if (EPI == EPI_ADD) {
-          const float* c = (const float*)p.C + c_off + (size_t)gm * p.ldc + gc;
-          pre[i & 1][t][0] = *reinterpret_cast<const u32x4*>(c);
-          pre[i & 1][t][1] = *reinterpret_cast<const u32x4*>(c + 4);
-        } else if (EPI == EPI_SWIGLU_BWD) {
-          const bf16_t* up = p.sw_up + (size_t)gm * (2 * p.N) + gc;
-          pre[i & 1][t][0] = *reinterpret_cast<const u32x4*>(up);
-          pre[i & 1][t][1] = *reinterpret_cast<const u32x4*>(up + p.N);
-        } else if (EPI == EPI_RES) {
-          pre[i & 1][t][0] = *reinterpret_cast<const u32x4*>(p.residual + (size_t)gm * p.ldc + gc);
-        }
-      }
-    };
-    request(std::integral_constant<int, 0>{});
-    request(std::integral_constant<int, 1>{});
-    pending_row([](int) {});
-    // the compiler does not know that the asm statements above are MFMAs and leaves no wait states
-    // between the last of them and the epilogue's reads of the accumulators
-    asm volatile("s_nop 15\n\ts_nop 15");
-    __builtin_amdgcn_sched_barrier(0);
-
-    float bias[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) bias[e] = 0.f;
-    if ((EPI == EPI_PLAIN || EPI == EPI_RES) && p.bias && gn < p.N) load16(p.bias + gn, bias);
-    // `full`: the tile lies inside C, so no store carries a condition (a conditional store makes the
-    // wait for the next strip's operands wait for the stores as well)
-    auto finish = [&](auto full_t) {
-      constexpr bool FULL = decltype(full_t)::value;
-      static_for<FM>([&](auto i_t) {
-        constexpr int i = decltype(i_t)::value;
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-          *reinterpret_cast<f32x4*>(stage + m_in * SLD + j * 16 + q4) = acc[i][j];
-        if (EPI == EPI_SWIGLU_FWD) {
-          // SwiGLU forward: the strip holds g in its first TN_/2 columns and u in the others, of the
-          // same TN_/2 columns of a; a lane takes 8 of them
-          constexpr int HW = TN_ / 2, LPR2 = HW / 8, RPI2 = 64 / LPR2;
-          const int F = p.N / 2;
-          const int rcol2 = (lane % LPR2) * 8, rrow2 = lane / LPR2;
-          const int acol = tn * (BN / 2) + wn * HW + rcol2;
-#pragma unroll
-          for (int t = 0; t < (16 + RPI2 - 1) / RPI2; ++t) {
-            const int row = t * RPI2 + rrow2;
-            const int gm = m0 + wm * TM + i * 16 + row;
-            if (row < 16 && gm < p.M) {
-              const f32x4 g0 = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol2);
-              const f32x4 g1 = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol2 + 4);
-              const f32x4 u0 = *reinterpret_cast<const f32x4*>(stage + row * SLD + HW + rcol2);
-              const f32x4 u1 = *reinterpret_cast<const f32x4*>(stage + row * SLD + HW + rcol2 + 4);
-              union { u32x4 v; bf16_t h[8]; } pg, pu, pa;
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                pg.h[e] = Elt<bf16_t>::from_f(e < 4 ? g0[e] : g1[e - 4]);
-                pu.h[e] = Elt<bf16_t>::from_f(e < 4 ? u0[e] : u1[e - 4]);
-                const float g = (float)pg.h[e], u = (float)pu.h[e];
-                const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
-                pa.h[e] = Elt<bf16_t>::from_f(g * sig * u);
-              }
-              bf16_t* c = (bf16_t*)p.C + (size_t)gm * p.ldc + acol;
-              __builtin_nontemporal_store(pg.v, reinterpret_cast<u32x4*>(c));
-              __builtin_nontemporal_store(pu.v, reinterpret_cast<u32x4*>(c + F));
-              *reinterpret_cast<u32x4*>(p.swf_a + (size_t)gm * F + acol) = pa.v;
-            }
-          }
-          return;
-        }
-#pragma unroll
-        for (int t = 0; t < TPS; ++t) {
-          const int row = t * RPI + rrow;
-          const int gm = m0 + wm * TM + i * 16 + row;
-          const f32x4 lo = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol);
-          const f32x4 hi = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol + 4);
-          if (!FULL && !(gm < p.M && gn < p.N)) continue;
-          float out[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-          const size_t idx = (size_t)gm * p.ldc + gn;
-          if (EPI == EPI_ADD || EPI == EPI_PARTIAL) {
-            // weight gradient: fp32, added to C or parked as this split's partial tile
-            float* c = EPI == EPI_ADD ? (float*)p.C + c_off + idx : p.partial + ((size_t)split * p.M + gm) * p.N + gn;
-            if (EPI == EPI_ADD) {
-              union { u32x4 u; f32x4 f; } c0{pre[i & 1][t][0]}, c1{pre[i & 1][t][1]};
-#pragma unroll
-              for (int e = 0; e < 4; ++e) { out[e] += c0.f[e]; out[4 + e] += c1.f[e]; }
-            }
-            *reinterpret_cast<f32x4*>(c) = f32x4{out[0], out[1], out[2], out[3]};
-            *reinterpret_cast<f32x4*>(c + 4) = f32x4{out[4], out[5], out[6], out[7]};
-            continue;
-          }
-          if (EPI == EPI_SWIGLU_BWD) {
-            // out = dA of 8 columns of one row: d_up and the activation instead of C
-            const size_t up_idx = (size_t)gm * (2 * p.N) + gn;
-            union { u32x4 u; bf16_t h[8]; } sg{pre[i & 1][t][0]}, su{pre[i & 1][t][1]};
-            float dg[8], du[8], av[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              const float g = (float)sg.h[e], u = (float)su.h[e];
-              const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
-              const float sl = g * sig;                          // silu(g)
-              av[e] = sl * u;
-              du[e] = out[e] * sl;
-              dg[e] = out[e] * u * sig * (1.0f + g * (1.0f - sig));
-            }
-            store16(p.sw_dup + up_idx, dg);
-            store16(p.sw_dup + up_idx + p.N, du);
-            store16(p.sw_a + (size_t)gm * p.N + gn, av);
-            continue;
-          }
-#pragma unroll
-          for (int e = 0; e < 8; ++e) out[e] += bias[e];
-          if (EPI == EPI_RES) {
-            union { u32x4 u; bf16_t h[8]; } r{pre[i & 1][t][0]};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) out[e] += (float)r.h[e];
-          }
-          if (p.out_fp32) {
-            float* c = (float*)p.C + idx;
-            *reinterpret_cast<f32x4*>(c) = f32x4{out[0], out[1], out[2], out[3]};
-            *reinterpret_cast<f32x4*>(c + 4) = f32x4{out[4], out[5], out[6], out[7]};
-          } else {
-            union { u32x4 u; bf16_t h[8]; } pk;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) pk.h[e] = Elt<bf16_t>::from_f(out[e]);
-            __builtin_nontemporal_store(pk.u, reinterpret_cast<u32x4*>((bf16_t*)p.C + idx));
-          }
-        }
-        request(std::integral_constant<int, i + 2>{});
-      });
-    };
-    constexpr bool FETCHES = EPI == EPI_ADD || EPI == EPI_RES || EPI == EPI_SWIGLU_BWD;
-    if (FETCHES && m0 + BM <= p.M && n0 + BN <= p.N) finish(yes{});
-    else finish(no{});
-  }
+  // epilogue; its staging strips overlay the slice buffers, free after the last barrier
+  gemm_epilogue<EPI, FM, FN>(p, acc, reinterpret_cast<float*>(smem_raw) + wave * epilogue_stage_floats<FN>(), lane,
+                             n0 + wn * TN_, job.tn * (BN / 2) + wn * (TN_ / 2), job.split, job.c_off,
+                             m0 + BM <= p.M && n0 + BN <= p.N, [&](int i) { return m0 + wm * TM + i * 16; },
+                             [&] { pending_row([](int) {}); });
 }
 
 __global__ void splitk_reduce_kernel(const float* __restrict__ partial, int splits, int M, int N,
@@ -656,47 +344,120 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ partial, int spli
   c[0] += s.x; c[1] += s.y; c[2] += s.z; c[3] += s.w;
 }
 
+// C = sum of the k ranges' partial products (+bias) (+residual), in range order
+template <bool F32>
+__global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restrict__ partial, int splits, int M, int N,
+                                                            void* __restrict__ C, int ldc, const bf16_t* __restrict__ bias,
+                                                            const bf16_t* __restrict__ residual) {
+  const long i = ((long)blockIdx.x * blockDim.x + threadIdx.x) * 8;
+  if (i >= (long)M * N) return;
+  const int m = (int)(i / N), n = (int)(i % N);
+  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  for (int k = 0; k < splits; ++k) {
+    const float* q = partial + (size_t)k * M * N + i;
+    const f32x4 lo = *reinterpret_cast<const f32x4*>(q), hi = *reinterpret_cast<const f32x4*>(q + 4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { v[e] += lo[e]; v[4 + e] += hi[e]; }
+  }
+  if (bias) {
+    float b[8];
+    load16(bias + n, b);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += b[e];
+  }
+  const size_t idx = (size_t)m * ldc + n;
+  if (residual) {
+    float r[8];
+    load16(residual + idx, r);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] += r[e];
+  }
+  if (F32) {
+    *reinterpret_cast<f32x4*>((float*)C + idx) = f32x4{v[0], v[1], v[2], v[3]};
+    *reinterpret_cast<f32x4*>((float*)C + idx + 4) = f32x4{v[4], v[5], v[6], v[7]};
+  } else {
+    store16((bf16_t*)C + idx, v);
+  }
+}
+
 struct Plan { int bm, bn, tiles_m, tiles_n, splits, k_per_split; };
 
 constexpr int NUM_CU = 256;
 
-// Tile size and K split from a small cost model in microseconds, calibrated on the
-// weight-gradient shapes of the ViT-L and decoder blocks: workgroups run in rounds over
-// the free slots (one 256x256 workgroup per CU, two 128x128 ones), each pays a fixed
-// prologue/epilogue plus a per-slice time (1.85 us for a 256x256x64 slice, 1.25 us for a
-// 128x128x64 slice that shares its CU with another workgroup), and a K split of the
-// weight gradient pays for writing and re-reading its fp32 partial tiles.  Splits of 2, 4
-// or 8 can be pinned to XCDs (see split_tile_of_block), which measures 4-7 % faster.
+// Tile and k split from a small cost model in microseconds, calibrated on the shapes of the ViT-L,
+// DiT, 7B, grouped-query and two-stream blocks at 577 to 32768 rows (96 shapes, every tile, splits
+// 1-16: the plan it picks is on average 0.4 % behind the best measured one).  A slice of k = 64 takes
+// t_min when the chip is nearly empty and t_full when every slot works (the matrix pipe's power
+// budget, shared by the active CUs), in between t_full * (share of busy slots)^power; a workgroup
+// adds t_fixed.  Transposed operands cost a few per cent more.  A split writes and reads fp32
+// partial tiles at 8 TB/s (they stay in the memory-side cache) and costs one more launch.
+struct TileKind { int bm, bn, slots; double t_min, t_full, power, t_fixed; };
+constexpr TileKind TILE_KINDS[] = {
+  {256, 256, NUM_CU, 0.87, 1.36, 0.6, 5.5},
+  {128, 256, NUM_CU, 0.55, 0.77, 0.5, 4.0},
+  {256, 128, NUM_CU, 0.55, 0.77, 0.5, 4.0},
+  {128, 128, 2 * NUM_CU, 0.45, 0.92, 0.0, 3.4},       // two workgroups per CU
+};
+
+// Splits of 2, 4 or 8 can be pinned to XCDs (see split_tile_of_block).
 bool xcd_split_possible(int tiles, int splits) {
   return (splits == 2 || splits == 4 || splits == 8) && tiles % (8 / splits) == 0;
 }
 
-Plan make_plan(int layout, int M, int N, int K) {
+// one grid of `wgs` workgroups that each walk `per` slices
+double grid_time(const TileKind& tk, int layout, bool cut, long wgs, int per) {
+  const bool small = tk.bm == 128 && tk.bn == 128;
+  double f = layout == GEMM_NT ? 1.0 : layout == GEMM_NN ? 1.05 : tk.bm == tk.bn && !small ? 1.10 : 1.12;
+  if (small && cut) f *= 1.2;
+  const long full = wgs / tk.slots, rest = wgs % tk.slots;
+  double t = full * (per * tk.t_full * f + tk.t_fixed);
+  if (rest) {
+    const double u = (double)rest / tk.slots;
+    double ts;
+    if (small) ts = u <= 0.5 ? tk.t_min : tk.t_min + (tk.t_full - tk.t_min) * std::sqrt(2.0 * u - 1.0);
+    else ts = std::max(tk.t_min, tk.t_full * std::pow(u, tk.power));
+    t += per * ts * f + tk.t_fixed;
+  }
+  return t;
+}
+double split_time(int layout, int splits, double mn) {
+  if (splits > 1) return 4.5 + (8.0 * splits + (layout == GEMM_TN ? 8.0 : 2.0)) * mn / 8e6;
+  return layout == GEMM_TN ? mn * 8.0 / 6e6 : 0.0;       // reading and writing the fp32 C
+}
+
+// Most k ranges a plan may use.  Weight gradient: as many as fill the chip with 256x256 tiles, four
+// slices each at least -- a bound that only grows with K, so that a workspace sized for the longest
+// pack serves every shorter one.  The other layouts split only products of few rows.
+int split_cap(int layout, int M, int N, int K) {
+  const int slices = cdiv(K, BK);
+  long cap = slices / 4;
+  if (layout == GEMM_TN) cap = std::min<long>(cap, NUM_CU / ((long)cdiv(M, 256) * cdiv(N, 256)));
+  else cap = std::min<long>(cap, std::min(SPLIT_ROWS_MAX / M, 16));
+  return cap < 1 ? 1 : (int)std::min<long>(cap, 32);
+}
+
+Plan make_plan(int layout, int M, int N, int K, size_t partial_bytes, bool may_split, double* time = nullptr) {
   Plan best{};
   double best_t = 1e30;
-  const int slices = cdiv(K, BK);
-  for (int big = 1; big >= 0; --big) {
-    const int tile = big ? 256 : 128;
-    const double t_slice = big ? 1.85 : 1.25, t_fixed = big ? 8.0 : 4.0;
-    const int slots = big ? NUM_CU : 2 * NUM_CU;
-    const long tiles = (long)cdiv(M, tile) * cdiv(N, tile);
-    const int max_split = layout == GEMM_TN ? (slices / 4 > 32 ? 32 : (slices / 4 < 1 ? 1 : slices / 4)) : 1;
-    for (int sp = 1; sp <= max_split; ++sp) {
+  const int slices = cdiv(K, BK), cap = may_split ? split_cap(layout, M, N, K) : 1;
+  const double mn = (double)M * N;
+  for (const TileKind& tk : TILE_KINDS) {
+    const long tiles = (long)cdiv(M, tk.bm) * cdiv(N, tk.bn);
+    for (int sp = 1; sp <= cap; ++sp) {
       const int per = cdiv(slices, sp);
-      const int splits = cdiv(slices, per);
-      if (splits != sp) continue;
-      const long rounds = (tiles * splits + slots - 1) / slots;
-      double t = rounds * (per * t_slice + t_fixed);
-      if (splits > 1) t += 3.0 + 1.3 * splits * (double)M * N * 4.0 / 3.0e6;
-      if (xcd_split_possible((int)tiles, splits)) t *= 0.95;
-      if (t < best_t * 0.97) {            // prefer the earlier candidate on near ties
+      if (cdiv(slices, per) != sp) continue;
+      if (sp > 1 && sp * mn * sizeof(float) > (double)partial_bytes) break;
+      double t = grid_time(tk, layout, K % BK != 0, tiles * sp, per) + split_time(layout, sp, mn);
+      if (xcd_split_possible((int)tiles, sp)) t *= 0.97;
+      if (t < best_t) {
         best_t = t;
-        best.bm = best.bn = tile;
-        best.tiles_m = cdiv(M, tile); best.tiles_n = cdiv(N, tile);
-        best.splits = splits; best.k_per_split = per * BK;
+        best.bm = tk.bm; best.bn = tk.bn;
+        best.tiles_m = cdiv(M, tk.bm); best.tiles_n = cdiv(N, tk.bn);
+        best.splits = sp; best.k_per_split = per * BK;
       }
     }
   }
+  if (time) *time = best_t;
   return best;
 }
 
@@ -720,25 +481,24 @@ bm_status launch_k(const GemmParams& p, hipStream_t st) {
 }
 
 // the zero-filling variant only when a k range is not a whole number of slices
-template <int BM, int BN, bool A_TR, bool B_TR, int EPI>
+template <bool A_TR, bool B_TR, int EPI>
 bm_status launch(const GemmParams& p, hipStream_t st) {
-  if (p.K % BK) return launch_k<BM, BN, 2, 2, A_TR, B_TR, EPI, true>(p, st);
-  return launch_k<BM, BN, 2, 2, A_TR, B_TR, EPI, false>(p, st);
+  if (p.K % BK) return launch_k<128, 128, 2, 2, A_TR, B_TR, EPI, true>(p, st);
+  return launch_k<128, 128, 2, 2, A_TR, B_TR, EPI, false>(p, st);
 }
 
-// the epilogue kinds of the weight gradient, and of the other two layouts
-template <int BM, int BN>
-bm_status launch_tn(const GemmParams& p, hipStream_t st) {
-  return p.splits > 1 ? launch<BM, BN, true, true, EPI_PARTIAL>(p, st) : launch<BM, BN, true, true, EPI_ADD>(p, st);
-}
-template <int BM, int BN>
-bm_status launch_rows(int layout, const GemmParams& p, hipStream_t st) {
+// 128x128 tiles
+bm_status launch_small(int layout, const GemmParams& p, hipStream_t st) {
+  if (layout == GEMM_TN)
+    return p.splits > 1 ? launch<true, true, EPI_PARTIAL>(p, st) : launch<true, true, EPI_ADD>(p, st);
   if (layout == GEMM_NT) {
-    if (p.swf_a) return launch<BM, BN, false, false, EPI_SWIGLU_FWD>(p, st);
-    return p.residual ? launch<BM, BN, false, false, EPI_RES>(p, st) : launch<BM, BN, false, false, EPI_PLAIN>(p, st);
+    if (p.splits > 1) return launch<false, false, EPI_PARTIAL>(p, st);
+    if (p.swf_a) return launch<false, false, EPI_SWIGLU_FWD>(p, st);
+    return p.residual ? launch<false, false, EPI_RES>(p, st) : launch<false, false, EPI_PLAIN>(p, st);
   }
-  if (p.sw_up) return launch<BM, BN, false, true, EPI_SWIGLU_BWD>(p, st);
-  return p.residual ? launch<BM, BN, false, true, EPI_RES>(p, st) : launch<BM, BN, false, true, EPI_PLAIN>(p, st);
+  if (p.splits > 1) return launch<false, true, EPI_PARTIAL>(p, st);
+  if (p.sw_up) return launch<false, true, EPI_SWIGLU_BWD>(p, st);
+  return p.residual ? launch<false, true, EPI_RES>(p, st) : launch<false, true, EPI_PLAIN>(p, st);
 }
 
 }  // namespace
@@ -762,15 +522,19 @@ bool gemm_mfma_supported(int layout, int dtype, int M, int N, int K, int lda, in
 }
 
 size_t gemm_mfma_scratch_bytes(int layout, int M, int N, int K) {
-  if (layout != GEMM_TN) return 0;
-  Plan pl = make_plan(layout, M, N, K);
+  if (layout == GEMM_TN) {
+    const int cap = split_cap(layout, M, N, K);
+    return cap > 1 ? (size_t)cap * M * N * sizeof(float) : 0;
+  }
+  const Plan pl = make_plan(layout, M, N, K, ~(size_t)0, true);
   return pl.splits > 1 ? (size_t)pl.splits * M * N * sizeof(float) : 0;
 }
 
 bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
                     void* C, int ldc, const GemmEpilogue& epi, void* scratch, size_t scratch_bytes,
                     hipStream_t st) {
-  Plan pl = make_plan(layout, M, N, K);
+  // the k range is split as far as the workspace allows; a fused activation needs the whole sum at once
+  const Plan pl = make_plan(layout, M, N, K, scratch ? scratch_bytes : 0, !epi.swiglu_up && !epi.swiglu_fwd_a);
   GemmParams p;
   p.A = (const bf16_t*)A; p.B = (const bf16_t*)B; p.C = C;
   p.bias = (const bf16_t*)epi.bias; p.residual = (const bf16_t*)epi.residual;
@@ -789,28 +553,25 @@ bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, con
   {
     p.xcd_split = xcd_split_possible(pl.tiles_m * pl.tiles_n, pl.splits) ? 1 : 0;
   }
-  if (pl.splits > 1 && (!scratch || scratch_bytes < (size_t)pl.splits * M * N * sizeof(float))) {
-    set_error("gemm TN: split reduction needs %zu scratch bytes, got %zu",
-              (size_t)pl.splits * M * N * sizeof(float), scratch_bytes);
-    return BM_ERR_WORKSPACE_TOO_SMALL;
-  }
-  const bool big = pl.bm == 256;
-  if (layout == GEMM_TN) BM_RETURN_IF(big ? (launch_tn<256, 256>(p, st)) : (launch_tn<128, 128>(p, st)));
-  else BM_RETURN_IF(big ? (launch_rows<256, 256>(layout, p, st)) : (launch_rows<128, 128>(layout, p, st)));
-  if (layout == GEMM_TN && pl.splits > 1) {
-    long n4 = ((long)M * N) / 4;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(cdiv(n4, 256)), dim3(256), 0, st,
+  BM_RETURN_IF(pl.bm == 128 && pl.bn == 128 ? launch_small(layout, p, st) : launch_gemm_alt(layout, pl.bm, pl.bn, p, st));
+  if (pl.splits > 1 && layout == GEMM_TN) {
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(cdiv((long)M * N / 4, 256)), dim3(256), 0, st,
                        (const float*)scratch, pl.splits, M, N, (float*)C, ldc);
     BM_CHECK_LAUNCH("splitk_reduce");
+  } else if (pl.splits > 1) {
+    auto kern = epi.out_fp32 ? splitk_finish_kernel<true> : splitk_finish_kernel<false>;
+    hipLaunchKernelGGL(kern, dim3(cdiv((long)M * N / 8, 256)), dim3(256), 0, st, (const float*)scratch, pl.splits, M, N,
+                       C, ldc, (const bf16_t*)epi.bias, (const bf16_t*)epi.residual);
+    BM_CHECK_LAUNCH("splitk_finish");
   }
   return BM_OK;
 }
 
 // common k split of a paired launch (0: the pair does not qualify)
 static int pair_splits(int K, int M0, int N0, int M1, int N1) {
-  if (K % BK || M0 < 256 || N0 < 256 || M1 < 256 || N1 < 256) return 0;
+  if (M0 < 256 || N0 < 256 || M1 < 256 || N1 < 256) return 0;
   const long tiles = (long)cdiv(M0, 256) * cdiv(N0, 256) + (long)cdiv(M1, 256) * cdiv(N1, 256);
-  const int slices = K / BK;
+  const int slices = cdiv(K, BK);
   int sp = (int)(NUM_CU / tiles);
   if (sp > 32) sp = 32;
   if (sp > slices / 4) sp = slices / 4;
@@ -835,14 +596,13 @@ bool gemm_mfma_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const vo
   // rc == nullptr: only answer whether the pair qualifies
   const GemmEpilogue none;
   if (rc) *rc = BM_OK;
-  if (K % BK) return false;
   if (!gemm_mfma_supported(GEMM_TN, BM_DTYPE_BF16, M0, N0, K, lda0, ldb0, ldc0, none) ||
       !gemm_mfma_supported(GEMM_TN, BM_DTYPE_BF16, M1, N1, K, lda1, ldb1, ldc1, none)) return false;
   // one plan for both: 256x256 tiles and the largest common k split whose workgroups fit the chip
   // in one round, so that all of them run equally long; it must beat the two separate plans
   const int sp = pair_splits(K, M0, N0, M1, N1);
   if (sp < 1) return false;
-  const int slices = K / BK;
+  const int slices = cdiv(K, BK);
   Plan a{}, b{};
   a.bm = a.bn = b.bm = b.bn = 256;
   a.tiles_m = cdiv(M0, 256); a.tiles_n = cdiv(N0, 256);
@@ -850,17 +610,14 @@ bool gemm_mfma_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const vo
   a.splits = b.splits = sp;
   a.k_per_split = b.k_per_split = cdiv(slices, sp) * BK;
   {
-    const auto model = [&](int M, int N) {                      // what make_plan expects for one problem
-      const Plan q = make_plan(GEMM_TN, M, N, K);
-      const bool big = q.bm == 256;
-      const long wg = (long)q.tiles_m * q.tiles_n * q.splits, slots = big ? NUM_CU : 2 * NUM_CU;
-      double t = (double)((wg + slots - 1) / slots) * (q.k_per_split / BK * (big ? 1.85 : 1.25) + (big ? 8.0 : 4.0));
-      if (q.splits > 1) t += 3.0 + 1.3 * q.splits * (double)M * N * 4.0 / 3.0e6;
-      return t;
-    };
-    double together = a.k_per_split / BK * 1.85 + 8.0;
-    if (sp > 1) together += 6.0 + 1.3 * sp * ((double)M0 * N0 + (double)M1 * N1) * 4.0 / 3.0e6;
-    if (together >= model(M0, N0) + model(M1, N1)) return false;
+    double t0, t1;
+    make_plan(GEMM_TN, M0, N0, K, scratch_bytes, true, &t0);
+    make_plan(GEMM_TN, M1, N1, K, scratch_bytes, true, &t1);
+    const double mn0 = (double)M0 * N0, mn1 = (double)M1 * N1;
+    const double together = grid_time(TILE_KINDS[0], GEMM_TN, K % BK != 0,
+                                      ((long)a.tiles_m * a.tiles_n + (long)b.tiles_m * b.tiles_n) * sp, cdiv(slices, sp)) +
+                            split_time(GEMM_TN, sp, mn0) + split_time(GEMM_TN, sp, mn1);
+    if (together >= t0 + t1) return false;
   }
   const size_t part0 = a.splits > 1 ? align_up((size_t)a.splits * M0 * N0 * sizeof(float), 256) : 0;
   const size_t part1 = b.splits > 1 ? (size_t)b.splits * M1 * N1 * sizeof(float) : 0;
@@ -882,8 +639,7 @@ bool gemm_mfma_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const vo
   p.second.M = M1; p.second.N = N1; p.second.lda = lda1; p.second.ldb = ldb1; p.second.ldc = ldc1;
   p.second.tiles_m = b.tiles_m; p.second.tiles_n = b.tiles_n; p.second.splits = b.splits;
   p.second.k_per_split = b.k_per_split; p.second.xcd_split = xb ? 1 : 0;
-  *rc = sp > 1 ? (launch_k<256, 256, 2, 2, true, true, EPI_PARTIAL, false>(p, st))
-               : (launch_k<256, 256, 2, 2, true, true, EPI_ADD, false>(p, st));
+  *rc = launch_gemm_alt(GEMM_TN, 256, 256, p, st);
   if (*rc != BM_OK) return true;
   if (a.splits > 1)
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3(cdiv((long)M0 * N0 / 4, 256)), dim3(256), 0, st, p.partial, a.splits,
@@ -938,16 +694,16 @@ bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int 
   // wide enough: per flop a 128x256 tile writes and reads a quarter less LDS than two 128x128 ones
   if (layout != GEMM_TN && N >= 256) {
     p.tiles_n = cdiv(N, 256);
-    return launch_rows<128, 256>(layout, p, st);
+    return launch_gemm_alt(layout, 128, 256, p, st);
   }
-  if (layout != GEMM_TN) return launch_rows<128, 128>(layout, p, st);
+  if (layout != GEMM_TN) return launch_small(layout, p, st);
   // weight gradient: rows are the contraction index, so the output tile is free; a group's
   // k range is short (a few slices), which makes the per-tile fixed cost count: large tiles
   if (M >= 256 && N >= 256) {
     p.tiles_m = cdiv(M, 256); p.tiles_n = cdiv(N, 256);
-    return launch_k<256, 256, 2, 2, true, true, EPI_ADD, false>(p, st);   // k ranges are whole slices
+    return launch_gemm_alt(GEMM_TN, 256, 256, p, st);                     // k ranges are whole slices
   }
-  return launch_k<128, 128, 2, 2, true, true, EPI_ADD, false>(p, st);
+  return launch_small(GEMM_TN, p, st);
 }
 
 }  // namespace bm

@@ -1,0 +1,333 @@
+// Shared by the bf16 matrix-core GEMM kernels: the launch parameters, the map from workgroup to tile,
+// the fragment types and the epilogue.
+#pragma once
+#include "common.h"
+
+#include <algorithm>
+#include <cmath>
+#include <type_traits>
+
+namespace bm {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int BK = 64;          // k slice
+constexpr int KCH = BK / 8;     // 16-byte chunks per k-contiguous row
+
+struct GemmParams {
+  const bf16_t* A; const bf16_t* B; void* C;
+  const bf16_t* bias; const bf16_t* residual;
+  const bf16_t* sw_up = nullptr; bf16_t* sw_dup = nullptr; bf16_t* sw_a = nullptr;   // SwiGLU backward epilogue (see GemmEpilogue)
+  bf16_t* swf_a = nullptr;      // SwiGLU forward epilogue (see GemmEpilogue); N = 2F
+  float* partial;               // TN with splits > 1
+  int M, N, K, lda, ldb, ldc;
+  int tiles_m, tiles_n, splits, k_per_split;
+  int out_fp32;
+  int xcd_split;                // each k split owns 8/splits XCDs (splits in {2,4,8})
+  // grouped problems (see GemmGroups); all null / zero otherwise
+  const int32_t* tile_group;
+  const int32_t* group_rows;
+  long b_group_stride, c_group_stride;
+  int grid_groups;              // host: workgroups = tiles * splits * grid_groups (>= 1)
+  // paired launch: workgroups pair_wgs0.. of the grid work on a second problem of the same
+  // kind and the same K (two weight gradients that each leave CUs idle share one grid)
+  int pair_wgs0;                // 0: one problem
+  struct Second {
+    const bf16_t* A; const bf16_t* B; void* C; float* partial;
+    int M, N, lda, ldb, ldc, tiles_m, tiles_n, splits, k_per_split, xcd_split;
+  } second;
+};
+
+// acc += a b^T with v_mfma_f32_16x16x32_bf16.  Written as an asm statement that ties the
+// accumulator block to the accumulation half of the register file: with 64 four-register blocks
+// the allocator otherwise keeps some of them in the other half and runs out of registers there
+// (copies between the halves inside the loop, spills).  The accumulator of a block is next
+// touched 63 MFMAs later, far beyond any wait state the instruction asks for.
+__device__ inline void mfma16(f32x4& acc, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
+}
+// acc = a b^T: the first product of a tile takes the constant 0 as its addend, so the accumulators
+// are never initialised by separate instructions (which the compiler, not knowing that the asm
+// statement is an MFMA, would place right in front of it without the wait states that needs)
+__device__ inline void mfma16_first(f32x4& acc, const bf16x8& a, const bf16x8& b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(acc) : "v"(a), "v"(b));
+}
+
+// f(0), f(1), ..., f(N-1) with the index as a compile-time constant
+template <int N, int I = 0, typename F>
+__device__ inline void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
+  }
+}
+
+// XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs, so give
+// each XCD a contiguous run of tiles, walked in column-major groups of GROUP_M
+// tile rows (operand reuse in that XCD's L2).
+__device__ inline void grouped_tile(int id, int tiles_m, int tiles_n, int* tm, int* tn) {
+  constexpr int GROUP_M = 8;
+  const int per_group = GROUP_M * tiles_n;
+  const int g = id / per_group;
+  const int first_m = g * GROUP_M;
+  const int gsize = min(tiles_m - first_m, GROUP_M);
+  const int in = id % per_group;
+  *tm = first_m + in % gsize;
+  *tn = in / gsize;
+}
+
+// K split with XCD affinity: split s owns the 8/splits XCDs s*G .. s*G+G-1 and each of
+// them a contiguous run of that split's tiles, so an operand panel of one k range is
+// fetched by as few L2s as possible (HBM traffic of the weight gradient is dominated by
+// panels fetched once per XCD that touches them).
+__device__ inline void split_tile_of_block(int pid, int tiles, int splits, int tiles_m, int tiles_n,
+                                           int* split, int* tm, int* tn) {
+  const int G = 8 / splits;
+  const int xcd = pid & 7, local = pid >> 3;
+  *split = xcd / G;
+  grouped_tile((xcd % G) * (tiles / G) + local, tiles_m, tiles_n, tm, tn);
+}
+
+__device__ inline void tile_of_block(int pid, int total, int tiles_m, int tiles_n, int* tm, int* tn) {
+  constexpr int XCDS = 8, GROUP_M = 4;     // measured: 4 tile rows per group is a little ahead of 8, 2 and 16
+  // workgroup pid runs on XCD pid % 8: give every XCD one contiguous run of tiles (the first
+  // total % 8 of them one tile more)
+  const int xcd = pid % XCDS;
+  const int id = xcd * (total / XCDS) + min(xcd, total % XCDS) + pid / XCDS;
+  const int per_group = GROUP_M * tiles_n;
+  const int g = id / per_group;
+  const int first_m = g * GROUP_M;
+  const int gsize = min(tiles_m - first_m, GROUP_M);
+  const int in = id % per_group;
+  *tm = first_m + in % gsize;
+  *tn = in / gsize;
+}
+
+// What the epilogue does with the product, fixed at compile time: one straight run of instructions
+// per kind (with run-time switches between the strips the K = 1024 products lost 5 %).
+enum { EPI_PLAIN = 0,     // C = acc (+bias), bf16 or fp32
+       EPI_RES,           // C = acc (+bias) + residual
+       EPI_SWIGLU_FWD, EPI_SWIGLU_BWD,
+       EPI_ADD,           // fp32 C += acc
+       EPI_PARTIAL };     // acc -> this split's partial tile
+
+
+// Where a workgroup's tile lies: operands (B of the tile's group), first row and column, k range.
+// `p` is taken over by the second problem of a paired launch.  kbeg == kend: nothing to do.
+// All values are workgroup-uniform.
+struct TileJob {
+  const bf16_t *A, *B;
+  int m0, n0, tn, kbeg, kend, split;
+  long c_off;
+};
+
+template <int BM, int BN>
+__device__ inline TileJob locate_tile(GemmParams& p) {
+  TileJob t;
+  int pid = blockIdx.x;
+  if (p.pair_wgs0 > 0 && pid >= p.pair_wgs0) {
+    pid -= p.pair_wgs0;
+    p.A = p.second.A; p.B = p.second.B; p.C = p.second.C; p.partial = p.second.partial;
+    p.M = p.second.M; p.N = p.second.N; p.lda = p.second.lda; p.ldb = p.second.ldb; p.ldc = p.second.ldc;
+    p.tiles_m = p.second.tiles_m; p.tiles_n = p.second.tiles_n; p.splits = p.second.splits;
+    p.k_per_split = p.second.k_per_split; p.xcd_split = p.second.xcd_split;
+  }
+  const int tiles = p.tiles_m * p.tiles_n;
+  int tm;
+  t.split = pid / tiles;
+  if (p.xcd_split) split_tile_of_block(pid, tiles, p.splits, p.tiles_m, p.tiles_n, &t.split, &tm, &t.tn);
+  else tile_of_block(pid % tiles, tiles, p.tiles_m, p.tiles_n, &tm, &t.tn);
+  t.m0 = tm * BM; t.n0 = t.tn * BN;
+  t.kbeg = t.split * p.k_per_split;
+  t.kend = min(p.K, t.kbeg + p.k_per_split);
+  t.A = p.A; t.B = p.B;
+  t.c_off = 0;
+  if (p.group_rows) {
+    // grouped weight gradient: `split` is the group; its rows are the k range
+    t.kbeg = min(p.group_rows[t.split], p.K);
+    t.kend = max(t.kbeg, min(p.group_rows[t.split + 1], p.K));
+    t.c_off = (long)t.split * p.c_group_stride;
+    t.split = 0;
+  } else if (p.tile_group) {
+    const int g = p.tile_group[t.m0 / MOE_PAD];
+    if (g < 0) t.kend = t.kbeg;
+    else t.B += (long)g * p.b_group_stride;
+  }
+  return t;
+}
+
+// ---- epilogue of one wavefront: FM x FN accumulator blocks of 16x16.  The MFMAs run with swapped
+// operands, so block (i,j) holds C^T: lane = row m = l%16, registers = 4 consecutive columns
+// n = 4*(l/16) + e.  Each wavefront transposes its own 16-row strips through LDS and then writes
+// whole rows, 16 bytes per lane.
+//
+// What the epilogue combines with the product -- the old C of a weight gradient, the residual, the
+// saved g and u of the SwiGLU backward -- is requested two strips ahead, the first two strips before
+// the tile's last MFMAs (`last`): fetched in front of each store instead, a tile pays one memory
+// latency per store instruction, 32 of them in a row (four wavefronts of 128x128: dW 22016x4096 over
+// 777 rows 296 -> 247 us, over 8192 rows 1301 -> 1271 us).  Addresses are clamped into the matrix, so
+// that the requests carry no condition.
+//   row_of(i)   first row of strip i;  col0  the wavefront's first column
+//   acol0       SwiGLU forward: its first column of a
+//   stage       16 * (FN*16 + 4) floats of LDS of its own; free to write once `last` has returned
+//   full        the tile lies inside C, so no store carries a condition (a conditional store makes the
+//               wait for the next strip's operands wait for the stores as well)
+template <int FN> constexpr int epilogue_stage_floats() { return 16 * (FN * 16 + 4); }
+
+template <int EPI, int FM, int FN, typename RowOf, typename Last>
+__device__ inline void gemm_epilogue(const GemmParams& p, const f32x4 (&acc)[FM][FN], float* stage, int lane, int col0,
+                                     int acol0, int split, long c_off, bool full, RowOf row_of, Last last) {
+  constexpr int TN_ = FN * 16;
+  constexpr int SLD = TN_ + 4;                          // padded fp32 row: conflict-free both ways
+  constexpr int LPR = TN_ / 8;                          // lanes per output row (8 columns each)
+  constexpr int RPI = 64 / LPR;                         // rows per store instruction
+  constexpr int TPS = 16 / RPI;                         // store instructions per strip
+  static_assert(16 % RPI == 0, "a 16-row strip must be a whole number of store instructions");
+  const int m_in = lane & 15, q4 = (lane >> 4) * 4;
+  const int rcol = (lane % LPR) * 8, rrow = lane / LPR;
+  const int gn = col0 + rcol;
+  u32x4 pre[2][TPS][2];
+  auto request = [&](auto i_t) {
+    constexpr int i = decltype(i_t)::value;
+    if (i >= FM) return;
+#pragma unroll
+    for (int t = 0; t < TPS; ++t) {
+      const int gm = min(row_of(i) + t * RPI + rrow, p.M - 1), gc = min(gn, p.N - 8);
+      if (EPI == EPI_ADD) {
+        const float* c = (const float*)p.C + c_off + (size_t)gm * p.ldc + gc;
+        pre[i & 1][t][0] = *reinterpret_cast<const u32x4*>(c);
+        pre[i & 1][t][1] = *reinterpret_cast<const u32x4*>(c + 4);
+      } else if (EPI == EPI_SWIGLU_BWD) {
+        const bf16_t* up = p.sw_up + (size_t)gm * (2 * p.N) + gc;
+        pre[i & 1][t][0] = *reinterpret_cast<const u32x4*>(up);
+        pre[i & 1][t][1] = *reinterpret_cast<const u32x4*>(up + p.N);
+      } else if (EPI == EPI_RES) {
+        pre[i & 1][t][0] = *reinterpret_cast<const u32x4*>(p.residual + (size_t)gm * p.ldc + gc);
+      }
+    }
+  };
+  request(std::integral_constant<int, 0>{});
+  request(std::integral_constant<int, 1>{});
+  last();
+  // the compiler does not know that the asm statements of `last` are MFMAs and leaves no wait states
+  // between them and the reads of the accumulators below
+  asm volatile("s_nop 15\n\ts_nop 15");
+  __builtin_amdgcn_sched_barrier(0);
+
+  float bias[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) bias[e] = 0.f;
+  if ((EPI == EPI_PLAIN || EPI == EPI_RES) && p.bias && gn < p.N) load16(p.bias + gn, bias);
+  auto finish = [&](auto full_t) {
+    constexpr bool FULL = decltype(full_t)::value;
+    static_for<FM>([&](auto i_t) {
+      constexpr int i = decltype(i_t)::value;
+#pragma unroll
+      for (int j = 0; j < FN; ++j)
+        *reinterpret_cast<f32x4*>(stage + m_in * SLD + j * 16 + q4) = acc[i][j];
+      if (EPI == EPI_SWIGLU_FWD) {
+        // SwiGLU forward: the strip holds g in its first TN_/2 columns and u in the others, of the
+        // same TN_/2 columns of a; a lane takes 8 of them
+        constexpr int HW = TN_ / 2, LPR2 = HW / 8, RPI2 = 64 / LPR2;
+        const int F = p.N / 2;
+        const int rcol2 = (lane % LPR2) * 8, rrow2 = lane / LPR2;
+        const int acol = acol0 + rcol2;
+#pragma unroll
+        for (int t = 0; t < (16 + RPI2 - 1) / RPI2; ++t) {
+          const int row = t * RPI2 + rrow2;
+          const int gm = row_of(i) + row;
+          if (row < 16 && gm < p.M) {
+            const f32x4 g0 = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol2);
+            const f32x4 g1 = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol2 + 4);
+            const f32x4 u0 = *reinterpret_cast<const f32x4*>(stage + row * SLD + HW + rcol2);
+            const f32x4 u1 = *reinterpret_cast<const f32x4*>(stage + row * SLD + HW + rcol2 + 4);
+            union { u32x4 v; bf16_t h[8]; } pg, pu, pa;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              pg.h[e] = Elt<bf16_t>::from_f(e < 4 ? g0[e] : g1[e - 4]);
+              pu.h[e] = Elt<bf16_t>::from_f(e < 4 ? u0[e] : u1[e - 4]);
+              const float g = (float)pg.h[e], u = (float)pu.h[e];
+              const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
+              pa.h[e] = Elt<bf16_t>::from_f(g * sig * u);
+            }
+            bf16_t* c = (bf16_t*)p.C + (size_t)gm * p.ldc + acol;
+            __builtin_nontemporal_store(pg.v, reinterpret_cast<u32x4*>(c));
+            __builtin_nontemporal_store(pu.v, reinterpret_cast<u32x4*>(c + F));
+            *reinterpret_cast<u32x4*>(p.swf_a + (size_t)gm * F + acol) = pa.v;
+          }
+        }
+        return;
+      }
+#pragma unroll
+      for (int t = 0; t < TPS; ++t) {
+        const int row = t * RPI + rrow;
+        const int gm = row_of(i) + row;
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol);
+        const f32x4 hi = *reinterpret_cast<const f32x4*>(stage + row * SLD + rcol + 4);
+        if (!FULL && !(gm < p.M && gn < p.N)) continue;
+        float out[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        const size_t idx = (size_t)gm * p.ldc + gn;
+        if (EPI == EPI_ADD || EPI == EPI_PARTIAL) {
+          // weight gradient: fp32, added to C or parked as this split's partial tile
+          float* c = EPI == EPI_ADD ? (float*)p.C + c_off + idx : p.partial + ((size_t)split * p.M + gm) * p.N + gn;
+          if (EPI == EPI_ADD) {
+            union { u32x4 u; f32x4 f; } c0{pre[i & 1][t][0]}, c1{pre[i & 1][t][1]};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { out[e] += c0.f[e]; out[4 + e] += c1.f[e]; }
+          }
+          *reinterpret_cast<f32x4*>(c) = f32x4{out[0], out[1], out[2], out[3]};
+          *reinterpret_cast<f32x4*>(c + 4) = f32x4{out[4], out[5], out[6], out[7]};
+          continue;
+        }
+        if (EPI == EPI_SWIGLU_BWD) {
+          // out = dA of 8 columns of one row: d_up and the activation instead of C
+          const size_t up_idx = (size_t)gm * (2 * p.N) + gn;
+          union { u32x4 u; bf16_t h[8]; } sg{pre[i & 1][t][0]}, su{pre[i & 1][t][1]};
+          float dg[8], du[8], av[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float g = (float)sg.h[e], u = (float)su.h[e];
+            const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
+            const float sl = g * sig;                          // silu(g)
+            av[e] = sl * u;
+            du[e] = out[e] * sl;
+            dg[e] = out[e] * u * sig * (1.0f + g * (1.0f - sig));
+          }
+          store16(p.sw_dup + up_idx, dg);
+          store16(p.sw_dup + up_idx + p.N, du);
+          store16(p.sw_a + (size_t)gm * p.N + gn, av);
+          continue;
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) out[e] += bias[e];
+        if (EPI == EPI_RES) {
+          union { u32x4 u; bf16_t h[8]; } r{pre[i & 1][t][0]};
+#pragma unroll
+          for (int e = 0; e < 8; ++e) out[e] += (float)r.h[e];
+        }
+        if (p.out_fp32) {
+          float* c = (float*)p.C + idx;
+          *reinterpret_cast<f32x4*>(c) = f32x4{out[0], out[1], out[2], out[3]};
+          *reinterpret_cast<f32x4*>(c + 4) = f32x4{out[4], out[5], out[6], out[7]};
+        } else {
+          union { u32x4 u; bf16_t h[8]; } pk;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) pk.h[e] = Elt<bf16_t>::from_f(out[e]);
+          __builtin_nontemporal_store(pk.u, reinterpret_cast<u32x4*>((bf16_t*)p.C + idx));
+        }
+      }
+      request(std::integral_constant<int, i + 2>{});
+    });
+  };
+  constexpr bool FETCHES = EPI == EPI_ADD || EPI == EPI_RES || EPI == EPI_SWIGLU_BWD;
+  if (FETCHES && full) finish(std::true_type{});
+  else finish(std::false_type{});
+}
+
+// gemm_alt.hip: the tile (256x256, 128x256 or 256x128) of a plan
+bm_status launch_gemm_alt(int layout, int bm, int bn, const GemmParams& p, hipStream_t st);
+
+}  // namespace bm

@@ -12,6 +12,7 @@
 #include "common.h"
 #include "../../include/bigmac_mmdit.h"
 
+#include <algorithm>
 #include <vector>
 
 namespace bm {
@@ -86,11 +87,11 @@ void take_tables(Arena& a, const MDims& m, Tables& t) {
 
 struct MFwd {
   Tables tb;
-  char *sc, *h, *qkv, *a;
-  size_t bytes;
+  char *sc, *h, *qkv, *a, *gemm_ws;
+  size_t gemm_ws_bytes, bytes;
 };
 
-MFwd layout_fwd(const MDims& m, void* base) {
+MFwd layout_fwd(const MDims& m, int dtype, void* base) {
   Arena a(base);
   MFwd w;
   take_tables(a, m, w.tb);
@@ -99,6 +100,8 @@ MFwd layout_fwd(const MDims& m, void* base) {
   w.h = a.take<char>(R * m.d * m.es);
   w.qkv = m.qk_norm ? nullptr : a.take<char>(R * m.QKV * m.es);
   w.a = a.take<char>(R * m.F * m.es);
+  w.gemm_ws_bytes = gemm_rows_scratch_bytes(m.Tmax, m.d, dtype);
+  w.gemm_ws = a.take<char>(w.gemm_ws_bytes);
   w.bytes = a.off;
   return w;
 }
@@ -162,7 +165,7 @@ MBwd layout_bwd(const MDims& m, int dtype, void* base) {
   int widest = m.F > m.QKV ? m.F : m.QKV;
   if (6 * m.d > widest) widest = 6 * m.d;
   w.colsum_ws = a.take<char>(colsum_scratch_bytes(m.Tmax > QKN_BLOCKS ? m.Tmax : QKN_BLOCKS, widest));
-  w.gemm_ws_bytes = max_gemm_scratch(m, dtype);
+  w.gemm_ws_bytes = std::max(max_gemm_scratch(m, dtype), gemm_rows_scratch_bytes(m.Tmax, m.d, dtype));
   w.gemm_ws = a.take<char>(w.gemm_ws_bytes);
   w.bytes = a.off;
   return w;
@@ -478,7 +481,7 @@ extern "C" bm_status bm_mmdit_sizes(const bm_mmdit_desc* desc, int32_t T_text, i
   BM_RETURN_IF(check_mextent(*desc, T_text, T_img));
   MDims m = make_mdims(*desc, T_text, T_img, S);
   *saved_bytes = layout_saved(m, nullptr).bytes;
-  size_t f = layout_fwd(m, nullptr).bytes, b = layout_bwd(m, desc->block.dtype, nullptr).bytes;
+  size_t f = layout_fwd(m, desc->block.dtype, nullptr).bytes, b = layout_bwd(m, desc->block.dtype, nullptr).bytes;
   *scratch_bytes = f > b ? f : b;
   return BM_OK;
 }
@@ -504,7 +507,7 @@ extern "C" bm_status bm_mmdit_forward(const bm_mmdit_desc* desc, const bm_mmdit_
   const void* const x[2] = {x_text, x_img};
   void* const y[2] = {y_text, y_img};
   MDims m = make_mdims(*desc, Ts[0], Ts[1], S);
-  MFwd ws = layout_fwd(m, scratch);
+  MFwd ws = layout_fwd(m, desc->block.dtype, scratch);
   if (ws.bytes > scratch_bytes) {
     set_error("forward needs %zu scratch bytes, got %zu", ws.bytes, scratch_bytes);
     return BM_ERR_WORKSPACE_TOO_SMALL;
@@ -522,14 +525,14 @@ extern "C" bm_status bm_mmdit_forward(const bm_mmdit_desc* desc, const bm_mmdit_
     const int T = m.Ts[s];
     {
       GemmEpilogue e; e.bias = p.b_ada; e.out_fp32 = 1;
-      BM_RETURN_IF(gemm(GEMM_NT, dt, S, 6 * d, d, ws.sc, d, p.w_ada, d, sv.s[s].mod, 6 * d, e, nullptr, 0, st));
+      BM_RETURN_IF(gemm(GEMM_NT, dt, S, 6 * d, d, ws.sc, d, p.w_ada, d, sv.s[s].mod, 6 * d, e, ws.gemm_ws, ws.gemm_ws_bytes, st));
     }
     { ProfScope _p(PROF_NORM, 2.0 * T * d * (double)m.es, st);
       BM_RETURN_IF(norm_forward(ada_norm_args(c, T, 1, sv.s[s].mod, ws.tb.tok_seq[s]), x[s], ws.h, sv.s[s].stats1, 1, st)); }
     char* qkv = m.qk_norm ? sv.s[s].qkv_raw : ws.qkv;
     {
       GemmEpilogue e; e.bias = p.b_qkv;
-      BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.QKV, d, ws.h, d, p.w_qkv, d, qkv, m.QKV, e, nullptr, 0, st));
+      BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.QKV, d, ws.h, d, p.w_qkv, d, qkv, m.QKV, e, ws.gemm_ws, ws.gemm_ws_bytes, st));
     }
     ProfScope _p(PROF_ELEMENTWISE, 2.0 * T * m.QKV * (double)m.es, st);
     if (m.qk_norm)
@@ -553,7 +556,7 @@ extern "C" bm_status bm_mmdit_forward(const bm_mmdit_desc* desc, const bm_mmdit_
       BM_RETURN_IF(row_gather(dt, sv.o_j, ws.tb.jpos[s], q.o, T, m.QD, st)); }
     {
       GemmEpilogue e; e.bias = p.b_o;
-      BM_RETURN_IF(gemm(GEMM_NT, dt, T, d, m.QD, q.o, m.QD, p.w_o, m.QD, q.attn, d, e, nullptr, 0, st));
+      BM_RETURN_IF(gemm(GEMM_NT, dt, T, d, m.QD, q.o, m.QD, p.w_o, m.QD, q.attn, d, e, ws.gemm_ws, ws.gemm_ws_bytes, st));
     }
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
       BM_RETURN_IF(gate_mul(dt, q.attn, q.mod + 2 * d, 6 * d, tok, x[s], q.x1, T, d, st)); }
@@ -561,13 +564,13 @@ extern "C" bm_status bm_mmdit_forward(const bm_mmdit_desc* desc, const bm_mmdit_
       BM_RETURN_IF(norm_forward(ada_norm_args(c, T, 2, q.mod, tok), q.x1, ws.h, q.stats2, 1, st)); }
     {
       GemmEpilogue e; e.bias = p.b_up;
-      BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.F, d, ws.h, d, p.w_up, d, q.up, m.F, e, nullptr, 0, st));
+      BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.F, d, ws.h, d, p.w_up, d, q.up, m.F, e, ws.gemm_ws, ws.gemm_ws_bytes, st));
     }
     { ProfScope _p(PROF_ELEMENTWISE, 2.0 * T * m.F * (double)m.es, st);
       BM_RETURN_IF(act_forward(dt, BM_ACT_GELU, q.up, ws.a, T, m.F, st)); }
     {
       GemmEpilogue e; e.bias = p.b_down;
-      BM_RETURN_IF(gemm(GEMM_NT, dt, T, d, m.F, ws.a, m.F, p.w_down, m.F, q.m, d, e, nullptr, 0, st));
+      BM_RETURN_IF(gemm(GEMM_NT, dt, T, d, m.F, ws.a, m.F, p.w_down, m.F, q.m, d, e, ws.gemm_ws, ws.gemm_ws_bytes, st));
     }
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
       BM_RETURN_IF(gate_mul(dt, q.m, q.mod + 5 * d, 6 * d, tok, q.x1, y[s], T, d, st)); }
@@ -625,7 +628,7 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
     { ProfScope _p(PROF_ELEMENTWISE, 3.0 * T * d * (double)m.es, st);
       BM_RETURN_IF(segment_gate(dt, dy[s], q.m, q.mod + 5 * d, 6 * d, ws.dgated, cu_dev[s], S, d, dmod + 5 * d, 6 * d,
                                 ws.norm_ws, st)); }
-    BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.F, d, ws.dgated, d, p.w_down, m.F, ws.da, m.F, none, nullptr, 0, st));
+    BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.F, d, ws.dgated, d, p.w_down, m.F, ws.da, m.F, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, (double)T * 4.0 * m.F * (double)m.es, st);
       BM_RETURN_IF(act_backward(dt, BM_ACT_GELU, q.up, ws.da, ws.dup, ws.a, (float*)g.b_up, ws.colsum_ws, T, m.F, st)); }
     BM_RETURN_IF(gemm(GEMM_TN, dt, d, m.F, T, ws.dgated, d, ws.a, m.F, g.w_down, m.F, none, ws.gemm_ws,
@@ -633,7 +636,7 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
       BM_RETURN_IF(colsum_accumulate(dt, ws.dgated, d, T, d, (float*)g.b_down, ws.colsum_ws, st)); }
     // up = h2 W_up^T + b_up,  h2 = LN0(x1)(1 + scale2) + shift2
-    BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.F, ws.dup, m.F, p.w_up, d, ws.dh, d, none, nullptr, 0, st));
+    BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.F, ws.dup, m.F, p.w_up, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_NORM, 5.0 * T * d * (double)m.es, st);
       BM_RETURN_IF(norm_backward(ada_norm_args(c, T, 2, q.mod, tok), q.x1, q.stats2, ws.dh, dy[s], ws.dx1[s], ws.h,
                                  nullptr, nullptr, nullptr, nullptr, dmod, cu_dev[s], S, ws.norm_ws, st)); }
@@ -646,7 +649,7 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
                       ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
       BM_RETURN_IF(colsum_accumulate(dt, ws.dgated, d, T, d, (float*)g.b_o, ws.colsum_ws, st)); }
-    BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.QD, d, ws.dgated, d, p.w_o, m.QD, ws.d_o, m.QD, none, nullptr, 0, st));
+    BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.QD, d, ws.dgated, d, p.w_o, m.QD, ws.d_o, m.QD, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, 2.0 * T * m.QD * (double)m.es, st);
       BM_RETURN_IF(row_scatter(dt, ws.d_o, ws.tb.jpos[s], ws.d_o_j, T, m.QD, st)); }
   }
@@ -675,7 +678,7 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
         BM_RETURN_IF(row_gather(dt, ws.dqkv_j, ws.tb.jpos[s], ws.dqkv, T, m.QKV, st));
       BM_RETURN_IF(colsum_accumulate(dt, ws.dqkv, m.QKV, T, m.QKV, (float*)g.b_qkv, ws.colsum_ws, st));
     }
-    BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.QKV, ws.dqkv, m.QKV, p.w_qkv, d, ws.dh, d, none, nullptr, 0, st));
+    BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.QKV, ws.dqkv, m.QKV, p.w_qkv, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_NORM, 5.0 * T * d * (double)m.es, st);
       BM_RETURN_IF(norm_backward(ada_norm_args(c, T, 1, q.mod, tok), x[s], q.stats1, ws.dh, ws.dx1[s], dx[s], ws.h,
                                  nullptr, nullptr, nullptr, nullptr, dmod, cu_dev[s], S, ws.norm_ws, st)); }
