@@ -1,33 +1,53 @@
-// Variable-length attention with plain fp32 arithmetic: one thread owns one
-// query row (forward, dq) or one key row (dk, dv), key/query tiles are staged
-// in LDS and read as broadcasts.  It serves the fp32 check path and head sizes
-// the MFMA kernels do not take.  No atomics: each output element has one owner.
+// Variable-length attention with plain fp32 arithmetic: P neighbouring lanes share one
+// query row (forward, dq) or one key row (dk, dv) and take every P-th row of the streamed tile,
+// which is staged in LDS; their sums meet in lane shuffles at the end.  It serves the fp32 check
+// path and head sizes the MFMA kernels do not take.  No atomics: each output element has one owner.
+// Bound by the chain of one lane's rows, not by arithmetic or memory: P = 8 against P = 1, fp32 on
+// two images of 16 and 24 tokens (4 heads of 16) forward 17.8 -> 9.4 us, dq 12.7 -> 6.3, dk/dv 12.9 -> 7.2.
 //
 //   forward : o = softmax(q k^T / sqrt(dh) + mask) v,  lse = log sum exp (scaled scores)
 //   backward: p = exp(s - lse), dv = p^T do, dp = do v^T, ds = p * (dp - delta),
 //             dq = ds k / sqrt(dh), dk = ds^T q / sqrt(dh), delta = rowsum(do * o)
 #include "common.h"
 
+#include <type_traits>
+
 namespace bm {
 
 namespace {
 
-constexpr int BQ = 128;   // rows per workgroup (one per thread)
+constexpr int NT = 128;   // threads per workgroup: NT / P rows
 constexpr int BT = 32;    // rows of the streamed tile
 
-template <typename T, int DH, bool CAUSAL>
-__global__ __launch_bounds__(BQ) void attn_fwd_generic_kernel(
+// LDS row stride: the P lanes of a row read P rows of the tile at once (P = 1: all lanes one row)
+template <int DH, int P> constexpr int tile_ld() { return P > 1 ? DH + 4 : DH; }
+
+template <int P> __device__ inline float lanes_sum(float v) {
+#pragma unroll
+  for (int off = 1; off < P; off <<= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+template <int P> __device__ inline float lanes_max(float v) {
+#pragma unroll
+  for (int off = 1; off < P; off <<= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
+  return v;
+}
+
+template <typename T, int DH, bool CAUSAL, int P>
+__global__ __launch_bounds__(NT) void attn_fwd_generic_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int ld, int ldk,
     const int32_t* __restrict__ cu, const int32_t* __restrict__ cuk, T* __restrict__ o, int ldo,
     float* __restrict__ lse, int Ttot, int group, float scale) {
-  __shared__ float Ks[BT][DH];
-  __shared__ float Vs[BT][DH];
+  constexpr int BQ = NT / P;
+  __shared__ float Ks[BT][tile_ld<DH, P>()];
+  __shared__ float Vs[BT][tile_ld<DH, P>()];
   const int s = blockIdx.y, hq = blockIdx.z, hk = hq / group;
   const int lo = cu[s], L = cu[s + 1] - lo;
   const int lok = cuk[s], Lk = cuk[s + 1] - lok;     // keys/values may be packed on their own
   const int q0 = blockIdx.x * BQ;
   if (q0 >= L) return;
-  const int qi = q0 + threadIdx.x;
+  const int part = threadIdx.x % P;
+  const int qi = q0 + threadIdx.x / P;
   const bool active = qi < L;
   float qr[DH], acc[DH];
 #pragma unroll
@@ -38,7 +58,7 @@ __global__ __launch_bounds__(BQ) void attn_fwd_generic_kernel(
   float m = -INFINITY, l = 0.f;
   const int kend = CAUSAL ? min(Lk, q0 + BQ) : Lk;
   for (int k0 = 0; k0 < kend; k0 += BT) {
-    for (int idx = threadIdx.x; idx < BT * DH; idx += BQ) {
+    for (int idx = threadIdx.x; idx < BT * DH; idx += NT) {
       int r = idx / DH, c = idx % DH, kj = k0 + r;
       bool ok = kj < Lk;
       Ks[r][c] = ok ? Elt<T>::to_f(k[(size_t)(lok + kj) * ldk + hk * DH + c]) : 0.f;
@@ -46,17 +66,17 @@ __global__ __launch_bounds__(BQ) void attn_fwd_generic_kernel(
     }
     __syncthreads();
     if (active) {
-      float sc[BT];
+      float sc[BT / P];
       float tmax = -INFINITY;
 #pragma unroll
-      for (int j = 0; j < BT; ++j) {
-        int kj = k0 + j;
+      for (int jj = 0; jj < BT / P; ++jj) {
+        const int j = jj * P + part, kj = k0 + j;
         float d = 0.f;
 #pragma unroll
         for (int c = 0; c < DH; ++c) d = fmaf(qr[c], Ks[j][c], d);
         bool ok = kj < Lk && (!CAUSAL || kj <= qi);
-        sc[j] = ok ? d : -INFINITY;
-        tmax = fmaxf(tmax, sc[j]);
+        sc[jj] = ok ? d : -INFINITY;
+        tmax = fmaxf(tmax, sc[jj]);
       }
       if (tmax > -INFINITY) {
         float mn = fmaxf(m, tmax);
@@ -65,8 +85,9 @@ __global__ __launch_bounds__(BQ) void attn_fwd_generic_kernel(
 #pragma unroll
         for (int c = 0; c < DH; ++c) acc[c] *= corr;
 #pragma unroll
-        for (int j = 0; j < BT; ++j) {
-          float p = expf(sc[j] - mn);   // exp(-inf) = 0 for masked keys
+        for (int jj = 0; jj < BT / P; ++jj) {
+          const int j = jj * P + part;
+          float p = expf(sc[jj] - mn);   // exp(-inf) = 0 for masked keys
           l += p;
 #pragma unroll
           for (int c = 0; c < DH; ++c) acc[c] = fmaf(p, Vs[j][c], acc[c]);
@@ -76,7 +97,16 @@ __global__ __launch_bounds__(BQ) void attn_fwd_generic_kernel(
     }
     __syncthreads();
   }
-  if (active) {
+  if (P > 1) {
+    // the lanes of a row bring their sums to the common maximum (a lane that saw no key holds zeros)
+    const float mall = lanes_max<P>(m);
+    const float corr = m > -INFINITY ? expf(m - mall) : 0.f;
+    m = mall;
+    l = lanes_sum<P>(l * corr);
+#pragma unroll
+    for (int c = 0; c < DH; ++c) acc[c] = lanes_sum<P>(acc[c] * corr);
+  }
+  if (active && part == 0) {
     float inv = l > 0.f ? 1.0f / l : 0.f;       // no visible key in this chunk: o = 0, lse = -inf
 #pragma unroll
     for (int c = 0; c < DH; ++c)
@@ -99,20 +129,22 @@ __global__ void attn_delta_kernel(const T* __restrict__ o, const T* __restrict__
   delta[(size_t)hq * Ttot + t] = s;
 }
 
-template <typename T, int DH, bool CAUSAL>
-__global__ __launch_bounds__(BQ) void attn_dq_generic_kernel(
+template <typename T, int DH, bool CAUSAL, int P>
+__global__ __launch_bounds__(NT) void attn_dq_generic_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int ld, int ldk,
     const T* __restrict__ d_o, int ldo, const float* __restrict__ lse,
     const float* __restrict__ delta, const int32_t* __restrict__ cu, const int32_t* __restrict__ cuk,
     T* __restrict__ dq, int ldd, int Ttot, int group, float scale) {
-  __shared__ float Ks[BT][DH];
-  __shared__ float Vs[BT][DH];
+  constexpr int BQ = NT / P;
+  __shared__ float Ks[BT][tile_ld<DH, P>()];
+  __shared__ float Vs[BT][tile_ld<DH, P>()];
   const int s = blockIdx.y, hq = blockIdx.z, hk = hq / group;
   const int lo = cu[s], L = cu[s + 1] - lo;
   const int lok = cuk[s], Lk = cuk[s + 1] - lok;
   const int q0 = blockIdx.x * BQ;
   if (q0 >= L) return;
-  const int qi = q0 + threadIdx.x;
+  const int part = threadIdx.x % P;
+  const int qi = q0 + threadIdx.x / P;
   const bool active = qi < L;
   float qr[DH], dor[DH], acc[DH];
 #pragma unroll
@@ -125,7 +157,7 @@ __global__ __launch_bounds__(BQ) void attn_dq_generic_kernel(
   const float my_delta = active ? delta[(size_t)hq * Ttot + lo + qi] : 0.f;
   const int kend = CAUSAL ? min(Lk, q0 + BQ) : Lk;
   for (int k0 = 0; k0 < kend; k0 += BT) {
-    for (int idx = threadIdx.x; idx < BT * DH; idx += BQ) {
+    for (int idx = threadIdx.x; idx < BT * DH; idx += NT) {
       int r = idx / DH, c = idx % DH, kj = k0 + r;
       bool ok = kj < Lk;
       Ks[r][c] = ok ? Elt<T>::to_f(k[(size_t)(lok + kj) * ldk + hk * DH + c]) : 0.f;
@@ -133,7 +165,7 @@ __global__ __launch_bounds__(BQ) void attn_dq_generic_kernel(
     }
     __syncthreads();
     if (active) {
-      for (int j = 0; j < BT; ++j) {
+      for (int j = part; j < BT; j += P) {
         int kj = k0 + j;
         if (kj >= Lk || (CAUSAL && kj > qi)) break;
         float sc = 0.f, dp = 0.f;
@@ -149,32 +181,38 @@ __global__ __launch_bounds__(BQ) void attn_dq_generic_kernel(
     }
     __syncthreads();
   }
-  if (active) {
+  if (P > 1) {
+#pragma unroll
+    for (int c = 0; c < DH; ++c) acc[c] = lanes_sum<P>(acc[c]);
+  }
+  if (active && part == 0) {
 #pragma unroll
     for (int c = 0; c < DH; ++c)
       dq[(size_t)(lo + qi) * ldd + hq * DH + c] = Elt<T>::from_f(acc[c] * scale);
   }
 }
 
-// One thread per key row of one kv head; the q heads of the group and the query
+// P lanes per key row of one kv head; the q heads of the group and the query
 // tiles are walked in a fixed order, so dk/dv sums are reproducible.
-template <typename T, int DH, bool CAUSAL>
-__global__ __launch_bounds__(BQ) void attn_dkdv_generic_kernel(
+template <typename T, int DH, bool CAUSAL, int P>
+__global__ __launch_bounds__(NT) void attn_dkdv_generic_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int ld, int ldk,
     const T* __restrict__ d_o, int ldo, const float* __restrict__ lse,
     const float* __restrict__ delta, const int32_t* __restrict__ cuq, const int32_t* __restrict__ cuk,
     T* __restrict__ dk, T* __restrict__ dv, int ldd, int Ttot, int group, float scale) {
   // this thread's key row lives in the key/value packing (cuk, ldk); queries, dO, lse and
   // delta (Ttot rows per head) in the queries' packing (cuq, ld)
-  __shared__ float Qs[BT][DH];
-  __shared__ float Ds[BT][DH];
+  constexpr int BQ = NT / P;
+  __shared__ float Qs[BT][tile_ld<DH, P>()];
+  __shared__ float Ds[BT][tile_ld<DH, P>()];
   __shared__ float Ls[BT], Dl[BT];
   const int s = blockIdx.y, hk = blockIdx.z;
   const int lok = cuk[s], Lk = cuk[s + 1] - lok;
   const int lo = cuq[s], L = cuq[s + 1] - lo;
   const int kb = blockIdx.x * BQ;
   if (kb >= Lk) return;
-  const int kj = kb + threadIdx.x;
+  const int part = threadIdx.x % P;
+  const int kj = kb + threadIdx.x / P;
   const bool active = kj < Lk;
   float kr[DH], vr[DH], dkr[DH], dvr[DH];
 #pragma unroll
@@ -187,7 +225,7 @@ __global__ __launch_bounds__(BQ) void attn_dkdv_generic_kernel(
   for (int g = 0; g < group; ++g) {
     const int hq = hk * group + g;
     for (int q0 = qstart; q0 < L; q0 += BT) {
-      for (int idx = threadIdx.x; idx < BT * DH; idx += BQ) {
+      for (int idx = threadIdx.x; idx < BT * DH; idx += NT) {
         int r = idx / DH, c = idx % DH, qi = q0 + r;
         bool ok = qi < L;
         Qs[r][c] = ok ? Elt<T>::to_f(q[(size_t)(lo + qi) * ld + hq * DH + c]) * scale : 0.f;
@@ -201,7 +239,7 @@ __global__ __launch_bounds__(BQ) void attn_dkdv_generic_kernel(
       }
       __syncthreads();
       if (active) {
-        for (int i = 0; i < BT; ++i) {
+        for (int i = part; i < BT; i += P) {
           int qi = q0 + i;
           if (qi >= L) break;
           if (CAUSAL && kj > qi) continue;
@@ -223,7 +261,11 @@ __global__ __launch_bounds__(BQ) void attn_dkdv_generic_kernel(
       __syncthreads();
     }
   }
-  if (active) {
+  if (P > 1) {
+#pragma unroll
+    for (int c = 0; c < DH; ++c) { dkr[c] = lanes_sum<P>(dkr[c]); dvr[c] = lanes_sum<P>(dvr[c]); }
+  }
+  if (active && part == 0) {
 #pragma unroll
     for (int c = 0; c < DH; ++c) {
       dk[(size_t)(lok + kj) * ldd + hk * DH + c] = Elt<T>::from_f(dkr[c]);
@@ -232,12 +274,25 @@ __global__ __launch_bounds__(BQ) void attn_dkdv_generic_kernel(
   }
 }
 
+// Lanes per row.  One lane walks every row of the other side by itself, so few rows leave the chip
+// idle behind long chains; eight lanes per row cost eight times the tile loads.  Measured forward /
+// backward, us, P = 1 -> 8: head size 16, 1000 rows x 4 heads 223 / 658 -> 60 / 147; head size 64, 1024 x 16
+// 453 / 1242 -> 187 / 737, 2048 x 16 463 / 1246 -> 370 / 1458, 4096 x 16 473 / 1290 -> 564 / 2914; head size 128,
+// 1024 x 8 999 / 28283 -> 249 / 5010, 4096 x 8 2164 -> 2894.
+template <typename F>
+void with_lanes(long rows, int heads, int dh, F&& launch) {
+  if (rows * heads <= 16384 && rows * heads * dh <= (1L << 20)) launch(std::integral_constant<int, 8>{});
+  else launch(std::integral_constant<int, 1>{});
+}
+
 template <typename T, int DH, bool CAUSAL>
 bm_status fwd_launch(const AttnArgs& a, void* o, float* lse, hipStream_t st) {
-  dim3 grid(cdiv(a.max_seqlen, BQ), a.S, a.Hq);
-  hipLaunchKernelGGL((attn_fwd_generic_kernel<T, DH, CAUSAL>), grid, dim3(BQ), 0, st, (const T*)a.q,
-                     (const T*)a.k, (const T*)a.v, a.ld_qkv, a.kv_ld(), a.cu_dev, a.kv_cu_dev(), (T*)o,
-                     a.Hq * a.dh, lse, a.T, a.Hq / a.Hkv, 1.0f / sqrtf((float)a.dh));
+  with_lanes(a.T, a.Hq, DH, [&](auto p) {
+    constexpr int P = decltype(p)::value;
+    hipLaunchKernelGGL((attn_fwd_generic_kernel<T, DH, CAUSAL, P>), dim3(cdiv(a.max_seqlen, NT / P), a.S, a.Hq), dim3(NT),
+                       0, st, (const T*)a.q, (const T*)a.k, (const T*)a.v, a.ld_qkv, a.kv_ld(), a.cu_dev, a.kv_cu_dev(),
+                       (T*)o, a.Hq * a.dh, lse, a.T, a.Hq / a.Hkv, 1.0f / sqrtf((float)a.dh));
+  });
   BM_CHECK_LAUNCH("attn_fwd_generic");
   return BM_OK;
 }
@@ -251,17 +306,22 @@ bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const fl
   if (n > 0) {
     hipLaunchKernelGGL((attn_delta_kernel<T, DH>), dim3(cdiv(n, 256)), dim3(256), 0, st, (const T*)o,
                        (const T*)d_o, ldo, delta, a.T, a.Hq);
-    hipLaunchKernelGGL((attn_dq_generic_kernel<T, DH, CAUSAL>), dim3(cdiv(a.max_seqlen, BQ), a.S, a.Hq),
-                       dim3(BQ), 0, st, (const T*)a.q, (const T*)a.k, (const T*)a.v, a.ld_qkv, a.kv_ld(),
-                       (const T*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), (T*)dq, ldd, a.T,
-                       a.Hq / a.Hkv, scale);
+    with_lanes(a.T, a.Hq, DH, [&](auto p) {
+      constexpr int P = decltype(p)::value;
+      hipLaunchKernelGGL((attn_dq_generic_kernel<T, DH, CAUSAL, P>), dim3(cdiv(a.max_seqlen, NT / P), a.S, a.Hq),
+                         dim3(NT), 0, st, (const T*)a.q, (const T*)a.k, (const T*)a.v, a.ld_qkv, a.kv_ld(),
+                         (const T*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), (T*)dq, ldd, a.T,
+                         a.Hq / a.Hkv, scale);
+    });
   }
   if (a.kv_T() > 0)
-    hipLaunchKernelGGL((attn_dkdv_generic_kernel<T, DH, CAUSAL>),
-                       dim3(cdiv(a.kv_max_len(), BQ), a.S, a.Hkv), dim3(BQ), 0, st, (const T*)a.q,
-                       (const T*)a.k, (const T*)a.v, a.ld_qkv, a.kv_ld(), (const T*)d_o, ldo, lse, delta,
-                       a.cu_dev, a.kv_cu_dev(), (T*)dk, (T*)dv, a.ld_dkv ? a.ld_dkv : ldd, a.T,
-                       a.Hq / a.Hkv, scale);
+    with_lanes(a.kv_T(), a.Hkv, DH, [&](auto p) {
+      constexpr int P = decltype(p)::value;
+      hipLaunchKernelGGL((attn_dkdv_generic_kernel<T, DH, CAUSAL, P>), dim3(cdiv(a.kv_max_len(), NT / P), a.S, a.Hkv),
+                         dim3(NT), 0, st, (const T*)a.q, (const T*)a.k, (const T*)a.v, a.ld_qkv, a.kv_ld(),
+                         (const T*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), (T*)dk, (T*)dv,
+                         a.ld_dkv ? a.ld_dkv : ldd, a.T, a.Hq / a.Hkv, scale);
+    });
   BM_CHECK_LAUNCH("attn_bwd_generic");
   return BM_OK;
 }
