@@ -543,6 +543,8 @@ __global__ void fa_delta_kernel(const bf16_t* __restrict__ o, const bf16_t* __re
   if (live && c == 0) delta[(size_t)hq * Ttot + t] = s;
 }
 
+constexpr int NUM_CU = 256;
+constexpr int WIDE_KEYS = 256;  // keys per workgroup of the wide dK/dV kernel
 constexpr int BK_KEYS = 128;   // keys per workgroup in the dK/dV kernel (32 per wavefront)
 constexpr int BK_Q = 64;       // query rows per step
 
@@ -1001,6 +1003,303 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_pair_kernel(
   }
 }
 
+// dK, dV at head size 128 over many keys: the pair scheme with 64 keys per pair (256 per workgroup).
+// Every Q / dO fragment read from LDS feeds two MFMAs instead of one, and a Q / dO tile is brought in
+// for twice the keys: with 32 keys per pair the LDS pipe is busy as long as the matrix pipe (fragment
+// reads, fills and the P exchange of a 32x32 block: about 1130 clocks of LDS for 1024 of MFMAs).
+// 128 accumulator registers and 64 of K or V leave 64 for everything else, so
+//  - a step is one 32-query block;
+//  - tiles lie in LDS so that every read is one lane constant plus an immediate offset:
+//    16-byte chunk c of row r at (r >> 2) * RUN + (c >> 2) * 256 + (r & 3) * 64 + (c & 3) * 16.  A run of
+//    four rows is the 1 KiB that one load instruction fills, four lanes to 64 contiguous bytes of a
+//    row; the 16 bytes between runs keep row reads and transpose reads free of bank conflicts.
+// Tiles go through a ring of four buffers, requested three steps ahead; one barrier per step hands over
+// P and the next tile.
+// Against 32 keys per pair, us: 8192 queries x 8192 keys, 32 / 8 heads, 2207 -> 1875 (1.17 PFLOP/s of MFMAs), causal
+// 1138 -> 1002; 16 samples of about 1160 tokens, 24 heads, 848 -> 657; 8192 tokens of causal documents, 32
+// heads, 435 -> 362.  Fragments requested three steps ahead and a raised wave priority around the MFMAs
+// changed nothing.
+struct WideTile {
+  static constexpr int ROWS = 32, RUN = 1024 + 16, RUNS = ROWS / 4;
+  static constexpr int Q = 0, D = RUNS * RUN, LSE = 2 * RUNS * RUN, DELTA = LSE + ROWS * 4, BYTES = DELTA + ROWS * 4;
+  static constexpr int RING = 4;
+};
+
+__device__ inline const bf16_t* scalar_ptr(const void* p) {
+  const uint64_t b = reinterpret_cast<uint64_t>(p);
+  return reinterpret_cast<const bf16_t*>(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32) |
+                                         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b));
+}
+
+// the lane index, computed anew
+__device__ inline int fresh_lane() {
+  int l;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+  return l;
+}
+
+template <bool CAUSAL>
+__global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
+    int ldk, const bf16_t* __restrict__ d_o, int ldo, const float* __restrict__ lse,
+    const float* __restrict__ delta, const int32_t* __restrict__ cuq, const int32_t* __restrict__ cu,
+    int S, bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int ldd, int Tq, int Ttot, int Hkv, int group,
+    float scale, float scale_log2, int gsplit,
+    float* __restrict__ part /* [gsplit][2][Ttot][Hkv*DH] fp32 when gsplit > 1 */, SeqOrder ord) {
+  constexpr int DH = 128, KS = 8, NB = 4, KB = 2;
+  using W = WideTile;
+  __shared__ __attribute__((aligned(1024))) unsigned char tiles[W::RING * W::BYTES];
+  __shared__ __attribute__((aligned(1024))) unsigned char Pbuf[2 * 4 * 4096];   // [parity][pair][key block, half k-step][lane]
+  int seq, kt, nkt, tile_id, hk, hk_gs;
+  tile_and_head(Hkv * gsplit, &tile_id, &hk_gs);
+  hk = hk_gs / gsplit;
+  const int gs = hk_gs % gsplit;
+  const int gpart = group / gsplit;
+  if (!find_tile(cu, ord, S, WIDE_KEYS, tile_id, &seq, &kt, &nkt)) return;
+  kt = nkt - 1 - kt;                                   // early key tiles see the most queries
+  const int lo = cu[seq], L = cu[seq + 1] - lo;
+  const int loq = cuq[seq], Lq = cuq[seq + 1] - loq;
+  const int kb0 = kt * WIDE_KEYS;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int pair = wave & 3;                            // wavefronts w and w+4 share a SIMD
+  const int key0 = kb0 + pair * 64;                     // the pair's first key
+  const int qstart = CAUSAL ? kb0 : 0;
+  const int nqt = Lq > qstart ? (Lq - qstart + W::ROWS - 1) / W::ROWS : 0;   // no query: dk = dv = 0
+  const int iters = nqt * gpart;
+  const int head0 = hk * group + gs * gpart;
+  // A pair needs the mask tests where its keys are cut by the sequence end, on the last query tile when that is
+  // cut, and up to its last key under a causal mask; it sits out the query tiles before its first key,
+  // and all of them if it lies past the sequence.
+  const bool keys_cut = key0 + 64 > L;
+  const int skip = key0 >= L ? nqt : CAUSAL ? min(nqt, (key0 - qstart) / W::ROWS) : 0;
+  const uint32_t lds0 = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)tiles;
+  constexpr int LOADS = 3;
+
+  // Everything of a role is compiled on its own: its registers are allocated for it alone.  Addresses are derived
+  // from the lane index in every step; kept in registers, they would push K or V fragments out to memory.
+  auto run = [&](auto role_t) {
+    constexpr int ROLE = decltype(role_t)::value;
+    constexpr int ROWS_AT = ROLE == 0 ? W::Q : W::D, COLS_AT = ROLE == 0 ? W::D : W::Q;
+    constexpr int STATS_AT = ROLE == 0 ? W::LSE : W::DELTA;
+    bf16x8 kvf[KB][KS];                                   // role 0 keeps K (for S), role 1 keeps V (for dP)
+    {
+      const int l = fresh_lane();
+#pragma unroll
+      for (int b = 0; b < KB; ++b) {
+        const bf16_t* p = (ROLE == 0 ? k : v) + (size_t)(lo + min(key0 + b * 32 + (l & 31), L - 1)) * ldk + hk * DH;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) kvf[b][ks] = load_chunk<DH>(p, ks * 2 + (l >> 5));
+      }
+    }
+    f32x16 acc[NB][KB];                                   // role 0: dV^T, role 1: dK^T (unscaled)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int b = 0; b < KB; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[j][b][r] = 0.f;
+
+    // role 0's wavefronts bring in Q and lse, role 1's dO and delta: two runs and a quarter of the row
+    // statistics each, three loads per wavefront and step
+    const int sld = ROLE == 0 ? ld : ldo;
+    const bf16_t* src = scalar_ptr((ROLE == 0 ? q : d_o) + ((size_t)loq + qstart) * sld + head0 * DH);
+    const float* stat = reinterpret_cast<const float*>(scalar_ptr((ROLE == 0 ? lse : delta) + (size_t)head0 * Tq + loq + qstart));
+    int fn = 0, ft = 0;                                   // next tile to request: step, query tile of its head
+    auto fetch = [&] {
+      if (fn >= iters) return;
+      const int last = Lq - qstart - 1 - ft * W::ROWS;    // rows past the sequence are clamped: their P is 0
+      const uint32_t dst = lds0 + (fn & (W::RING - 1)) * W::BYTES;
+      const int l = fresh_lane();
+      const int row = (l >> 2) & 3, chunk = ((l >> 4) * 4 + (l & 3)) * 16;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int r = pair * 2 + i;
+        const uint32_t off = (uint32_t)min(r * 4 + row, last) * (uint32_t)sld * 2u + (uint32_t)chunk;
+        TileAsync<32, DH, 256>::load16(src, off, dst + ROWS_AT + r * W::RUN);
+      }
+      const uint32_t off = (uint32_t)min(pair * 8 + (l & 7), last) * 4u;
+      if (l < 8)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+                     :: "s"(dst + STATS_AT + pair * 32), "v"(off), "s"(stat) : "memory", "m0");
+      ++fn;
+      src += (size_t)W::ROWS * sld;
+      stat += W::ROWS;
+      if (++ft == nqt) {                                  // first query tile of the next head
+        ft = 0;
+        src += DH - (size_t)nqt * W::ROWS * sld;
+        stat += Tq - (size_t)nqt * W::ROWS;
+      }
+    };
+    auto tile_of = [&](int n) { return tiles + (n & (W::RING - 1)) * W::BYTES; };
+    auto p_of = [&](int n) { return Pbuf + (n & 1) * (4 * 4096) + pair * 4096 + fresh_lane() * 16; };
+    auto barrier = [] {
+      __builtin_amdgcn_sched_barrier(0);
+      asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // between the phases of step n: its P is in LDS, and the next step's tile; the one after may still be on its way
+    auto hand_over = [&](int n) {
+      if (n + 2 < iters) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((W::RING - 3) * LOADS) : "memory");
+      else wait_async_tiles();
+      barrier();
+    };
+    // phase 1: X[q, key] += rows(Q or dO) . (K or V)^T
+    auto scores = [&](int n, f32x16 (&x)[KB]) {
+      const int l = fresh_lane();
+      const unsigned char* rows = tile_of(n) + ROWS_AT + ((l & 31) >> 2) * W::RUN + (l & 3) * 64 + (l >> 5) * 16;
+      constexpr int AHEAD = 2;
+      bf16x8 fx[AHEAD + 1];
+      auto request = [&](int ks) {
+        fx[ks % (AHEAD + 1)] = *reinterpret_cast<const bf16x8*>(rows + (ks >> 1) * 256 + (ks & 1) * 32);
+      };
+#pragma unroll
+      for (int ks = 0; ks < AHEAD; ++ks) request(ks);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {
+        if (ks + AHEAD < KS) request(ks + AHEAD);
+#pragma unroll
+        for (int b = 0; b < KB; ++b)
+          x[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fx[ks % (AHEAD + 1)], kvf[b][ks], x[b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    // phase 2: acc^T[c, key] += cols(dO or Q)^T . (P or dS), transposed operands requested ahead
+    auto accumulate = [&](int n, const bf16x8 (&op)[KB][2]) {
+      const int l = fresh_lane(), gi = l >> 4, s = l & 15;
+      const unsigned char* cols = tile_of(n) + COLS_AT + (gi >> 1) * W::RUN + (s >> 2) * 64 +
+                                  ((gi & 1) * 2 + ((s & 3) >> 1)) * 16 + (s & 1) * 8;
+      auto request = [&](int m) {                          // m = j * 2 + t: 32 columns of dh, 16 query rows
+        const unsigned char* a = cols + (m >> 1) * 256 + (m & 1) * 4 * W::RUN;
+        s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)a);
+        s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(a + 2 * W::RUN));
+        union { struct { s16x4 a, b; } s; bf16x8 v; } u;
+        u.s.a = lo4; u.s.b = hi4;
+        return u.v;
+      };
+      constexpr int AHEAD = 2;
+      bf16x8 fc[AHEAD + 1];
+#pragma unroll
+      for (int m = 0; m < AHEAD; ++m) fc[m] = request(m);
+      if (ROLE == 0) fetch();                              // step n + 3, over the tile of step n - 1
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int m = 0; m < NB * 2; ++m) {
+        if (m + AHEAD < NB * 2) fc[(m + AHEAD) % (AHEAD + 1)] = request(m + AHEAD);
+#pragma unroll
+        for (int b = 0; b < KB; ++b)
+          acc[m >> 1][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fc[m % (AHEAD + 1)], op[b][m & 1], acc[m >> 1][b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    };
+    auto step = [&](int n, int q0) {
+      // accumulator element (g, b, e) of a lane: query q0 + 4 half + (8 g + e), key key0 + lane % 32 + 32 b
+      f32x16 x[KB];
+      bf16x8 op[KB][2];
+      if constexpr (ROLE == 0) {
+        x[0] = x[1] = f32x16{};
+        scores(n, x);
+        if (keys_cut || q0 + W::ROWS > Lq || (CAUSAL && q0 < key0 + 63)) {
+          const int l = fresh_lane(), h4 = (l >> 5) * 4, ki = key0 + (l & 31);
+          const int q_left = Lq - q0 - h4, k_left = L - ki, ahead = ki - q0 - h4;
+#pragma unroll
+          for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int b = 0; b < KB; ++b)
+#pragma unroll
+              for (int e = 0; e < 4; ++e)
+                if (q_left <= g * 8 + e || k_left <= b * 32 || (CAUSAL && ahead > g * 8 + e - b * 32))
+                  x[b][g * 4 + e] = -INFINITY;              // P = 0
+        }
+        const unsigned char* stats = tile_of(n) + STATS_AT + (fresh_lane() >> 5) * 16;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 l4 = *reinterpret_cast<const f32x4*>(stats + g * 32) * LOG2E;
+#pragma unroll
+          for (int b = 0; b < KB; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              x[b][g * 4 + e] = __builtin_amdgcn_exp2f(fmaf(x[b][g * 4 + e], scale_log2, -l4[e]));
+        }
+        unsigned char* my_p = p_of(n);
+#pragma unroll
+        for (int b = 0; b < KB; ++b)
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            op[b][t] = acc_to_operand(x[b], t);
+            *reinterpret_cast<bf16x8*>(my_p + (b * 2 + t) * 1024) = op[b][t];
+          }
+        hand_over(n);
+      } else {
+        const unsigned char* stats = tile_of(n) + STATS_AT + (fresh_lane() >> 5) * 16;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const f32x4 d4 = *reinterpret_cast<const f32x4*>(stats + g * 32);
+#pragma unroll
+          for (int b = 0; b < KB; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[b][g * 4 + e] = -d4[e];   // dP starts at -delta of its query row
+        }
+        scores(n, x);
+        hand_over(n);
+        const unsigned char* my_p = p_of(n);
+#pragma unroll
+        for (int b = 0; b < KB; ++b)
+#pragma unroll
+          for (int t = 0; t < 2; ++t) op[b][t] = *reinterpret_cast<const bf16x8*>(my_p + (b * 2 + t) * 1024);
+        fetch();                                           // step n + 3, over the tile of step n - 1
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int b = 0; b < KB; ++b)
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[b][t * 8 + e] *= (float)op[b][t][e];
+            op[b][t] = acc_to_operand(x[b], t);
+          }
+      }
+      accumulate(n, op);
+    };
+
+    settle_compiler_loads();                              // K / V fragments, offsets
+    for (int n = 0; n < W::RING - 1; ++n) fetch();
+    if (iters > W::RING - 2) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((W::RING - 2) * LOADS) : "memory");
+    else wait_async_tiles();
+    barrier();
+    for (int n = 0; n < iters;) {
+      for (int t = 0; t < skip; ++t, ++n) { hand_over(n); fetch(); }
+      for (int t = skip; t < nqt; ++t, ++n) step(n, qstart + t * W::ROWS);
+    }
+
+    const float out_scale = ROLE == 0 ? 1.0f : scale;     // dV as it is, dK times the softmax scale
+    const int l = fresh_lane();
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+      const int key = key0 + b * 32 + (l & 31);
+      if (key >= L) continue;
+      const size_t row = (size_t)(lo + key);
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const int c = hk * DH + j * 32 + g * 8 + (l >> 5) * 4;
+          f32x4 w;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) w[e] = acc[j][b][g * 4 + e] * out_scale;
+          if (gsplit > 1) {
+            *reinterpret_cast<f32x4*>(part + ((size_t)gs * 2 + (ROLE == 0 ? 1 : 0)) * Ttot * Hkv * DH + row * (Hkv * DH) + c) = w;
+          } else {
+            bf16x4 h;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) h[e] = (bf16_t)w[e];
+            *reinterpret_cast<bf16x4*>((ROLE == 0 ? dv : dk) + row * ldd + c) = h;
+          }
+        }
+    }
+  };
+  if (wave < 4) run(std::integral_constant<int, 0>{});
+  else run(std::integral_constant<int, 1>{});
+}
+
 // dQ of one 128-row query tile of one q head: walks the key tiles, scores kept as
 // S^T[key, q] as in the forward kernel.
 template <int DH, bool CAUSAL>
@@ -1209,6 +1508,21 @@ int dkdv_group_split(int tiles, int Hkv, int group) {
   return gsplit;
 }
 
+// The wide dK/dV kernel (head size 128) or the one with 128 keys per workgroup?  Both hold a CU alone.  The
+// wide one needs three workgroups per CU to even out the tiles of a causal pack, or to be done in one round where
+// the other is not, and sequences that 256-key tiles cut about as well.  Whole backward, us, narrow ->
+// wide: three rounds or more, 8 documents of 411 to 1800, 32 heads, 482 -> 447; 8 x 600, 32 / 8 heads, 238 -> 231; one
+// round, 4 x 400, 24 heads, 85 -> 71; neither, 777 tokens, 32 heads, 70 -> 88; 4 x 2048, 16 / 4 heads, 346 -> 376; cut
+// badly, 32 x 257, 16 heads, 168 -> 190.
+bool dkdv_wide(const AttnArgs& a) {
+  const int tw = count_tiles(a.kv_cu_host(), a.S, WIDE_KEYS), tn = count_tiles(a.kv_cu_host(), a.S, BK_KEYS);
+  if (tw == 0 || tw * 2L * 4 > tn * 5L) return false;
+  const int group = a.Hq / a.Hkv;
+  const long wide = (long)tw * a.Hkv * dkdv_group_split(tw, a.Hkv, group);
+  const long narrow = (long)tn * a.Hkv * dkdv_group_split(tn, a.Hkv, group);
+  return wide >= 3 * NUM_CU || (wide <= NUM_CU && narrow > NUM_CU);
+}
+
 template <int DH>
 bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const float* lse, void* dq,
                      void* dk, void* dv, int ldd, float* delta, hipStream_t st) {
@@ -1220,16 +1534,24 @@ bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const fl
   if (n > 0)
     hipLaunchKernelGGL((fa_delta_kernel<DH>), dim3(cdiv(n * DeltaLanes<DH>::N, 256)), dim3(256), 0, st, (const bf16_t*)o,
                        (const bf16_t*)d_o, ldo, delta, a.T, a.Hq);
-  const int ktiles = count_tiles(a.kv_cu_host(), a.S, BK_KEYS);
+  const bool wide = DH == 128 && dkdv_wide(a);
+  const int key_rows = wide ? WIDE_KEYS : BK_KEYS;
+  const int ktiles = count_tiles(a.kv_cu_host(), a.S, key_rows);
   const int gsplit = ktiles > 0 ? dkdv_group_split(ktiles, a.Hkv, a.Hq / a.Hkv) : 1;
   float* part = delta + align_up((size_t)a.Hq * a.T, 64);      // after the delta plane
   const int Tk = a.kv_T();
   dim3 gkv(ktiles * a.Hkv * gsplit), gq(count_tiles(a.cu_host, a.S, FQ) * a.Hq);
   // a key tile runs as long as its sequence has queries, a query tile as long as it has keys
-  const SeqOrder ord_kv = make_seq_order(a.kv_cu_host(), a.cu_host, a.S, BK_KEYS, !a.causal);
+  const SeqOrder ord_kv = make_seq_order(a.kv_cu_host(), a.cu_host, a.S, key_rows, !a.causal);
   const SeqOrder ord_q = make_seq_order(a.cu_host, a.kv_cu_host(), a.S, FQ, !a.causal);
 #define BM_L(C)                                                                                  \
-  if (ktiles > 0 && DH > 64)                                                                     \
+  if (wide && ktiles > 0)                                                                        \
+    hipLaunchKernelGGL((fa_bwd_dkdv_wide_kernel<C>), gkv, dim3(512), 0, st, (const bf16_t*)a.q,  \
+                       (const bf16_t*)a.k, (const bf16_t*)a.v, a.ld_qkv, a.kv_ld(),              \
+                       (const bf16_t*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), a.S,        \
+                       (bf16_t*)dk, (bf16_t*)dv, ldd_kv, a.T, Tk, a.Hkv, a.Hq / a.Hkv, scale, sl2, \
+                       gsplit, part, ord_kv);                                                    \
+  else if (ktiles > 0 && DH > 64)                                                                     \
     hipLaunchKernelGGL((fa_bwd_dkdv_pair_kernel<(DH > 64 ? DH : 128), C>), gkv, dim3(512), 0, st, \
                        (const bf16_t*)a.q,                                                       \
                        (const bf16_t*)a.k, (const bf16_t*)a.v, a.ld_qkv, a.kv_ld(),              \
