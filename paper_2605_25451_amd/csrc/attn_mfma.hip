@@ -71,6 +71,15 @@ __device__ inline bf16x8 load_chunk(const bf16_t* row, int c) {
   return z;
 }
 
+// -v; the result passes through an empty asm, or the compiler would rather turn the sign in every use
+__device__ inline bf16x8 turn_sign(bf16x8 v) {
+  union { bf16x8 b; u32x4 u; } x;
+  x.b = v;
+  x.u ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
+  asm volatile("" : "+v"(x.u));
+  return x.b;
+}
+
 // operand fragment, rows of the tile are the MFMA row/col index, dh is the k index:
 // lane l -> tile row row0 + l%32, dh = ks*16 + (l/32)*8 .. +7
 template <int DH>
@@ -393,9 +402,7 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(
     // block 0 run under the softmax of block 1.
     f32x16 sacc[FK / 32];
 #pragma unroll
-    for (int b = 0; b < FK / 32; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) sacc[b][r] = 0.f;
+    for (int b = 0; b < FK / 32; ++b) sacc[b] = f32x16{};
     {
       // K fragments are requested from LDS AHEAD MFMAs before their use (a ring of register sets)
       constexpr int KS = HeadDim<DH>::KS, NSTEP = (FK / 32) * KS, AHEAD = 2;
@@ -582,6 +589,10 @@ __global__ __launch_bounds__(256, DH <= 64 ? 2 : 1) void fa_bwd_dkdv_kernel(
   const int kpos = kb0 + wave * 32 + (lane & 31);       // this lane's key (column of S)
   const int krow = min(kpos, L - 1);
 
+  // With several resident wavefronts to hide the LDS read, dP starts at the delta of its query row and V
+  // enters with its sign turned, so that the MFMAs leave -(dP - delta) at no cost on the vector unit;
+  // dK then carries the turned sign.  (With one wavefront per SIMD the read in front of the MFMAs costs more.)
+  constexpr bool FOLD_DELTA = DH <= 64;
   bf16x8 kf[HeadDim<DH>::KS], vf[HeadDim<DH>::KS];
   {
     const bf16_t* kp = k + (size_t)(lo + krow) * ldk + hk * DH;
@@ -590,6 +601,7 @@ __global__ __launch_bounds__(256, DH <= 64 ? 2 : 1) void fa_bwd_dkdv_kernel(
     for (int ks = 0; ks < HeadDim<DH>::KS; ++ks) {
       kf[ks] = load_chunk<DH>(kp, ks * 2 + half);
       vf[ks] = load_chunk<DH>(vp, ks * 2 + half);
+      if (FOLD_DELTA) vf[ks] = turn_sign(vf[ks]);
     }
   }
   f32x16 dkacc[HeadDim<DH>::NB], dvacc[HeadDim<DH>::NB];
@@ -626,7 +638,6 @@ __global__ __launch_bounds__(256, DH <= 64 ? 2 : 1) void fa_bwd_dkdv_kernel(
   if (iters > 0) fetch(0, 0);
   settle_compiler_loads();                              // K and V fragments, lse, delta (and, with them, tile 0)
   // one step; MASKED is a compile-time copy with the per-element tests (see the forward kernel)
-  constexpr bool FOLD_DELTA = DH <= 64;
   auto step = [&](int it, auto masked, auto parity) {
     constexpr bool MASKED = decltype(masked)::value;
     constexpr int PAR = decltype(parity)::value;
@@ -644,17 +655,14 @@ __global__ __launch_bounds__(256, DH <= 64 ? 2 : 1) void fa_bwd_dkdv_kernel(
     f32x16 sacc[BK_Q / 32], dpacc[BK_Q / 32];
 #pragma unroll
     for (int qb = 0; qb < BK_Q / 32; ++qb) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) { sacc[qb][r] = 0.f; dpacc[qb][r] = 0.f; }
-      // With several resident wavefronts to hide the LDS read, dP starts at -delta of its query
-      // row, so that the MFMAs leave dP - delta: one subtraction per score element less on the
-      // vector unit.  (With one wavefront per SIMD the read in front of the MFMAs costs more.)
+      sacc[qb] = f32x16{};
+      if (!FOLD_DELTA) dpacc[qb] = f32x16{};
       if (FOLD_DELTA) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x4 d4 = *reinterpret_cast<const f32x4*>(Dl + qb * 32 + g * 8 + half * 4);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) dpacc[qb][g * 4 + e] = -d4[e];
+          for (int e = 0; e < 4; ++e) dpacc[qb][g * 4 + e] = d4[e];
         }
       }
     }
@@ -744,6 +752,7 @@ __global__ __launch_bounds__(256, DH <= 64 ? 2 : 1) void fa_bwd_dkdv_kernel(
       else { if (masked) step(it, std::true_type{}, P0{}); else step(it, std::false_type{}, P0{}); }
     }
   }
+  if (FOLD_DELTA) scale = -scale;
   if (kpos < L && gsplit > 1) {
     const size_t plane = (size_t)Ttot * Hkv * DH;
     float* pk = part + ((size_t)gs * 2 + 0) * plane + (size_t)(lo + kpos) * (Hkv * DH) + hk * DH;
@@ -881,9 +890,7 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_pair_kernel(
     // phase 1: X[q, key] = rows(Q or dO) . (K or V)^T for both 32-query blocks
     f32x16 xacc[NQB];
 #pragma unroll
-    for (int qb = 0; qb < NQB; ++qb)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) xacc[qb][r] = 0.f;
+    for (int qb = 0; qb < NQB; ++qb) xacc[qb] = f32x16{};
     {
       constexpr int NSTEP = NQB * KS, AHEAD = 2;
       bf16x8 fx[AHEAD + 1];
@@ -1081,14 +1088,17 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
     constexpr int ROLE = decltype(role_t)::value;
     constexpr int ROWS_AT = ROLE == 0 ? W::Q : W::D, COLS_AT = ROLE == 0 ? W::D : W::Q;
     constexpr int STATS_AT = ROLE == 0 ? W::LSE : W::DELTA;
-    bf16x8 kvf[KB][KS];                                   // role 0 keeps K (for S), role 1 keeps V (for dP)
+    bf16x8 kvf[KB][KS];                                   // role 0 keeps K (for S), role 1 keeps -V (for -(dP - delta))
     {
       const int l = fresh_lane();
 #pragma unroll
       for (int b = 0; b < KB; ++b) {
         const bf16_t* p = (ROLE == 0 ? k : v) + (size_t)(lo + min(key0 + b * 32 + (l & 31), L - 1)) * ldk + hk * DH;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) kvf[b][ks] = load_chunk<DH>(p, ks * 2 + (l >> 5));
+        for (int ks = 0; ks < KS; ++ks) {
+          kvf[b][ks] = load_chunk<DH>(p, ks * 2 + (l >> 5));
+          if (ROLE == 1) kvf[b][ks] = turn_sign(kvf[b][ks]);
+        }
       }
     }
     f32x16 acc[NB][KB];                                   // role 0: dV^T, role 1: dK^T (unscaled)
@@ -1199,6 +1209,7 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
         x[0] = x[1] = f32x16{};
         scores(n, x);
         if (keys_cut || q0 + W::ROWS > Lq || (CAUSAL && q0 < key0 + 63)) {
+          asm volatile("");                                 // keeps the tests out of the steps that need none
           const int l = fresh_lane(), h4 = (l >> 5) * 4, ki = key0 + (l & 31);
           const int q_left = Lq - q0 - h4, k_left = L - ki, ahead = ki - q0 - h4;
 #pragma unroll
@@ -1237,7 +1248,7 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
 #pragma unroll
           for (int b = 0; b < KB; ++b)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[b][g * 4 + e] = -d4[e];   // dP starts at -delta of its query row
+            for (int e = 0; e < 4; ++e) x[b][g * 4 + e] = d4[e];   // starts at the delta of its query row
         }
         scores(n, x);
         hand_over(n);
@@ -1270,7 +1281,7 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
       for (int t = skip; t < nqt; ++t, ++n) step(n, qstart + t * W::ROWS);
     }
 
-    const float out_scale = ROLE == 0 ? 1.0f : scale;     // dV as it is, dK times the softmax scale
+    const float out_scale = ROLE == 0 ? 1.0f : -scale;    // dV as it is, -dK times the softmax scale
     const int l = fresh_lane();
 #pragma unroll
     for (int b = 0; b < KB; ++b) {
@@ -1375,7 +1386,11 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(
   tile.issue(vbase, ldk, Lk, Vbuf, wave_u);
   settle_compiler_loads();                 // the Q and dO fragments, lse, delta (and, with them, tile 0)
   // two copies of the step, without and with the mask test, as in the forward kernel
-  constexpr bool FOLD_DELTA = DH <= 64;      // dP accumulators start at -delta (see the dK/dV kernel)
+  constexpr bool FOLD_DELTA = DH <= 64;      // dP accumulators start at -delta: the MFMAs leave dP - delta
+  f32x16 dp_start = {};
+  if (FOLD_DELTA)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) dp_start[r] = -my_delta;
   auto step = [&](int kt, auto masked, auto parity) {
     constexpr bool MASKED = decltype(masked)::value;
     constexpr int PAR = decltype(parity)::value;
@@ -1397,9 +1412,7 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(
     for (int b0 = 0; b0 < NBLK; b0 += BP) {
       f32x16 sacc[BP], dpacc[BP];
 #pragma unroll
-      for (int bi = 0; bi < BP; ++bi)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) { sacc[bi][r] = 0.f; dpacc[bi][r] = FOLD_DELTA ? -my_delta : 0.f; }   // MFMAs leave dP - delta
+      for (int bi = 0; bi < BP; ++bi) { sacc[bi] = f32x16{}; dpacc[bi] = dp_start; }
       {
         // operand fragments are requested AHEAD MFMA pairs before their use (see the dK/dV kernel)
         constexpr int NSTEP = BP * KS, AHEAD = 2;
