@@ -309,6 +309,7 @@ __device__ inline void tile_and_head(int H, int* tile, int* head) {
 // =============================================================================
 // forward
 // =============================================================================
+constexpr int NUM_CU = 256;
 constexpr int FQ = 128;   // query rows per workgroup (32 per wavefront)
 constexpr int FK = 64;    // keys per step
 
@@ -500,17 +501,273 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(
   }
 }
 
+// ---- tiles whose reads are one lane constant plus an immediate offset (head sizes 64 and 128) ----------
+// A run of 512 / DH rows is the 1 KiB that one load instruction of a wavefront fills.  In a run, 64-byte groups of
+// four chunks lie row after row, and the runs are PAD bytes apart from each other, so that row reads and transpose
+// reads are free of bank conflicts; for 64, the lowest bit of the chunk is turned in every second four rows.
+template <int DH>
+struct RunTile {
+  static constexpr int RPR = 512 / DH, RUN = 1024 + (DH == 128 ? 16 : 32);
+  static constexpr int bytes(int rows) { return rows / RPR * RUN; }
+  // this lane's row (in the run) and 16-byte chunk in a load
+  static __device__ inline int load_row(int l) { return (l >> 2) & (RPR - 1); }
+  static __device__ inline int load_chunk(int l) {
+    return DH == 128 ? (l >> 4) * 4 + (l & 3) : (l >> 5) * 4 + ((l & 3) ^ ((l >> 4) & 1));
+  }
+  // operand with rows as MFMA rows: lane l holds row l % 32 of a block, dh = ks * 16 + (l / 32) * 8 .. + 7
+  static __device__ inline int rows_at(int l) {
+    const int r = l & 31, half = l >> 5;
+    return r / RPR * RUN + (r & (RPR - 1)) * 64 + (DH == 128 ? half : half ^ ((r >> 2) & 1)) * 16;
+  }
+  static constexpr int rows_imm(int block, int ks) { return block * (32 / RPR) * RUN + (ks >> 1) * (RPR * 64) + (ks & 1) * 32; }
+  // transposed operand: MFMA row = dh index j * 32 + l % 32, k index = tile rows r16 * 16 .. (see frag_cols)
+  static __device__ inline int cols_at(int l) {
+    const int gi = l >> 4, s = l & 15, c = (gi & 1) * 2 + ((s & 3) >> 1);
+    return DH == 128 ? (gi >> 1) * RUN + (s >> 2) * 64 + c * 16 + (s & 1) * 8
+                     : ((gi >> 1) * 4 + (s >> 2)) * 64 + (c ^ (gi >> 1)) * 16 + (s & 1) * 8;
+  }
+  static constexpr int cols_imm(int j, int r16) { return j * (RPR * 64) + r16 * (16 / RPR) * RUN; }
+  static __device__ inline bf16x8 read_rows(const unsigned char* base, int block, int ks) {
+    return *reinterpret_cast<const bf16x8*>(base + rows_imm(block, ks));
+  }
+  static __device__ inline bf16x8 read_cols(const unsigned char* base, int j, int r16) {
+    const unsigned char* a = base + cols_imm(j, r16);
+    s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)a);
+    s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(a + 8 / RPR * RUN));
+    union { struct { s16x4 a, b; } s; bf16x8 v; } u;
+    u.s.a = lo; u.s.b = hi;
+    return u.v;
+  }
+};
+
+__device__ inline const bf16_t* scalar_ptr(const void* p) {
+  const uint64_t b = reinterpret_cast<uint64_t>(p);
+  return reinterpret_cast<const bf16_t*>(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32) |
+                                         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b));
+}
+
+// end of a phase: this wavefront's LDS accesses are done, then the workgroup meets
+__device__ inline void phase_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Forward with two groups of wavefronts that take turns (head sizes 64 and 128, long sequences): wavefronts w and
+// w + 4 share a SIMD, and while one multiplies -- P V of a key tile, then Q K of the next -- the other one does
+// the softmax of its tile.  Left to themselves (two workgroups of four wavefronts), two wavefronts of a SIMD
+// often want the same unit: matrix pipe busy 50 % of the cycles at head size 128, vector unit 56 %.
+// Two workgroups of four wavefronts -> this, us: 4 x 4096 bidirectional, 16 heads of 128, 577 -> 482 (1140 TFLOP/s), of
+// 64, 369 -> 330; 32768 tokens of causal documents, 32 / 8 heads of 128, 2914 -> 2501; 16 samples of about 1130, 24 heads,
+// 360 -> 327.  Bound by the vector unit at head size 64 (78 % busy before) and by power at 128.
+constexpr int AQ = 256;   // query rows per workgroup
+
+template <int DH, bool CAUSAL>
+__global__ __launch_bounds__(512, 2) void fa_fwd_alt_kernel(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
+    int ldk, const int32_t* __restrict__ cu, const int32_t* __restrict__ cuk, int S,
+    bf16_t* __restrict__ o, int ldo, float* __restrict__ lse, int Ttot, int Hq, int group,
+    float scale_log2, SeqOrder ord) {
+  using RT = RunTile<DH>;
+  constexpr int KS = DH / 16, NB = DH / 32, KBL = FK / 32, TILE = RT::bytes(FK), RUNS = FK / RT::RPR / 8;
+  constexpr int RING = 3;
+  __shared__ __attribute__((aligned(1024))) unsigned char Kbuf[RING * TILE];
+  __shared__ __attribute__((aligned(1024))) unsigned char Vbuf[RING * TILE];
+  int seq, qt, nqt, tile_id, hq;
+  tile_and_head(Hq, &tile_id, &hq);
+  if (!find_tile(cu, ord, S, AQ, tile_id, &seq, &qt, &nqt)) return;
+  const int hk = hq / group;
+  const int lo = cu[seq], L = cu[seq + 1] - lo;
+  const int lok = cuk[seq], Lk = cuk[seq + 1] - lok;
+  const int q0 = qt * AQ;
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qfirst = q0 + wave * 32;
+  const int qpos = qfirst + (lane & 31);                  // this lane's query (column of S^T)
+  bf16x8 qf[KS];
+  {
+    const bf16_t* qp = q + (size_t)(lo + min(qpos, L - 1)) * ld + hq * DH;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[ks] = load_chunk<DH>(qp, ks * 2 + half);
+  }
+  f32x16 oacc[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) oacc[j] = f32x16{};
+  float m = -INFINITY, lsum = 0.f;
+  // key tiles of the workgroup, and those of this wavefront (none if its queries lie past the sequence)
+  const int nkt = ((CAUSAL ? min(Lk, q0 + AQ) : Lk) + FK - 1) / FK;
+  const int mine = qfirst >= L ? 0 : CAUSAL ? min(nkt, (qfirst + 31) / FK + 1) : nkt;
+  const int plain = CAUSAL ? min(Lk / FK, (qfirst + 1) / FK) : Lk / FK;   // leading tiles that need no mask test
+  const bf16_t* kbase = scalar_ptr(k + (size_t)lok * ldk + hk * DH);
+  const bf16_t* vbase = scalar_ptr(v + (size_t)lok * ldk + hk * DH);
+  const uint32_t klds = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)Kbuf;
+  const uint32_t vlds = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)Vbuf;
+  const uint32_t lrow = RT::load_row(lane), lchunk = RT::load_chunk(lane) * 16;
+  // tile t of K or V into ring slot `slot` (t % 3); rows past the keys are clamped (their P is 0)
+  auto fetch = [&](const bf16_t* base, uint32_t lds, int t, int slot) {
+    if (t >= nkt) return;
+    const bf16_t* src = base + (size_t)t * FK * ldk;
+    const int last = Lk - t * FK - 1;
+    const uint32_t dst = lds + slot * TILE;
+#pragma unroll
+    for (int i = 0; i < RUNS; ++i) {
+      const int r = wave * RUNS + i;
+      const uint32_t off = (uint32_t)min(r * RT::RPR + (int)lrow, last) * (uint32_t)ldk * 2u + lchunk;
+      TileAsync<FK, DH, 512>::load16(src, off, dst + r * RT::RUN);
+    }
+  };
+  f32x16 sacc[KBL];
+  bf16x8 pb[KBL][2];
+  const int rows_at = RT::rows_at(lane), cols_at = RT::cols_at(lane);
+  auto scores = [&](int slot) {                           // S^T = K Q^T of the key tile in a ring slot
+    int at = slot * TILE + rows_at;
+    asm volatile("" : "+v"(at));                           // one register; the rest is immediates
+    const unsigned char* base = Kbuf + at;
+    constexpr int NSTEP = KBL * KS, AHEAD = 3;
+    bf16x8 f[AHEAD + 1];
+#pragma unroll
+    for (int b = 0; b < KBL; ++b) sacc[b] = f32x16{};
+#pragma unroll
+    for (int n = 0; n < AHEAD; ++n) f[n] = RT::read_rows(base, n % KBL, n / KBL);
+#pragma unroll
+    for (int n = 0; n < NSTEP; ++n) {
+      if (n + AHEAD < NSTEP) f[(n + AHEAD) % (AHEAD + 1)] = RT::read_rows(base, (n + AHEAD) % KBL, (n + AHEAD) / KBL);
+      sacc[n % KBL] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[n % (AHEAD + 1)], qf[n / KBL], sacc[n % KBL], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto values = [&](int slot) {                           // O^T += V^T P^T
+    int at = slot * TILE + cols_at;
+    asm volatile("" : "+v"(at));
+    const unsigned char* base = Vbuf + at;
+    constexpr int NSTEP = KBL * 2 * NB, AHEAD = 3;         // step n: 16 keys n / NB, 32 columns n % NB
+    bf16x8 f[AHEAD + 1];
+#pragma unroll
+    for (int n = 0; n < AHEAD; ++n) f[n] = RT::read_cols(base, n % NB, n / NB);
+#pragma unroll
+    for (int n = 0; n < NSTEP; ++n) {
+      if (n + AHEAD < NSTEP) f[(n + AHEAD) % (AHEAD + 1)] = RT::read_cols(base, (n + AHEAD) % NB, (n + AHEAD) / NB);
+      oacc[n % NB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[n % (AHEAD + 1)], pb[n / NB / 2][n / NB % 2], oacc[n % NB], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto softmax = [&](int t) {
+    if (t >= plain) {
+      asm volatile("");                                    // keeps the tests out of the tiles that need none
+      // element (b, r): key t * 64 + b * 32 + (r / 4) * 8 + half * 4 + r % 4
+      const int left = Lk - t * FK - half * 4, ahead = qpos - t * FK - half * 4;
+#pragma unroll
+      for (int b = 0; b < KBL; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int e = b * 32 + (r >> 2) * 8 + (r & 3);
+          if (e >= left || (CAUSAL && e > ahead)) sacc[b][r] = -INFINITY;
+        }
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int b = 0; b < KBL; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[b][r]);
+    mx = max_with_other_half(mx) * scale_log2;
+    // lazy rescaling, as in the kernel below
+    if (__builtin_amdgcn_ballot_w64(mx > m + 8.0f) != 0) {
+      const float m_new = fmaxf(m, mx);
+      const float corr = __builtin_amdgcn_exp2f(m - m_new);   // m = -inf at the start: 0
+      m = m_new;
+      lsum *= corr;
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) oacc[j][r] *= corr;
+    }
+    float psum[KBL] = {};
+#pragma unroll
+    for (int b = 0; b < KBL; ++b) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(sacc[b][r], scale_log2, -m));   // masked: exp2(-inf) = 0
+        sacc[b][r] = p;
+        psum[b] += p;
+      }
+      pb[b][0] = acc_to_operand(sacc[b], 0);
+      pb[b][1] = acc_to_operand(sacc[b], 1);
+    }
+#pragma unroll
+    for (int b = 0; b < KBL; ++b) lsum += psum[b];
+  };
+  settle_compiler_loads();                                // Q fragments, offsets
+  fetch(kbase, klds, 0, 0);
+  fetch(vbase, vlds, 0, 0);
+  fetch(kbase, klds, 1, 1);
+  wait_async_tiles();
+  phase_barrier();
+  if (wave >= 4) phase_barrier();                         // the second group stays one phase behind
+  if (mine > 0) scores(0);
+  phase_barrier();
+  for (int t = 0, s0 = 0, s1 = 1, s2 = 2; t < nkt; ++t) {   // ring slots of tiles t, t + 1, t + 2
+    // both groups are past the tiles these overwrite (V t - 2, K t - 1); they are read two phases from now
+    fetch(vbase, vlds, t + 1, s1);
+    fetch(kbase, klds, t + 2, s2);
+    if (t < mine) softmax(t);
+    phase_barrier();
+    if (t < mine) values(s0);
+    if (t + 1 < mine) scores(s1);
+    wait_async_tiles();
+    phase_barrier();
+    const int s = s0;
+    s0 = s1; s1 = s2; s2 = s;
+  }
+  if (wave < 4) phase_barrier();
+  lsum = sum_with_other_half(lsum);
+  if (qpos < L) {
+    // no key in this chunk: zero output, lse = -inf
+    const float inv = Lk > 0 ? 1.0f / lsum : 0.f;
+    bf16_t* op = o + (size_t)(lo + qpos) * ldo + hq * DH;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        bf16x4 w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = (bf16_t)(oacc[j][g * 4 + e] * inv);
+        *reinterpret_cast<bf16x4*>(op + j * 32 + g * 8 + half * 4) = w;
+      }
+    if (half == 0) lse[(size_t)hq * Ttot + lo + qpos] = Lk > 0 ? (m + log2f(lsum)) * LN2 : -INFINITY;
+  }
+}
+
 int count_tiles(const int32_t* cu_host, int S, int rows) {
   long n = 0;
   for (int s = 0; s < S; ++s) n += (cu_host[s + 1] - cu_host[s] + rows - 1) / rows;
   return (int)n;
 }
 
+// 256-row tiles and alternating groups where they cut the sequences about as well as 128-row tiles and give every
+// CU two of them, us: 25 x 640, 16 heads of 64, 63 -> 64; 8 documents of 411 to 1800, 32 heads of 128, 138 -> 124; too few, one
+// image of 577, 14 -> 19; 777 tokens, 32 heads of 128, 23 -> 26.
+bool fwd_alternating(const AttnArgs& a) {
+  const long ta = count_tiles(a.cu_host, a.S, AQ), tn = count_tiles(a.cu_host, a.S, FQ);
+  return ta * a.Hq >= 2 * NUM_CU && ta * 8 <= tn * 5;
+}
+
 template <int DH>
 bm_status fwd_launch(const AttnArgs& a, void* o, float* lse, hipStream_t st) {
+  const float sl2 = LOG2E / sqrtf((float)a.dh);
+  if constexpr (DH != 72) {
+    if (fwd_alternating(a)) {
+      const dim3 grid(count_tiles(a.cu_host, a.S, AQ) * a.Hq);
+      const SeqOrder ord = make_seq_order(a.cu_host, a.kv_cu_host(), a.S, AQ, !a.causal);
+      auto kern = a.causal ? fa_fwd_alt_kernel<DH, true> : fa_fwd_alt_kernel<DH, false>;
+      hipLaunchKernelGGL(kern, grid, dim3(512), 0, st, (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v,
+                         a.ld_qkv, a.kv_ld(), a.cu_dev, a.kv_cu_dev(), a.S, (bf16_t*)o, a.Hq * a.dh, lse, a.T, a.Hq,
+                         a.Hq / a.Hkv, sl2, ord);
+      BM_CHECK_LAUNCH("fa_fwd_alt");
+      return BM_OK;
+    }
+  }
   dim3 grid(count_tiles(a.cu_host, a.S, FQ) * a.Hq), block(256);
   if (grid.x == 0) return BM_OK;
-  const float sl2 = LOG2E / sqrtf((float)a.dh);
   // a query tile runs as long as its sequence has keys
   const SeqOrder ord = make_seq_order(a.cu_host, a.kv_cu_host(), a.S, FQ, !a.causal);
 #define BM_L(C)                                                                                  \
@@ -550,7 +807,6 @@ __global__ void fa_delta_kernel(const bf16_t* __restrict__ o, const bf16_t* __re
   if (live && c == 0) delta[(size_t)hq * Ttot + t] = s;
 }
 
-constexpr int NUM_CU = 256;
 constexpr int WIDE_KEYS = 256;  // keys per workgroup of the wide dK/dV kernel
 constexpr int BK_KEYS = 128;   // keys per workgroup in the dK/dV kernel (32 per wavefront)
 constexpr int BK_Q = 64;       // query rows per step
@@ -1031,12 +1287,6 @@ struct WideTile {
   static constexpr int Q = 0, D = RUNS * RUN, LSE = 2 * RUNS * RUN, DELTA = LSE + ROWS * 4, BYTES = DELTA + ROWS * 4;
   static constexpr int RING = 4;
 };
-
-__device__ inline const bf16_t* scalar_ptr(const void* p) {
-  const uint64_t b = reinterpret_cast<uint64_t>(p);
-  return reinterpret_cast<const bf16_t*>(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32) |
-                                         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b));
-}
 
 // the lane index, computed anew
 __device__ inline int fresh_lane() {
