@@ -746,7 +746,7 @@ int count_tiles(const int32_t* cu_host, int S, int rows) {
 // 256-row tiles and alternating groups where they cut the sequences about as well as 128-row tiles and give every
 // CU two of them, us: 25 x 640, 16 heads of 64, 63 -> 64; 8 documents of 411 to 1800, 32 heads of 128, 138 -> 124; too few, one
 // image of 577, 14 -> 19; 777 tokens, 32 heads of 128, 23 -> 26.
-bool fwd_alternating(const AttnArgs& a) {
+bool queries_alternating(const AttnArgs& a) {
   const long ta = count_tiles(a.cu_host, a.S, AQ), tn = count_tiles(a.cu_host, a.S, FQ);
   return ta * a.Hq >= 2 * NUM_CU && ta * 8 <= tn * 5;
 }
@@ -755,7 +755,7 @@ template <int DH>
 bm_status fwd_launch(const AttnArgs& a, void* o, float* lse, hipStream_t st) {
   const float sl2 = LOG2E / sqrtf((float)a.dh);
   if constexpr (DH != 72) {
-    if (fwd_alternating(a)) {
+    if (queries_alternating(a)) {
       const dim3 grid(count_tiles(a.cu_host, a.S, AQ) * a.Hq);
       const SeqOrder ord = make_seq_order(a.cu_host, a.kv_cu_host(), a.S, AQ, !a.causal);
       auto kern = a.causal ? fa_fwd_alt_kernel<DH, true> : fa_fwd_alt_kernel<DH, false>;
@@ -1741,6 +1741,171 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(
   }
 }
 
+// dQ with two groups of wavefronts that take turns (see the forward kernel): while one multiplies -- dS K of a key
+// tile, then Q K and dO V of the next -- the other one turns its scores into dS.  At head size 64, where the
+// MFMAs of a tile are no longer than its softmax, the kernel above is ahead (96 against 112 us on 16384 tokens of images).
+// us, two workgroups of four wavefronts -> this: 8192 x 8192 keys, 32 / 8 heads, 1522 -> 1332, causal 782 -> 687; 32768 tokens
+// of causal documents 4217 -> 3630; 8192 tokens of documents, 32 heads, 262 -> 253; 16 samples of about 1130, 24 heads, 445 both.
+template <bool CAUSAL>
+__global__ __launch_bounds__(512, 2) void fa_bwd_dq_alt_kernel(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
+    int ldk, const bf16_t* __restrict__ d_o, int ldo, const float* __restrict__ lse,
+    const float* __restrict__ delta, const int32_t* __restrict__ cu, const int32_t* __restrict__ cuk,
+    int S, bf16_t* __restrict__ dq, int ldd, int Ttot, int Hq, int group, float scale, float scale_log2,
+    SeqOrder ord) {
+  constexpr int DH = 128;
+  using RT = RunTile<DH>;
+  constexpr int KS = DH / 16, NB = DH / 32, KBL = FK / 32, TILE = RT::bytes(FK), RUNS = FK / RT::RPR / 8;
+  constexpr int KRING = 4, VRING = 3;                     // a K tile is read as rows in one phase, as columns two later
+  __shared__ __attribute__((aligned(1024))) unsigned char Kbuf[KRING * TILE];
+  __shared__ __attribute__((aligned(1024))) unsigned char Vbuf[VRING * TILE];
+  int seq, qt, nqt, tile_id, hq;
+  tile_and_head(Hq, &tile_id, &hq);
+  if (!find_tile(cu, ord, S, AQ, tile_id, &seq, &qt, &nqt)) return;
+  const int hk = hq / group;
+  const int lo = cu[seq], L = cu[seq + 1] - lo;
+  const int lok = cuk[seq], Lk = cuk[seq + 1] - lok;
+  const int q0 = qt * AQ;
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int qfirst = q0 + wave * 32;
+  const int qpos = qfirst + (lane & 31);                  // this lane's query (column of S^T)
+  const int qrow = min(qpos, L - 1);
+  bf16x8 qf[KS], dof[KS];
+  {
+    const bf16_t* qp = q + (size_t)(lo + qrow) * ld + hq * DH;
+    const bf16_t* dp = d_o + (size_t)(lo + qrow) * ldo + hq * DH;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      qf[ks] = load_chunk<DH>(qp, ks * 2 + half);
+      dof[ks] = load_chunk<DH>(dp, ks * 2 + half);
+    }
+  }
+  const float my_lse = lse[(size_t)hq * Ttot + lo + qrow] * LOG2E;
+  const float my_delta = delta[(size_t)hq * Ttot + lo + qrow];
+  f32x16 dqacc[NB];
+#pragma unroll
+  for (int j = 0; j < NB; ++j) dqacc[j] = f32x16{};
+  // key tiles of the workgroup, and those of this wavefront (none if its queries lie past the sequence)
+  const int nkt = ((CAUSAL ? min(Lk, q0 + AQ) : Lk) + FK - 1) / FK;
+  const int mine = qfirst >= L ? 0 : CAUSAL ? min(nkt, (qfirst + 31) / FK + 1) : nkt;
+  const int plain = CAUSAL ? min(Lk / FK, (qfirst + 1) / FK) : Lk / FK;   // leading tiles that need no mask test
+  const bf16_t* kbase = scalar_ptr(k + (size_t)lok * ldk + hk * DH);
+  const bf16_t* vbase = scalar_ptr(v + (size_t)lok * ldk + hk * DH);
+  const uint32_t klds = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)Kbuf;
+  const uint32_t vlds = (uint32_t)(size_t)(__attribute__((address_space(3))) unsigned char*)Vbuf;
+  // tile t of K or V into a ring slot; rows past the keys are clamped (their dS is 0)
+  auto fetch = [&](const bf16_t* base, uint32_t dst, int t) {
+    if (t >= nkt) return;
+    const int l = fresh_lane();
+    const bf16_t* src = base + (size_t)t * FK * ldk;
+    const int last = Lk - t * FK - 1;
+#pragma unroll
+    for (int i = 0; i < RUNS; ++i) {
+      const int r = wave * RUNS + i;
+      const uint32_t off = (uint32_t)min(r * RT::RPR + RT::load_row(l), last) * (uint32_t)ldk * 2u + (uint32_t)RT::load_chunk(l) * 16u;
+      TileAsync<FK, DH, 512>::load16(src, off, dst + r * RT::RUN);
+    }
+  };
+  f32x16 sacc[KBL], dpacc[KBL];
+  bf16x8 ds[KBL][2];
+  auto scores = [&](int kslot, int vslot) {               // S^T = K Q^T, dP^T = V dO^T of a key tile
+    const int at = RT::rows_at(fresh_lane());
+    int ka = kslot * TILE + at, va = vslot * TILE + at;
+    asm volatile("" : "+v"(ka), "+v"(va));                 // one register each; the rest is immediates
+    constexpr int NSTEP = KBL * KS, AHEAD = 2;             // step n: key block n % KBL, k-step n / KBL
+    bf16x8 fk[AHEAD + 1], fv[AHEAD + 1];
+    auto request = [&](int n) {
+      fk[n % (AHEAD + 1)] = RT::read_rows(Kbuf + ka, n % KBL, n / KBL);
+      fv[n % (AHEAD + 1)] = RT::read_rows(Vbuf + va, n % KBL, n / KBL);
+    };
+#pragma unroll
+    for (int b = 0; b < KBL; ++b) sacc[b] = dpacc[b] = f32x16{};
+#pragma unroll
+    for (int n = 0; n < AHEAD; ++n) request(n);
+#pragma unroll
+    for (int n = 0; n < NSTEP; ++n) {
+      if (n + AHEAD < NSTEP) request(n + AHEAD);
+      sacc[n % KBL] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fk[n % (AHEAD + 1)], qf[n / KBL], sacc[n % KBL], 0, 0, 0);
+      dpacc[n % KBL] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fv[n % (AHEAD + 1)], dof[n / KBL], dpacc[n % KBL], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto accumulate = [&](int kslot) {                      // dQ^T += K^T dS^T
+    int at = kslot * TILE + RT::cols_at(fresh_lane());
+    asm volatile("" : "+v"(at));
+    constexpr int NSTEP = KBL * 2 * NB, AHEAD = 3;         // step n: 16 keys n / NB, 32 columns n % NB
+    bf16x8 f[AHEAD + 1];
+#pragma unroll
+    for (int n = 0; n < AHEAD; ++n) f[n] = RT::read_cols(Kbuf + at, n % NB, n / NB);
+#pragma unroll
+    for (int n = 0; n < NSTEP; ++n) {
+      if (n + AHEAD < NSTEP) f[(n + AHEAD) % (AHEAD + 1)] = RT::read_cols(Kbuf + at, (n + AHEAD) % NB, (n + AHEAD) / NB);
+      dqacc[n % NB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[n % (AHEAD + 1)], ds[n / NB / 2][n / NB % 2], dqacc[n % NB], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  auto softmax = [&](int t) {
+    if (t >= plain) {
+      asm volatile("");                                    // keeps the tests out of the tiles that need none
+      const int h4 = (fresh_lane() >> 5) * 4, left = Lk - t * FK - h4, ahead = qfirst + (fresh_lane() & 31) - t * FK - h4;
+#pragma unroll
+      for (int b = 0; b < KBL; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int e = b * 32 + (r >> 2) * 8 + (r & 3);
+          if (e >= left || (CAUSAL && e > ahead)) sacc[b][r] = -INFINITY;   // P = 0
+        }
+    }
+#pragma unroll
+    for (int b = 0; b < KBL; ++b) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const float p = __builtin_amdgcn_exp2f(fmaf(sacc[b][r], scale_log2, -my_lse));
+        dpacc[b][r] = p * (dpacc[b][r] - my_delta);
+      }
+      ds[b][0] = acc_to_operand(dpacc[b], 0);
+      ds[b][1] = acc_to_operand(dpacc[b], 1);
+    }
+  };
+  settle_compiler_loads();                                // Q and dO fragments, lse, delta, offsets
+  fetch(kbase, klds, 0);
+  fetch(vbase, vlds, 0);
+  fetch(kbase, klds + TILE, 1);
+  fetch(vbase, vlds + TILE, 1);
+  wait_async_tiles();
+  phase_barrier();
+  if (wave >= 4) phase_barrier();                         // the second group stays one phase behind
+  if (mine > 0) scores(0, 0);
+  phase_barrier();
+  for (int t = 0, v1 = 1, v2 = 2; t < nkt; ++t) {         // V slots of tiles t + 1, t + 2
+    // both groups are past the tiles these overwrite (K t - 2, V t - 1); they are read two phases from now
+    fetch(kbase, klds + ((t + 2) & (KRING - 1)) * TILE, t + 2);
+    fetch(vbase, vlds + v2 * TILE, t + 2);
+    if (t < mine) softmax(t);
+    phase_barrier();
+    if (t < mine) accumulate(t & (KRING - 1));
+    if (t + 1 < mine) scores((t + 1) & (KRING - 1), v1);
+    wait_async_tiles();
+    phase_barrier();
+    v1 = v2;
+    v2 = v2 == VRING - 1 ? 0 : v2 + 1;
+  }
+  if (wave < 4) phase_barrier();
+  if (qpos < L) {
+    bf16_t* pq = dq + (size_t)(lo + qpos) * ldd + hq * DH;
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        bf16x4 w;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = (bf16_t)(dqacc[j][g * 4 + e] * scale);
+        *reinterpret_cast<bf16x4*>(pq + j * 32 + g * 8 + half * 4) = w;
+      }
+  }
+}
+
 // dk, dv = sum over the q-head parts of the fp32 partials, in part order
 __global__ void fa_dkdv_reduce_kernel(const float* __restrict__ part, int gsplit, int Ttot, int W /* Hkv*dh */,
                                       bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int ldd) {
@@ -1799,14 +1964,16 @@ bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const fl
                        (const bf16_t*)d_o, ldo, delta, a.T, a.Hq);
   const bool wide = DH == 128 && dkdv_wide(a);
   const int key_rows = wide ? WIDE_KEYS : BK_KEYS;
+  const bool alt = DH == 128 && queries_alternating(a);
+  const int query_rows = alt ? AQ : FQ;
   const int ktiles = count_tiles(a.kv_cu_host(), a.S, key_rows);
   const int gsplit = ktiles > 0 ? dkdv_group_split(ktiles, a.Hkv, a.Hq / a.Hkv) : 1;
   float* part = delta + align_up((size_t)a.Hq * a.T, 64);      // after the delta plane
   const int Tk = a.kv_T();
-  dim3 gkv(ktiles * a.Hkv * gsplit), gq(count_tiles(a.cu_host, a.S, FQ) * a.Hq);
+  dim3 gkv(ktiles * a.Hkv * gsplit), gq(count_tiles(a.cu_host, a.S, query_rows) * a.Hq);
   // a key tile runs as long as its sequence has queries, a query tile as long as it has keys
   const SeqOrder ord_kv = make_seq_order(a.kv_cu_host(), a.cu_host, a.S, key_rows, !a.causal);
-  const SeqOrder ord_q = make_seq_order(a.cu_host, a.kv_cu_host(), a.S, FQ, !a.causal);
+  const SeqOrder ord_q = make_seq_order(a.cu_host, a.kv_cu_host(), a.S, query_rows, !a.causal);
 #define BM_L(C)                                                                                  \
   if (wide && ktiles > 0)                                                                        \
     hipLaunchKernelGGL((fa_bwd_dkdv_wide_kernel<C>), gkv, dim3(512), 0, st, (const bf16_t*)a.q,  \
@@ -1827,7 +1994,12 @@ bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const fl
                        (const bf16_t*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), a.S,        \
                        (bf16_t*)dk, (bf16_t*)dv, ldd_kv, a.T, Tk, a.Hkv, a.Hq / a.Hkv, scale, sl2, \
                        gsplit, part, ord_kv);                                                    \
-  if (gq.x > 0)                                                                                  \
+  if (alt && gq.x > 0)                                                                           \
+    hipLaunchKernelGGL((fa_bwd_dq_alt_kernel<C>), gq, dim3(512), 0, st,    \
+                       (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, a.ld_qkv, a.kv_ld(), \
+                       (const bf16_t*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), a.S,        \
+                       (bf16_t*)dq, ldd, a.T, a.Hq, a.Hq / a.Hkv, scale, sl2, ord_q);            \
+  else if (gq.x > 0)                                                                             \
     hipLaunchKernelGGL((fa_bwd_dq_kernel<DH, C>), gq, dim3(256), 0, st, (const bf16_t*)a.q,      \
                        (const bf16_t*)a.k, (const bf16_t*)a.v, a.ld_qkv, a.kv_ld(),              \
                        (const bf16_t*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), a.S,        \
