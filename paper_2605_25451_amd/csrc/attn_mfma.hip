@@ -71,15 +71,6 @@ __device__ inline bf16x8 load_chunk(const bf16_t* row, int c) {
   return z;
 }
 
-// -v; the result passes through an empty asm, or the compiler would rather turn the sign in every use
-__device__ inline bf16x8 turn_sign(bf16x8 v) {
-  union { bf16x8 b; u32x4 u; } x;
-  x.b = v;
-  x.u ^= u32x4{0x80008000u, 0x80008000u, 0x80008000u, 0x80008000u};
-  asm volatile("" : "+v"(x.u));
-  return x.b;
-}
-
 // operand fragment, rows of the tile are the MFMA row/col index, dh is the k index:
 // lane l -> tile row row0 + l%32, dh = ks*16 + (l/32)*8 .. +7
 template <int DH>
@@ -618,6 +609,9 @@ __global__ __launch_bounds__(512, 2) void fa_fwd_alt_kernel(
   };
   f32x16 sacc[KBL];
   bf16x8 pb[KBL][2];
+  static_assert(KBL == 2, "one factor between the blocks of a tile");
+  bool late = false;                                      // the maximum moved in the tile's second block, by late_corr
+  float late_corr = 1.f;
   const int rows_at = RT::rows_at(lane), cols_at = RT::cols_at(lane);
   auto scores = [&](int slot) {                           // S^T = K Q^T of the key tile in a ring slot
     int at = slot * TILE + rows_at;
@@ -646,6 +640,12 @@ __global__ __launch_bounds__(512, 2) void fa_fwd_alt_kernel(
     for (int n = 0; n < AHEAD; ++n) f[n] = RT::read_cols(base, n % NB, n / NB);
 #pragma unroll
     for (int n = 0; n < NSTEP; ++n) {
+      if (n == 2 * NB && late) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) oacc[j][r] *= late_corr;
+      }
       if (n + AHEAD < NSTEP) f[(n + AHEAD) % (AHEAD + 1)] = RT::read_cols(base, (n + AHEAD) % NB, (n + AHEAD) / NB);
       oacc[n % NB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f[n % (AHEAD + 1)], pb[n / NB / 2][n / NB % 2], oacc[n % NB], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
@@ -664,37 +664,41 @@ __global__ __launch_bounds__(512, 2) void fa_fwd_alt_kernel(
           if (e >= left || (CAUSAL && e > ahead)) sacc[b][r] = -INFINITY;
         }
     }
-    float mx = -INFINITY;
-#pragma unroll
-    for (int b = 0; b < KBL; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[b][r]);
-    mx = max_with_other_half(mx) * scale_log2;
-    // lazy rescaling, as in the kernel below
-    if (__builtin_amdgcn_ballot_w64(mx > m + 8.0f) != 0) {
-      const float m_new = fmaxf(m, mx);
-      const float corr = __builtin_amdgcn_exp2f(m - m_new);   // m = -inf at the start: 0
-      m = m_new;
-      lsum *= corr;
-#pragma unroll
-      for (int j = 0; j < NB; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) oacc[j][r] *= corr;
-    }
-    float psum[KBL] = {};
+    late = false;
 #pragma unroll
     for (int b = 0; b < KBL; ++b) {
+      float mx = -INFINITY;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, sacc[b][r]);
+      mx = max_with_other_half(mx) * scale_log2;
+      // lazy rescaling, as in the kernel above; the output takes the factor of a later block between the
+      // blocks' products (see values)
+      if (__builtin_amdgcn_ballot_w64(mx > m + 8.0f) != 0) {
+        const float m_new = fmaxf(m, mx);
+        const float corr = __builtin_amdgcn_exp2f(m - m_new);   // m = -inf at the start: 0
+        m = m_new;
+        lsum *= corr;
+        if (b == 0) {
+#pragma unroll
+          for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) oacc[j][r] *= corr;
+        } else {
+          late = true;
+          late_corr = corr;
+        }
+      }
+      float psum = 0.f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const float p = __builtin_amdgcn_exp2f(fmaf(sacc[b][r], scale_log2, -m));   // masked: exp2(-inf) = 0
         sacc[b][r] = p;
-        psum[b] += p;
+        psum += p;
       }
+      lsum += psum;
       pb[b][0] = acc_to_operand(sacc[b], 0);
       pb[b][1] = acc_to_operand(sacc[b], 1);
     }
-#pragma unroll
-    for (int b = 0; b < KBL; ++b) lsum += psum[b];
   };
   settle_compiler_loads();                                // Q fragments, offsets
   fetch(kbase, klds, 0, 0);
@@ -845,9 +849,8 @@ __global__ __launch_bounds__(256, DH <= 64 ? 2 : 1) void fa_bwd_dkdv_kernel(
   const int kpos = kb0 + wave * 32 + (lane & 31);       // this lane's key (column of S)
   const int krow = min(kpos, L - 1);
 
-  // With several resident wavefronts to hide the LDS read, dP starts at the delta of its query row and V
-  // enters with its sign turned, so that the MFMAs leave -(dP - delta) at no cost on the vector unit;
-  // dK then carries the turned sign.  (With one wavefront per SIMD the read in front of the MFMAs costs more.)
+  // With several resident wavefronts to hide the LDS read, dP starts at -delta of its query row, so that the
+  // MFMAs leave dP - delta.  (With one wavefront per SIMD the read in front of the MFMAs costs more.)
   constexpr bool FOLD_DELTA = DH <= 64;
   bf16x8 kf[HeadDim<DH>::KS], vf[HeadDim<DH>::KS];
   {
@@ -857,7 +860,6 @@ __global__ __launch_bounds__(256, DH <= 64 ? 2 : 1) void fa_bwd_dkdv_kernel(
     for (int ks = 0; ks < HeadDim<DH>::KS; ++ks) {
       kf[ks] = load_chunk<DH>(kp, ks * 2 + half);
       vf[ks] = load_chunk<DH>(vp, ks * 2 + half);
-      if (FOLD_DELTA) vf[ks] = turn_sign(vf[ks]);
     }
   }
   f32x16 dkacc[HeadDim<DH>::NB], dvacc[HeadDim<DH>::NB];
@@ -918,7 +920,7 @@ __global__ __launch_bounds__(256, DH <= 64 ? 2 : 1) void fa_bwd_dkdv_kernel(
         for (int g = 0; g < 4; ++g) {
           const f32x4 d4 = *reinterpret_cast<const f32x4*>(Dl + qb * 32 + g * 8 + half * 4);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) dpacc[qb][g * 4 + e] = d4[e];
+          for (int e = 0; e < 4; ++e) dpacc[qb][g * 4 + e] = -d4[e];
         }
       }
     }
@@ -1008,7 +1010,6 @@ __global__ __launch_bounds__(256, DH <= 64 ? 2 : 1) void fa_bwd_dkdv_kernel(
       else { if (masked) step(it, std::true_type{}, P0{}); else step(it, std::false_type{}, P0{}); }
     }
   }
-  if (FOLD_DELTA) scale = -scale;
   if (kpos < L && gsplit > 1) {
     const size_t plane = (size_t)Ttot * Hkv * DH;
     float* pk = part + ((size_t)gs * 2 + 0) * plane + (size_t)(lo + kpos) * (Hkv * DH) + hk * DH;
@@ -1280,7 +1281,7 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_pair_kernel(
 // P and the next tile.
 // Against 32 keys per pair, us: 8192 queries x 8192 keys, 32 / 8 heads, 2207 -> 1875 (1.17 PFLOP/s of MFMAs), causal
 // 1138 -> 1002; 16 samples of about 1160 tokens, 24 heads, 848 -> 657; 8192 tokens of causal documents, 32
-// heads, 435 -> 362.  Fragments requested three steps ahead and a raised wave priority around the MFMAs
+// heads, 435 -> 365.  Fragments requested three steps ahead and a raised wave priority around the MFMAs
 // changed nothing.
 struct WideTile {
   static constexpr int ROWS = 32, RUN = 1024 + 16, RUNS = ROWS / 4;
@@ -1338,17 +1339,14 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
     constexpr int ROLE = decltype(role_t)::value;
     constexpr int ROWS_AT = ROLE == 0 ? W::Q : W::D, COLS_AT = ROLE == 0 ? W::D : W::Q;
     constexpr int STATS_AT = ROLE == 0 ? W::LSE : W::DELTA;
-    bf16x8 kvf[KB][KS];                                   // role 0 keeps K (for S), role 1 keeps -V (for -(dP - delta))
+    bf16x8 kvf[KB][KS];                                   // role 0 keeps K (for S), role 1 keeps V (for dP)
     {
       const int l = fresh_lane();
 #pragma unroll
       for (int b = 0; b < KB; ++b) {
         const bf16_t* p = (ROLE == 0 ? k : v) + (size_t)(lo + min(key0 + b * 32 + (l & 31), L - 1)) * ldk + hk * DH;
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-          kvf[b][ks] = load_chunk<DH>(p, ks * 2 + (l >> 5));
-          if (ROLE == 1) kvf[b][ks] = turn_sign(kvf[b][ks]);
-        }
+        for (int ks = 0; ks < KS; ++ks) kvf[b][ks] = load_chunk<DH>(p, ks * 2 + (l >> 5));
       }
     }
     f32x16 acc[NB][KB];                                   // role 0: dV^T, role 1: dK^T (unscaled)
@@ -1491,6 +1489,10 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
           }
         hand_over(n);
       } else {
+        x[0] = x[1] = f32x16{};
+        scores(n, x);
+        // dP - delta while the partner takes its exponentials (dP that starts at -delta saves the subtractions and
+        // 2 % of the kernel, and rounds some sums differently)
         const unsigned char* stats = tile_of(n) + STATS_AT + (fresh_lane() >> 5) * 16;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -1498,9 +1500,9 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
 #pragma unroll
           for (int b = 0; b < KB; ++b)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) x[b][g * 4 + e] = d4[e];   // starts at the delta of its query row
+            for (int e = 0; e < 4; ++e) x[b][g * 4 + e] -= d4[e];
         }
-        scores(n, x);
+        asm volatile("" : "+v"(x[0]), "+v"(x[1]));          // (subtracted here: behind the barrier, delta would push V fragments out)
         hand_over(n);
         const unsigned char* my_p = p_of(n);
 #pragma unroll
@@ -1531,7 +1533,7 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
       for (int t = skip; t < nqt; ++t, ++n) step(n, qstart + t * W::ROWS);
     }
 
-    const float out_scale = ROLE == 0 ? 1.0f : -scale;    // dV as it is, -dK times the softmax scale
+    const float out_scale = ROLE == 0 ? 1.0f : scale;     // dV as it is, dK times the softmax scale
     const int l = fresh_lane();
 #pragma unroll
     for (int b = 0; b < KB; ++b) {
