@@ -115,25 +115,13 @@ __global__ __launch_bounds__(NT) void attn_fwd_generic_kernel(
   }
 }
 
-template <typename T, int DH>
-__global__ void attn_delta_kernel(const T* __restrict__ o, const T* __restrict__ d_o, int ldo,
-                                  float* __restrict__ delta, int Ttot, int Hq) {
-  long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (long)Ttot * Hq) return;
-  int t = (int)(gid / Hq), hq = (int)(gid % Hq);
-  const T* po = o + (size_t)t * ldo + hq * DH;
-  const T* pd = d_o + (size_t)t * ldo + hq * DH;
-  float s = 0.f;
-#pragma unroll
-  for (int c = 0; c < DH; ++c) s = fmaf(Elt<T>::to_f(po[c]), Elt<T>::to_f(pd[c]), s);
-  delta[(size_t)hq * Ttot + t] = s;
-}
-
+// dq, and on the way delta = rowsum(dO * O) of its rows, which the dk/dv kernel reads: a small step is bound by its
+// launches, and delta's was one of 27 (4.2 us on its own).
 template <typename T, int DH, bool CAUSAL, int P>
 __global__ __launch_bounds__(NT) void attn_dq_generic_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int ld, int ldk,
-    const T* __restrict__ d_o, int ldo, const float* __restrict__ lse,
-    const float* __restrict__ delta, const int32_t* __restrict__ cu, const int32_t* __restrict__ cuk,
+    const T* __restrict__ o, const T* __restrict__ d_o, int ldo, const float* __restrict__ lse,
+    float* __restrict__ delta, const int32_t* __restrict__ cu, const int32_t* __restrict__ cuk,
     T* __restrict__ dq, int ldd, int Ttot, int group, float scale) {
   constexpr int BQ = NT / P;
   __shared__ float Ks[BT][tile_ld<DH, P>()];
@@ -154,7 +142,12 @@ __global__ __launch_bounds__(NT) void attn_dq_generic_kernel(
     acc[c] = 0.f;
   }
   const float my_lse = active ? lse[(size_t)hq * Ttot + lo + qi] : 0.f;
-  const float my_delta = active ? delta[(size_t)hq * Ttot + lo + qi] : 0.f;
+  float my_delta = 0.f;
+  if (active) {
+#pragma unroll
+    for (int c = 0; c < DH; ++c) my_delta = fmaf(Elt<T>::to_f(o[(size_t)(lo + qi) * ldo + hq * DH + c]), dor[c], my_delta);
+    if (part == 0) delta[(size_t)hq * Ttot + lo + qi] = my_delta;
+  }
   const int kend = CAUSAL ? min(Lk, q0 + BQ) : Lk;
   for (int k0 = 0; k0 < kend; k0 += BT) {
     for (int idx = threadIdx.x; idx < BT * DH; idx += NT) {
@@ -302,15 +295,12 @@ bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const fl
                      void* dk, void* dv, int ldd, float* delta, hipStream_t st) {
   const int ldo = a.Hq * a.dh;
   const float scale = 1.0f / sqrtf((float)a.dh);
-  long n = (long)a.T * a.Hq;
-  if (n > 0) {
-    hipLaunchKernelGGL((attn_delta_kernel<T, DH>), dim3(cdiv(n, 256)), dim3(256), 0, st, (const T*)o,
-                       (const T*)d_o, ldo, delta, a.T, a.Hq);
+  if (a.T > 0) {
     with_lanes(a.T, a.Hq, DH, [&](auto p) {
       constexpr int P = decltype(p)::value;
       hipLaunchKernelGGL((attn_dq_generic_kernel<T, DH, CAUSAL, P>), dim3(cdiv(a.max_seqlen, NT / P), a.S, a.Hq),
                          dim3(NT), 0, st, (const T*)a.q, (const T*)a.k, (const T*)a.v, a.ld_qkv, a.kv_ld(),
-                         (const T*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), (T*)dq, ldd, a.T,
+                         (const T*)o, (const T*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), (T*)dq, ldd, a.T,
                          a.Hq / a.Hkv, scale);
     });
   }
