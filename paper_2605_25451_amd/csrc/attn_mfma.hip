@@ -1,7 +1,7 @@
 // Variable-length flash attention on the gfx950 matrix cores (bf16 in, fp32
 // accumulate, online softmax in base 2), forward and backward.
 //
-// Packing: a workgroup owns one 128-row tile of ONE sequence and one head, so
+// Packing: a workgroup owns one tile of 128 or 256 rows of ONE sequence and one head, so
 // attention is block-diagonal by construction; tiles are enumerated by walking
 // cu_seqlens (no padded grid), longest-running tiles first.
 //
