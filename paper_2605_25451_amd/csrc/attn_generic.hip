@@ -68,6 +68,7 @@ __global__ __launch_bounds__(NT) void attn_fwd_generic_kernel(
     if (active) {
       float sc[BT / P];
       float tmax = -INFINITY;
+      bool counts = false;             // a score above -inf, or NaN, which fmaxf drops: it has to reach the row's sums
 #pragma unroll
       for (int jj = 0; jj < BT / P; ++jj) {
         const int j = jj * P + part, kj = k0 + j;
@@ -77,8 +78,9 @@ __global__ __launch_bounds__(NT) void attn_fwd_generic_kernel(
         bool ok = kj < Lk && (!CAUSAL || kj <= qi);
         sc[jj] = ok ? d : -INFINITY;
         tmax = fmaxf(tmax, sc[jj]);
+        counts |= sc[jj] != -INFINITY;
       }
-      if (tmax > -INFINITY) {
+      if (counts) {
         float mn = fmaxf(m, tmax);
         float corr = expf(m - mn);
         l *= corr;

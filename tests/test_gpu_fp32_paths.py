@@ -1,6 +1,6 @@
 """The kernels in fp32 arithmetic at the edges of their variants (needs a GPU): every tile of the GEMM with
 ragged edges, single elements and rows that are not aligned for wide loads; attention with eight lanes
-per row and with one."""
+per row and with one, also with a key that is not a number."""
 import numpy as np
 import pytest
 
@@ -52,3 +52,32 @@ def test_gemm(layout, dtype, M, N, K, pad):
 ])
 def test_attention(dtype, Hq, Hkv, dh, lens, causal):
     ops.test_attention_matches_definition(dtype, Hq, Hkv, dh, lens, causal)
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,dh,lens,key,causal", [
+    (synth.DTYPE_FP32, 4, 4, 16, [40, 33], 35, 0), (synth.DTYPE_FP32, 4, 2, 32, [70], 64, 1),   # the only key of its lane in the tile
+    (synth.DTYPE_FP32, 2, 2, 72, [65], 0, 1), (synth.DTYPE_BF16, 4, 2, 16, [12, 36], 12 + 35, 0), (synth.DTYPE_FP32, 2, 1, 128, [33], 32, 1),
+    (synth.DTYPE_FP32, 4, 4, 16, [40], 10, 0),                                                  # among others
+    (synth.DTYPE_FP32, 16, 16, 16, [129, 900], 128, 0), (synth.DTYPE_FP32, 16, 4, 16, [1057], 1056, 1),   # one lane per row: alone in its tile
+])
+def test_a_nan_key_reaches_every_row_that_sees_it(dtype, Hq, Hkv, dh, lens, key, causal):
+    import torch
+    from paper_2605_25451_amd import binding as bm
+    from paper_2605_25451_amd.runner import to_device
+    rng = np.random.default_rng(sum(lens) + key)
+    cu = synth.cu_from_lengths(lens)
+    T, W = int(cu[-1]), (Hq + 2 * Hkv) * dh
+    qkv = synth.to_storage(rng.standard_normal((T, W), dtype=np.float32), dtype)
+    dqkv = to_device(qkv, dtype)
+    dqkv[key, Hq * dh:(Hq + Hkv) * dh:dh] = float("nan")                 # one component of the key in every head
+    o = torch.zeros((T, Hq * dh), dtype=dqkv.dtype, device="cuda")
+    lse = torch.zeros((Hq, T), dtype=torch.float32, device="cuda")
+    print(f"nan key dtype={dtype} Hq={Hq} Hkv={Hkv} dh={dh} lens={lens} key={key} causal={causal}", flush=True)
+    bm.attention_forward(dtype, causal, Hq, Hkv, dh, dqkv, dqkv[:, Hq * dh:], dqkv[:, (Hq + Hkv) * dh:], W,
+                         torch.from_numpy(cu).cuda(), cu, len(lens), T, max(lens), o, lse)
+    torch.cuda.synchronize()
+    rows = np.arange(T)
+    s = np.searchsorted(cu, key, side="right") - 1
+    sees = (rows >= (key if causal else cu[s])) & (rows < cu[s + 1])
+    assert (np.isnan(o.float().cpu().numpy()).all(axis=1) == sees).all()
+    assert (np.isfinite(lse.cpu().numpy()).all(axis=0) == ~sees).all()
