@@ -6,6 +6,7 @@
 #include <stdarg.h>
 #include <stdio.h>
 
+#include <algorithm>
 #include <mutex>
 #include <vector>
 
@@ -56,6 +57,13 @@ size_t gemm_scratch_bytes(int layout, int M, int N, int K, int dtype) {
 size_t gemm_scratch_need(int layout, int M, int N, int K, int dtype) {
   if (layout == GEMM_TN) return gemm_scratch_bytes(layout, M, N, K, dtype);
   return gemm_generic_scratch_bytes(M, N, K);
+}
+
+size_t gemm_tn_scratch_rows(int M, int N, int K, int dtype) {
+  // more rows mean more tiles and so fewer ranges: the largest need is at a row count that fills its tiles
+  size_t b = gemm_scratch_bytes(GEMM_TN, M, N, K, dtype);
+  for (int m = 64; m < M; m += 64) b = std::max(b, gemm_scratch_bytes(GEMM_TN, m, N, K, dtype));
+  return b;
 }
 
 bm_status gemm(int layout, int dtype, int M, int N, int K, const void* A, int lda, const void* B,

@@ -144,6 +144,8 @@ struct GemmEpilogue {
 // back end need gemm_scratch_need().  TN: grows with K only.
 size_t gemm_scratch_bytes(int layout, int M, int N, int K, int dtype);
 size_t gemm_scratch_need(int layout, int M, int N, int K, int dtype);
+// workspace of a TN product of up to M rows (of C); grows with M
+size_t gemm_tn_scratch_rows(int M, int N, int K, int dtype);
 // workspace of the NT / NN products of up to `rows` rows and N columns: their k ranges are split only
 // while splits x rows stays below SPLIT_ROWS_MAX (few rows leave the chip idle otherwise).  Grows with
 // `rows`, so that a buffer sized for the longest pack serves every shorter one.

@@ -567,21 +567,24 @@ bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, con
   return BM_OK;
 }
 
-// common k split of a paired launch (0: the pair does not qualify)
-static int pair_splits(int K, int M0, int N0, int M1, int N1) {
+// Most k ranges of a paired launch (0: the pair does not qualify).  As split_cap(), it only grows with K.
+static int pair_split_cap(int K, int M0, int N0, int M1, int N1) {
   if (M0 < 256 || N0 < 256 || M1 < 256 || N1 < 256) return 0;
   const long tiles = (long)cdiv(M0, 256) * cdiv(N0, 256) + (long)cdiv(M1, 256) * cdiv(N1, 256);
+  return (int)std::min<long>(std::min<long>(NUM_CU / tiles, 32), cdiv(K, BK) / 4);
+}
+
+// the number of ranges it takes: the most that a whole number of slices each comes to
+static int pair_splits(int K, int M0, int N0, int M1, int N1) {
   const int slices = cdiv(K, BK);
-  int sp = (int)(NUM_CU / tiles);
-  if (sp > 32) sp = 32;
-  if (sp > slices / 4) sp = slices / 4;
+  int sp = pair_split_cap(K, M0, N0, M1, N1);
   for (; sp >= 1; --sp)
     if (cdiv(slices, cdiv(slices, sp)) == sp) break;
-  return sp < 1 ? 0 : sp;
+  return sp;
 }
 
 size_t gemm_mfma_tn_pair_scratch_bytes(int K, int M0, int N0, int M1, int N1) {
-  const int sp = pair_splits(K, M0, N0, M1, N1);
+  const int sp = pair_split_cap(K, M0, N0, M1, N1);
   if (sp <= 1) return 0;
   return align_up((size_t)sp * M0 * N0 * sizeof(float), 256) + (size_t)sp * M1 * N1 * sizeof(float);
 }

@@ -131,7 +131,7 @@ size_t max_gemm_scratch(const MDims& m, int dtype) {
     v = gemm_scratch_bytes(GEMM_TN, m.QKV, m.d, T, dtype); b = v > b ? v : b;
   }
   v = gemm_scratch_bytes(GEMM_TN, 6 * m.d, m.d, m.S, dtype); b = v > b ? v : b;
-  v = gemm_scratch_bytes(GEMM_TN, (int)align_up(m.S, 8), m.d, 6 * m.d, dtype); b = v > b ? v : b;
+  v = gemm_tn_scratch_rows((int)align_up(m.S, 8), m.d, 6 * m.d, dtype); b = v > b ? v : b;
   return b;
 }
 

@@ -157,6 +157,35 @@ def test_static_workspace_entry_refuses_oversized_packs_without_a_gpu():
     assert "built-in workspace" in str(e.value)
 
 
+@pytest.mark.parametrize("base,hidden,heads,kv_heads,mlp,dtype", [
+    (synth.decoder_7b, 1024, 8, 2, 1024, synth.DTYPE_BF16), (synth.decoder_moe, 1024, 8, 2, 256, synth.DTYPE_BF16),
+    (synth.vit_large, 512, 8, 8, 512, synth.DTYPE_BF16), (synth.vit_large, 256, 8, 8, 256, synth.DTYPE_FP32),
+    (synth.dit_block, 1024, 8, 8, 1024, synth.DTYPE_FP32), (synth.dit_block, 2048, 16, 16, 2048, synth.DTYPE_BF16),
+])
+def test_workspace_for_the_longest_pack_serves_every_shorter_one(base, hidden, heads, kv_heads, mlp, dtype):
+    cfg = synth.scaled(base(), hidden=hidden, n_q_heads=heads, n_kv_heads=kv_heads, head_dim=hidden // heads,
+                       mlp_hidden=mlp, dtype=dtype)
+    desc, last = bm.make_desc(cfg), (0, 0)
+    for T in range(1, 2200):
+        size = bm.block_sizes(desc, T, 1, T)
+        assert size[0] >= last[0] and size[1] >= last[1], T
+        last = size
+    last = 0
+    for S in range(1, 300):                                 # as many sequences as adaLN conditions
+        size = bm.block_sizes(desc, 600, S, 600)[1]
+        assert size >= last, S
+        last = size
+
+
+def test_two_stream_workspace_grows_with_tokens_and_samples():
+    cfg = synth.scaled(synth.dit_block(), hidden=1024, n_q_heads=8, n_kv_heads=8, head_dim=128, mlp_hidden=1024)
+    desc = bm.make_mmdit_desc(cfg, 1)
+    for sizes in ([bm.mmdit_sizes(desc, T, 300, 1)[1] for T in range(1, 2200)],
+                  [bm.mmdit_sizes(desc, 300, T, 1)[1] for T in range(1, 2200)],
+                  [bm.mmdit_sizes(desc, 600, 600, S)[1] for S in range(1, 300)]):
+        assert sizes == sorted(sizes)
+
+
 def test_mfma_yardstick_refuses_unknown_switches_without_a_gpu():
     """bm_probe_mfma_ex checks its arguments before it launches anything."""
     import ctypes as C
