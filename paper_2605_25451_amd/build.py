@@ -21,6 +21,7 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-mllvm", "-pragma-unroll-threshold=1000000",       # the GEMM k-step is one unrolled run of 64 MFMAs
     "-Wno-unused-command-line-argument", "-Wno-unused-result", "-Wno-unused-value",
+    "-Wno-inline-asm",                                  # m0 in a clobber list is reported as a reserved register
 ]
 
 

@@ -41,7 +41,8 @@ __device__ inline void end_phase() {
   __builtin_amdgcn_sched_barrier(0);
 }
 __device__ inline void load_to_lds(const bf16_t* base, uint32_t off, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" :: "s"(lds), "v"(off), "s"(base) : "memory");
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :: "s"(lds), "v"(off), "s"(base) : "memory", "m0");
 }
 
 // LDS layouts of a region of R rows x 64 k (the swizzles keep fragment reads free of bank conflicts):

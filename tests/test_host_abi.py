@@ -28,6 +28,18 @@ def test_library_exports_every_declared_symbol():
         assert hasattr(lib, n), n
 
 
+def test_assembly_that_writes_m0_says_so():
+    """An asm statement that sets m0 (the LDS address of a load that writes LDS) without declaring it lets the
+    compiler keep a value of its own there across the statement."""
+    src, found = os.path.join(ROOT, "paper_2605_25451_amd", "csrc"), 0
+    for f in sorted(os.listdir(src)):
+        for stmt in re.findall(r"asm volatile\((.*?)\);", open(os.path.join(src, f)).read(), flags=re.S):
+            if re.search(r"s_mov_b32 m0", stmt):
+                found += 1
+                assert '"m0"' in stmt, (f, stmt)
+    assert found >= 3
+
+
 @pytest.mark.parametrize("M", [1, 2, 3, 5, 8, 16, 32])
 @pytest.mark.parametrize("us", [1, 2, 4])
 @pytest.mark.parametrize("gen", [0, 1])
