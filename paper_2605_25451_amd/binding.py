@@ -156,6 +156,8 @@ def lib() -> C.CDLL:
         l.bm_probe_lds.restype = C.c_int
         l.bm_probe_issue.argtypes = [i32, i32, vp, vp]
         l.bm_probe_issue.restype = C.c_int
+        l.bm_probe_gemm_plan.argtypes = [i32] * 4 + [sz, pi32, pi32, pi32]
+        l.bm_probe_gemm_plan.restype = C.c_int
         l.bm_probe_read.restype = C.c_int
         l.bm_probe_fill.restype = C.c_int
         l.bm_probe_mfma.restype = C.c_int
@@ -482,6 +484,15 @@ def probe_lds(what, iters, src, src_bytes, out, stream=None):
 
 def probe_issue(n_valu, iters, out, stream=None):
     _check(lib().bm_probe_issue(n_valu, iters, _ptr(out), _stream() if stream is None else stream))
+
+
+def probe_gemm_plan(layout, M, N, K, scratch_bytes=None):
+    """(rows, columns of an output tile, number of k ranges); the workspace asked for unless given."""
+    if scratch_bytes is None:
+        scratch_bytes = gemm_scratch_bytes(layout, M, N, K, 0)
+    m, n, r = C.c_int32(), C.c_int32(), C.c_int32()
+    _check(lib().bm_probe_gemm_plan(layout, M, N, K, scratch_bytes, C.byref(m), C.byref(n), C.byref(r)))
+    return m.value, n.value, r.value
 
 
 def profile_begin():

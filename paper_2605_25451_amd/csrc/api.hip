@@ -181,6 +181,18 @@ extern "C" bm_status bm_gemm(int32_t layout, int32_t dtype, int32_t M, int32_t N
               (hipStream_t)hip_stream);
 }
 
+extern "C" bm_status bm_probe_gemm_plan(int32_t layout, int32_t M, int32_t N, int32_t K, size_t scratch_bytes,
+                                        int32_t* tile_m, int32_t* tile_n, int32_t* k_ranges) {
+  BM_ARG_CHECK(layout >= 0 && layout <= 2, "bm_probe_gemm_plan: layout %d", layout);
+  BM_ARG_CHECK(M > 0 && N > 0 && K > 0, "bm_probe_gemm_plan: sizes must be positive");
+  BM_ARG_CHECK(tile_m && tile_n && k_ranges, "bm_probe_gemm_plan: NULL output");
+  *tile_m = *tile_n = 0; *k_ranges = 0;
+  const int a_cols = layout == GEMM_TN ? M : K, b_cols = layout == GEMM_NT ? K : N;
+  if (gemm_mfma_supported(layout, BM_DTYPE_BF16, M, N, K, a_cols, b_cols, N, GemmEpilogue{}))
+    gemm_mfma_plan(layout, M, N, K, scratch_bytes, tile_m, tile_n, k_ranges);
+  return BM_OK;
+}
+
 static bm_status check_attn(int32_t dtype, int32_t mask, int32_t Hq, int32_t Hkv, int32_t dh,
                             const int32_t* cu_dev, const int32_t* cu_host, int32_t S, int32_t T,
                             int32_t max_seqlen, int32_t ld) {

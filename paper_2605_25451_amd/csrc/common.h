@@ -233,6 +233,7 @@ bm_status gemm_generic(int layout, int dtype, int M, int N, int K, const void* A
 bool gemm_mfma_supported(int layout, int dtype, int M, int N, int K, int lda, int ldb, int ldc,
                          const GemmEpilogue& epi);
 size_t gemm_mfma_scratch_bytes(int layout, int M, int N, int K);
+void gemm_mfma_plan(int layout, int M, int N, int K, size_t scratch_bytes, int* bm, int* bn, int* splits);
 bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
                     void* C, int ldc, const GemmEpilogue& epi, void* scratch, size_t scratch_bytes,
                     hipStream_t st);

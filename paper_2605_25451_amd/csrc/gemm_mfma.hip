@@ -384,19 +384,22 @@ struct Plan { int bm, bn, tiles_m, tiles_n, splits, k_per_split; };
 
 constexpr int NUM_CU = 256;
 
-// Tile and k split from a small cost model in microseconds, calibrated on the shapes of the ViT-L,
-// DiT, 7B, grouped-query and two-stream blocks at 577 to 32768 rows (96 shapes, every tile, splits
-// 1-16: the plan it picks is on average 0.4 % behind the best measured one).  A slice of k = 64 takes
-// t_min when the chip is nearly empty and t_full when every slot works (the matrix pipe's power
-// budget, shared by the active CUs), in between t_full * (share of busy slots)^power; a workgroup
-// adds t_fixed.  Transposed operands cost a few per cent more.  A split writes and reads fp32
-// partial tiles at 8 TB/s (they stay in the memory-side cache) and costs one more launch.
-struct TileKind { int bm, bn, slots; double t_min, t_full, power, t_fixed; };
+// Tile and k split from a small cost model in microseconds.  A slice of k = 64 takes t_min when the chip is
+// nearly empty and t_full when every slot works (the matrix pipe's power budget, shared by the active CUs), in
+// between t_full * (share of busy slots)^power; a workgroup adds t_fixed, and t_cut more if its k range ends inside
+// a slice.  f_tn: a slice with both operands transposed against one with none.  A weight gradient reads and writes
+// its fp32 C at 5.2 TB/s, a share `hidden` of which runs under the slices of others -- most where a CU holds two
+// workgroups, so that short contractions want the smallest tile (TN 12288x3072 over 128 rows: 83 us with 256x256
+// tiles, 70 with 128x128; over 1536 rows 154 both).  A split writes and reads fp32 partial tiles at 8 TB/s
+// (they stay in the memory-side cache) and costs one more launch.
+// Measured on 483 shapes (blocks of 1024 to 4096 columns at 300 to 16384 rows and shapes drawn over the same range;
+// every tile, splits 1-32): the plan it picks takes 0.9 % longer than the best one on average, 21 % at worst.
+struct TileKind { int bm, bn, slots; double t_min, t_full, power, t_fixed, t_cut, f_tn, hidden; };
 constexpr TileKind TILE_KINDS[] = {
-  {256, 256, NUM_CU, 0.87, 1.36, 0.6, 5.5},
-  {128, 256, NUM_CU, 0.55, 0.77, 0.5, 4.0},
-  {256, 128, NUM_CU, 0.55, 0.77, 0.5, 4.0},
-  {128, 128, 2 * NUM_CU, 0.45, 0.92, 0.0, 3.4},       // two workgroups per CU
+  {256, 256, NUM_CU, 0.87, 1.36, 0.6, 5.5, 2.3, 1.05, 0.25},
+  {128, 256, NUM_CU, 0.55, 0.77, 0.5, 4.0, 0.0, 1.12, 0.30},
+  {256, 128, NUM_CU, 0.55, 0.77, 0.5, 4.0, 0.0, 1.12, 0.30},
+  {128, 128, 2 * NUM_CU, 0.45, 0.92, 0.0, 3.4, 0.0, 1.12, 0.50},       // two workgroups per CU
 };
 
 // Splits of 2, 4 or 8 can be pinned to XCDs (see split_tile_of_block).
@@ -407,22 +410,25 @@ bool xcd_split_possible(int tiles, int splits) {
 // one grid of `wgs` workgroups that each walk `per` slices
 double grid_time(const TileKind& tk, int layout, bool cut, long wgs, int per) {
   const bool small = tk.bm == 128 && tk.bn == 128;
-  double f = layout == GEMM_NT ? 1.0 : layout == GEMM_NN ? 1.05 : tk.bm == tk.bn && !small ? 1.10 : 1.12;
-  if (small && cut) f *= 1.2;
+  const double f = layout == GEMM_NT ? 1.0 : layout == GEMM_NN ? 1.05 : tk.f_tn;
+  const double fixed = tk.t_fixed + (cut ? tk.t_cut : 0.0);
   const long full = wgs / tk.slots, rest = wgs % tk.slots;
-  double t = full * (per * tk.t_full * f + tk.t_fixed);
+  double t = full * (per * tk.t_full * f + fixed);
   if (rest) {
     const double u = (double)rest / tk.slots;
     double ts;
     if (small) ts = u <= 0.5 ? tk.t_min : tk.t_min + (tk.t_full - tk.t_min) * std::sqrt(2.0 * u - 1.0);
     else ts = std::max(tk.t_min, tk.t_full * std::pow(u, tk.power));
-    t += per * ts * f + tk.t_fixed;
+    t += per * ts * f + fixed;
   }
   return t;
 }
-double split_time(int layout, int splits, double mn) {
+// ... and its output of mn elements: the partial tiles of a split and their reduction, or a weight gradient's C
+double output_time(const TileKind& tk, int layout, int splits, double mn, double grid) {
   if (splits > 1) return 4.5 + (8.0 * splits + (layout == GEMM_TN ? 8.0 : 2.0)) * mn / 8e6;
-  return layout == GEMM_TN ? mn * 8.0 / 6e6 : 0.0;       // reading and writing the fp32 C
+  if (layout != GEMM_TN) return 0.0;
+  const double c = mn * 8.0 / 5.2e6;
+  return c - tk.hidden * std::min(c, grid);
 }
 
 // Most k ranges a plan may use.  Weight gradient: as many as fill the chip with 256x256 tiles, four
@@ -447,7 +453,8 @@ Plan make_plan(int layout, int M, int N, int K, size_t partial_bytes, bool may_s
       const int per = cdiv(slices, sp);
       if (cdiv(slices, per) != sp) continue;
       if (sp > 1 && sp * mn * sizeof(float) > (double)partial_bytes) break;
-      double t = grid_time(tk, layout, K % BK != 0, tiles * sp, per) + split_time(layout, sp, mn);
+      double t = grid_time(tk, layout, K % BK != 0, tiles * sp, per);
+      t += output_time(tk, layout, sp, mn, t);
       if (xcd_split_possible((int)tiles, sp)) t *= 0.97;
       if (t < best_t) {
         best_t = t;
@@ -528,6 +535,11 @@ size_t gemm_mfma_scratch_bytes(int layout, int M, int N, int K) {
   }
   const Plan pl = make_plan(layout, M, N, K, ~(size_t)0, true);
   return pl.splits > 1 ? (size_t)pl.splits * M * N * sizeof(float) : 0;
+}
+
+void gemm_mfma_plan(int layout, int M, int N, int K, size_t scratch_bytes, int* bm, int* bn, int* splits) {
+  const Plan pl = make_plan(layout, M, N, K, scratch_bytes, true);
+  *bm = pl.bm; *bn = pl.bn; *splits = pl.splits;
 }
 
 bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
@@ -617,9 +629,10 @@ bool gemm_mfma_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const vo
     make_plan(GEMM_TN, M0, N0, K, scratch_bytes, true, &t0);
     make_plan(GEMM_TN, M1, N1, K, scratch_bytes, true, &t1);
     const double mn0 = (double)M0 * N0, mn1 = (double)M1 * N1;
-    const double together = grid_time(TILE_KINDS[0], GEMM_TN, K % BK != 0,
-                                      ((long)a.tiles_m * a.tiles_n + (long)b.tiles_m * b.tiles_n) * sp, cdiv(slices, sp)) +
-                            split_time(GEMM_TN, sp, mn0) + split_time(GEMM_TN, sp, mn1);
+    double together = grid_time(TILE_KINDS[0], GEMM_TN, K % BK != 0,
+                                ((long)a.tiles_m * a.tiles_n + (long)b.tiles_m * b.tiles_n) * sp, cdiv(slices, sp));
+    if (sp > 1) together += output_time(TILE_KINDS[0], GEMM_TN, sp, mn0, 0.0) + output_time(TILE_KINDS[0], GEMM_TN, sp, mn1, 0.0);
+    else together += output_time(TILE_KINDS[0], GEMM_TN, 1, mn0 + mn1, together);
     if (together >= t0 + t1) return false;
   }
   const size_t part0 = a.splits > 1 ? align_up((size_t)a.splits * M0 * N0 * sizeof(float), 256) : 0;

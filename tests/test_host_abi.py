@@ -198,6 +198,27 @@ def test_two_stream_workspace_grows_with_tokens_and_samples():
         assert sizes == sorted(sizes)
 
 
+@pytest.mark.parametrize("layout,M,N,K,tile", [
+    # weight gradients of few rows are bound by C: two workgroups per CU
+    (2, 12288, 3072, 64, 128), (2, 5784, 3528, 102, 128), (2, 7536, 2872, 97, 128), (2, 15168, 1520, 512, 128),
+    (2, 12288, 3072, 8192, 256), (2, 12288, 3072, 2304, 256),
+    # short contractions that end inside a slice
+    (0, 2204, 7856, 200, 128), (1, 2204, 7856, 72, 128), (0, 8192, 12288, 4096, 256),
+])
+def test_tile_of_short_contractions(layout, M, N, K, tile):
+    assert bm.probe_gemm_plan(layout, M, N, K)[:2] == (tile, tile)
+
+
+def test_gemm_plan_without_a_workspace_and_off_the_matrix_path():
+    assert bm.probe_gemm_plan(0, 577, 1024, 4096)[2] > 1                       # few rows: the k range is split ...
+    assert bm.probe_gemm_plan(0, 577, 1024, 4096, 0)[2] == 1                   # ... in the workspace that is given
+    assert bm.probe_gemm_plan(0, 4096, 1024, 4096)[2] == 1                     # many rows: never
+    assert bm.probe_gemm_plan(2, 64, 64, 7) == bm.probe_gemm_plan(0, 64, 60, 64) == (0, 0, 0)
+    for bad in ((3, 1, 1, 1), (0, 0, 1, 1), (0, 1, 1, -1)):
+        with pytest.raises(bm.BmError):
+            bm.probe_gemm_plan(*bad, 0)
+
+
 def test_mfma_yardstick_refuses_unknown_switches_without_a_gpu():
     """bm_probe_mfma_ex checks its arguments before it launches anything."""
     import ctypes as C
