@@ -1,7 +1,7 @@
-"""GEMM parity at the edges of the tiles and of the k split (needs a GPU): every tile the plan knows, with
-ragged rows, columns and contractions, few rows against a long contraction, and a product that is given
-no workspace to split in.  Tolerances are those of the other GEMM tests (bf16 storage of the result
-2e-2, fp32 weight gradient 1e-4)."""
+"""GEMM parity at the edges of the tiles and of the k split (needs a GPU): every tile the plan knows in every layout,
+with ragged rows, columns and contractions, few rows against a long contraction, and a product that is given
+no workspace to split in.  The plan of each case is asserted, so that another choice of tiles cannot drop a
+kernel from this file."""
 import numpy as np
 import pytest
 
@@ -9,49 +9,70 @@ from paper_2605_25451_amd import synth
 
 pytestmark = pytest.mark.gpu
 
+T256, T128x256, T256x128, T128 = (256, 256), (128, 256), (256, 128), (128, 128)
 CASES = [
-    # layout, M, N, K
-    (0, 5477, 1024, 1024), (1, 5477, 1024, 1016), (0, 1032, 5480, 1024), (1, 1032, 5480, 584),   # 128 x 256 and 256 x 128
-    (0, 2049, 4104, 64), (0, 2049, 4104, 120), (1, 2049, 4104, 136), (1, 2049, 4104, 200),       # 256 x 256: 1 to 4 slices, cut
-    (2, 4104, 2056, 1), (2, 4104, 2056, 65), (2, 4104, 2056, 129), (2, 4104, 2056, 777),
-    (0, 577, 1024, 4096), (1, 577, 1032, 4104), (0, 1, 1024, 4096), (1, 40, 1024, 11008), (0, 300, 2048, 2056),   # split
-    (2, 1024, 1032, 5477), (2, 264, 256, 4001),
+    # layout, M, N, K, tile, k range split
+    (0, 2049, 4104, 64, T256, False), (0, 2049, 4104, 184, T256, False), (1, 2049, 4104, 136, T256, False),   # 1 to 4 slices, cut
+    (1, 2049, 4104, 200, T256, False), (2, 2976, 2960, 640, T256, False), (2, 1704, 4640, 808, T256, False),
+    (0, 932, 5288, 448, T128x256, False), (0, 1590, 4600, 264, T128x256, False), (1, 1466, 5272, 256, T128x256, False),
+    (1, 1351, 5008, 272, T128x256, False), (2, 1456, 3520, 1536, T128x256, False), (2, 1176, 4856, 1168, T128x256, False),
+    (0, 2960, 2096, 320, T256x128, False), (0, 2698, 2944, 288, T256x128, False), (1, 1187, 4896, 320, T256x128, False),
+    (1, 6786, 784, 336, T256x128, False), (2, 2720, 2072, 1408, T256x128, False), (2, 4568, 1040, 1473, T256x128, False),
+    (2, 4104, 2056, 1, (0, 0), False), (2, 4104, 2056, 65, T128, False), (2, 4104, 2056, 129, T128, False), (2, 4104, 2056, 777, T256, False),
+    (0, 5477, 1024, 1024, T128x256, False), (1, 5477, 1024, 1016, T128x256, False), (0, 1032, 5480, 1024, T128x256, False),
+    (1, 1032, 5480, 584, T128x256, False),
+    # split
+    (0, 577, 1024, 4096, T128, True), (1, 577, 1032, 4104, T128, True), (0, 1, 1024, 4096, T128, True), (1, 40, 1024, 11008, T128, True),
+    (0, 300, 2048, 2056, T128, True), (2, 264, 256, 4001, T128, True),
+    (0, 2, 4856, 4288, T128x256, True), (0, 1, 5280, 5968, T128x256, True), (1, 2, 5264, 6848, T128x256, True), (1, 1, 3392, 7064, T128x256, True),
+    (0, 129, 3640, 8032, T256x128, True), (1, 142, 4384, 4472, T256x128, True),
+    (2, 592, 4192, 6272, T128x256, True), (2, 264, 3920, 4087, T128x256, True), (2, 152, 4448, 8451, T256x128, True), (2, 1024, 1032, 5477, T128, True),
+    (2, 3696, 672, 8923, T256, True),
 ]
 
 
 @pytest.mark.parametrize("scratch", [True, False], ids=["workspace", "no-workspace"])
-@pytest.mark.parametrize("layout,M,N,K", CASES)
-def test_gemm_tiles(layout, M, N, K, scratch):
+@pytest.mark.parametrize("layout,M,N,K,tile,split", CASES)
+def test_gemm_tiles(layout, M, N, K, tile, split, scratch):
     import torch
     from paper_2605_25451_amd import binding as bm
     from paper_2605_25451_amd.runner import to_device
     if not scratch and (layout == 2 or M < 577):
         pytest.skip("weight gradients and skinny products are given the workspace they ask for")
+    if scratch:
+        plan = bm.probe_gemm_plan(layout, M, N, K)
+        assert plan[:2] == tile and (plan[2] > 1) == split, plan
     rng = np.random.default_rng(M + 3 * N + 7 * K + layout)
     A = synth.round_to_bf16(rng.standard_normal((K, M) if layout == 2 else (M, K), dtype=np.float32))
     B = synth.round_to_bf16(rng.standard_normal((N, K) if layout == 0 else (K, N), dtype=np.float32))
     bias = None if layout == 2 else synth.round_to_bf16(rng.standard_normal(N, dtype=np.float32))
     A64, B64 = A.astype(np.float64), B.astype(np.float64)
+    a, b = A64.T if layout == 2 else A64, B64.T if layout == 0 else B64
     dA, dB = to_device(A, synth.DTYPE_BF16), to_device(B, synth.DTYPE_BF16)
     if layout == 2:
-        C0 = rng.standard_normal((M, N), dtype=np.float32)
-        ref, dC = C0 + A64.T @ B64, torch.from_numpy(C0).cuda()
+        start = rng.standard_normal((M, N), dtype=np.float32)
+        dC = torch.from_numpy(start).cuda()
     else:
-        ref = A64 @ (B64.T if layout == 0 else B64) + bias
+        start = bias
         dC = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+    ref = a @ b + start
     nbytes = bm.gemm_scratch_bytes(layout, M, N, K, synth.DTYPE_BF16) if scratch else 0
     ws = torch.empty(max(nbytes, 16), dtype=torch.uint8, device="cuda")
     print(f"gemm layout={layout} M={M} N={N} K={K} scratch={nbytes}", flush=True)
     bm.gemm(layout, synth.DTYPE_BF16, M, N, K, dA, A.shape[1], dB, B.shape[1], dC, N,
             None if bias is None else to_device(bias, synth.DTYPE_BF16), ws if nbytes else None, nbytes)
     torch.cuda.synchronize()
-    got = dC.double().cpu().numpy()
-    assert np.abs(got - ref).max() <= (1e-4 if layout == 2 else 2e-2) * np.abs(ref).max()
+    # a sum of K products in fp32 in any order, and the bias or the old C: at most K + 2 roundings of the
+    # sum of absolute values; and the rounding of a bf16 result
+    bound = (K + 2) * 2.0 ** -24 * (np.abs(a) @ np.abs(b) + np.abs(start)) + (0 if layout == 2 else 2.0 ** -8 * np.abs(ref))
+    assert (np.abs(dC.double().cpu().numpy() - ref) <= bound).all()
 
 
 @pytest.mark.parametrize("layout,M,N,K", [
-    (0, 2049, 4104, 72), (0, 2049, 4104, 184), (1, 2049, 4104, 88), (0, 1032, 5480, 120), (1, 1032, 5480, 136),
-    (2, 4104, 2056, 71), (2, 4104, 2056, 95), (2, 2056, 4104, 129), (2, 4104, 2056, 190), (2, 1032, 5480, 76), (2, 5480, 1032, 67),
+    (0, 2049, 4104, 184), (1, 1700, 4704, 136), (2, 1432, 5424, 391), (2, 2776, 2976, 456),         # 256 x 256
+    (0, 1368, 4592, 272), (1, 1703, 4272, 208), (2, 4232, 1160, 1281),                              # 128 x 256
+    (0, 2738, 2360, 272), (1, 8590, 800, 216), (2, 1160, 4368, 1217),                               # 256 x 128
+    (0, 1032, 5480, 72), (1, 1032, 5480, 88), (2, 4104, 2056, 71), (2, 2056, 4104, 95),             # 128 x 128
 ])
 def test_cut_slices(layout, M, N, K):
     """Contractions that end inside a slice: what memory holds behind them (here: not a number) stays out of the sums."""
