@@ -5,13 +5,12 @@
 //   NT: C[M,N]  = A[M,K] B[N,K]^T      NN: C[M,N] = A[M,K] B[K,N]
 //   TN: C[M,N] += A[K,M]^T B[K,N]      (C fp32, accumulated)
 //
-// Operands go from memory straight into the registers of v_mfma_f32_16x16x4_f32: no LDS, no barrier
-// in the loop, and many loads in flight.  The small products this serves are bound by latency, and
-// the 64x64 LDS tiles that were here paid one memory latency, two barriers and 16 rounds of LDS
-// reads per 16 k: NT 40x64x256 27.5 -> 8.2 us (the launch itself), 1024x256x256 29.6 -> 8.3,
-// 256x64x1000 96 -> 8.5, 1000x1000x1000 118 -> 36, 2048x2048x2048 461 -> 157, 4096x4096x1024 927 -> 355
-// (TN 526 -> 391).  Error against fp64 as before, half of it where four wavefronts share a k range.
-// Every access is clamped into its matrix; what lies past the k range counts as zero.
+// Two kernels.  In gemm_direct_kernel operands go from memory straight into the registers of
+// v_mfma_f32_16x16x4_f32: no LDS, no barrier in the loop, and many loads in flight, which is what small products,
+// bound by latency, want; every wavefront reads its own rows.  gemm_tiled_kernel stages 64x64 tiles in LDS, so that
+// how the rows lie costs little, but pays a memory latency and two barriers per 16 k.  See choose_kernel()
+// for the line between them.  Every access of either is clamped into its matrix or left out, and what lies past the
+// k range counts as zero.
 #include "common.h"
 
 namespace bm {
@@ -21,8 +20,8 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int NUM_CU = 256;
-constexpr int GT = 64;   // tile edge the k split is chosen for
-constexpr int GK = 16;   // k step: four MFMAs; lane l holds k = 4 (l/16) + s of step s
+constexpr int GT = 64;   // tile edge of the tiled kernel, for which the k split is chosen too
+constexpr int GK = 16;   // k step (direct kernel: four MFMAs; lane l holds k = 4 (l/16) + s of step s)
 
 // Operand values of one 16(row) x 16(k) block: lane l has row l%16, v[s] is k = k0 + 4 (l/16) + s.
 // KCONT: k is contiguous in memory (row stride ld), else rows are (k stride ld).  WIDE: the four values
@@ -47,12 +46,12 @@ __device__ inline void load_block(const T* __restrict__ p, int ld, int row, int 
 }
 
 // F = 1: a workgroup owns one 16x16 tile and its four wavefronts take every fourth k step each; the
-// four sums meet in LDS.  F = 2, 4: a wavefront owns F x F blocks, a workgroup 32F x 32F.
+// four sums meet in LDS.  F = 2: a wavefront owns 2x2 blocks, a workgroup 64x64.
 // With k_per_split < K the grid's z index selects a k range and the workgroup stores
 // its fp32 partial tile into `partial` [z][M][N]; finish_kernel then sums the ranges
 // in order and applies the epilogue (skinny problems: few output tiles, long K).
 template <typename T, int LAYOUT, int F, bool WIDE>
-__global__ __launch_bounds__(256) void gemm_generic_kernel(
+__global__ __launch_bounds__(256) void gemm_direct_kernel(
     int M, int N, int K, const T* __restrict__ A, int lda, const T* __restrict__ B, int ldb,
     void* __restrict__ Cv, int ldc, const T* __restrict__ bias, const T* __restrict__ residual,
     int out_fp32, int k_per_split, float* __restrict__ partial, GemmGroups grp) {
@@ -152,6 +151,109 @@ __global__ __launch_bounds__(256) void gemm_generic_kernel(
   }
 }
 
+// 64x64 output tile per workgroup, 16-deep k slices staged in LDS, a 4x4 register tile per thread.  Every
+// access is bounds-checked.  k ranges as above.
+template <typename T, int LAYOUT>
+__global__ __launch_bounds__(256) void gemm_tiled_kernel(
+    int M, int N, int K, const T* __restrict__ A, int lda, const T* __restrict__ B, int ldb,
+    void* __restrict__ Cv, int ldc, const T* __restrict__ bias, const T* __restrict__ residual,
+    int out_fp32, int k_per_split, float* __restrict__ partial, GemmGroups grp) {
+  __shared__ float As[GK][GT + 4];
+  __shared__ float Bs[GK][GT + 4];
+  const int tid = threadIdx.x;
+  const int m0 = blockIdx.y * GT, n0 = blockIdx.x * GT;
+  int kbeg = blockIdx.z * k_per_split;
+  int kfin = min(K, kbeg + k_per_split);
+  if (grp.group_rows) {              // grouped weight gradient: blockIdx.z is the group
+    kbeg = min(grp.group_rows[blockIdx.z], K);
+    kfin = min(grp.group_rows[blockIdx.z + 1], K);
+    if (kbeg >= kfin) return;
+    Cv = (float*)Cv + (long)blockIdx.z * grp.c_stride;
+  } else if (grp.tile_group) {       // grouped forward / input gradient: B of this row block's group
+    const int g = grp.tile_group[m0 / MOE_PAD];
+    if (g < 0) return;
+    B += (long)g * grp.b_stride;
+  }
+  const int ty = tid >> 4, tx = tid & 15;
+  float acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+
+  for (int k0 = kbeg; k0 < kfin; k0 += GK) {
+    // A slice -> As[k][m]
+    if (LAYOUT == GEMM_TN) {
+      int k = tid >> 4, m = (tid & 15) * 4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        int gm = m0 + m + e, gk = k0 + k;
+        As[k][m + e] = (gm < M && gk < kfin) ? Elt<T>::to_f(A[(size_t)gk * lda + gm]) : 0.f;
+      }
+    } else {
+      int m = tid >> 2, k = (tid & 3) * 4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        int gm = m0 + m, gk = k0 + k + e;
+        As[k + e][m] = (gm < M && gk < kfin) ? Elt<T>::to_f(A[(size_t)gm * lda + gk]) : 0.f;
+      }
+    }
+    // B slice -> Bs[k][n]
+    if (LAYOUT == GEMM_NT) {
+      int n = tid >> 2, k = (tid & 3) * 4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        int gn = n0 + n, gk = k0 + k + e;
+        Bs[k + e][n] = (gn < N && gk < kfin) ? Elt<T>::to_f(B[(size_t)gn * ldb + gk]) : 0.f;
+      }
+    } else {
+      int k = tid >> 4, n = (tid & 15) * 4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        int gn = n0 + n + e, gk = k0 + k;
+        Bs[k][n + e] = (gn < N && gk < kfin) ? Elt<T>::to_f(B[(size_t)gk * ldb + gn]) : 0.f;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < GK; ++k) {
+      float a[4], b[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) a[i] = As[k][ty * 4 + i];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) b[j] = Bs[k][tx * 4 + j];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
+    }
+    __syncthreads();
+  }
+
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    int gm = m0 + ty * 4 + i;
+    if (gm >= M) continue;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      int gn = n0 + tx * 4 + j;
+      if (gn >= N) continue;
+      size_t idx = (size_t)gm * ldc + gn;
+      float v = acc[i][j];
+      if (partial) {
+        partial[((size_t)blockIdx.z * M + gm) * N + gn] = v;
+      } else if (LAYOUT == GEMM_TN) {
+        ((float*)Cv)[idx] += v;
+      } else {
+        if (bias) v += Elt<T>::to_f(bias[gn]);
+        if (residual) v += Elt<T>::to_f(residual[idx]);
+        if (out_fp32) ((float*)Cv)[idx] = v;
+        else ((T*)Cv)[idx] = Elt<T>::from_f(v);
+      }
+    }
+  }
+}
+
 template <typename T, int LAYOUT>
 __global__ void finish_kernel(const float* __restrict__ partial, int splits, int M, int N,
                               void* __restrict__ Cv, int ldc, const T* __restrict__ bias,
@@ -179,41 +281,50 @@ int generic_splits(int M, int N, int K) {
   return s < 1 ? 1 : s;
 }
 
-// Blocks per wavefront edge: the largest tile that still gives every CU a workgroup (a wavefront of
-// F x F blocks loads 2F blocks of operands for F^2 of products).
-int block_edge(int M, int N) {
-  if ((long)cdiv(M, 128) * cdiv(N, 128) >= NUM_CU) return 4;
-  return (long)cdiv(M, 64) * cdiv(N, 64) >= NUM_CU ? 2 : 1;
-}
-
 bool aligned_rows(const void* p, int ld, size_t es) { return reinterpret_cast<uintptr_t>(p) % (4 * es) == 0 && ld % 4 == 0; }
 
-template <typename T, int LAYOUT, int F>
-void launch_kernel(bool wide, int M, int N, int K, const T* A, int lda, const T* B, int ldb, void* C, int ldc,
+// Which kernel: 0 tiled, else F of the direct one.
+//  - Few 64x64 tiles x k ranges per CU (`load`) are bound by the chain of k steps: one 16x16 tile per workgroup, whose
+//    wavefronts share the k range.  Later its loads (64 values per 16 products) cost more than the chain:
+//    2x2 blocks.
+//  - Where k is contiguous (NT, NN), one value at a time or four bf16 values leave most of every 64-byte segment that
+//    is requested unused, and a short contraction is nothing but those requests: the tiled kernel, from about a
+//    workgroup per CU on (NN: one of its operands is read along its rows).  The same goes for bf16 weight gradients
+//    of less than a k step (12288x4096 over 3 rows 147 / 318 / 165 us).
+// us, tiled / direct with 16x16 / with 2x2 blocks.  fp32: NT 40x64x256 27.5 / 8.2 / -, 1028^3 135 / 65 / 55, 2052^3 421 / 468 / 272,
+// TN 2052^3 353 / 590 / 275; odd rows, NT 1540^3 271 / 557 / 362, 1000x256x1024 31 / 75 / 29.  bf16: NT 2052^3 384 / 922 / 585, NN 343 /
+// 565 / 373, TN 302 / 454 / 313.  Over 4226 shapes of both types, 24 to 6000 rows and columns and K from 1 to 4000: 30 % less time
+// than the tiled kernel alone (geometric mean), 2.4 % more than the best of the three.
+int choose_kernel(int layout, int M, int N, int K, int z, bool bf16, bool wide) {
+  const double load = (double)cdiv(M, GT) * cdiv(N, GT) * z / NUM_CU;
+  if (load < (wide || layout == GEMM_TN ? 0.75 : 0.5)) return 1;
+  if (layout == GEMM_TN) return bf16 && K < 16 ? 0 : 2;
+  if (wide && !bf16) return 2;
+  if (wide && K < 80) return 0;
+  return load < (layout == GEMM_NT ? 1.0 : wide ? 2.0 : 3.0) ? 2 : 0;
+}
+
+template <typename T, int LAYOUT>
+void launch_kernel(int which, bool wide, int M, int N, int K, const T* A, int lda, const T* B, int ldb, void* C, int ldc,
                    const GemmEpilogue& epi, int per, float* partial, int z, const GemmGroups& g, hipStream_t st) {
-  constexpr int TILE = F == 1 ? 16 : 32 * F;
-  auto kern = wide ? gemm_generic_kernel<T, LAYOUT, F, true> : gemm_generic_kernel<T, LAYOUT, F, false>;
-  hipLaunchKernelGGL(kern, dim3(cdiv(N, TILE), cdiv(M, TILE), z), dim3(256), 0, st, M, N, K, A, lda, B, ldb, C, ldc,
+  const int tile = which == 1 ? 16 : 64;
+  auto kern = which == 0 ? gemm_tiled_kernel<T, LAYOUT>
+            : which == 1 ? (wide ? gemm_direct_kernel<T, LAYOUT, 1, true> : gemm_direct_kernel<T, LAYOUT, 1, false>)
+                         : (wide ? gemm_direct_kernel<T, LAYOUT, 2, true> : gemm_direct_kernel<T, LAYOUT, 2, false>);
+  hipLaunchKernelGGL(kern, dim3(cdiv(N, tile), cdiv(M, tile), z), dim3(256), 0, st, M, N, K, A, lda, B, ldb, C, ldc,
                      (const T*)epi.bias, (const T*)epi.residual, epi.out_fp32, per, partial, g);
 }
 
 template <typename T>
 void launch_layout(int layout, int M, int N, int K, const T* A, int lda, const T* B, int ldb, void* C, int ldc,
                    const GemmEpilogue& epi, int per, float* partial, int z, const GemmGroups& g, hipStream_t st) {
-  const int f = block_edge(M, N);
   // every operand whose k is contiguous can be read four values at a time
   const bool wide = K % 4 == 0 && (layout == GEMM_TN || aligned_rows(A, lda, sizeof(T))) &&
                     (layout != GEMM_NT || aligned_rows(B, ldb, sizeof(T))) && g.b_stride % 4 == 0;
-#define BM_F(LAY)                                                                                          \
-  do {                                                                                                     \
-    if (f == 1) launch_kernel<T, LAY, 1>(wide, M, N, K, A, lda, B, ldb, C, ldc, epi, per, partial, z, g, st);      \
-    else if (f == 2) launch_kernel<T, LAY, 2>(wide, M, N, K, A, lda, B, ldb, C, ldc, epi, per, partial, z, g, st); \
-    else launch_kernel<T, LAY, 4>(wide, M, N, K, A, lda, B, ldb, C, ldc, epi, per, partial, z, g, st);             \
-  } while (0)
-  if (layout == GEMM_NT) BM_F(GEMM_NT);
-  else if (layout == GEMM_NN) BM_F(GEMM_NN);
-  else BM_F(GEMM_TN);
-#undef BM_F
+  const int which = choose_kernel(layout, M, N, K, z, sizeof(T) == 2, wide);
+  if (layout == GEMM_NT) launch_kernel<T, GEMM_NT>(which, wide, M, N, K, A, lda, B, ldb, C, ldc, epi, per, partial, z, g, st);
+  else if (layout == GEMM_NN) launch_kernel<T, GEMM_NN>(which, wide, M, N, K, A, lda, B, ldb, C, ldc, epi, per, partial, z, g, st);
+  else launch_kernel<T, GEMM_TN>(which, wide, M, N, K, A, lda, B, ldb, C, ldc, epi, per, partial, z, g, st);
 }
 
 template <typename T>

@@ -1,5 +1,5 @@
-"""The kernels in fp32 arithmetic at the edges of their variants (needs a GPU): every tile of the GEMM with
-ragged edges, single elements and rows that are not aligned for wide loads; attention with eight lanes
+"""The kernels in fp32 arithmetic at the edges of their variants (needs a GPU): both GEMM kernels and every block of
+theirs with ragged edges, single elements and rows that are not aligned for wide loads; attention with eight lanes
 per row and with one, also with a key that is not a number."""
 import numpy as np
 import pytest
@@ -12,8 +12,10 @@ pytestmark = pytest.mark.gpu
 GEMM_CASES = [
     # M, N, K, extra columns of the operands
     (1, 1, 1, 0), (16, 16, 16, 0), (17, 15, 5, 0), (40, 192, 64, 0), (33, 70, 68, 4), (129, 47, 257, 3), (64, 16, 1000, 1),
-    (1030, 1025, 36, 0), (1030, 1025, 35, 1),      # a wavefront owns 2x2 blocks
-    (2060, 2050, 20, 0), (2060, 2050, 33, 3),      # 4x4 blocks
+    (1030, 1025, 36, 0), (1030, 1025, 35, 1),      # 2x2 blocks per wavefront, or tiles in LDS
+    (2060, 2050, 20, 0), (2060, 2050, 33, 3),
+    (700, 830, 45, 1), (830, 900, 100, 4),         # about a tile per CU
+    (1000, 250, 1030, 1), (1000, 250, 1032, 0),    # k ranges
 ]
 
 
