@@ -391,9 +391,10 @@ constexpr int NUM_CU = 256;
 // its fp32 C at 5.2 TB/s, a share `hidden` of which runs under the slices of others -- most where a CU holds two
 // workgroups, so that short contractions want the smallest tile (TN 12288x3072 over 128 rows: 83 us with 256x256
 // tiles, 70 with 128x128; over 1536 rows 154 both).  A split writes and reads fp32 partial tiles at 8 TB/s
-// (they stay in the memory-side cache) and costs one more launch.
-// Measured on 483 shapes (blocks of 1024 to 4096 columns at 300 to 16384 rows and shapes drawn over the same range;
-// every tile, splits 1-32): the plan it picks takes 0.9 % longer than the best one on average, 21 % at worst.
+// (they stay in the memory-side cache) and costs one more launch (TN 8x1024 over 802 rows: 12.1 us, in three ranges 9.0).
+// Measured on 527 shapes (blocks of 1024 to 4096 columns at 300 to 16384 rows, shapes drawn over the same range, and
+// gradients of 8 to 128 conditions; every tile, splits 1-32): the plan it picks takes 1.6 % longer than the best one on
+// average, 29 % at worst.
 struct TileKind { int bm, bn, slots; double t_min, t_full, power, t_fixed, t_cut, f_tn, hidden; };
 constexpr TileKind TILE_KINDS[] = {
   {256, 256, NUM_CU, 0.87, 1.36, 0.6, 5.5, 2.3, 1.05, 0.25},
@@ -425,7 +426,7 @@ double grid_time(const TileKind& tk, int layout, bool cut, long wgs, int per) {
 }
 // ... and its output of mn elements: the partial tiles of a split and their reduction, or a weight gradient's C
 double output_time(const TileKind& tk, int layout, int splits, double mn, double grid) {
-  if (splits > 1) return 4.5 + (8.0 * splits + (layout == GEMM_TN ? 8.0 : 2.0)) * mn / 8e6;
+  if (splits > 1) return layout == GEMM_TN ? 2.5 + (splits + 1) * mn / 1e6 : 4.5 + (4 * splits + 1) * mn / 4e6;
   if (layout != GEMM_TN) return 0.0;
   const double c = mn * 8.0 / 5.2e6;
   return c - tk.hidden * std::min(c, grid);
