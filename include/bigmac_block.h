@@ -264,6 +264,12 @@ bm_status bm_probe_issue(int32_t n_valu, int32_t iters, float* out_dev, void* hi
  * to the kernels for any shape instead. */
 bm_status bm_probe_gemm_plan(int32_t layout, int32_t M, int32_t N, int32_t K, size_t scratch_bytes,
                              int32_t* tile_m /* host */, int32_t* tile_n /* host */, int32_t* k_ranges /* host */);
+/* What bf16 attention launches for a pack (host only): rows per workgroup of the forward, dQ and dK/dV kernels,
+ * 0 where the head size goes to the kernels in plain fp32 arithmetic.  cu_k_host: the keys' own packing, NULL if
+ * it is the queries'. */
+bm_status bm_probe_attention_plan(int32_t mask, int32_t Hq, int32_t Hkv, int32_t dh, const int32_t* cu_q_host,
+                                  const int32_t* cu_k_host, int32_t S, int32_t* fwd_rows /* host */,
+                                  int32_t* dq_rows /* host */, int32_t* dkdv_rows /* host */);
 
 /* ---- nested schedule (host only; Sec. 3.1 and the BuildSchedule figure) ------------ */
 

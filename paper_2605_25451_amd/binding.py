@@ -158,6 +158,8 @@ def lib() -> C.CDLL:
         l.bm_probe_issue.restype = C.c_int
         l.bm_probe_gemm_plan.argtypes = [i32] * 4 + [sz, pi32, pi32, pi32]
         l.bm_probe_gemm_plan.restype = C.c_int
+        l.bm_probe_attention_plan.argtypes = [i32] * 4 + [vp, vp, i32, pi32, pi32, pi32]
+        l.bm_probe_attention_plan.restype = C.c_int
         l.bm_probe_read.restype = C.c_int
         l.bm_probe_fill.restype = C.c_int
         l.bm_probe_mfma.restype = C.c_int
@@ -493,6 +495,16 @@ def probe_gemm_plan(layout, M, N, K, scratch_bytes=None):
     m, n, r = C.c_int32(), C.c_int32(), C.c_int32()
     _check(lib().bm_probe_gemm_plan(layout, M, N, K, scratch_bytes, C.byref(m), C.byref(n), C.byref(r)))
     return m.value, n.value, r.value
+
+
+def probe_attention_plan(mask, Hq, Hkv, dh, cu_q_host, cu_k_host=None):
+    """Rows per workgroup of the forward, dQ and dK/dV kernels."""
+    q = _host_cu(cu_q_host)
+    k = None if cu_k_host is None else _host_cu(cu_k_host)
+    f, d, w = C.c_int32(), C.c_int32(), C.c_int32()
+    _check(lib().bm_probe_attention_plan(mask, Hq, Hkv, dh, q.ctypes.data, None if k is None else k.ctypes.data, len(q) - 1,
+                                         C.byref(f), C.byref(d), C.byref(w)))
+    return f.value, d.value, w.value
 
 
 def profile_begin():

@@ -747,12 +747,30 @@ int count_tiles(const int32_t* cu_host, int S, int rows) {
   return (int)n;
 }
 
-// 256-row tiles and alternating groups where they cut the sequences about as well as 128-row tiles and give every
-// CU two of them, us: 25 x 640, 16 heads of 64, 63 -> 64; 8 documents of 411 to 1800, 32 heads of 128, 138 -> 124; too few, one
-// image of 577, 14 -> 19; 777 tokens, 32 heads of 128, 23 -> 26.
+// keys a query walks on average
+double keys_per_query(const AttnArgs& a) {
+  const int32_t* ck = a.kv_cu_host();
+  double pairs = 0;
+  for (int s = 0; s < a.S; ++s) pairs += (double)(a.cu_host[s + 1] - a.cu_host[s]) * (ck[s + 1] - ck[s]);
+  return a.T > 0 ? (a.causal ? 0.5 : 1.0) * pairs / a.T : 0.0;
+}
+
+// 256-row tiles and alternating groups, or 128-row tiles and two workgroups per CU?  The former where they cut the
+// sequences about as well and come to two per CU or more, and
+//  - where a query walks enough keys to pay for the turns' start and end.  Forward, 128 -> 256 rows, us: head size 128,
+//    bidirectional, 24 x 256, 32 heads, 55 -> 62; 16 x 512, 24 heads, 74 -> 78; 4 x 2048, 24 heads, 217 -> 197; causal 12 x 520,
+//    24 heads, 60 -> 70; 8 documents of 411 to 1800, 32 heads, 128 -> 122.  Head size 64, bidirectional, 4 x 900, 32 heads, 48 -> 44.
+//  - under a full mask, where the last round is nearly full, since all tiles of a sequence take equally long: head size 64,
+//    8 x 768, 24 heads (2.25 rounds), 47 -> 52; 128, 6 x 1000, 16 heads (1.5 rounds), 65 -> 69.
+//  - not at head size 64 under a causal mask, where the vector unit bounds both and long tiles cannot be evened out: 4 x 2048,
+//    16 heads, 66 -> 72; 2 x 2600, 24 heads, 73 -> 87; ahead only with 64 heads (4096, 172 -> 157).
+// 189 packs of 577 to 18432 tokens, both masks, 16 to 64 heads: no choice of 256 rows is more than 4 % behind 128.
 bool queries_alternating(const AttnArgs& a) {
-  const long ta = count_tiles(a.cu_host, a.S, AQ), tn = count_tiles(a.cu_host, a.S, FQ);
-  return ta * a.Hq >= 2 * NUM_CU && ta * 8 <= tn * 5;
+  if (a.causal && a.dh == 64) return false;
+  const long ta = count_tiles(a.cu_host, a.S, AQ), tn = count_tiles(a.cu_host, a.S, FQ), wgs = ta * a.Hq;
+  if (wgs < 2 * NUM_CU || ta * 8 > tn * 5) return false;
+  if (a.causal) return keys_per_query(a) >= 600;
+  return keys_per_query(a) >= 800 && (long)cdiv(wgs, NUM_CU) * NUM_CU * 4 <= wgs * 5;
 }
 
 template <int DH>
@@ -762,7 +780,8 @@ bm_status fwd_launch(const AttnArgs& a, void* o, float* lse, hipStream_t st) {
     if (queries_alternating(a)) {
       const dim3 grid(count_tiles(a.cu_host, a.S, AQ) * a.Hq);
       const SeqOrder ord = make_seq_order(a.cu_host, a.kv_cu_host(), a.S, AQ, !a.causal);
-      auto kern = a.causal ? fa_fwd_alt_kernel<DH, true> : fa_fwd_alt_kernel<DH, false>;
+      auto kern = fa_fwd_alt_kernel<DH, false>;
+      if constexpr (DH == 128) if (a.causal) kern = fa_fwd_alt_kernel<DH, true>;
       hipLaunchKernelGGL(kern, grid, dim3(512), 0, st, (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v,
                          a.ld_qkv, a.kv_ld(), a.cu_dev, a.kv_cu_dev(), a.S, (bf16_t*)o, a.Hq * a.dh, lse, a.T, a.Hq,
                          a.Hq / a.Hkv, sl2, ord);
@@ -1938,19 +1957,23 @@ int dkdv_group_split(int tiles, int Hkv, int group) {
   return gsplit;
 }
 
-// The wide dK/dV kernel (head size 128) or the one with 128 keys per workgroup?  Both hold a CU alone.  The
-// wide one needs three workgroups per CU to even out the tiles of a causal pack, or to be done in one round where
-// the other is not, and sequences that 256-key tiles cut about as well.  Whole backward, us, narrow ->
-// wide: three rounds or more, 8 documents of 411 to 1800, 32 heads, 482 -> 447; 8 x 600, 32 / 8 heads, 238 -> 231; one
-// round, 4 x 400, 24 heads, 85 -> 71; neither, 777 tokens, 32 heads, 70 -> 88; 4 x 2048, 16 / 4 heads, 346 -> 376; cut
-// badly, 32 x 257, 16 heads, 168 -> 190.
+// The wide dK/dV kernel (head size 128) or the one with 128 keys per workgroup?  Both hold a CU alone.  Whole
+// backward, us, narrow -> wide.  The wide one needs
+//  - sequences that 256-key tiles cut about as well: 32 x 257, 16 heads, 168 -> 190;
+//  - three workgroups per CU to even out its tiles (8 documents of 411 to 1800, 32 heads, 473 -> 431; 777 tokens, 32 heads, 70 ->
+//    88), or, when all tiles take equally long, to be done in one round where the other is not: bidirectional 4 x 400,
+//    24 heads, 85 -> 71; under a causal mask the longest tile decides: 4096, 16 heads, 297 -> 360; 2048 + 900 + two short, 16
+//    heads, 145 -> 187;
+//  - heads of a group that it splits no further than the other, or enough queries per key to pay for the fp32 partials:
+//    32 / 8 heads, bidirectional, 24 x 256 (split 4 against 2), 193 -> 243; 12 x 640 403 -> 465; 16 x 1152 1398 -> 1371;
+//    causal 4 x 2048 618 -> 639.  dK/dV alone of 8192 x 8192 keys 2207 -> 1875, causal 1138 -> 1002.
 bool dkdv_wide(const AttnArgs& a) {
   const int tw = count_tiles(a.kv_cu_host(), a.S, WIDE_KEYS), tn = count_tiles(a.kv_cu_host(), a.S, BK_KEYS);
   if (tw == 0 || tw * 2L * 4 > tn * 5L) return false;
-  const int group = a.Hq / a.Hkv;
-  const long wide = (long)tw * a.Hkv * dkdv_group_split(tw, a.Hkv, group);
-  const long narrow = (long)tn * a.Hkv * dkdv_group_split(tn, a.Hkv, group);
-  return wide >= 3 * NUM_CU || (wide <= NUM_CU && narrow > NUM_CU);
+  const int group = a.Hq / a.Hkv, split_w = dkdv_group_split(tw, a.Hkv, group), split_n = dkdv_group_split(tn, a.Hkv, group);
+  if (split_w != split_n && keys_per_query(a) < (a.causal ? 3000 : 1100)) return false;
+  const long wide = (long)tw * a.Hkv * split_w, narrow = (long)tn * a.Hkv * split_n;
+  return wide >= 3 * NUM_CU || (!a.causal && wide <= NUM_CU && narrow > NUM_CU);
 }
 
 template <int DH>
@@ -2028,6 +2051,13 @@ bm_status attention_forward_mfma(const AttnArgs& a, void* o, float* lse, hipStre
   if (a.dh == 128) return fwd_launch<128>(a, o, lse, st);
   if (a.dh == 72) return fwd_launch<72>(a, o, lse, st);
   return fwd_launch<64>(a, o, lse, st);
+}
+
+void attention_mfma_plan(const AttnArgs& a, int* fwd_rows, int* dq_rows, int* dkdv_rows) {
+  const bool alt = a.dh != 72 && queries_alternating(a);
+  *fwd_rows = alt ? AQ : FQ;
+  *dq_rows = alt && a.dh == 128 ? AQ : FQ;
+  *dkdv_rows = a.dh == 128 && dkdv_wide(a) ? WIDE_KEYS : BK_KEYS;
 }
 
 size_t attention_backward_mfma_scratch_bytes(int Hq, int Hkv, int dh, int Tq, int Tk) {

@@ -219,6 +219,24 @@ def test_gemm_plan_without_a_workspace_and_off_the_matrix_path():
             bm.probe_gemm_plan(*bad, 0)
 
 
+@pytest.mark.parametrize("mask,Hq,Hkv,dh,lens,rows", [
+    # too few keys per query for turns, or for the fp32 partials of a head split
+    (0, 32, 32, 128, [256] * 24, (128, 128, 256)), (0, 32, 8, 128, [640] * 12, (128, 128, 128)), (1, 24, 24, 128, [520] * 12, (128, 128, 256)),
+    (1, 16, 4, 128, [2048] * 4, (256, 256, 128)), (0, 16, 16, 64, [500] * 16, (128, 128, 128)),
+    # a last round that is nearly empty; the longest tile of a causal pack alone in its round
+    (0, 24, 24, 64, [900] * 4, (128, 128, 128)), (0, 16, 16, 128, [1000] * 6, (128, 128, 128)), (1, 16, 16, 128, [4096], (128, 128, 128)),
+    # head size 64 under a causal mask; head size 72; the kernels for any head size
+    (1, 16, 16, 64, [8192], (128, 128, 128)), (0, 16, 16, 72, [8192], (128, 128, 128)), (0, 16, 16, 32, [8192], (0, 0, 0)),
+    # long sequences
+    (0, 24, 24, 128, [1152] * 16, (256, 256, 256)), (1, 32, 32, 128, [2048] * 4, (256, 256, 256)), (0, 16, 16, 64, [8192], (256, 128, 128)),
+    (1, 32, 8, 128, [8192], (256, 256, 256)), (0, 24, 24, 128, [400] * 4, (128, 128, 256)),
+])
+def test_rows_per_workgroup_of_the_attention_kernels(mask, Hq, Hkv, dh, lens, rows):
+    cu = synth.cu_from_lengths(lens)
+    assert bm.probe_attention_plan(mask, Hq, Hkv, dh, cu) == rows
+    assert bm.probe_attention_plan(mask, Hq, Hkv, dh, cu, cu) == rows          # keys with a packing of their own
+
+
 def test_mfma_yardstick_refuses_unknown_switches_without_a_gpu():
     """bm_probe_mfma_ex checks its arguments before it launches anything."""
     import ctypes as C
