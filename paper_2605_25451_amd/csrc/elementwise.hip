@@ -175,7 +175,7 @@ __global__ __launch_bounds__(NormBwdWaves<NV>::N * 64) void norm_bwd_kernel(
   constexpr int NS = SUMS ? NV : 1;
   constexpr int NW = NormBwdWaves<NV>::N;
   constexpr int RPB = NW / SPLIT;          // rows per workgroup and trip
-  extern __shared__ __attribute__((aligned(16))) float sm[];   // [RPB][d]
+  extern __shared__ __attribute__((aligned(16))) float sm[];   // [RPB][d]; none without column sums
   __shared__ float rowsum[2][RPB][SPLIT][2];     // two trips' worth: one barrier per trip is enough
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int slot = wave / SPLIT, part = wave % SPLIT;
@@ -565,7 +565,7 @@ static bm_status norm_bwd_dispatch(const NormArgs& a, const void* x, const float
   constexpr int VEC = Elt<T>::VEC;
   int nv = cdiv(a.d, WAVE * VEC);
   dim3 grid(norm_bwd_blocks(a.T, a.d));
-  const size_t row_lds = (size_t)a.d * sizeof(float);
+  const size_t row_lds = NormBwdParts<KIND, SUMS>::NP > 0 ? (size_t)a.d * sizeof(float) : 0;
 #define BM_LAUNCH_NV(NVV, SP)                                                                    \
   const size_t lds = row_lds * (NormBwdWaves<NVV>::N / SP);                                      \
   if (lds > 60 * 1024)  /* rows of 8192: more than a launch gets unasked */                      \
