@@ -6,6 +6,8 @@
 // dependency order is the execution order.
 #include "common.h"
 
+#include <algorithm>
+
 #include <vector>
 
 using namespace bm;
@@ -160,19 +162,21 @@ Sizes plan_sizes(const bm_executor_config& c, const bm_microbatch* mbs, const bm
                  al((size_t)z.maxT_gen * c.gen.hidden * es);
   }
   // scratch: block workspaces, projector split-K partials, loss partials; two ping-pong gradients.
-  // A block's workspace is not monotone in the token count (a shorter contraction can be cut into
-  // more k ranges, each with its own fp32 partial tile), so the largest pack alone does not bound
-  // it: the maximum is taken over the shape of every unit and microbatch that will run.
+  // The maximum over every unit and microbatch that will run.  The projectors get what they can make use of,
+  // whatever the blocks need: how far a product is split, and with it its rounding, then depends on its own
+  // shape and not on what else runs.
   size_t sc = loss_scratch_bytes(), v;
   auto upto = [&](size_t b) { sc = b > sc ? b : sc; };
   for (int m = 0; m < c.M; ++m) upto(scratch_bytes_of(c.llm, mbs[m].T, mbs[m].S));
   for (int u = 0; u < U; ++u) {
     upto(scratch_bytes_of(c.enc, units[u].T, units[u].S));
     upto(gemm_scratch_bytes(GEMM_TN, c.llm.hidden, c.enc.hidden, units[u].T, c.llm.dtype));
+    upto(gemm_rows_scratch_bytes(units[u].T, std::max(c.llm.hidden, c.enc.hidden), c.llm.dtype));
     if (c.n_gen_blocks > 0) {
       const int tpi = c.gen_tokens_per_image > 0 ? c.gen_tokens_per_image : 1;
       upto(scratch_bytes_of(c.gen, units[u].S * tpi, units[u].S));
       upto(gemm_scratch_bytes(GEMM_TN, c.gen.hidden, c.llm.hidden, units[u].S, c.llm.dtype));
+      upto(gemm_rows_scratch_bytes(units[u].S, std::max(c.llm.hidden, c.gen.hidden), c.llm.dtype));
     }
   }
   z.scratch = al(sc);

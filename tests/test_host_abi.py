@@ -189,6 +189,23 @@ def test_workspace_for_the_longest_pack_serves_every_shorter_one(base, hidden, h
         last = size
 
 
+def test_executor_workspace_covers_its_projectors():
+    """Eight short microbatches that share one encoder unit: the unit's rows, not the blocks of one microbatch, decide
+    how far the projector's k range is split."""
+    import numpy as np
+    enc = synth.scaled(synth.vit_large(), hidden=64, n_q_heads=1, n_kv_heads=1, head_dim=64, mlp_hidden=64)
+    llm, M, rows = synth.decoder_7b(), 8, 8
+    cu, ecu, p = np.array([0, rows], np.int32), np.arange(M + 1, dtype=np.int32) * rows, 256      # p: never dereferenced
+    mbs, units = (bm.Microbatch * M)(), (bm.Unit * M)()
+    for m in range(M):
+        mbs[m] = bm.Microbatch(rows, 1, p, cu.ctypes.data, p, rows, p, 1, p, p)
+    units[0] = bm.Unit(M * rows, M, p, ecu.ctypes.data, p, None, None, None, None)
+    cfg = bm.ExecutorConfig(bm.make_desc(enc), bm.make_desc(llm), bm.make_desc(synth.dit_block()), 1, 1, 0, M, M, 1)
+    partials = 16 * M * rows * llm.hidden * 4                                                    # 16 ranges
+    saved = bm.executor_arena_bytes(cfg, mbs, units, 2, 2) - bm.executor_arena_bytes(cfg, mbs, units, 1, 1)
+    assert bm.executor_arena_bytes(cfg, mbs, units, 1, 1) >= partials + saved
+
+
 def test_two_stream_workspace_grows_with_tokens_and_samples():
     cfg = synth.scaled(synth.dit_block(), hidden=1024, n_q_heads=8, n_kv_heads=8, head_dim=128, mlp_hidden=1024)
     desc = bm.make_mmdit_desc(cfg, 1)
