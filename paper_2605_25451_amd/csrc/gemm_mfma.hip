@@ -546,7 +546,9 @@ void gemm_mfma_plan(int layout, int M, int N, int K, size_t scratch_bytes, int* 
 bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
                     void* C, int ldc, const GemmEpilogue& epi, void* scratch, size_t scratch_bytes,
                     hipStream_t st) {
-  // the k range is split as far as the workspace allows; a fused activation needs the whole sum at once
+  // the k range is split as far as the workspace allows; a fused activation needs the whole sum at once.  NT and NN
+  // need no workspace, so one that is not aligned for the partial tiles counts as none.
+  if (layout != GEMM_TN && reinterpret_cast<uintptr_t>(scratch) % 16) scratch_bytes = 0;
   const Plan pl = make_plan(layout, M, N, K, scratch ? scratch_bytes : 0, !epi.swiglu_up && !epi.swiglu_fwd_a);
   GemmParams p;
   p.A = (const bf16_t*)A; p.B = (const bf16_t*)B; p.C = C;

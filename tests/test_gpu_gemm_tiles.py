@@ -99,3 +99,20 @@ def test_cut_slices(layout, M, N, K):
     # at most K + 1 roundings of fp32 in any order of the sum, and the rounding of a bf16 result
     bound = (K + 1) * 2.0 ** -24 * (np.abs(a) @ np.abs(b)) + (0 if layout == 2 else 2.0 ** -8 * np.abs(ref))
     assert (np.abs(dC.double().cpu().numpy() - ref) <= bound).all()
+
+
+def test_a_workspace_that_is_not_aligned_is_left_alone():
+    import torch
+    from paper_2605_25451_amd import binding as bm
+    M, N, K = 577, 1024, 4096
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    A, B = (torch.randn(s, device="cuda", generator=gen).bfloat16() for s in ((M, K), (N, K)))
+    nbytes = bm.gemm_scratch_bytes(0, M, N, K, synth.DTYPE_BF16)
+    assert nbytes > 0
+    ws = torch.zeros(nbytes + 16, dtype=torch.uint8, device="cuda")
+    out = [torch.empty((M, N), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    print("gemm unaligned workspace", flush=True)
+    bm.gemm(0, synth.DTYPE_BF16, M, N, K, A, K, B, K, out[0], N)
+    bm.gemm(0, synth.DTYPE_BF16, M, N, K, A, K, B, K, out[1], N, None, ws[4:], nbytes)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], out[1]) and not ws.any()
