@@ -74,7 +74,10 @@ typedef struct {
   int32_t linear_bias;  /* 0/1: biases on the four linear layers                           */
   int32_t dtype;        /* BM_DTYPE_*                                                      */
   int32_t deterministic;/* ignored: every kernel here is free of floating-point atomics, so
-                           results are run-to-run bit-identical whatever this field holds  */
+                           the same call gives bit-identical results whatever this field
+                           holds.  A sequence on its own and the same sequence in a longer
+                           pack may differ in rounding: how sums are split over the chip
+                           goes by the number of rows (of sequences, for the modulation)   */
   int32_t n_experts;    /* 0: dense FFN.  > 0 (<= 256): mixture-of-experts FFN (the paper's
                            LLM backbone, Sec. 4.1): router logits h W_r^T, softmax over the
                            experts, the top_k most probable experts (ties: lower index) with
@@ -161,8 +164,12 @@ bm_status bm_block_backward(const bm_block_desc* desc, const bm_block_params* w,
  *   1 "NN": C[M,N]  = A[M,K] B[K,N]          (input gradient,  dX = dY W)
  *   2 "TN": C[M,N] += A[K,M]^T B[K,N]        (weight gradient, dW += dY^T X; C is fp32)
  * A, B (and C for layouts 0/1, bias[N]) are in the storage dtype; leading dimensions
- * in elements.  scratch may be NULL when scratch_bytes is 0; bm_gemm_scratch_bytes
- * gives what the split reduction of layout 2 wants. */
+ * in elements.  bm_gemm_scratch_bytes gives what a product can make use of for fp32 partial sums of
+ * ranges of K.  Layout 2, and sizes that go to the kernels for any shape, need it: with less they
+ * return BM_ERR_WORKSPACE_TOO_SMALL.  Otherwise layouts 0 and 1 in bf16 need none (scratch may be NULL when
+ * scratch_bytes is 0): few rows (M up to 2048) are split into ranges as far as the workspace
+ * allows, which is faster.  The order of an element's fp32 sum, and with it its last bits, then depends on
+ * M and on scratch_bytes; for the same arguments it is always the same. */
 size_t    bm_gemm_scratch_bytes(int32_t layout, int32_t M, int32_t N, int32_t K, int32_t dtype);
 bm_status bm_gemm(int32_t layout, int32_t dtype, int32_t M, int32_t N, int32_t K,
                   const void* A, int32_t lda, const void* B, int32_t ldb,

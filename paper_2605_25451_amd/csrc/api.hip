@@ -1,5 +1,5 @@
-// Error text, back-end selection (MFMA kernels when the shape allows, the
-// generic fp32-FMA kernels otherwise) and the C-ABI wrappers of the single
+// Error text, back-end selection (bf16 MFMA kernels when the shape allows, the
+// generic fp32 kernels otherwise) and the C-ABI wrappers of the single
 // operations.
 #include "common.h"
 

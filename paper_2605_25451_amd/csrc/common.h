@@ -225,7 +225,7 @@ bm_status moe_combine(int dtype, const void* rows, const MoeTables& m, int use_g
 bm_status moe_router_backward(int dtype, const void* dm, const void* y_rows, const MoeTables& m,
                               void* dlogits, int T, int E, int k, int d, hipStream_t st);
 
-// generic (any shape, fp32 FMA) and MFMA (bf16) back ends
+// generic (any shape, fp32 arithmetic) and MFMA (bf16) back ends
 size_t gemm_generic_scratch_bytes(int M, int N, int K);
 bm_status gemm_generic(int layout, int dtype, int M, int N, int K, const void* A, int lda,
                        const void* B, int ldb, void* C, int ldc, const GemmEpilogue& epi,

@@ -418,7 +418,8 @@ bm_status launch_tile(int layout, const GemmParams& p, hipStream_t st) {
     return p.splits > 1 ? launch_cut<BM, BN, true, true, EPI_PARTIAL>(p, st) : launch_cut<BM, BN, true, true, EPI_ADD>(p, st);
   if (layout == GEMM_NT) {
     if (p.splits > 1) return launch_cut<BM, BN, false, false, EPI_PARTIAL>(p, st);
-    if (p.swf_a) return launch_cut<BM, BN, false, false, EPI_SWIGLU_FWD>(p, st);
+    // (256x128: N is a multiple of 256 there, so 128x256 tiles are never more and the plan takes them)
+    if constexpr (BN == 256) if (p.swf_a) return launch_cut<BM, BN, false, false, EPI_SWIGLU_FWD>(p, st);
     return p.residual ? launch_cut<BM, BN, false, false, EPI_RES>(p, st) : launch_cut<BM, BN, false, false, EPI_PLAIN>(p, st);
   }
   if (p.splits > 1) return launch_cut<BM, BN, false, true, EPI_PARTIAL>(p, st);
@@ -429,6 +430,7 @@ bm_status launch_tile(int layout, const GemmParams& p, hipStream_t st) {
 }  // namespace
 
 bm_status launch_gemm_alt(int layout, int bm, int bn, const GemmParams& p, hipStream_t st) {
+  if (bn == 128 && p.swf_a) { set_error("gemm: no SwiGLU forward on 256x128 tiles"); return BM_ERR_UNSUPPORTED; }
   if (bm == 256 && bn == 256) return launch_tile<256, 256>(layout, p, st);
   if (bm == 256 && bn == 128) return launch_tile<256, 128>(layout, p, st);
   return launch_tile<128, 256>(layout, p, st);

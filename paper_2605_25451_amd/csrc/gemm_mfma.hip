@@ -18,6 +18,8 @@
 // tiles that a second kernel sums in a fixed order: no floating-point atomics.
 #include "gemm_tile.h"
 
+#include <atomic>
+
 namespace bm {
 
 namespace {
@@ -76,14 +78,13 @@ struct Stage {
   u32x4 v[CH];
   uint32_t goff[CH];    // byte offset from the slice base pointer
   unsigned live = 0u;   // KTAIL: bit i = chunk i lies inside the k range (else stored as zeros)
-  // LDS byte offset of chunk i = soff[i & 1] + i * SSTRIDE: from one chunk of a thread to the next
+  // LDS byte offset of chunk i = soff + i * SSTRIDE: from one chunk of a thread to the next
   // the row (k-contiguous layout) or the k-row (transposed layout) advances by a fixed count that
-  // leaves the XOR swizzle alone, except for bit 3 of the k-row, which alternates when that count is 8
+  // leaves the XOR swizzle alone
   static constexpr int IROWS = TR ? NT / (R / 8) : NT / KCH;      // rows (k-rows) between chunks i and i+1
   static constexpr int SSTRIDE = IROWS * (TR ? R : BK) * 2;
-  static constexpr bool ALT = TR && IROWS % 16 == 8;
-  static_assert(TR ? IROWS % 8 == 0 : IROWS % 16 == 0, "the chunk stride would move the swizzle");
-  uint32_t soff[ALT ? 2 : 1];
+  static_assert(IROWS % 16 == 0, "the chunk stride would move the swizzle");
+  uint32_t soff;
 
   // k index of chunk i inside a slice
   __device__ static inline int chunk_k(int i, int tid) {
@@ -115,12 +116,7 @@ struct Stage {
         goff[i] = ((uint32_t)row * (uint32_t)ld + (uint32_t)(id % KCH) * 8u) * 2u;
       }
     }
-#pragma unroll
-    for (int i = 0; i < (ALT ? 2 : 1); ++i) {
-      const int id = tid + i * NT;
-      const int off = TR ? tr_offset<R>(id / (R / 8), id % (R / 8)) : kc_offset(id / KCH, id % KCH);
-      soff[i] = (uint32_t)(off * 2 - i * SSTRIDE);
-    }
+    soff = (uint32_t)(TR ? tr_offset<R>(tid / (R / 8), tid % (R / 8)) : kc_offset(tid / KCH, tid % KCH)) * 2u;
   }
 
   // base: this tile's first row at the slice's first k (wave-uniform); k_left = valid k from there
@@ -140,26 +136,25 @@ struct Stage {
     v[i] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const char*>(base) + o);
   }
 
-  __device__ inline void store_one(int i, bf16_t* lds, int tid) const {
-    (void)tid;
+  __device__ inline void store_one(int i, bf16_t* lds) const {
     u32x4 val = v[i];
     if (KTAIL && !((live >> i) & 1u)) val = u32x4{0u, 0u, 0u, 0u};
-    *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(lds) + soff[ALT ? (i & 1) : 0] + i * SSTRIDE) = val;
+    *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(lds) + soff + i * SSTRIDE) = val;
   }
 
   __device__ inline void load(const bf16_t* __restrict__ base, int ld, int k_left, int tid) {
 #pragma unroll
     for (int i = 0; i < CH; ++i) load_one(i, base, ld, k_left, tid);
   }
-  __device__ inline void store(bf16_t* lds, int tid) const {
+  __device__ inline void store(bf16_t* lds) const {
 #pragma unroll
-    for (int i = 0; i < CH; ++i) store_one(i, lds, tid);
+    for (int i = 0; i < CH; ++i) store_one(i, lds);
   }
 };
 
-template <int BM, int BN, int WM, int WN, bool A_TR, bool B_TR, int EPI, bool KTAIL>
-__global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
-  constexpr int NT = WM * WN * 64;
+template <bool A_TR, bool B_TR, int EPI, bool KTAIL>
+__global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmParams p) {
+  constexpr int BM = 128, BN = 128, WM = 2, WN = 2, NT = WM * WN * 64;
   constexpr int TM = BM / WM, TN_ = BN / WN;       // wave tile
   constexpr int FM = TM / 16, FN = TN_ / 16;       // 16x16 blocks per wave
   extern __shared__ __attribute__((aligned(16))) unsigned char smem_raw[];
@@ -193,8 +188,8 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
   const size_t b_step = B_TR ? (size_t)BK * p.ldb : (size_t)BK;
   sa.load(a_base, p.lda, kend - kbeg, tid);
   sb.load(b_base, p.ldb, kend - kbeg, tid);
-  sa.store(smem, tid);
-  sb.store(smem + 2 * A_TILE, tid);
+  sa.store(smem);
+  sb.store(smem + 2 * A_TILE);
   if (kbeg + BK < kend) {
     // same issue order as in the steady-state loop (part by part, A then B): the compiler's
     // wait-count bookkeeping merges this order with the loop's at the loop header, and any
@@ -289,9 +284,9 @@ __global__ __launch_bounds__(WM * WN * 64) void gemm_mfma_kernel(GemmParams p) {
           if (o < FN) {
             bfr[nb][o] = b_frag(ks + 1, o);
           } else if (o < FN + PA) {
-            if (NEXT1) sa.store_one(ks * PA + (o - FN), a_nxt, tid);
+            if (NEXT1) sa.store_one(ks * PA + (o - FN), a_nxt);
           } else if (o < FN + PA + PB) {
-            if (NEXT1) sb.store_one(ks * PB + (o - FN - PA), b_nxt, tid);
+            if (NEXT1) sb.store_one(ks * PB + (o - FN - PA), b_nxt);
           } else if (o < FN + 2 * PA + PB) {
             if (NEXT2) sa.load_one(ks * PA + (o - FN - PA - PB), a_g2, p.lda, k_left2, tid);
           } else {
@@ -469,21 +464,17 @@ Plan make_plan(int layout, int M, int N, int K, size_t partial_bytes, bool may_s
   return best;
 }
 
-template <int BM, int BN, int WM, int WN, bool A_TR, bool B_TR, int EPI, bool KTAIL>
+template <bool A_TR, bool B_TR, int EPI, bool KTAIL>
 bm_status launch_k(const GemmParams& p, hipStream_t st) {
-  constexpr size_t lds_pipe = (size_t)2 * (BM + BN) * BK * sizeof(bf16_t);
-  constexpr size_t lds_epi = (size_t)WM * WN * 16 * (BN / WN + 4) * sizeof(float);
-  constexpr size_t lds = lds_pipe > lds_epi ? lds_pipe : lds_epi;
-  auto kern = gemm_mfma_kernel<BM, BN, WM, WN, A_TR, B_TR, EPI, KTAIL>;
-  static bool attr_done = false;
-  if (!attr_done) {
+  constexpr size_t lds = (size_t)2 * (128 + 128) * BK * sizeof(bf16_t);
+  static_assert(lds >= 4 * epilogue_stage_floats<4>() * sizeof(float), "the epilogue's strips overlay the slices");
+  auto kern = gemm_mfma_kernel<A_TR, B_TR, EPI, KTAIL>;
+  static std::atomic<bool> attr_done{false};
+  if (!attr_done.load(std::memory_order_relaxed)) {
     BM_CHECK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    attr_done = true;
+    attr_done.store(true, std::memory_order_relaxed);
   }
-  int wgs = p.tiles_m * p.tiles_n * p.splits * p.grid_groups;
-  if (p.pair_wgs0 > 0) wgs = p.pair_wgs0 + p.second.tiles_m * p.second.tiles_n * p.second.splits;
-  dim3 grid(wgs), block(WM * WN * 64);
-  hipLaunchKernelGGL(kern, grid, block, lds, st, p);
+  hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n * p.splits * p.grid_groups), dim3(256), lds, st, p);
   BM_CHECK_LAUNCH("gemm_mfma");
   return BM_OK;
 }
@@ -491,8 +482,8 @@ bm_status launch_k(const GemmParams& p, hipStream_t st) {
 // the zero-filling variant only when a k range is not a whole number of slices
 template <bool A_TR, bool B_TR, int EPI>
 bm_status launch(const GemmParams& p, hipStream_t st) {
-  if (p.K % BK) return launch_k<128, 128, 2, 2, A_TR, B_TR, EPI, true>(p, st);
-  return launch_k<128, 128, 2, 2, A_TR, B_TR, EPI, false>(p, st);
+  if (p.K % BK) return launch_k<A_TR, B_TR, EPI, true>(p, st);
+  return launch_k<A_TR, B_TR, EPI, false>(p, st);
 }
 
 // 128x128 tiles
@@ -565,9 +556,7 @@ bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, con
   }
   p.tile_group = nullptr; p.group_rows = nullptr; p.b_group_stride = 0; p.c_group_stride = 0;
   p.grid_groups = 1; p.pair_wgs0 = 0; p.second = {};
-  {
-    p.xcd_split = xcd_split_possible(pl.tiles_m * pl.tiles_n, pl.splits) ? 1 : 0;
-  }
+  p.xcd_split = xcd_split_possible(pl.tiles_m * pl.tiles_n, pl.splits) ? 1 : 0;
   BM_RETURN_IF(pl.bm == 128 && pl.bn == 128 ? launch_small(layout, p, st) : launch_gemm_alt(layout, pl.bm, pl.bn, p, st));
   if (pl.splits > 1 && layout == GEMM_TN) {
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3(cdiv((long)M * N / 4, 256)), dim3(256), 0, st,

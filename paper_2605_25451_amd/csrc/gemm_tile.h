@@ -22,7 +22,7 @@ struct GemmParams {
   const bf16_t* bias; const bf16_t* residual;
   const bf16_t* sw_up = nullptr; bf16_t* sw_dup = nullptr; bf16_t* sw_a = nullptr;   // SwiGLU backward epilogue (see GemmEpilogue)
   bf16_t* swf_a = nullptr;      // SwiGLU forward epilogue (see GemmEpilogue); N = 2F
-  float* partial;               // TN with splits > 1
+  float* partial;               // splits > 1: fp32 partial tiles [split][M][N]
   int M, N, K, lda, ldb, ldc;
   int tiles_m, tiles_n, splits, k_per_split;
   int out_fp32;
@@ -42,10 +42,11 @@ struct GemmParams {
 };
 
 // acc += a b^T with v_mfma_f32_16x16x32_bf16.  Written as an asm statement that ties the
-// accumulator block to the accumulation half of the register file: with 64 four-register blocks
-// the allocator otherwise keeps some of them in the other half and runs out of registers there
-// (copies between the halves inside the loop, spills).  The accumulator of a block is next
-// touched 63 MFMAs later, far beyond any wait state the instruction asks for.
+// accumulator block to the accumulation half of the register file: the allocator otherwise keeps
+// some blocks in the other half, with copies between the halves inside the loop.  The compiler
+// does not know that the statement is an MFMA; what keeps the accumulators safe is that a block is next
+// touched 16 MFMAs later, as the accumulator of the same instruction again, which asks for no wait
+// state at any distance, and that gemm_epilogue() waits before it reads them.
 __device__ inline void mfma16(f32x4& acc, const bf16x8& a, const bf16x8& b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(a), "v"(b));
 }
