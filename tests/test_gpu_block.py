@@ -138,6 +138,23 @@ def test_edge_shapes_match_oracle(case):
     compare(case, run_hip(case), run_oracle(case))
 
 
+@pytest.mark.parametrize("hidden,mlp,T,product,tile", [
+    # product: layout, columns and contraction in units of (hidden, mlp); its epilogue on tiles that the rows do not fill
+    (512, 2688, 1100, (0, "2F", "d"), (128, 256)), (512, 2048, 2077, (0, "2F", "d"), (256, 256)),        # SwiGLU forward
+    (512, 2688, 2077, (1, "F", "d"), (128, 256)), (512, 2688, 2200, (1, "F", "d"), (256, 128)),          # SwiGLU backward
+    (512, 2688, 3300, (1, "F", "d"), (256, 256)),
+    (768, 512, 7001, (0, "d", "F"), (128, 256)), (896, 512, 6001, (0, "d", "F"), (256, 128)),            # residual
+])
+def test_fused_epilogues_on_ragged_tiles(hidden, mlp, T, product, tile):
+    from paper_2605_25451_amd import binding as bm
+    size = {"d": hidden, "F": mlp, "2F": 2 * mlp}
+    assert bm.probe_gemm_plan(product[0], T, size[product[1]], size[product[2]], 0)[:2] == tile
+    cfg = synth.scaled(synth.decoder_8b_gqa(), hidden=hidden, n_q_heads=hidden // 128, n_kv_heads=1, mlp_hidden=mlp)
+    lens = [T // 4 + 3, T // 8, T // 2]
+    case = synth.make_case(cfg, lens + [T - sum(lens)], T, name=f"ragged_{hidden}_{mlp}_{T}")
+    compare(case, run_hip(case), run_oracle(case))
+
+
 def test_gradients_accumulate_and_runs_are_bit_identical():
     from paper_2605_25451_amd.runner import CaseOnDevice
     case = synth.make_case(synth.vit_large(), [200, 120], 48, name="vit_large_accumulate")
