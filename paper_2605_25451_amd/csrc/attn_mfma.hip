@@ -1292,10 +1292,7 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_pair_kernel(
 // reads, fills and the P exchange of a 32x32 block: about 1130 clocks of LDS for 1024 of MFMAs).
 // 128 accumulator registers and 64 of K or V leave 64 for everything else, so
 //  - a step is one 32-query block;
-//  - tiles lie in LDS so that every read is one lane constant plus an immediate offset:
-//    16-byte chunk c of row r at (r >> 2) * RUN + (c >> 2) * 256 + (r & 3) * 64 + (c & 3) * 16.  A run of
-//    four rows is the 1 KiB that one load instruction fills, four lanes to 64 contiguous bytes of a
-//    row; the 16 bytes between runs keep row reads and transpose reads free of bank conflicts.
+//  - tiles lie in LDS as RunTile has them, so that every read is one lane constant plus an immediate offset.
 // Tiles go through a ring of four buffers, requested three steps ahead; one barrier per step hands over
 // P and the next tile.
 // Against 32 keys per pair, us: 8192 queries x 8192 keys, 32 / 8 heads, 2207 -> 1875 (1.17 PFLOP/s of MFMAs), causal
@@ -1303,8 +1300,8 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_pair_kernel(
 // heads, 435 -> 365.  Fragments requested three steps ahead and a raised wave priority around the MFMAs
 // changed nothing.
 struct WideTile {
-  static constexpr int ROWS = 32, RUN = 1024 + 16, RUNS = ROWS / 4;
-  static constexpr int Q = 0, D = RUNS * RUN, LSE = 2 * RUNS * RUN, DELTA = LSE + ROWS * 4, BYTES = DELTA + ROWS * 4;
+  static constexpr int ROWS = 32, PART = RunTile<128>::bytes(ROWS);
+  static constexpr int Q = 0, D = PART, LSE = 2 * PART, DELTA = LSE + ROWS * 4, BYTES = DELTA + ROWS * 4;
   static constexpr int RING = 4;
 };
 
@@ -1325,6 +1322,7 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
     float* __restrict__ part /* [gsplit][2][Ttot][Hkv*DH] fp32 when gsplit > 1 */, SeqOrder ord) {
   constexpr int DH = 128, KS = 8, NB = 4, KB = 2;
   using W = WideTile;
+  using RT = RunTile<DH>;
   __shared__ __attribute__((aligned(1024))) unsigned char tiles[W::RING * W::BYTES];
   __shared__ __attribute__((aligned(1024))) unsigned char Pbuf[2 * 4 * 4096];   // [parity][pair][key block, half k-step][lane]
   int seq, kt, nkt, tile_id, hk, hk_gs;
@@ -1387,12 +1385,12 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
       const int last = Lq - qstart - 1 - ft * W::ROWS;    // rows past the sequence are clamped: their P is 0
       const uint32_t dst = lds0 + (fn & (W::RING - 1)) * W::BYTES;
       const int l = fresh_lane();
-      const int row = (l >> 2) & 3, chunk = ((l >> 4) * 4 + (l & 3)) * 16;
+      const int row = RT::load_row(l), chunk = RT::load_chunk(l) * 16;
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
         const int r = pair * 2 + i;
-        const uint32_t off = (uint32_t)min(r * 4 + row, last) * (uint32_t)sld * 2u + (uint32_t)chunk;
-        TileAsync<32, DH, 256>::load16(src, off, dst + ROWS_AT + r * W::RUN);
+        const uint32_t off = (uint32_t)min(r * RT::RPR + row, last) * (uint32_t)sld * 2u + (uint32_t)chunk;
+        TileAsync<32, DH, 256>::load16(src, off, dst + ROWS_AT + r * RT::RUN);
       }
       const uint32_t off = (uint32_t)min(pair * 8 + (l & 7), last) * 4u;
       if (l < 8)
@@ -1422,13 +1420,10 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
     };
     // phase 1: X[q, key] += rows(Q or dO) . (K or V)^T
     auto scores = [&](int n, f32x16 (&x)[KB]) {
-      const int l = fresh_lane();
-      const unsigned char* rows = tile_of(n) + ROWS_AT + ((l & 31) >> 2) * W::RUN + (l & 3) * 64 + (l >> 5) * 16;
+      const unsigned char* rows = tile_of(n) + ROWS_AT + RT::rows_at(fresh_lane());
       constexpr int AHEAD = 2;
       bf16x8 fx[AHEAD + 1];
-      auto request = [&](int ks) {
-        fx[ks % (AHEAD + 1)] = *reinterpret_cast<const bf16x8*>(rows + (ks >> 1) * 256 + (ks & 1) * 32);
-      };
+      auto request = [&](int ks) { fx[ks % (AHEAD + 1)] = RT::read_rows(rows, 0, ks); };
 #pragma unroll
       for (int ks = 0; ks < AHEAD; ++ks) request(ks);
 #pragma unroll
@@ -1442,17 +1437,8 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
     };
     // phase 2: acc^T[c, key] += cols(dO or Q)^T . (P or dS), transposed operands requested ahead
     auto accumulate = [&](int n, const bf16x8 (&op)[KB][2]) {
-      const int l = fresh_lane(), gi = l >> 4, s = l & 15;
-      const unsigned char* cols = tile_of(n) + COLS_AT + (gi >> 1) * W::RUN + (s >> 2) * 64 +
-                                  ((gi & 1) * 2 + ((s & 3) >> 1)) * 16 + (s & 1) * 8;
-      auto request = [&](int m) {                          // m = j * 2 + t: 32 columns of dh, 16 query rows
-        const unsigned char* a = cols + (m >> 1) * 256 + (m & 1) * 4 * W::RUN;
-        s16x4 lo4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)a);
-        s16x4 hi4 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(a + 2 * W::RUN));
-        union { struct { s16x4 a, b; } s; bf16x8 v; } u;
-        u.s.a = lo4; u.s.b = hi4;
-        return u.v;
-      };
+      const unsigned char* cols = tile_of(n) + COLS_AT + RT::cols_at(fresh_lane());
+      auto request = [&](int m) { return RT::read_cols(cols, m >> 1, m & 1); };   // m = j * 2 + t: 32 columns of dh, 16 query rows
       constexpr int AHEAD = 2;
       bf16x8 fc[AHEAD + 1];
 #pragma unroll
