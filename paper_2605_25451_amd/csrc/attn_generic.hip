@@ -68,7 +68,6 @@ __global__ __launch_bounds__(NT) void attn_fwd_generic_kernel(
     if (active) {
       float sc[BT / P];
       float tmax = -INFINITY;
-      bool counts = false;             // a score above -inf, or NaN, which fmaxf drops: it has to reach the row's sums
 #pragma unroll
       for (int jj = 0; jj < BT / P; ++jj) {
         const int j = jj * P + part, kj = k0 + j;
@@ -77,10 +76,9 @@ __global__ __launch_bounds__(NT) void attn_fwd_generic_kernel(
         for (int c = 0; c < DH; ++c) d = fmaf(qr[c], Ks[j][c], d);
         bool ok = kj < Lk && (!CAUSAL || kj <= qi);
         sc[jj] = ok ? d : -INFINITY;
-        tmax = fmaxf(tmax, sc[jj]);
-        counts |= sc[jj] != -INFINITY;
+        tmax = sc[jj] > tmax || sc[jj] != sc[jj] ? sc[jj] : tmax;   // keeps NaN, which has to reach the row's sums
       }
-      if (counts) {
+      if (tmax != -INFINITY) {
         float mn = fmaxf(m, tmax);
         float corr = expf(m - mn);
         l *= corr;
