@@ -381,22 +381,24 @@ constexpr int NUM_CU = 256;
 
 // Tile and k split from a small cost model in microseconds.  A slice of k = 64 takes t_min when the chip is
 // nearly empty and t_full when every slot works (the matrix pipe's power budget, shared by the active CUs), in
-// between t_full * (share of busy slots)^power; a workgroup adds t_fixed, and t_cut more if its k range ends inside
-// a slice.  f_tn: a slice with both operands transposed against one with none.  A weight gradient reads and writes
-// its fp32 C at 5.2 TB/s, a share `hidden` of which runs under the slices of others -- most where a CU holds two
-// workgroups, so that short contractions want the smallest tile (TN 12288x3072 over 128 rows: 83 us with 256x256
-// tiles, 70 with 128x128; over 1536 rows 154 both).  A split writes and reads fp32 partial tiles at 8 TB/s
-// (they stay in the memory-side cache) and costs one more launch (TN 8x1024 over 802 rows: 12.1 us, in three ranges 9.0).
+// between t_full * (share of busy slots)^power; a workgroup adds t_fixed.  A contraction that ends inside a slice adds
+// t_cut; the 128x128 kernel tests every chunk of every slice for it instead (CUT_SMALL).  f_tn: a slice with both
+// operands transposed against one with none.  A weight gradient reads and writes its fp32 C at 5.2 TB/s, a share
+// `hidden` of which runs under the slices of others -- most where a CU holds two workgroups, so that short
+// contractions want the smallest tile (TN 12288x3072 over 128 rows: 83 us with 256x256 tiles, 70 with 128x128; over
+// 1536 rows 154 both).  A split writes and reads fp32 partial tiles at 8 TB/s (they stay in the memory-side
+// cache) and costs one more launch (TN 8x1024 over 802 rows: 12.1 us, in three ranges 9.0).
 // Measured on 527 shapes (blocks of 1024 to 4096 columns at 300 to 16384 rows, shapes drawn over the same range, and
-// gradients of 8 to 128 conditions; every tile, splits 1-32): the plan it picks takes 1.6 % longer than the best one on
-// average, 29 % at worst.
+// gradients of 8 to 128 conditions; every tile, splits 1-32): the plan it picks takes 1.2 % longer than the best one on
+// average, 23 % at worst.
 struct TileKind { int bm, bn, slots; double t_min, t_full, power, t_fixed, t_cut, f_tn, hidden; };
 constexpr TileKind TILE_KINDS[] = {
-  {256, 256, NUM_CU, 0.87, 1.36, 0.6, 5.5, 2.3, 1.05, 0.25},
-  {128, 256, NUM_CU, 0.55, 0.77, 0.5, 4.0, 0.0, 1.12, 0.30},
-  {256, 128, NUM_CU, 0.55, 0.77, 0.5, 4.0, 0.0, 1.12, 0.30},
-  {128, 128, 2 * NUM_CU, 0.45, 0.92, 0.0, 3.4, 0.0, 1.12, 0.50},       // two workgroups per CU
+  {256, 256, NUM_CU, 0.87, 1.36, 0.6, 5.5, 3.6, 1.13, 0.23},
+  {128, 256, NUM_CU, 0.55, 0.77, 0.5, 4.0, 2.3, 1.34, 0.27},
+  {256, 128, NUM_CU, 0.55, 0.77, 0.5, 4.0, 2.3, 1.34, 0.27},
+  {128, 128, 2 * NUM_CU, 0.45, 0.92, 0.0, 3.4, 0.0, 1.12, 0.53},       // two workgroups per CU
 };
+constexpr double CUT_SMALL = 1.33;
 
 // Splits of 2, 4 or 8 can be pinned to XCDs (see split_tile_of_block).
 bool xcd_split_possible(int tiles, int splits) {
@@ -406,7 +408,7 @@ bool xcd_split_possible(int tiles, int splits) {
 // one grid of `wgs` workgroups that each walk `per` slices
 double grid_time(const TileKind& tk, int layout, bool cut, long wgs, int per) {
   const bool small = tk.bm == 128 && tk.bn == 128;
-  const double f = layout == GEMM_NT ? 1.0 : layout == GEMM_NN ? 1.05 : tk.f_tn;
+  const double f = (layout == GEMM_NT ? 1.0 : layout == GEMM_NN ? 1.05 : tk.f_tn) * (small && cut ? CUT_SMALL : 1.0);
   const double fixed = tk.t_fixed + (cut ? tk.t_cut : 0.0);
   const long full = wgs / tk.slots, rest = wgs % tk.slots;
   double t = full * (per * tk.t_full * f + fixed);
@@ -421,7 +423,7 @@ double grid_time(const TileKind& tk, int layout, bool cut, long wgs, int per) {
 }
 // ... and its output of mn elements: the partial tiles of a split and their reduction, or a weight gradient's C
 double output_time(const TileKind& tk, int layout, int splits, double mn, double grid) {
-  if (splits > 1) return layout == GEMM_TN ? 2.5 + (splits + 1) * mn / 1e6 : 4.5 + (4 * splits + 1) * mn / 4e6;
+  if (splits > 1) return layout == GEMM_TN ? 2.4 + (splits + 1) * mn / 1e6 : 4.5 + (4 * splits + 1) * mn / 4e6;
   if (layout != GEMM_TN) return 0.0;
   const double c = mn * 8.0 / 5.2e6;
   return c - tk.hidden * std::min(c, grid);

@@ -14,19 +14,19 @@ CASES = [
     # layout, M, N, K, tile, k range split
     (0, 2049, 4104, 64, T256, False), (0, 2049, 4104, 184, T256, False), (1, 2049, 4104, 136, T256, False),   # 1 to 4 slices, cut
     (1, 2049, 4104, 200, T256, False), (2, 2976, 2960, 640, T256, False), (2, 1704, 4640, 808, T256, False),
-    (0, 932, 5288, 448, T128x256, False), (0, 1590, 4600, 264, T128x256, False), (1, 1466, 5272, 256, T128x256, False),
-    (1, 1351, 5008, 272, T128x256, False), (2, 1456, 3520, 1536, T128x256, False), (2, 1176, 4856, 1168, T128x256, False),
-    (0, 2960, 2096, 320, T256x128, False), (0, 2698, 2944, 288, T256x128, False), (1, 1187, 4896, 320, T256x128, False),
-    (1, 6786, 784, 336, T256x128, False), (2, 2720, 2072, 1408, T256x128, False), (2, 4568, 1040, 1473, T256x128, False),
+    (0, 932, 5288, 448, T128x256, False), (0, 8273, 656, 456, T128x256, False), (1, 1466, 5272, 256, T128x256, False),
+    (1, 7117, 648, 520, T128x256, False), (2, 4672, 1160, 1256, T128x256, False),
+    (0, 2960, 2096, 320, T256x128, False), (0, 4339, 1312, 456, T256x128, False), (1, 1187, 4896, 320, T256x128, False),
+    (1, 6004, 800, 568, T256x128, False), (2, 2752, 2088, 1224, T256x128, False), (2, 4568, 1040, 1473, T256x128, False),
     (2, 4104, 2056, 1, (0, 0), False), (2, 4104, 2056, 65, T128, False), (2, 4104, 2056, 129, T128, False), (2, 4104, 2056, 777, T256, False),
     (0, 5477, 1024, 1024, T128x256, False), (1, 5477, 1024, 1016, T128x256, False), (0, 1032, 5480, 1024, T128x256, False),
     (1, 1032, 5480, 584, T128x256, False),
     # split
     (0, 577, 1024, 4096, T128, True), (1, 577, 1032, 4104, T128, True), (0, 1, 1024, 4096, T128, True), (1, 40, 1024, 11008, T128, True),
     (0, 300, 2048, 2056, T128, True), (2, 264, 256, 4001, T128, True),
-    (0, 2, 4856, 4288, T128x256, True), (0, 1, 5280, 5968, T128x256, True), (1, 2, 5264, 6848, T128x256, True), (1, 1, 3392, 7064, T128x256, True),
+    (0, 2, 4856, 4288, T128x256, True), (0, 1, 5280, 5968, T128x256, True), (1, 2, 5264, 6848, T128x256, True), (1, 1, 3736, 8536, T128x256, True),
     (0, 129, 3640, 8032, T256x128, True), (1, 142, 4384, 4472, T256x128, True),
-    (2, 592, 4192, 6272, T128x256, True), (2, 264, 3920, 4087, T128x256, True), (2, 152, 4448, 8451, T256x128, True), (2, 1024, 1032, 5477, T128, True),
+    (2, 64, 5544, 7545, T128x256, True), (2, 264, 3920, 4087, T128x256, True), (2, 152, 4448, 8451, T256x128, True), (2, 1024, 1032, 5477, T128, True),
     (2, 3696, 672, 8923, T256, True),
 ]
 
@@ -70,8 +70,8 @@ def test_gemm_tiles(layout, M, N, K, tile, split, scratch):
 
 @pytest.mark.parametrize("layout,M,N,K", [
     (0, 2049, 4104, 184), (1, 1700, 4704, 136), (2, 1432, 5424, 391), (2, 2776, 2976, 456),         # 256 x 256
-    (0, 1368, 4592, 272), (1, 1703, 4272, 208), (2, 4232, 1160, 1281),                              # 128 x 256
-    (0, 2738, 2360, 272), (1, 8590, 800, 216), (2, 1160, 4368, 1217),                               # 256 x 128
+    (0, 8273, 656, 456), (1, 7117, 648, 520), (2, 1040, 4568, 1473),                               # 128 x 256
+    (0, 4339, 1312, 456), (1, 3637, 1848, 400), (2, 4568, 1040, 1473),                              # 256 x 128
     (0, 1032, 5480, 72), (1, 1032, 5480, 88), (2, 4104, 2056, 71), (2, 2056, 4104, 95),             # 128 x 128
 ])
 def test_cut_slices(layout, M, N, K):
