@@ -9,7 +9,7 @@
 //
 // What this buys over one wavefront per SIMD that interleaves both (register-staged slices, four
 // wavefronts of 128x128): NT 8192x12288x4096 1400 -> 1560 TFLOP/s, NN 8192x4096x12288 1390 -> 1560,
-// TN 12288x4096x8192 1230 -> 1330, NT 16384x3072x1024 1150 -> 1280 (random operands, one box).  It is
+// TN 12288x4096x8192 1230 -> 1370, NT 16384x3072x1024 1150 -> 1280 (random operands, one box).  It is
 // bound by the power the matrix pipe draws: priorities, the order of a phase's memory instructions
 // and the tile order changed nothing.
 //
@@ -85,10 +85,10 @@ struct Region {
   }
   // k_left < 64: a slice that ends inside the k range; what lies past it is fetched from its last
   // valid k (row or chunk) and zeroed in the fragments
-  template <bool CUT>
+  template <bool CUT, int FIRST = 0, int COUNT = LOADS>
   __device__ inline void load(const bf16_t* base, int ld, int k_left, uint32_t lds, int wave, int lane) const {
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
+    for (int i = FIRST; i < FIRST + COUNT; ++i) {
       uint32_t o = off[i];
       if (CUT && k_left < BK) {
         int r, c;
@@ -165,14 +165,14 @@ __device__ inline void clear(f32x4 (&acc)[FM][FN]) {
     for (int j = 0; j < FN; ++j) mfma16_first(acc[i][j], z, z);
 }
 
-// ---- 256x256 tile.  Each wavefront owns 128x64: 64 rows in each half of A, 64 columns of B.  A slice is
+// ---- 256x256 tile of NT and NN.  Each wavefront owns 128x64: 64 rows in each half of A, 64 columns of B.  A slice is
 // two phases per group (first and second half of A); LDS holds two slices, and a slice's first half
 // of A with B, and its second half, are re-filled as soon as both groups have read them: loads are
 // in flight for more than a slice (4 to 5 phases of 512 clocks).
-template <bool A_TR, bool B_TR, int EPI, bool CUT>
+template <bool B_TR, int EPI, bool CUT>
 __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_kernel(GemmParams p) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  using RegA = Region<128, A_TR>;
+  using RegA = Region<128, false>;
   using RegB = Region<256, B_TR>;
   constexpr uint32_t A1 = RegA::BYTES, B0 = 2 * RegA::BYTES, BUF = B0 + RegB::BYTES;
   constexpr int LATE = RegA::LOADS, EARLY = RegA::LOADS + RegB::LOADS;      // loads of a slice's two parts
@@ -190,10 +190,10 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_kernel(GemmParams p) {
   ra1.init(p.lda, 128, p.M - m0, wave, lane);
   if (SWF) rb.init(p.ldb, 0, 256, wave, lane, 32, p.N / 2, job.tn * 128);
   else rb.init(p.ldb, 0, p.N - n0, wave, lane);
-  const bf16_t* a_base = A_TR ? job.A + (size_t)job.kbeg * p.lda + m0 : job.A + (size_t)m0 * p.lda + job.kbeg;
+  const bf16_t* a_base = job.A + (size_t)m0 * p.lda + job.kbeg;
   const bf16_t* b_base = B_TR ? job.B + (size_t)job.kbeg * p.ldb + n0
                               : job.B + (SWF ? (size_t)0 : (size_t)n0 * p.ldb) + job.kbeg;
-  const size_t a_step = A_TR ? (size_t)BK * p.lda : (size_t)BK, b_step = B_TR ? (size_t)BK * p.ldb : (size_t)BK;
+  const size_t a_step = BK, b_step = B_TR ? (size_t)BK * p.ldb : (size_t)BK;
   auto load_early = [&](int j, uint32_t buf) {
     const int left = CUT && j == n - 1 ? k_left : BK;
     rb.template load<CUT>(b_base + (size_t)j * b_step, p.ldb, left, buf + B0, wave, lane);
@@ -203,7 +203,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_kernel(GemmParams p) {
     ra1.template load<CUT>(a_base + (size_t)j * a_step, p.lda, CUT && j == n - 1 ? k_left : BK, buf + A1, wave, lane);
   };
 
-  Fragments<128, A_TR, 4> fa;
+  Fragments<128, false, 4> fa;
   Fragments<256, B_TR, 4> fb;
   fa.init(wm * 64, lane);
   fb.init(wn * 64, lane);
@@ -285,6 +285,114 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_kernel(GemmParams p) {
                            [&](int i) { return m0 + (i >> 2) * 128 + wm * 64 + (i & 3) * 16; },
                            [&] {
                              multiply(Int<1>{});
+                             // group 0 writes its strips over the buffers group 1 has just read
+                             if (wm == 0) end_phase();
+                           });
+}
+
+// ---- 256x256 tile of a weight gradient (TN).  Both operands lie [k][row] in LDS, so a slice is cut along k: each of
+// its two phases per group reads 12 fragments of 32 k (8 of A, 4 of B) and multiplies 8x4 blocks.  Cut along
+// the rows of A as above, the phases read 16 and 8 fragments, and 32 transpose reads with their latency do not fit under
+// 512 clocks of MFMAs.  A slice of a tile that has the chip to itself: 1.17 us cut along the rows, 0.96 along k (NT 0.87);
+// with all CUs at work 1.45 and 1.33 (power).  12288x4096 over 8192 rows 621 -> 604 us, 22016x4096 over 777 247 -> 241.
+// The first 32 k of a slice are re-filled while its last 32 are read, and the other way round.  (K-contiguous operands
+// are cut along the rows because half a slice of theirs would be half of every 128-byte line.)
+template <int EPI, bool CUT>
+__global__ __launch_bounds__(THREADS, 2) void gemm_alt256_tn_kernel(GemmParams p) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  using Reg = Region<256, true>;
+  constexpr uint32_t B0 = Reg::BYTES, BUF = 2 * Reg::BYTES;
+  constexpr int HL = Reg::LOADS;                                             // loads of half a slice, A and B
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave >> 2, wn = wave & 3;                                   // wm is the group
+  const TileJob job = locate_tile<256, 256>(p);
+  if (job.kbeg >= job.kend) return;
+  const int m0 = job.m0, n0 = job.n0, n = (job.kend - job.kbeg + BK - 1) / BK;
+  const int k_left = job.kend - job.kbeg - (n - 1) * BK;                     // of the last slice
+
+  Reg ra, rb;
+  ra.init(p.lda, 0, p.M - m0, wave, lane);
+  rb.init(p.ldb, 0, p.N - n0, wave, lane);
+  const bf16_t* a_base = job.A + (size_t)job.kbeg * p.lda + m0;
+  const bf16_t* b_base = job.B + (size_t)job.kbeg * p.ldb + n0;
+  const size_t a_step = (size_t)BK * p.lda, b_step = (size_t)BK * p.ldb;
+  auto load_half = [&](auto half_t, int j, uint32_t buf) {
+    constexpr int FIRST = decltype(half_t)::value * (HL / 2);
+    const int left = CUT && j == n - 1 ? k_left : BK;
+    rb.template load<CUT, FIRST, HL / 2>(b_base + (size_t)j * b_step, p.ldb, left, buf + B0, wave, lane);
+    ra.template load<CUT, FIRST, HL / 2>(a_base + (size_t)j * a_step, p.lda, left, buf, wave, lane);
+  };
+
+  // rows wm*64.. of each half of A: the second half lies 128 rows on in every k row
+  Fragments<256, true, 4> fa, fb;
+  fa.init(wm * 64, lane);
+  fb.init(wn * 64, lane);
+  bf16x8 af[8], bf[4];
+  f32x4 acc[8][4];
+  auto multiply = [&] {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) mfma16(acc[i][j], bf[j], af[i]);
+  };
+  auto read = [&](auto ks_t, uint32_t buf) {
+    constexpr int KS = decltype(ks_t)::value;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) bf[q] = fb.read(smem, q, KS, buf + B0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) af[q] = fa.read(smem, q, KS, buf);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) af[4 + q] = fa.read(smem, q, KS, buf + 128 * 2);
+  };
+  auto cut = [&](int ks) {
+    const u32x4 mask = cut_mask(ks, k_left, lane);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) cut_fragment(bf[q], mask);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) cut_fragment(af[q], mask);
+  };
+  // COME: slices that follow this one (2: two or more, 0: this is the last).  A wait names the half slice that is read
+  // next: everything older than the two halves requested since must have landed.
+  auto slice = [&](auto come_t, int j) {
+    constexpr int COME = decltype(come_t)::value;
+    const uint32_t buf = (j & 1) * BUF;
+    read(Int<0>{}, buf);
+    if (COME >= 1) load_half(Int<1>{}, j + 1, buf ^ BUF);
+    wait_fragments();
+    if (CUT && COME == 0 && k_left < BK) cut(0);
+    wait_loads<COME >= 1 ? 2 * HL : 0>();
+    end_phase();
+    multiply();
+    wait_loads<COME >= 1 ? 2 * HL : 0>();
+    end_phase();
+    read(Int<1>{}, buf);
+    if (COME >= 2) load_half(Int<0>{}, j + 2, buf);
+    wait_fragments();
+    if (CUT && COME == 0 && k_left < BK) cut(1);
+    if (COME == 0) { end_phase(); return; }                 // the last MFMAs belong to the epilogue
+    wait_loads<COME >= 2 ? 2 * HL : HL>();
+    end_phase();
+    multiply();
+    wait_loads<COME >= 2 ? 2 * HL : HL>();
+    end_phase();
+  };
+  load_half(Int<0>{}, 0, 0);
+  load_half(Int<1>{}, 0, 0);
+  if (n > 1) load_half(Int<0>{}, 1, BUF);
+  clear(acc);                                               // under the latency of the first loads
+  if (n > 1) wait_loads<2 * HL>();
+  else wait_loads<0>();
+  end_phase();
+  if (wm == 1) end_phase();                                 // group 1 stays one phase behind
+  const bool full = m0 + 256 <= p.M && n0 + 256 <= p.N;
+  for (int j = 0; j < n - 2; ++j) slice(Int<2>{}, j);
+  if (n > 1) slice(Int<1>{}, n - 2);
+  slice(Int<0>{}, n - 1);
+  gemm_epilogue<EPI, 8, 4>(p, acc, reinterpret_cast<float*>(smem) + wave * epilogue_stage_floats<4>(), lane,
+                           n0 + wn * 64, 0, job.split, job.c_off, full,
+                           [&](int i) { return m0 + (i >> 2) * 128 + wm * 64 + (i & 3) * 16; },
+                           [&] {
+                             multiply();
                              // group 0 writes its strips over the buffers group 1 has just read
                              if (wm == 0) end_phase();
                            });
@@ -392,7 +500,8 @@ bm_status launch_one(const GemmParams& p, hipStream_t st) {
   constexpr bool LARGE = BM == 256 && BN == 256;
   constexpr size_t lds = (size_t)(LARGE ? 2 : 3) * (BM + BN) * BK * sizeof(bf16_t);
   void (*kern)(GemmParams);
-  if constexpr (LARGE) kern = gemm_alt256_kernel<A_TR, B_TR, EPI, CUT>;
+  if constexpr (LARGE && A_TR) kern = gemm_alt256_tn_kernel<EPI, CUT>;
+  else if constexpr (LARGE) kern = gemm_alt256_kernel<B_TR, EPI, CUT>;
   else kern = gemm_alt128_kernel<BM, BN, A_TR, B_TR, EPI, CUT>;
   static std::atomic<bool> attr_done{false};
   if (!attr_done.load(std::memory_order_relaxed)) {
