@@ -176,6 +176,19 @@ __device__ inline TileJob locate_tile(GemmParams& p) {
 //   stage       epilogue_stage_floats() of LDS of its own; free to write once `last` has returned
 //   full        the tile lies inside C, so no store carries a condition (a conditional store makes the
 //               wait for the next strip's operands wait for the stores as well)
+// The accumulators behind the last MFMAs, readable: the compiler does not know that the asm statements are MFMAs and
+// leaves no wait states between them and what reads their results, and arithmetic on the results (a conversion, a copy to
+// the other half of the register file) may move in front of the wait unless it depends on it.
+template <int FM, int FN>
+__device__ inline void settle(f32x4 (&acc)[FM][FN]) {
+  asm volatile("s_nop 15\n\ts_nop 15");
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) asm volatile("" : "+a"(acc[i][j]));
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 template <int FN> constexpr int epilogue_stage_floats() { return 2 * 16 * (FN * 16 + 4); }
 
 // fp32 outputs of weight gradients and k ranges (EPI_ADD, EPI_PARTIAL): 4 columns per lane, so that a load or store
@@ -186,7 +199,7 @@ template <int FN> constexpr int epilogue_stage_floats() { return 2 * 16 * (FN * 
 // One lane offset serves all rows of a tile that lies inside C: with an address per row the ragged and the full path
 // together spill.
 template <int EPI, int FM, int FN, typename RowOf, typename Last>
-__device__ inline void gemm_epilogue_f32(const GemmParams& p, const f32x4 (&acc)[FM][FN], float* stage, int lane, int col0,
+__device__ inline void gemm_epilogue_f32(const GemmParams& p, f32x4 (&acc)[FM][FN], float* stage, int lane, int col0,
                                          int split, long c_off, bool full, RowOf row_of, Last last) {
   constexpr int SLD = FN * 16 + 4;
   constexpr int LPR = FN * 4, RPI = 64 / LPR, TPS = 16 / RPI;
@@ -216,8 +229,7 @@ __device__ inline void gemm_epilogue_f32(const GemmParams& p, const f32x4 (&acc)
   request(std::integral_constant<int, 0>{}, full);
   request(std::integral_constant<int, 1>{}, full);
   last();
-  asm volatile("s_nop 15\n\ts_nop 15");
-  __builtin_amdgcn_sched_barrier(0);
+  settle(acc);
   auto finish = [&](auto full_t) {
     constexpr bool FULL = decltype(full_t)::value;
     static_for<AHEAD - 2>([&](auto i_t) { request(std::integral_constant<int, decltype(i_t)::value + 2>{}, FULL); });
@@ -248,7 +260,7 @@ __device__ inline void gemm_epilogue_f32(const GemmParams& p, const f32x4 (&acc)
 }
 
 template <int EPI, int FM, int FN, typename RowOf, typename Last>
-__device__ inline void gemm_epilogue(const GemmParams& p, const f32x4 (&acc)[FM][FN], float* stage, int lane, int col0,
+__device__ inline void gemm_epilogue(const GemmParams& p, f32x4 (&acc)[FM][FN], float* stage, int lane, int col0,
                                      int acol0, int split, long c_off, bool full, RowOf row_of, Last last) {
   if constexpr (EPI == EPI_ADD || EPI == EPI_PARTIAL) {
     gemm_epilogue_f32<EPI>(p, acc, stage, lane, col0, split, c_off, full, row_of, last);
@@ -282,10 +294,7 @@ __device__ inline void gemm_epilogue(const GemmParams& p, const f32x4 (&acc)[FM]
   request(std::integral_constant<int, 0>{});
   request(std::integral_constant<int, 1>{});
   last();
-  // the compiler does not know that the asm statements of `last` are MFMAs and leaves no wait states
-  // between them and the reads of the accumulators below
-  asm volatile("s_nop 15\n\ts_nop 15");
-  __builtin_amdgcn_sched_barrier(0);
+  settle(acc);
 
   float bias[8];
 #pragma unroll
