@@ -111,7 +111,8 @@ FwdScratch layout_fwd(const Dims& m, int dtype, void* base) {
 struct BwdScratch {
   int32_t* tok_seq;
   char *a, *dup, *da, *h, *dh, *dx1, *dgated, *d_o, *dqkv;
-  char *attn_ws, *norm_ws, *colsum_ws, *gemm_ws;
+  char *attn_ws, *norm_ws, *norm1_ws, *gemm_ws;   // norm1_ws: norm 1, whose column sums wait for the same flush as norm 2's
+  char *colsum_ws[5];                             // up, down, o, qkv, ada: the column sums of the bias gradients
   size_t attn_ws_bytes, gemm_ws_bytes;
   float *dmod, *dsc;
   char *dmod_e, *dmod_t, *sc;
@@ -154,9 +155,9 @@ BwdScratch layout_bwd(const Dims& m, int dtype, void* base) {
   s.attn_ws_bytes = attention_backward_scratch_bytes(m.Hq, m.Hkv, m.dh, m.T);
   s.attn_ws = a.take<char>(s.attn_ws_bytes);
   s.norm_ws = a.take<char>(norm_backward_scratch_bytes(m.T, m.d));
-  int widest = m.UP > m.QKV ? m.UP : m.QKV;
-  if (6 * m.d > widest && m.ada) widest = 6 * m.d;
-  s.colsum_ws = a.take<char>(colsum_scratch_bytes(m.T, widest));
+  s.norm1_ws = m.ada ? s.norm_ws : a.take<char>(norm_backward_scratch_bytes(m.T, m.d));
+  const int widths[5] = {m.F, m.d, m.d, m.QKV, 6 * m.d};
+  for (int i = 0; i < 5; ++i) s.colsum_ws[i] = a.take<char>(colsum_scratch_bytes(m.T, widths[i]));
   s.gemm_ws_bytes = std::max(max_gemm_tn_scratch(m, dtype), gemm_rows_scratch_bytes(m.T, m.d, dtype));
   s.gemm_ws = a.take<char>(s.gemm_ws_bytes);
   s.dyp = nullptr; s.xp = nullptr; s.dlogits = nullptr; s.dh2e = nullptr;
@@ -469,6 +470,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   const int dt = c.dtype;
   const GemmEpilogue none;
   const int d = m.d;
+  ColumnSums sums;
 
   // token -> sequence map: read by the rotary embedding and by the per-sequence modulation only
   if (c.rope || m.ada) BM_RETURN_IF(launch_tok_seq(cu_dev, S, T, ws.tok_seq, st));
@@ -502,7 +504,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     } else {
       BM_RETURN_IF(gemm_grouped(GEMM_NN, dt, m.cap, m.F, d, ws.dyp, d, w->w_down, m.F, ws.da, m.F, g, st));
       { ProfScope _p(PROF_ELEMENTWISE, (double)m.cap * (2.0 * m.UP + 2.0 * m.F) * (double)m.es, st);
-        BM_RETURN_IF(act_backward(dt, c.act, sv.up, ws.da, ws.dup, ws.a, nullptr, ws.colsum_ws, m.cap, m.F, st)); }
+        BM_RETURN_IF(act_backward(dt, c.act, sv.up, ws.da, ws.dup, ws.a, nullptr, nullptr, m.cap, m.F, nullptr, st)); }
     }
     g.c_stride = (long)d * m.F;
     BM_RETURN_IF(gemm_grouped(GEMM_TN, dt, d, m.F, m.cap, ws.dyp, d, ws.a, m.F, grads->w_down, m.F, g, st));
@@ -518,7 +520,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     NormArgs n2 = norm_args(c, m, 2, w, sv.mod, ws.tok_seq);
     { ProfScope _p(PROF_NORM, 5.0 * T * m.d * (double)m.es, st);
       BM_RETURN_IF(norm_backward(n2, sv.x1, sv.stats2, ws.dh, dy, ws.dx1, ws.h, (float*)grads->norm2_g,
-                                 (float*)grads->norm2_b, nullptr, nullptr, ws.dmod, cu_dev, S, ws.norm_ws, st)); }
+                                 (float*)grads->norm2_b, nullptr, nullptr, ws.dmod, cu_dev, S, ws.norm_ws, &sums, st)); }
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(moe_gather(dt, ws.h, sv.moe, 0, ws.xp, d, T, st)); }
     g.c_stride = (long)m.UP * d;
     BM_RETURN_IF(gemm_grouped(GEMM_TN, dt, m.UP, d, m.cap, ws.dup, m.UP, ws.xp, d, grads->w_up, d, g, st));
@@ -537,14 +539,14 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.F, d, dm, d, w->w_down, m.F, ws.da, m.F, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, (double)T * (2.0 * m.UP + 2.0 * m.F) * (double)m.es, st);
       BM_RETURN_IF(act_backward(dt, c.act, sv.up, ws.da, ws.dup, ws.a,
-                                c.linear_bias ? (float*)grads->b_up : nullptr, ws.colsum_ws, T, m.F, st)); }
+                                c.linear_bias ? (float*)grads->b_up : nullptr, ws.colsum_ws[0], T, m.F, &sums, st)); }
   }
   BM_RETURN_IF(gemm(GEMM_TN, dt, d, m.F, T, dm, d, ws.a, m.F, grads->w_down, m.F, none, ws.gemm_ws,
                     ws.gemm_ws_bytes, st));
   // bias gradients of the down and output projections are column sums of the two
   // gradients the norm backward below touches anyway (not so when a gate sits between)
   if (c.linear_bias && !fused_sums)
-    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, dm, d, T, d, (float*)grads->b_down, ws.colsum_ws, st)); }
+    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, dm, d, T, d, (float*)grads->b_down, ws.colsum_ws[1], &sums, st)); }
 
   // ---- up = h2 W_up^T + b_up,  h2 = N2(x1)
   NormArgs n2 = norm_args(c, m, 2, w, sv.mod, ws.tok_seq);
@@ -553,7 +555,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     BM_RETURN_IF(norm_backward(n2, sv.x1, sv.stats2, ws.dh, dy, ws.dx1, ws.h, (float*)grads->norm2_g,
                                (float*)grads->norm2_b, fused_sums ? (float*)grads->b_down : nullptr,
                                fused_sums ? (float*)grads->b_o : nullptr, ws.dmod, cu_dev, S,
-                               ws.norm_ws, st)); }
+                               ws.norm_ws, &sums, st)); }
   BM_RETURN_IF(gemm(GEMM_TN, dt, m.UP, d, T, ws.dup, m.UP, ws.h, d, grads->w_up, d, none, ws.gemm_ws,
                     ws.gemm_ws_bytes, st));
 
@@ -570,7 +572,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   // (the weight gradient of the output projection is small: it shares a launch with the one of
   // the QKV projection at the end; dattn and the saved o stay untouched until then)
   if (c.linear_bias && !fused_sums)
-    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, dattn, d, T, d, (float*)grads->b_o, ws.colsum_ws, st)); }
+    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, dattn, d, T, d, (float*)grads->b_o, ws.colsum_ws[2], &sums, st)); }
   BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.QD, d, dattn, d, w->w_o, m.QD, ws.d_o, m.QD, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
 
   // ---- attention
@@ -591,12 +593,12 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   // ---- qkv = h W_qkv^T + b_qkv,  h = N1(x)
   NormArgs n1 = norm_args(c, m, 1, w, sv.mod, ws.tok_seq);
   if (c.linear_bias)
-    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, ws.dqkv, m.QKV, T, m.QKV, (float*)grads->b_qkv, ws.colsum_ws, st)); }
+    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, ws.dqkv, m.QKV, T, m.QKV, (float*)grads->b_qkv, ws.colsum_ws[3], &sums, st)); }
   BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.QKV, ws.dqkv, m.QKV, w->w_qkv, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
   { ProfScope _p(PROF_NORM, 5.0 * T * m.d * (double)m.es, st);
     BM_RETURN_IF(norm_backward(n1, x, sv.stats1, ws.dh, ws.dx1, dx, ws.h, (float*)grads->norm1_g,
                                (float*)grads->norm1_b, nullptr, nullptr, ws.dmod, cu_dev, S,
-                               ws.norm_ws, st)); }
+                               ws.norm1_ws, &sums, st)); }
   BM_RETURN_IF(gemm_tn_pair(dt, T, m.QKV, d, ws.dqkv, m.QKV, ws.h, d, grads->w_qkv, d,
                             d, m.QD, dattn, d, sv.o, m.QD, grads->w_o, m.QD, ws.gemm_ws, ws.gemm_ws_bytes, st));
 
@@ -607,7 +609,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     BM_RETURN_IF(silu_forward(dt, cond, ws.sc, (long)S * d, st));
     BM_RETURN_IF(gemm(GEMM_TN, dt, 6 * d, d, S, ws.dmod_e, 6 * d, ws.sc, d, grads->w_ada, d, none,
                       ws.gemm_ws, ws.gemm_ws_bytes, st));
-    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, ws.dmod_e, 6 * d, S, 6 * d, (float*)grads->b_ada, ws.colsum_ws, st)); }
+    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, ws.dmod_e, 6 * d, S, 6 * d, (float*)grads->b_ada, ws.colsum_ws[4], &sums, st)); }
     // d silu(cond) = dmod W_ada: a few rows against a long reduction, so it runs as a weight-gradient
     // style product on the transposed dmod (rows padded to 8), whose k range splits over the chip
     const int S8 = (int)align_up(S, 8);
@@ -617,5 +619,6 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
                       ws.gemm_ws_bytes, st));
     BM_RETURN_IF(silu_backward_f32(dt, cond, ws.dsc, dcond, (long)S * d, st));
   }
+  { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(flush_column_sums(&sums, st)); }
   return BM_OK;
 }

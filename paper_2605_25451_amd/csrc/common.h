@@ -275,6 +275,21 @@ bm_status attention_backward_generic(const AttnArgs& a, const void* o, const voi
 // seq id of every token: tok_seq[t] = s with cu[s] <= t < cu[s+1]
 bm_status launch_tok_seq(const int32_t* cu_dev, int S, int T, int32_t* tok_seq, hipStream_t st);
 
+// Column sums that kernels have left as partial rows in scratch (bias and gain gradients); one launch folds all of a
+// list into their fp32 accumulators.  Scratch that a target points to stays untouched until the flush.
+struct ColumnSums {
+  static constexpr int MAX = 16;
+  struct Target { const float* partial; float* out; int parts, stride, n; } target[MAX];
+  int count = 0;
+  // out[c] += sum over p < parts of partial[p * stride + c], c < n
+  bm_status add(const float* partial, int parts, int stride, int n, float* out) {
+    if (count == MAX) { set_error("more than %d column sums in one list", MAX); return BM_ERR_INVALID_ARG; }
+    target[count++] = Target{partial, out, parts, stride, n};
+    return BM_OK;
+  }
+};
+bm_status flush_column_sums(ColumnSums* sums, hipStream_t st);
+
 struct NormArgs {
   int dtype, kind;          // BM_NORM_*
   int T, d;
@@ -289,12 +304,12 @@ struct NormArgs {
 bm_status norm_forward(const NormArgs& a, const void* x, void* h, float* stats, int write_stats,
                        hipStream_t st);
 size_t norm_backward_scratch_bytes(int T, int d);
-// dx = dres + dN/dx(dh);  dgamma/dbeta fp32 += (LayerNorm/RMSNorm)
+// dx = dres + dN/dx(dh);  dgamma/dbeta fp32 += (LayerNorm/RMSNorm) and dsum_res/dsum_out when `sums` is flushed
 // adaLN: dmod[:, shift_off..] = segsum(dh), dmod[:, scale_off..] = segsum(dh * xhat) (overwrite, fp32)
 bm_status norm_backward(const NormArgs& a, const void* x, const float* stats, const void* dh,
                         const void* dres, void* dx, void* h_out, float* dgamma, float* dbeta,
                         float* dsum_res, float* dsum_out, float* dmod, const int32_t* cu_dev, int S,
-                        void* scratch, hipStream_t st);
+                        void* scratch, ColumnSums* sums, hipStream_t st);
 
 // RoPE in place on the first n_heads heads of each row of qkv; sign=+1 fwd, -1 bwd
 bm_status rope_inplace(int dtype, void* qkv, int ld, int T, int n_heads, int dh, float base,
@@ -302,12 +317,12 @@ bm_status rope_inplace(int dtype, void* qkv, int ld, int T, int n_heads, int dh,
 
 bm_status act_forward(int dtype, int act, const void* up, void* a, int T, int F, hipStream_t st);
 bm_status act_backward(int dtype, int act, const void* up, const void* da, void* dup, void* a_out,
-                       float* bias_grad, void* scratch, int T, int F, hipStream_t st);
+                       float* bias_grad, void* scratch, int T, int F, ColumnSums* sums, hipStream_t st);
 
-// out[n] += sum_t a[t, n]   (fp32 accumulate, deterministic two-stage)
+// out[n] += sum_t a[t, n]   (fp32 accumulate, deterministic two-stage; the second stage is the list's flush)
 size_t colsum_scratch_bytes(int T, int N);
 bm_status colsum_accumulate(int dtype, const void* a, int lda, int T, int N, float* out,
-                            void* scratch, hipStream_t st);
+                            void* scratch, ColumnSums* sums, hipStream_t st);
 // out[s, n] = sum_{t in s} a[t,n] * b[t,n] (fp32, overwrite) and, when gated != nullptr,
 // gated[t, n] = a[t, n] * gate[s, n]; rows are N wide; scratch: segment_scratch_bytes()
 size_t segment_scratch_bytes();

@@ -113,8 +113,9 @@ struct MBwd {
   float* dsc[2];                // [S, d] per stream
   char *d_o_j, *dqkv_j;         // joint order
   char *a, *dup, *da, *h, *dh, *dgated, *d_o, *dqkv, *dmod_e, *dmod_t, *sc;   // per-stream temporaries, reused
-  float* gain_part;             // per-workgroup partial sums of the q/k gain gradients
-  char *attn_ws, *norm_ws, *colsum_ws, *gemm_ws;
+  float* gain_part[2];          // per stream: per-workgroup partial sums of the q/k gain gradients
+  char *attn_ws, *norm_ws, *gemm_ws;
+  char *colsum_ws[2][5];        // per stream: the column sums of the up, down, o, qkv and ada bias gradients
   size_t attn_ws_bytes, gemm_ws_bytes;
   size_t bytes;
 };
@@ -158,13 +159,13 @@ MBwd layout_bwd(const MDims& m, int dtype, void* base) {
   w.dmod_e = a.take<char>((size_t)m.S * 6 * m.d * m.es);
   w.dmod_t = a.take<char>(align_up(m.S, 8) * 6 * m.d * m.es);
   w.sc = a.take<char>((size_t)m.S * m.d * m.es);
-  w.gain_part = a.take<float>((size_t)QKN_BLOCKS * 2 * m.dh * sizeof(float));
+  for (int s = 0; s < 2; ++s) w.gain_part[s] = a.take<float>((size_t)QKN_BLOCKS * 2 * m.dh * sizeof(float));
   w.attn_ws_bytes = attention_backward_scratch_bytes(m.H, m.H, m.dh, m.T);
   w.attn_ws = a.take<char>(w.attn_ws_bytes);
   w.norm_ws = a.take<char>(norm_backward_scratch_bytes(m.Tmax, m.d));
-  int widest = m.F > m.QKV ? m.F : m.QKV;
-  if (6 * m.d > widest) widest = 6 * m.d;
-  w.colsum_ws = a.take<char>(colsum_scratch_bytes(m.Tmax > QKN_BLOCKS ? m.Tmax : QKN_BLOCKS, widest));
+  const int widths[5] = {m.F, m.d, m.d, m.QKV, 6 * m.d};
+  for (int s = 0; s < 2; ++s)
+    for (int i = 0; i < 5; ++i) w.colsum_ws[s][i] = a.take<char>(colsum_scratch_bytes(m.Tmax, widths[i]));
   w.gemm_ws_bytes = std::max(max_gemm_scratch(m, dtype), gemm_rows_scratch_bytes(m.Tmax, m.d, dtype));
   w.gemm_ws = a.take<char>(w.gemm_ws_bytes);
   w.bytes = a.off;
@@ -342,8 +343,8 @@ bm_status qk_norm_forward(int dtype, const void* raw, const int32_t* jpos, const
 }
 
 bm_status qk_norm_backward(int dtype, const void* dout_j, const void* raw, const int32_t* jpos, const void* gq,
-                           const void* gk, void* dqkv, float* part, float* dgq, float* dgk, void* colsum_ws,
-                           int rows, int H, int dh, float eps, hipStream_t st) {
+                           const void* gk, void* dqkv, float* part, float* dgq, float* dgk, int rows, int H, int dh,
+                           float eps, ColumnSums* sums, hipStream_t st) {
   if (rows == 0) return BM_OK;
   const int vec = dtype == BM_DTYPE_BF16 ? 8 : 4;
   const int lp = lanes_per_head(dh, vec);
@@ -363,9 +364,8 @@ bm_status qk_norm_backward(int dtype, const void* dout_j, const void* raw, const
 #undef BM_D
   BM_CHECK_LAUNCH("qk_norm_bwd");
   // fixed-order sum over workgroups, added to the gradients
-  BM_RETURN_IF(colsum_accumulate(BM_DTYPE_FP32, part, 2 * dh, blocks, dh, dgq, colsum_ws, st));
-  BM_RETURN_IF(colsum_accumulate(BM_DTYPE_FP32, part + dh, 2 * dh, blocks, dh, dgk, colsum_ws, st));
-  return BM_OK;
+  BM_RETURN_IF(sums->add(part, blocks, 2 * dh, dh, dgq));
+  return sums->add(part + dh, blocks, 2 * dh, dh, dgk);
 }
 
 // ------------------------------------------------------------------ argument checks
@@ -613,6 +613,7 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
   hipStream_t st = (hipStream_t)hip_stream;
   const int dt = c.dtype, d = m.d;
   const GemmEpilogue none;
+  ColumnSums sums;
 
   BM_RETURN_IF(build_tables(m, ws.tb, cu_dev, st));
 
@@ -630,16 +631,16 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
                                 ws.norm_ws, st)); }
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.F, d, ws.dgated, d, p.w_down, m.F, ws.da, m.F, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, (double)T * 4.0 * m.F * (double)m.es, st);
-      BM_RETURN_IF(act_backward(dt, BM_ACT_GELU, q.up, ws.da, ws.dup, ws.a, (float*)g.b_up, ws.colsum_ws, T, m.F, st)); }
+      BM_RETURN_IF(act_backward(dt, BM_ACT_GELU, q.up, ws.da, ws.dup, ws.a, (float*)g.b_up, ws.colsum_ws[s][0], T, m.F, &sums, st)); }
     BM_RETURN_IF(gemm(GEMM_TN, dt, d, m.F, T, ws.dgated, d, ws.a, m.F, g.w_down, m.F, none, ws.gemm_ws,
                       ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
-      BM_RETURN_IF(colsum_accumulate(dt, ws.dgated, d, T, d, (float*)g.b_down, ws.colsum_ws, st)); }
+      BM_RETURN_IF(colsum_accumulate(dt, ws.dgated, d, T, d, (float*)g.b_down, ws.colsum_ws[s][1], &sums, st)); }
     // up = h2 W_up^T + b_up,  h2 = LN0(x1)(1 + scale2) + shift2
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.F, ws.dup, m.F, p.w_up, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_NORM, 5.0 * T * d * (double)m.es, st);
       BM_RETURN_IF(norm_backward(ada_norm_args(c, T, 2, q.mod, tok), q.x1, q.stats2, ws.dh, dy[s], ws.dx1[s], ws.h,
-                                 nullptr, nullptr, nullptr, nullptr, dmod, cu_dev[s], S, ws.norm_ws, st)); }
+                                 nullptr, nullptr, nullptr, nullptr, dmod, cu_dev[s], S, ws.norm_ws, &sums, st)); }
     BM_RETURN_IF(gemm(GEMM_TN, dt, m.F, d, T, ws.dup, m.F, ws.h, d, g.w_up, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     // x1 = x + g1 * attn,  attn = o W_o^T + b_o
     { ProfScope _p(PROF_ELEMENTWISE, 3.0 * T * d * (double)m.es, st);
@@ -648,7 +649,7 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
     BM_RETURN_IF(gemm(GEMM_TN, dt, d, m.QD, T, ws.dgated, d, q.o, m.QD, g.w_o, m.QD, none, ws.gemm_ws,
                       ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
-      BM_RETURN_IF(colsum_accumulate(dt, ws.dgated, d, T, d, (float*)g.b_o, ws.colsum_ws, st)); }
+      BM_RETURN_IF(colsum_accumulate(dt, ws.dgated, d, T, d, (float*)g.b_o, ws.colsum_ws[s][2], &sums, st)); }
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.QD, d, ws.dgated, d, p.w_o, m.QD, ws.d_o, m.QD, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, 2.0 * T * m.QD * (double)m.es, st);
       BM_RETURN_IF(row_scatter(dt, ws.d_o, ws.tb.jpos[s], ws.d_o_j, T, m.QD, st)); }
@@ -672,16 +673,16 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
       ProfScope _p(PROF_ELEMENTWISE, (m.qk_norm ? 3.0 : 2.0) * T * m.QKV * (double)m.es, st);
       if (m.qk_norm)
         BM_RETURN_IF(qk_norm_backward(dt, ws.dqkv_j, q.qkv_raw, ws.tb.jpos[s], w->q_norm_g[s], w->k_norm_g[s],
-                                      ws.dqkv, ws.gain_part, (float*)grads->q_norm_g[s], (float*)grads->k_norm_g[s],
-                                      ws.colsum_ws, T, m.H, m.dh, desc->qk_norm_eps, st));
+                                      ws.dqkv, ws.gain_part[s], (float*)grads->q_norm_g[s],
+                                      (float*)grads->k_norm_g[s], T, m.H, m.dh, desc->qk_norm_eps, &sums, st));
       else
         BM_RETURN_IF(row_gather(dt, ws.dqkv_j, ws.tb.jpos[s], ws.dqkv, T, m.QKV, st));
-      BM_RETURN_IF(colsum_accumulate(dt, ws.dqkv, m.QKV, T, m.QKV, (float*)g.b_qkv, ws.colsum_ws, st));
+      BM_RETURN_IF(colsum_accumulate(dt, ws.dqkv, m.QKV, T, m.QKV, (float*)g.b_qkv, ws.colsum_ws[s][3], &sums, st));
     }
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.QKV, ws.dqkv, m.QKV, p.w_qkv, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_NORM, 5.0 * T * d * (double)m.es, st);
       BM_RETURN_IF(norm_backward(ada_norm_args(c, T, 1, q.mod, tok), x[s], q.stats1, ws.dh, ws.dx1[s], dx[s], ws.h,
-                                 nullptr, nullptr, nullptr, nullptr, dmod, cu_dev[s], S, ws.norm_ws, st)); }
+                                 nullptr, nullptr, nullptr, nullptr, dmod, cu_dev[s], S, ws.norm_ws, &sums, st)); }
     BM_RETURN_IF(gemm(GEMM_TN, dt, m.QKV, d, T, ws.dqkv, m.QKV, ws.h, d, g.w_qkv, d, none, ws.gemm_ws,
                       ws.gemm_ws_bytes, st));
     // mod = silu(cond) W_ada^T + b_ada
@@ -689,7 +690,7 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
     BM_RETURN_IF(gemm(GEMM_TN, dt, 6 * d, d, S, ws.dmod_e, 6 * d, ws.sc, d, g.w_ada, d, none, ws.gemm_ws,
                       ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
-      BM_RETURN_IF(colsum_accumulate(dt, ws.dmod_e, 6 * d, S, 6 * d, (float*)g.b_ada, ws.colsum_ws, st)); }
+      BM_RETURN_IF(colsum_accumulate(dt, ws.dmod_e, 6 * d, S, 6 * d, (float*)g.b_ada, ws.colsum_ws[s][4], &sums, st)); }
     // d silu(cond) = dmod W_ada as a weight-gradient style product on the transposed dmod
     // (few rows, long reduction: the k range splits over the chip)
     const int S8 = (int)align_up(S, 8);
@@ -701,5 +702,6 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
   // both streams read the same conditioning rows
   BM_RETURN_IF(add_inplace(BM_DTYPE_FP32, ws.dsc[0], ws.dsc[1], (long)S * d, st));
   BM_RETURN_IF(silu_backward_f32(dt, cond, ws.dsc[0], dcond, (long)S * d, st));
-  return BM_OK;
+  ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
+  return flush_column_sums(&sums, st);
 }
