@@ -84,22 +84,44 @@ size_t gemm_tn_pair_scratch_bytes(int K, int M0, int N0, int M1, int N1, int dty
   return both > one ? both : one;
 }
 
+bool gemm_tn_pair_shares_launch(int dtype, int K, int M0, int N0, const void* A0, int lda0, const void* B0, int ldb0,
+                                void* C0, int ldc0, int M1, int N1, const void* A1, int lda1, const void* B1, int ldb1,
+                                void* C1, int ldc1, void* scratch, size_t scratch_bytes, hipStream_t st) {
+  return dtype == BM_DTYPE_BF16 && K > 0 && M0 > 0 && N0 > 0 && M1 > 0 && N1 > 0 &&
+         gemm_mfma_tn_pair(K, M0, N0, A0, lda0, B0, ldb0, C0, ldc0, M1, N1, A1, lda1, B1, ldb1, C1, ldc1, scratch,
+                           scratch_bytes, st, nullptr);
+}
+
 bm_status gemm_tn_pair(int dtype, int K, int M0, int N0, const void* A0, int lda0, const void* B0, int ldb0,
                        void* C0, int ldc0, int M1, int N1, const void* A1, int lda1, const void* B1, int ldb1,
                        void* C1, int ldc1, void* scratch, size_t scratch_bytes, hipStream_t st) {
-  if (dtype == BM_DTYPE_BF16 && K > 0 && M0 > 0 && N0 > 0 && M1 > 0 && N1 > 0) {
-    if (gemm_mfma_tn_pair(K, M0, N0, A0, lda0, B0, ldb0, C0, ldc0, M1, N1, A1, lda1, B1, ldb1, C1, ldc1, scratch,
-                          scratch_bytes, st, nullptr)) {
-      bm_status rc;
-      ProfScope prof(PROF_GEMM_TN, 2.0 * K * ((double)M0 * N0 + (double)M1 * N1), st);
-      gemm_mfma_tn_pair(K, M0, N0, A0, lda0, B0, ldb0, C0, ldc0, M1, N1, A1, lda1, B1, ldb1, C1, ldc1, scratch,
-                        scratch_bytes, st, &rc);
-      return rc;
-    }
+  if (gemm_tn_pair_shares_launch(dtype, K, M0, N0, A0, lda0, B0, ldb0, C0, ldc0, M1, N1, A1, lda1, B1, ldb1, C1, ldc1, scratch,
+                                 scratch_bytes, st)) {
+    bm_status rc;
+    ProfScope prof(PROF_GEMM_TN, 2.0 * K * ((double)M0 * N0 + (double)M1 * N1), st);
+    gemm_mfma_tn_pair(K, M0, N0, A0, lda0, B0, ldb0, C0, ldc0, M1, N1, A1, lda1, B1, ldb1, C1, ldc1, scratch,
+                      scratch_bytes, st, &rc);
+    return rc;
   }
   const GemmEpilogue none;
   BM_RETURN_IF(gemm(GEMM_TN, dtype, M0, N0, K, A0, lda0, B0, ldb0, C0, ldc0, none, scratch, scratch_bytes, st));
   return gemm(GEMM_TN, dtype, M1, N1, K, A1, lda1, B1, ldb1, C1, ldc1, none, scratch, scratch_bytes, st);
+}
+
+bool gemm_nn_tn_joint(int dtype, const GemmCall& nn, const GemmCall& tn, void* scratch, size_t scratch_bytes, hipStream_t st,
+                      bm_status* rc) {
+  if (nn.M <= 0 || nn.N <= 0 || tn.M <= 0 || tn.N <= 0) return false;
+  return dtype == BM_DTYPE_BF16 ? gemm_mfma_nn_tn(nn, tn, scratch, scratch_bytes, st, rc)
+                                : gemm_generic_nn_tn(dtype, nn, tn, st, rc);
+}
+
+bm_status gemm_nn_tn(int dtype, const GemmCall& nn, const GemmCall& tn, void* scratch, size_t scratch_bytes, hipStream_t st) {
+  bm_status rc;
+  if (gemm_nn_tn_joint(dtype, nn, tn, scratch, scratch_bytes, st, &rc)) return rc;
+  const GemmEpilogue none;
+  // the weight gradient first: its operands are what the kernel before has just written
+  BM_RETURN_IF(gemm(GEMM_TN, dtype, tn.M, tn.N, tn.K, tn.A, tn.lda, tn.B, tn.ldb, tn.C, tn.ldc, none, scratch, scratch_bytes, st));
+  return gemm(GEMM_NN, dtype, nn.M, nn.N, nn.K, nn.A, nn.lda, nn.B, nn.ldb, nn.C, nn.ldc, none, scratch, scratch_bytes, st);
 }
 
 bm_status gemm_grouped(int layout, int dtype, int M, int N, int K, const void* A, int lda,

@@ -158,7 +158,7 @@ BwdScratch layout_bwd(const Dims& m, int dtype, void* base) {
   s.norm1_ws = m.ada ? s.norm_ws : a.take<char>(norm_backward_scratch_bytes(m.T, m.d));
   const int widths[5] = {m.F, m.d, m.d, m.QKV, 6 * m.d};
   for (int i = 0; i < 5; ++i) s.colsum_ws[i] = a.take<char>(colsum_scratch_bytes(m.T, widths[i]));
-  s.gemm_ws_bytes = std::max(max_gemm_tn_scratch(m, dtype), gemm_rows_scratch_bytes(m.T, m.d, dtype));
+  s.gemm_ws_bytes = max_gemm_tn_scratch(m, dtype) + gemm_rows_scratch_bytes(m.T, m.d, dtype);   // gemm_nn_tn: both at once
   s.gemm_ws = a.take<char>(s.gemm_ws_bytes);
   s.dyp = nullptr; s.xp = nullptr; s.dlogits = nullptr; s.dh2e = nullptr;
   if (m.E > 0) {
@@ -541,24 +541,20 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
       BM_RETURN_IF(act_backward(dt, c.act, sv.up, ws.da, ws.dup, ws.a,
                                 c.linear_bias ? (float*)grads->b_up : nullptr, ws.colsum_ws[0], T, m.F, &sums, st)); }
   }
-  BM_RETURN_IF(gemm(GEMM_TN, dt, d, m.F, T, dm, d, ws.a, m.F, grads->w_down, m.F, none, ws.gemm_ws,
-                    ws.gemm_ws_bytes, st));
+  // ---- up = h2 W_up^T + b_up,  h2 = N2(x1): its input gradient beside the weight gradient of the down projection
+  BM_RETURN_IF(gemm_nn_tn(dt, GemmCall{T, d, m.UP, ws.dup, m.UP, w->w_up, d, ws.dh, d},
+                          GemmCall{d, m.F, T, dm, d, ws.a, m.F, grads->w_down, m.F}, ws.gemm_ws, ws.gemm_ws_bytes, st));
   // bias gradients of the down and output projections are column sums of the two
   // gradients the norm backward below touches anyway (not so when a gate sits between)
   if (c.linear_bias && !fused_sums)
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, dm, d, T, d, (float*)grads->b_down, ws.colsum_ws[1], &sums, st)); }
 
-  // ---- up = h2 W_up^T + b_up,  h2 = N2(x1)
   NormArgs n2 = norm_args(c, m, 2, w, sv.mod, ws.tok_seq);
-  BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.UP, ws.dup, m.UP, w->w_up, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
   { ProfScope _p(PROF_NORM, 5.0 * T * m.d * (double)m.es, st);
     BM_RETURN_IF(norm_backward(n2, sv.x1, sv.stats2, ws.dh, dy, ws.dx1, ws.h, (float*)grads->norm2_g,
                                (float*)grads->norm2_b, fused_sums ? (float*)grads->b_down : nullptr,
                                fused_sums ? (float*)grads->b_o : nullptr, ws.dmod, cu_dev, S,
                                ws.norm_ws, &sums, st)); }
-  BM_RETURN_IF(gemm(GEMM_TN, dt, m.UP, d, T, ws.dup, m.UP, ws.h, d, grads->w_up, d, none, ws.gemm_ws,
-                    ws.gemm_ws_bytes, st));
-
   }
 
   // ---- x1 = x + [g1 *] attn,  attn = o W_o^T + b_o
@@ -573,7 +569,15 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   // the QKV projection at the end; dattn and the saved o stay untouched until then)
   if (c.linear_bias && !fused_sums)
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, dattn, d, T, d, (float*)grads->b_o, ws.colsum_ws[2], &sums, st)); }
-  BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.QD, d, dattn, d, w->w_o, m.QD, ws.d_o, m.QD, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
+  {
+    const GemmCall d_o{T, m.QD, d, dattn, d, w->w_o, m.QD, ws.d_o, m.QD};
+    if (m.E > 0)
+      BM_RETURN_IF(gemm(GEMM_NN, dt, d_o.M, d_o.N, d_o.K, d_o.A, d_o.lda, d_o.B, d_o.ldb, d_o.C, d_o.ldc, none, ws.gemm_ws,
+                        ws.gemm_ws_bytes, st));
+    else   // beside the weight gradient of the up projection, whose input ws.h holds until norm 1
+      BM_RETURN_IF(gemm_nn_tn(dt, d_o, GemmCall{m.UP, d, T, ws.dup, m.UP, ws.h, d, grads->w_up, d}, ws.gemm_ws,
+                              ws.gemm_ws_bytes, st));
+  }
 
   // ---- attention
   AttnArgs at;
@@ -594,12 +598,28 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   NormArgs n1 = norm_args(c, m, 1, w, sv.mod, ws.tok_seq);
   if (c.linear_bias)
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, ws.dqkv, m.QKV, T, m.QKV, (float*)grads->b_qkv, ws.colsum_ws[3], &sums, st)); }
-  BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.QKV, ws.dqkv, m.QKV, w->w_qkv, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
+  // the weight gradient of the output projection goes with the input gradient here, where that is one launch, or with
+  // the weight gradient of the QKV projection behind norm 1
+  const bool o_with_qkv = gemm_tn_pair_shares_launch(dt, T, m.QKV, d, ws.dqkv, m.QKV, ws.h, d, grads->w_qkv, d,
+                                                     d, m.QD, dattn, d, sv.o, m.QD, grads->w_o, m.QD, ws.gemm_ws,
+                                                     ws.gemm_ws_bytes, st);
+  bool o_done = false;
+  if (!o_with_qkv) {
+    bm_status rc;
+    o_done = gemm_nn_tn_joint(dt, GemmCall{T, d, m.QKV, ws.dqkv, m.QKV, w->w_qkv, d, ws.dh, d},
+                              GemmCall{d, m.QD, T, dattn, d, sv.o, m.QD, grads->w_o, m.QD}, ws.gemm_ws, ws.gemm_ws_bytes, st, &rc);
+    if (o_done) BM_RETURN_IF(rc);
+  }
+  if (!o_done)
+    BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.QKV, ws.dqkv, m.QKV, w->w_qkv, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
   { ProfScope _p(PROF_NORM, 5.0 * T * m.d * (double)m.es, st);
     BM_RETURN_IF(norm_backward(n1, x, sv.stats1, ws.dh, ws.dx1, dx, ws.h, (float*)grads->norm1_g,
                                (float*)grads->norm1_b, nullptr, nullptr, ws.dmod, cu_dev, S,
                                ws.norm1_ws, &sums, st)); }
-  BM_RETURN_IF(gemm_tn_pair(dt, T, m.QKV, d, ws.dqkv, m.QKV, ws.h, d, grads->w_qkv, d,
+  if (o_done)
+    BM_RETURN_IF(gemm(GEMM_TN, dt, m.QKV, d, T, ws.dqkv, m.QKV, ws.h, d, grads->w_qkv, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
+  else
+    BM_RETURN_IF(gemm_tn_pair(dt, T, m.QKV, d, ws.dqkv, m.QKV, ws.h, d, grads->w_qkv, d,
                             d, m.QD, dattn, d, sv.o, m.QD, grads->w_o, m.QD, ws.gemm_ws, ws.gemm_ws_bytes, st));
 
   // ---- adaLN: mod = silu(cond) W_ada^T + b_ada

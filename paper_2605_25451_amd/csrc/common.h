@@ -159,6 +159,16 @@ bm_status gemm(int layout, int dtype, int M, int N, int K, const void* A, int ld
                int ldb, void* C, int ldc, const GemmEpilogue& epi, void* scratch,
                size_t scratch_bytes, hipStream_t st);
 
+// An input gradient C[M,N] = A[M,K] B[K,N] and a weight gradient C[M,N] += A[K,M]^T B[K,N] (fp32 C) that do not depend on
+// one another: one launch where few rows leave the chip idle, else one after the other.  Scratch as for both.
+struct GemmCall { int M, N, K; const void* A; int lda; const void* B; int ldb; void* C; int ldc; };
+bm_status gemm_nn_tn(int dtype, const GemmCall& nn, const GemmCall& tn, void* scratch, size_t scratch_bytes, hipStream_t st);
+// one launch, with its status in *rc; or false and nothing launched: separate launches are the better choice
+bool gemm_nn_tn_joint(int dtype, const GemmCall& nn, const GemmCall& tn, void* scratch, size_t scratch_bytes, hipStream_t st,
+                      bm_status* rc);
+bool gemm_mfma_nn_tn(const GemmCall& nn, const GemmCall& tn, void* scratch, size_t scratch_bytes, hipStream_t st, bm_status* rc);
+bool gemm_generic_nn_tn(int dtype, const GemmCall& nn, const GemmCall& tn, hipStream_t st, bm_status* rc);
+
 // Grouped GEMM for the mixture-of-experts FFN: the rows of the activation matrices are
 // sorted by expert and every expert's segment is padded to MOE_PAD rows.
 //   NT / NN: row block t (MOE_PAD rows) of A and C belongs to group tile_group[t] (-1: no
@@ -182,6 +192,9 @@ size_t gemm_tn_pair_scratch_bytes(int K, int M0, int N0, int M1, int N1, int dty
 bm_status gemm_tn_pair(int dtype, int K, int M0, int N0, const void* A0, int lda0, const void* B0, int ldb0,
                        void* C0, int ldc0, int M1, int N1, const void* A1, int lda1, const void* B1, int ldb1,
                        void* C1, int ldc1, void* scratch, size_t scratch_bytes, hipStream_t st);
+bool gemm_tn_pair_shares_launch(int dtype, int K, int M0, int N0, const void* A0, int lda0, const void* B0, int ldb0,
+                                void* C0, int ldc0, int M1, int N1, const void* A1, int lda1, const void* B1, int ldb1,
+                                void* C1, int ldc1, void* scratch, size_t scratch_bytes, hipStream_t st);
 size_t gemm_mfma_tn_pair_scratch_bytes(int K, int M0, int N0, int M1, int N1);
 bool gemm_mfma_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const void* B0, int ldb0, void* C0, int ldc0,
                        int M1, int N1, const void* A1, int lda1, const void* B1, int ldb1, void* C1, int ldc1,

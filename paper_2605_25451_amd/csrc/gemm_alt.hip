@@ -178,7 +178,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_kernel(GemmParams p) {
   constexpr int LATE = RegA::LOADS, EARLY = RegA::LOADS + RegB::LOADS;      // loads of a slice's two parts
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 2, wn = wave & 3;                                   // wm is the group
-  const TileJob job = locate_tile<256, 256>(p);
+  const TileJob job = locate_tile<256, 256>(p, blockIdx.x);
   if (job.kbeg >= job.kend) return;
   const int m0 = job.m0, n0 = job.n0, n = (job.kend - job.kbeg + BK - 1) / BK;
   const int k_left = job.kend - job.kbeg - (n - 1) * BK;                     // of the last slice
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_tn_kernel(GemmParams p
   constexpr int HL = Reg::LOADS;                                             // loads of half a slice, A and B
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 2, wn = wave & 3;                                   // wm is the group
-  const TileJob job = locate_tile<256, 256>(p);
+  const TileJob job = locate_tile<256, 256>(p, blockIdx.x);
   if (job.kbeg >= job.kend) return;
   const int m0 = job.m0, n0 = job.n0, n = (job.kend - job.kbeg + BK - 1) / BK;
   const int k_left = job.kend - job.kbeg - (n - 1) * BK;                     // of the last slice
@@ -410,7 +410,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt128_kernel(GemmParams p) {
   constexpr int WN = BN / 64;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WN, wn = wave % WN, group = wave >> 2;
-  const TileJob job = locate_tile<BM, BN>(p);
+  const TileJob job = locate_tile<BM, BN>(p, blockIdx.x);
   if (job.kbeg >= job.kend) return;
   const int m0 = job.m0, n0 = job.n0, n = (job.kend - job.kbeg + BK - 1) / BK;
   const int k_left = job.kend - job.kbeg - (n - 1) * BK;

@@ -126,9 +126,8 @@ struct TileJob {
 };
 
 template <int BM, int BN>
-__device__ inline TileJob locate_tile(GemmParams& p) {
+__device__ inline TileJob locate_tile(GemmParams& p, int pid) {
   TileJob t;
-  int pid = blockIdx.x;
   if (p.pair_wgs0 > 0 && pid >= p.pair_wgs0) {
     pid -= p.pair_wgs0;
     p.A = p.second.A; p.B = p.second.B; p.C = p.second.C; p.partial = p.second.partial;
