@@ -290,8 +290,7 @@ __device__ inline bool find_tile(const int32_t* __restrict__ cu, const SeqOrder&
 // ids go round-robin over the 8 XCDs, head index i lands on XCD i%8: give XCD x
 // the consecutive heads x*(H/8).., so every tile of one head -- and the q heads of
 // one GQA group -- meet their K/V in the same XCD's L2.
-__device__ inline void tile_and_head(int H, int* tile, int* head) {
-  const int b = blockIdx.x;
+__device__ inline void tile_and_head(int H, int* tile, int* head, int b = blockIdx.x) {
   const int i = b % H;
   *tile = b / H;
   *head = (H % 8 == 0) ? (i % 8) * (H / 8) + i / 8 : i;
@@ -836,9 +835,9 @@ constexpr int BK_Q = 64;       // query rows per step
 
 // dK, dV of one 128-key tile of one kv head: walks the q heads of the group and the
 // query tiles; scores are kept as S[q, key] so that P and dS are B operands as they are.
+template <int DH> constexpr int dkdv_lds_bytes() { return 4 * BK_Q * HeadDim<DH>::DHL * 2 + 4 * BK_Q * 4; }
 template <int DH, bool CAUSAL>
-__global__ __launch_bounds__(256, DH <= 64 ? 2 : 1) void fa_bwd_dkdv_kernel(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
+__device__ inline void dkdv_tile(unsigned char* lds, int block, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
     int ldk, const bf16_t* __restrict__ d_o, int ldo, const float* __restrict__ lse,
     const float* __restrict__ delta, const int32_t* __restrict__ cuq, const int32_t* __restrict__ cu,
     int S, bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int ldd, int Tq, int Ttot, int Hkv, int group,
@@ -847,15 +846,15 @@ __global__ __launch_bounds__(256, DH <= 64 ? 2 : 1) void fa_bwd_dkdv_kernel(
   // cu, Ttot, ldk: the packing of the keys/values (and of dk, dv); cuq, Tq, ld: of the queries
   // Q and dO tiles are double-buffered and streamed into LDS (see TileAsync)
   constexpr int TILE = BK_Q * HeadDim<DH>::DHL;
-  __shared__ __attribute__((aligned(1024))) bf16_t Qbuf[2 * TILE];
-  __shared__ __attribute__((aligned(1024))) bf16_t Dbuf[2 * TILE];
-  __shared__ __attribute__((aligned(16))) float Lbuf[2 * BK_Q];
-  __shared__ __attribute__((aligned(16))) float Dlbuf[2 * BK_Q];
+  bf16_t* const Qbuf = reinterpret_cast<bf16_t*>(lds);
+  bf16_t* const Dbuf = Qbuf + 2 * TILE;
+  float* const Lbuf = reinterpret_cast<float*>(Dbuf + 2 * TILE);
+  float* const Dlbuf = Lbuf + 2 * BK_Q;
   int seq, kt, nkt, tile_id, hk;
   // with gsplit > 1 a workgroup takes group/gsplit of the q heads that share this kv head
   // and leaves an fp32 partial; the (kv head, q-head part) pair plays the head's role
   int hk_gs;
-  tile_and_head(Hkv * gsplit, &tile_id, &hk_gs);
+  tile_and_head(Hkv * gsplit, &tile_id, &hk_gs, block);
   hk = hk_gs / gsplit;
   const int gs = hk_gs % gsplit;
   const int gpart = group / gsplit;
@@ -1570,9 +1569,9 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
 
 // dQ of one 128-row query tile of one q head: walks the key tiles, scores kept as
 // S^T[key, q] as in the forward kernel.
+template <int DH> constexpr int dq_lds_bytes() { return 4 * (DH > 72 ? 32 : FK) * HeadDim<DH>::DHL * 2; }
 template <int DH, bool CAUSAL>
-__global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
+__device__ inline void dq_tile(unsigned char* lds, int block, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
     int ldk, const bf16_t* __restrict__ d_o, int ldo, const float* __restrict__ lse,
     const float* __restrict__ delta, const int32_t* __restrict__ cu, const int32_t* __restrict__ cuk,
     int S, bf16_t* __restrict__ dq, int ldd, int Ttot, int Hq, int group, float scale, float scale_log2,
@@ -1584,10 +1583,10 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(
   // reads per key block, measured 1 % slower.)
   constexpr int FKD = DH > 72 ? 32 : FK;
   constexpr int TILE = FKD * HeadDim<DH>::DHL;
-  __shared__ __attribute__((aligned(1024))) bf16_t Kbuf[2 * TILE];
-  __shared__ __attribute__((aligned(1024))) bf16_t Vbuf[2 * TILE];
+  bf16_t* const Kbuf = reinterpret_cast<bf16_t*>(lds);
+  bf16_t* const Vbuf = Kbuf + 2 * TILE;
   int seq, qt, nqt, tile_id, hq;
-  tile_and_head(Hq, &tile_id, &hq);
+  tile_and_head(Hq, &tile_id, &hq, block);
   if (!find_tile(cu, ord, S, FQ, tile_id, &seq, &qt, &nqt)) return;
   const int hk = hq / group;
   const int lo = cu[seq], L = cu[seq + 1] - lo;
@@ -1746,6 +1745,39 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(
           *reinterpret_cast<bf16x4*>(pq + j * 32 + g * 8 + half * 4) = w;
       }
   }
+}
+
+template <int DH, bool CAUSAL>
+__global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
+    int ldk, const bf16_t* __restrict__ d_o, int ldo, const float* __restrict__ lse,
+    const float* __restrict__ delta, const int32_t* __restrict__ cu, const int32_t* __restrict__ cuk,
+    int S, bf16_t* __restrict__ dq, int ldd, int Ttot, int Hq, int group, float scale, float scale_log2,
+    SeqOrder ord) {
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[dq_lds_bytes<DH>()];
+  dq_tile<DH, CAUSAL>(lds, blockIdx.x, q, k, v, ld, ldk, d_o, ldo, lse, delta, cu, cuk, S, dq, ldd, Ttot, Hq, group, scale,
+                      scale_log2, ord);
+}
+
+// The whole backward of head size 64 behind delta in one grid: the dK/dV tiles, which run longer, then the dQ tiles, which
+// fill the CUs that the last of them leave.  Both have two wavefronts per SIMD.  They share one piece of LDS (with one
+// each the dK/dV tile spills).  16 heads, two launches -> one: 577 tokens 41 -> 26 us, 6 images 47 -> 34, 26 images 236 -> 223, 8192
+// tokens 985 -> 970; causal 41 -> 26, 45 -> 31, 179 -> 165, 547 -> 507.
+template <int DH, bool CAUSAL>
+__global__ __launch_bounds__(256, 2) void fa_bwd_joint_kernel(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld, int ldk,
+    const bf16_t* __restrict__ d_o, int ldo, const float* __restrict__ lse, const float* __restrict__ delta,
+    const int32_t* __restrict__ cuq, const int32_t* __restrict__ cuk, int S, bf16_t* __restrict__ dq, int ldd,
+    bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int ldd_kv, int Tq, int Tk, int Hkv, int group, float scale,
+    float scale_log2, int gsplit, float* __restrict__ part, int kv_wgs, SeqOrder ord_kv, SeqOrder ord_q) {
+  constexpr int LDS = dkdv_lds_bytes<DH>() > dq_lds_bytes<DH>() ? dkdv_lds_bytes<DH>() : dq_lds_bytes<DH>();
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS];
+  if ((int)blockIdx.x < kv_wgs)
+    dkdv_tile<DH, CAUSAL>(lds, blockIdx.x, q, k, v, ld, ldk, d_o, ldo, lse, delta, cuq, cuk, S, dk, dv, ldd_kv, Tq, Tk, Hkv,
+                          group, scale, scale_log2, gsplit, part, ord_kv);
+  else
+    dq_tile<DH, CAUSAL>(lds, blockIdx.x - kv_wgs, q, k, v, ld, ldk, d_o, ldo, lse, delta, cuq, cuk, S, dq, ldd, Tq, Hkv * group,
+                        group, scale, scale_log2, ord_q);
 }
 
 // dQ with two groups of wavefronts that take turns (see the forward kernel): while one multiplies -- dS K of a key
@@ -1999,19 +2031,19 @@ bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const fl
                        (const bf16_t*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), a.S,        \
                        (bf16_t*)dk, (bf16_t*)dv, ldd_kv, a.T, Tk, a.Hkv, a.Hq / a.Hkv, scale, sl2, \
                        gsplit, part, ord_kv);                                                    \
-  else if (ktiles > 0)                                                                           \
-    hipLaunchKernelGGL((fa_bwd_dkdv_kernel<DH, C>), gkv, dim3(256), 0, st, (const bf16_t*)a.q,    \
-                       (const bf16_t*)a.k, (const bf16_t*)a.v, a.ld_qkv, a.kv_ld(),              \
+  if (DH <= 64 && gkv.x + gq.x > 0)                                                              \
+    hipLaunchKernelGGL((fa_bwd_joint_kernel<(DH <= 64 ? DH : 64), C>), dim3(gkv.x + gq.x), dim3(256), 0, st, \
+                       (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, a.ld_qkv, a.kv_ld(), \
                        (const bf16_t*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), a.S,        \
-                       (bf16_t*)dk, (bf16_t*)dv, ldd_kv, a.T, Tk, a.Hkv, a.Hq / a.Hkv, scale, sl2, \
-                       gsplit, part, ord_kv);                                                    \
-  if (alt && gq.x > 0)                                                                           \
+                       (bf16_t*)dq, ldd, (bf16_t*)dk, (bf16_t*)dv, ldd_kv, a.T, Tk, a.Hkv,       \
+                       a.Hq / a.Hkv, scale, sl2, gsplit, part, (int)gkv.x, ord_kv, ord_q);       \
+  else if (alt && gq.x > 0)                                                                           \
     hipLaunchKernelGGL((fa_bwd_dq_alt_kernel<C>), gq, dim3(512), 0, st,    \
                        (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, a.ld_qkv, a.kv_ld(), \
                        (const bf16_t*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), a.S,        \
                        (bf16_t*)dq, ldd, a.T, a.Hq, a.Hq / a.Hkv, scale, sl2, ord_q);            \
   else if (gq.x > 0)                                                                             \
-    hipLaunchKernelGGL((fa_bwd_dq_kernel<DH, C>), gq, dim3(256), 0, st, (const bf16_t*)a.q,      \
+    hipLaunchKernelGGL((fa_bwd_dq_kernel<(DH > 64 ? DH : 128), C>), gq, dim3(256), 0, st, (const bf16_t*)a.q,      \
                        (const bf16_t*)a.k, (const bf16_t*)a.v, a.ld_qkv, a.kv_ld(),              \
                        (const bf16_t*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), a.S,        \
                        (bf16_t*)dq, ldd, a.T, a.Hq, a.Hq / a.Hkv, scale, sl2, ord_q)
