@@ -290,7 +290,7 @@ __device__ inline bool find_tile(const int32_t* __restrict__ cu, const SeqOrder&
 // ids go round-robin over the 8 XCDs, head index i lands on XCD i%8: give XCD x
 // the consecutive heads x*(H/8).., so every tile of one head -- and the q heads of
 // one GQA group -- meet their K/V in the same XCD's L2.
-__device__ inline void tile_and_head(int H, int* tile, int* head, int b = blockIdx.x) {
+__device__ inline void tile_and_head(int H, int* tile, int* head, int b) {
   const int i = b % H;
   *tile = b / H;
   *head = (H % 8 == 0) ? (i % 8) * (H / 8) + i / 8 : i;
@@ -314,7 +314,7 @@ __global__ __launch_bounds__(256, 2) void fa_fwd_kernel(
   __shared__ __attribute__((aligned(1024))) bf16_t Kbuf[2 * TILE];
   __shared__ __attribute__((aligned(1024))) bf16_t Vbuf[2 * TILE];
   int seq, qt, nqt, tile_id, hq;
-  tile_and_head(Hq, &tile_id, &hq);
+  tile_and_head(Hq, &tile_id, &hq, blockIdx.x);
   if (!find_tile(cu, ord, S, FQ, tile_id, &seq, &qt, &nqt)) return;
   const int hk = hq / group;
   const int lo = cu[seq], L = cu[seq + 1] - lo;
@@ -564,7 +564,7 @@ __global__ __launch_bounds__(512, 2) void fa_fwd_alt_kernel(
   __shared__ __attribute__((aligned(1024))) unsigned char Kbuf[RING * TILE];
   __shared__ __attribute__((aligned(1024))) unsigned char Vbuf[RING * TILE];
   int seq, qt, nqt, tile_id, hq;
-  tile_and_head(Hq, &tile_id, &hq);
+  tile_and_head(Hq, &tile_id, &hq, blockIdx.x);
   if (!find_tile(cu, ord, S, AQ, tile_id, &seq, &qt, &nqt)) return;
   const int hk = hq / group;
   const int lo = cu[seq], L = cu[seq + 1] - lo;
@@ -1073,9 +1073,10 @@ __device__ inline void dkdv_tile(unsigned char* lds, int block, const bf16_t* __
 // two are resident per SIMD and one's vector work runs under the other's MFMAs.  P travels as
 // bf16 in the operand layout: role 0 feeds exactly these values to its own MFMAs, and role 1
 // owns the same (key, query) elements in the same lanes, so the exchange is lane-private.
+template <int DH> constexpr int dkdv_pair_lds_bytes() { return 4 * BK_Q * HeadDim<DH>::DHL * 2 + 4 * (BK_Q / 32) * 2 * 64 * 16 + 4 * BK_Q * 4; }
 template <int DH, bool CAUSAL>
-__global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_pair_kernel(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
+__device__ inline void dkdv_pair_tile(
+    unsigned char* lds, int block, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
     int ldk, const bf16_t* __restrict__ d_o, int ldo, const float* __restrict__ lse,
     const float* __restrict__ delta, const int32_t* __restrict__ cuq, const int32_t* __restrict__ cu,
     int S, bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int ldd, int Tq, int Ttot, int Hkv, int group,
@@ -1085,13 +1086,15 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_pair_kernel(
   // Q and dO tiles are double-buffered and streamed into LDS (see TileAsync): with one workgroup
   // per CU nothing else runs while a tile is parked between two barriers
   constexpr int TILE = BK_Q * DHL;
-  __shared__ __attribute__((aligned(1024))) bf16_t Qbuf[2 * TILE];
-  __shared__ __attribute__((aligned(1024))) bf16_t Dbuf[2 * TILE];
-  __shared__ __attribute__((aligned(16))) bf16_t Ps[4 * NQB * 2 * 64 * 8];   // [key block][q block][half k-step][lane] x 16 B
-  __shared__ __attribute__((aligned(16))) float Lbuf[2 * BK_Q];
-  __shared__ __attribute__((aligned(16))) float Dlbuf[2 * BK_Q];
+  // (in this order: with lse and delta behind 64 KiB, out of an immediate offset's reach, the bidirectional kernel of
+  // head size 128 spills 22 registers)
+  bf16_t* const Qbuf = reinterpret_cast<bf16_t*>(lds);
+  bf16_t* const Ps = Qbuf + 2 * TILE;                    // [key block][q block][half k-step][lane] x 16 B
+  float* const Lbuf = reinterpret_cast<float*>(Ps + 4 * NQB * 2 * 64 * 8);
+  float* const Dlbuf = Lbuf + 2 * BK_Q;
+  bf16_t* const Dbuf = reinterpret_cast<bf16_t*>(Dlbuf + 2 * BK_Q);
   int seq, kt, nkt, tile_id, hk, hk_gs;
-  tile_and_head(Hkv * gsplit, &tile_id, &hk_gs);
+  tile_and_head(Hkv * gsplit, &tile_id, &hk_gs, block);
   hk = hk_gs / gsplit;
   const int gs = hk_gs % gsplit;
   const int gpart = group / gsplit;
@@ -1311,9 +1314,10 @@ __device__ inline int fresh_lane() {
   return l;
 }
 
+constexpr int DKDV_WIDE_LDS_BYTES = WideTile::RING * WideTile::BYTES + 2 * 4 * 4096;
 template <bool CAUSAL>
-__global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
+__device__ inline void dkdv_wide_tile(
+    unsigned char* lds, int block, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
     int ldk, const bf16_t* __restrict__ d_o, int ldo, const float* __restrict__ lse,
     const float* __restrict__ delta, const int32_t* __restrict__ cuq, const int32_t* __restrict__ cu,
     int S, bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int ldd, int Tq, int Ttot, int Hkv, int group,
@@ -1322,10 +1326,11 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
   constexpr int DH = 128, KS = 8, NB = 4, KB = 2;
   using W = WideTile;
   using RT = RunTile<DH>;
-  __shared__ __attribute__((aligned(1024))) unsigned char tiles[W::RING * W::BYTES];
-  __shared__ __attribute__((aligned(1024))) unsigned char Pbuf[2 * 4 * 4096];   // [parity][pair][key block, half k-step][lane]
+  static_assert(W::RING * W::BYTES % 1024 == 0, "P starts where a tile run may");
+  unsigned char* const tiles = lds;
+  unsigned char* const Pbuf = lds + W::RING * W::BYTES;  // [parity][pair][key block, half k-step][lane]
   int seq, kt, nkt, tile_id, hk, hk_gs;
-  tile_and_head(Hkv * gsplit, &tile_id, &hk_gs);
+  tile_and_head(Hkv * gsplit, &tile_id, &hk_gs, block);
   hk = hk_gs / gsplit;
   const int gs = hk_gs % gsplit;
   const int gpart = group / gsplit;
@@ -1571,10 +1576,10 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dkdv_wide_kernel(
 // S^T[key, q] as in the forward kernel.
 template <int DH> constexpr int dq_lds_bytes() { return 4 * (DH > 72 ? 32 : FK) * HeadDim<DH>::DHL * 2; }
 template <int DH, bool CAUSAL>
-__device__ inline void dq_tile(unsigned char* lds, int block, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
+__device__ inline void dq_tile(unsigned char* lds, int tid, int tile_id, int hq, bool live, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
     int ldk, const bf16_t* __restrict__ d_o, int ldo, const float* __restrict__ lse,
     const float* __restrict__ delta, const int32_t* __restrict__ cu, const int32_t* __restrict__ cuk,
-    int S, bf16_t* __restrict__ dq, int ldd, int Ttot, int Hq, int group, float scale, float scale_log2,
+    int S, bf16_t* __restrict__ dq, int ldd, int Ttot, int group, float scale, float scale_log2,
     SeqOrder ord) {
   // K and V tiles are double-buffered and streamed into LDS as in the forward kernel; Q and dO of
   // this wavefront's 32 queries stay in registers.  At head size 128 a step is one 32-key block:
@@ -1585,19 +1590,18 @@ __device__ inline void dq_tile(unsigned char* lds, int block, const bf16_t* __re
   constexpr int TILE = FKD * HeadDim<DH>::DHL;
   bf16_t* const Kbuf = reinterpret_cast<bf16_t*>(lds);
   bf16_t* const Vbuf = Kbuf + 2 * TILE;
-  int seq, qt, nqt, tile_id, hq;
-  tile_and_head(Hq, &tile_id, &hq, block);
+  int seq, qt, nqt;
   if (!find_tile(cu, ord, S, FQ, tile_id, &seq, &qt, &nqt)) return;
   const int hk = hq / group;
   const int lo = cu[seq], L = cu[seq + 1] - lo;
   const int lok = cuk[seq], Lk = cuk[seq + 1] - lok;
   const int q0 = qt * FQ;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5;
+  const int lane = tid & 63, wave = tid >> 6, half = lane >> 5;
   const int qpos = q0 + wave * 32 + (lane & 31);
   const int qrow = min(qpos, L - 1);
   if (Lk == 0) {
     // no key in this chunk (workgroup-uniform): dq = 0
-    if (qpos < L) {
+    if (live && qpos < L) {
       bf16_t* pq = dq + (size_t)(lo + qpos) * ldd + hq * DH;
       for (int c = half * (DH / 2); c < (half + 1) * (DH / 2); c += 4) {
         bf16x4 z = {(bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f, (bf16_t)0.f};
@@ -1732,7 +1736,7 @@ __device__ inline void dq_tile(unsigned char* lds, int block, const bf16_t* __re
     if (kt & 1) { if (plain) step(kt, std::false_type{}, P1{}); else step(kt, std::true_type{}, P1{}); }
     else { if (plain) step(kt, std::false_type{}, P0{}); else step(kt, std::true_type{}, P0{}); }
   }
-  if (qpos < L) {
+  if (live && qpos < L) {
     bf16_t* pq = dq + (size_t)(lo + qpos) * ldd + hq * DH;
 #pragma unroll
     for (int j = 0; j < HeadDim<DH>::NB; ++j)
@@ -1747,6 +1751,7 @@ __device__ inline void dq_tile(unsigned char* lds, int block, const bf16_t* __re
   }
 }
 
+// head sizes above 64, two workgroups per CU: packs whose dK/dV tiles alone fill the chip (see bwd_launch)
 template <int DH, bool CAUSAL>
 __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
@@ -1755,8 +1760,10 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(
     int S, bf16_t* __restrict__ dq, int ldd, int Ttot, int Hq, int group, float scale, float scale_log2,
     SeqOrder ord) {
   __shared__ __attribute__((aligned(1024))) unsigned char lds[dq_lds_bytes<DH>()];
-  dq_tile<DH, CAUSAL>(lds, blockIdx.x, q, k, v, ld, ldk, d_o, ldo, lse, delta, cu, cuk, S, dq, ldd, Ttot, Hq, group, scale,
-                      scale_log2, ord);
+  int tile, head;
+  tile_and_head(Hq, &tile, &head, blockIdx.x);
+  dq_tile<DH, CAUSAL>(lds, threadIdx.x, tile, head, true, q, k, v, ld, ldk, d_o, ldo, lse, delta, cu, cuk, S, dq, ldd, Ttot,
+                      group, scale, scale_log2, ord);
 }
 
 // The whole backward of head size 64 behind delta in one grid: the dK/dV tiles, which run longer, then the dQ tiles, which
@@ -1776,8 +1783,12 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_joint_kernel(
     dkdv_tile<DH, CAUSAL>(lds, blockIdx.x, q, k, v, ld, ldk, d_o, ldo, lse, delta, cuq, cuk, S, dk, dv, ldd_kv, Tq, Tk, Hkv,
                           group, scale, scale_log2, gsplit, part, ord_kv);
   else
-    dq_tile<DH, CAUSAL>(lds, blockIdx.x - kv_wgs, q, k, v, ld, ldk, d_o, ldo, lse, delta, cuq, cuk, S, dq, ldd, Tq, Hkv * group,
+  {
+    int tile, head;
+    tile_and_head(Hkv * group, &tile, &head, blockIdx.x - kv_wgs);
+    dq_tile<DH, CAUSAL>(lds, threadIdx.x, tile, head, true, q, k, v, ld, ldk, d_o, ldo, lse, delta, cuq, cuk, S, dq, ldd, Tq,
                         group, scale, scale_log2, ord_q);
+  }
 }
 
 // dQ with two groups of wavefronts that take turns (see the forward kernel): while one multiplies -- dS K of a key
@@ -1785,9 +1796,10 @@ __global__ __launch_bounds__(256, 2) void fa_bwd_joint_kernel(
 // MFMAs of a tile are no longer than its softmax, the kernel above is ahead (96 against 112 us on 16384 tokens of images).
 // us, two workgroups of four wavefronts -> this: 8192 x 8192 keys, 32 / 8 heads, 1522 -> 1332, causal 782 -> 687; 32768 tokens
 // of causal documents 4217 -> 3630; 8192 tokens of documents, 32 heads, 262 -> 253; 16 samples of about 1130, 24 heads, 445 both.
+constexpr int DQ_ALT_LDS_BYTES = (4 + 3) * RunTile<128>::bytes(FK);
 template <bool CAUSAL>
-__global__ __launch_bounds__(512, 2) void fa_bwd_dq_alt_kernel(
-    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
+__device__ inline void dq_alt_tile(
+    unsigned char* lds, int block, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
     int ldk, const bf16_t* __restrict__ d_o, int ldo, const float* __restrict__ lse,
     const float* __restrict__ delta, const int32_t* __restrict__ cu, const int32_t* __restrict__ cuk,
     int S, bf16_t* __restrict__ dq, int ldd, int Ttot, int Hq, int group, float scale, float scale_log2,
@@ -1796,10 +1808,11 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dq_alt_kernel(
   using RT = RunTile<DH>;
   constexpr int KS = DH / 16, NB = DH / 32, KBL = FK / 32, TILE = RT::bytes(FK), RUNS = FK / RT::RPR / 8;
   constexpr int KRING = 4, VRING = 3;                     // a K tile is read as rows in one phase, as columns two later
-  __shared__ __attribute__((aligned(1024))) unsigned char Kbuf[KRING * TILE];
-  __shared__ __attribute__((aligned(1024))) unsigned char Vbuf[VRING * TILE];
+  static_assert((KRING + VRING) * TILE == DQ_ALT_LDS_BYTES && TILE % 16 == 0, "the caller's piece of LDS");
+  unsigned char* const Kbuf = lds;
+  unsigned char* const Vbuf = lds + KRING * TILE;
   int seq, qt, nqt, tile_id, hq;
-  tile_and_head(Hq, &tile_id, &hq);
+  tile_and_head(Hq, &tile_id, &hq, block);
   if (!find_tile(cu, ord, S, AQ, tile_id, &seq, &qt, &nqt)) return;
   const int hk = hq / group;
   const int lo = cu[seq], L = cu[seq + 1] - lo;
@@ -1945,6 +1958,41 @@ __global__ __launch_bounds__(512, 2) void fa_bwd_dq_alt_kernel(
   }
 }
 
+// ... and of the head sizes above 64, in workgroups of eight wavefronts: dK/dV by pairs of wavefronts (WIDE: with 64 keys a
+// pair), dQ with turns (ALT) or as the 128 rows of two heads side by side -- the same sequence and tile, so that both
+// halves of the workgroup make the same steps and meet at the same barriers; with an odd number of heads the last
+// workgroup's second half repeats the first and stores nothing.  Two launches -> one, us: 32 heads, 300 tokens 39 -> 27, causal
+// documents of 8192 tokens 537 -> 526; 32 / 8 heads, 777 causal tokens 76 -> 55, heavy-tailed documents 3515 -> 3267; two-stream
+// samples of 1170 tokens, 24 heads, 1112 -> 1069.
+template <int DH, bool CAUSAL, bool WIDE, bool ALT>
+__global__ __launch_bounds__(512, 2) void fa_bwd_joint512_kernel(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld, int ldk,
+    const bf16_t* __restrict__ d_o, int ldo, const float* __restrict__ lse, const float* __restrict__ delta,
+    const int32_t* __restrict__ cuq, const int32_t* __restrict__ cuk, int S, bf16_t* __restrict__ dq, int ldd,
+    bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int ldd_kv, int Tq, int Tk, int Hkv, int group, float scale,
+    float scale_log2, int gsplit, float* __restrict__ part, int kv_wgs, SeqOrder ord_kv, SeqOrder ord_q) {
+  constexpr int KV = WIDE ? DKDV_WIDE_LDS_BYTES : dkdv_pair_lds_bytes<DH>(), Q = ALT ? DQ_ALT_LDS_BYTES : 2 * dq_lds_bytes<DH>();
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[KV > Q ? KV : Q];
+  const int Hq = Hkv * group;
+  if ((int)blockIdx.x < kv_wgs) {
+    if constexpr (WIDE)
+      dkdv_wide_tile<CAUSAL>(lds, blockIdx.x, q, k, v, ld, ldk, d_o, ldo, lse, delta, cuq, cuk, S, dk, dv, ldd_kv, Tq, Tk, Hkv,
+                             group, scale, scale_log2, gsplit, part, ord_kv);
+    else
+      dkdv_pair_tile<DH, CAUSAL>(lds, blockIdx.x, q, k, v, ld, ldk, d_o, ldo, lse, delta, cuq, cuk, S, dk, dv, ldd_kv, Tq, Tk,
+                                 Hkv, group, scale, scale_log2, gsplit, part, ord_kv);
+  } else if constexpr (ALT) {
+    dq_alt_tile<CAUSAL>(lds, blockIdx.x - kv_wgs, q, k, v, ld, ldk, d_o, ldo, lse, delta, cuq, cuk, S, dq, ldd, Tq, Hq, group,
+                        scale, scale_log2, ord_q);
+  } else {
+    int tile, heads;
+    tile_and_head((Hq + 1) / 2, &tile, &heads, blockIdx.x - kv_wgs);
+    const int side = __builtin_amdgcn_readfirstlane(threadIdx.x >> 8), head = heads * 2 + side;
+    dq_tile<DH, CAUSAL>(lds + side * dq_lds_bytes<DH>(), threadIdx.x & 255, tile, min(head, Hq - 1), head < Hq, q, k, v, ld, ldk,
+                        d_o, ldo, lse, delta, cuq, cuk, S, dq, ldd, Tq, group, scale, scale_log2, ord_q);
+  }
+}
+
 // dk, dv = sum over the q-head parts of the fp32 partials, in part order
 __global__ void fa_dkdv_reduce_kernel(const float* __restrict__ part, int gsplit, int Ttot, int W /* Hkv*dh */,
                                       bf16_t* __restrict__ dk, bf16_t* __restrict__ dv, int ldd) {
@@ -2013,42 +2061,49 @@ bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const fl
   const int gsplit = ktiles > 0 ? dkdv_group_split(ktiles, a.Hkv, a.Hq / a.Hkv) : 1;
   float* part = delta + align_up((size_t)a.Hq * a.T, 64);      // after the delta plane
   const int Tk = a.kv_T();
-  dim3 gkv(ktiles * a.Hkv * gsplit), gq(count_tiles(a.cu_host, a.S, query_rows) * a.Hq);
+  const int kv_wgs = ktiles * a.Hkv * gsplit;
+  const int qtiles = count_tiles(a.cu_host, a.S, query_rows);
+  int q_wgs = qtiles * (DH > 64 && !alt ? (a.Hq + 1) / 2 : a.Hq);
+  // One launch or two?  One, where dQ takes the same workgroups anyway: head size 64, and 256-row query tiles (60 packs of
+  // 1500 to 36000 tokens: 57 faster, 3 % on average, 12 % at best, the slowest -1.6 %).  The 128 rows of two heads side by
+  // side are slower than two workgroups on a CU, so that is for packs whose workgroups all run at once, or nearly so where a
+  // causal mask makes most of them short or the wide dK/dV ones are few and long, and for those whose dQ fits into what
+  // a second round of dK/dV leaves idle.
+  // Two launches -> one, us: 16 / 4 heads, 777 tokens (168 workgroups) 83 -> 55; 24 heads, 1100 tokens (324) 92 -> 103, causal
+  // 86 -> 61; 32 heads, 777 (336) 69 -> 80, causal 69 -> 48; causal 8 x 256 (384) 50 -> 52.5; wide 500 + 700 (320) 89 -> 78, 1300 (368)
+  // 147 both; causal 1100 (288 of dK/dV, 432) 91 -> 82; 1500 (384, 576) 168 -> 170, causal 117 -> 121.
+  const int both = kv_wgs + q_wgs;
+  const int at_once = wide ? NUM_CU * 5 / 4 : a.causal && qtiles >= 3 * a.S ? NUM_CU * 3 / 2 : NUM_CU;
+  const bool together = DH <= 64 || alt || both <= at_once || (kv_wgs > NUM_CU && both <= 2 * NUM_CU);
+  if (!together) q_wgs = 0;
   // a key tile runs as long as its sequence has queries, a query tile as long as it has keys
   const SeqOrder ord_kv = make_seq_order(a.kv_cu_host(), a.cu_host, a.S, key_rows, !a.causal);
   const SeqOrder ord_q = make_seq_order(a.cu_host, a.kv_cu_host(), a.S, query_rows, !a.causal);
-#define BM_L(C)                                                                                  \
-  if (wide && ktiles > 0)                                                                        \
-    hipLaunchKernelGGL((fa_bwd_dkdv_wide_kernel<C>), gkv, dim3(512), 0, st, (const bf16_t*)a.q,  \
-                       (const bf16_t*)a.k, (const bf16_t*)a.v, a.ld_qkv, a.kv_ld(),              \
-                       (const bf16_t*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), a.S,        \
-                       (bf16_t*)dk, (bf16_t*)dv, ldd_kv, a.T, Tk, a.Hkv, a.Hq / a.Hkv, scale, sl2, \
-                       gsplit, part, ord_kv);                                                    \
-  else if (ktiles > 0 && DH > 64)                                                                     \
-    hipLaunchKernelGGL((fa_bwd_dkdv_pair_kernel<(DH > 64 ? DH : 128), C>), gkv, dim3(512), 0, st, \
-                       (const bf16_t*)a.q,                                                       \
-                       (const bf16_t*)a.k, (const bf16_t*)a.v, a.ld_qkv, a.kv_ld(),              \
-                       (const bf16_t*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), a.S,        \
-                       (bf16_t*)dk, (bf16_t*)dv, ldd_kv, a.T, Tk, a.Hkv, a.Hq / a.Hkv, scale, sl2, \
-                       gsplit, part, ord_kv);                                                    \
-  if (DH <= 64 && gkv.x + gq.x > 0)                                                              \
-    hipLaunchKernelGGL((fa_bwd_joint_kernel<(DH <= 64 ? DH : 64), C>), dim3(gkv.x + gq.x), dim3(256), 0, st, \
-                       (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, a.ld_qkv, a.kv_ld(), \
-                       (const bf16_t*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), a.S,        \
-                       (bf16_t*)dq, ldd, (bf16_t*)dk, (bf16_t*)dv, ldd_kv, a.T, Tk, a.Hkv,       \
-                       a.Hq / a.Hkv, scale, sl2, gsplit, part, (int)gkv.x, ord_kv, ord_q);       \
-  else if (alt && gq.x > 0)                                                                           \
-    hipLaunchKernelGGL((fa_bwd_dq_alt_kernel<C>), gq, dim3(512), 0, st,    \
-                       (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v, a.ld_qkv, a.kv_ld(), \
-                       (const bf16_t*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), a.S,        \
-                       (bf16_t*)dq, ldd, a.T, a.Hq, a.Hq / a.Hkv, scale, sl2, ord_q);            \
-  else if (gq.x > 0)                                                                             \
-    hipLaunchKernelGGL((fa_bwd_dq_kernel<(DH > 64 ? DH : 128), C>), gq, dim3(256), 0, st, (const bf16_t*)a.q,      \
-                       (const bf16_t*)a.k, (const bf16_t*)a.v, a.ld_qkv, a.kv_ld(),              \
-                       (const bf16_t*)d_o, ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), a.S,        \
-                       (bf16_t*)dq, ldd, a.T, a.Hq, a.Hq / a.Hkv, scale, sl2, ord_q)
-  if (a.causal) { BM_L(true); } else { BM_L(false); }
-#undef BM_L
+  auto launch = [&](auto kern, int threads) {
+    hipLaunchKernelGGL(kern, dim3(kv_wgs + q_wgs), dim3(threads), 0, st, (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v,
+                       a.ld_qkv, a.kv_ld(), (const bf16_t*)d_o, ldo, lse, (const float*)delta, a.cu_dev, a.kv_cu_dev(), a.S,
+                       (bf16_t*)dq, ldd, (bf16_t*)dk, (bf16_t*)dv, ldd_kv, a.T, Tk, a.Hkv, a.Hq / a.Hkv, scale, sl2, gsplit, part,
+                       kv_wgs, ord_kv, ord_q);
+  };
+  if (kv_wgs + q_wgs > 0) {
+    if constexpr (DH <= 64) {
+      launch(a.causal ? fa_bwd_joint_kernel<DH, true> : fa_bwd_joint_kernel<DH, false>, 256);
+    } else if constexpr (DH == 128) {
+      if (wide && alt) launch(a.causal ? fa_bwd_joint512_kernel<DH, true, true, true> : fa_bwd_joint512_kernel<DH, false, true, true>, 512);
+      else if (wide) launch(a.causal ? fa_bwd_joint512_kernel<DH, true, true, false> : fa_bwd_joint512_kernel<DH, false, true, false>, 512);
+      else if (alt) launch(a.causal ? fa_bwd_joint512_kernel<DH, true, false, true> : fa_bwd_joint512_kernel<DH, false, false, true>, 512);
+      else launch(a.causal ? fa_bwd_joint512_kernel<DH, true, false, false> : fa_bwd_joint512_kernel<DH, false, false, false>, 512);
+    } else {
+      launch(a.causal ? fa_bwd_joint512_kernel<DH, true, false, false> : fa_bwd_joint512_kernel<DH, false, false, false>, 512);
+    }
+  }
+  if constexpr (DH > 64)
+    if (!together && qtiles > 0) {
+      auto kern = a.causal ? fa_bwd_dq_kernel<DH, true> : fa_bwd_dq_kernel<DH, false>;
+      hipLaunchKernelGGL(kern, dim3(qtiles * a.Hq), dim3(256), 0, st, (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v,
+                         a.ld_qkv, a.kv_ld(), (const bf16_t*)d_o, ldo, lse, (const float*)delta, a.cu_dev, a.kv_cu_dev(), a.S,
+                         (bf16_t*)dq, ldd, a.T, a.Hq, a.Hq / a.Hkv, scale, sl2, ord_q);
+    }
   if (gsplit > 1 && ktiles > 0) {
     const long n4 = (long)Tk * a.Hkv * a.dh / 4;
     hipLaunchKernelGGL(fa_dkdv_reduce_kernel, dim3(cdiv(n4, 256)), dim3(256), 0, st, part, gsplit, Tk,
