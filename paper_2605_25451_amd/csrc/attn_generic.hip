@@ -115,21 +115,21 @@ __global__ __launch_bounds__(NT) void attn_fwd_generic_kernel(
   }
 }
 
-// dq, and on the way delta = rowsum(dO * O) of its rows, which the dk/dv kernel reads: a small step is bound by its
-// launches, and delta's was one of 27 (4.2 us on its own).
+// dq, and on the way delta = rowsum(dO * O) of its rows, which a dk/dv kernel of its own reads: a small step is bound by
+// its launches, and delta's was one of 27 (4.2 us on its own).  bx: the row tile, s: the sequence, hq: the head.
 template <typename T, int DH, bool CAUSAL, int P>
-__global__ __launch_bounds__(NT) void attn_dq_generic_kernel(
-    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int ld, int ldk,
+__device__ inline void dq_rows(
+    int bx, int s, int hq, const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int ld, int ldk,
     const T* __restrict__ o, const T* __restrict__ d_o, int ldo, const float* __restrict__ lse,
     float* __restrict__ delta, const int32_t* __restrict__ cu, const int32_t* __restrict__ cuk,
     T* __restrict__ dq, int ldd, int Ttot, int group, float scale) {
   constexpr int BQ = NT / P;
   __shared__ float Ks[BT][tile_ld<DH, P>()];
   __shared__ float Vs[BT][tile_ld<DH, P>()];
-  const int s = blockIdx.y, hq = blockIdx.z, hk = hq / group;
+  const int hk = hq / group;
   const int lo = cu[s], L = cu[s + 1] - lo;
   const int lok = cuk[s], Lk = cuk[s + 1] - lok;
-  const int q0 = blockIdx.x * BQ;
+  const int q0 = bx * BQ;
   if (q0 >= L) return;
   const int part = threadIdx.x % P;
   const int qi = q0 + threadIdx.x / P;
@@ -185,12 +185,23 @@ __global__ __launch_bounds__(NT) void attn_dq_generic_kernel(
   }
 }
 
+template <typename T, int DH, bool CAUSAL, int P>
+__global__ __launch_bounds__(NT) void attn_dq_generic_kernel(
+    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int ld, int ldk,
+    const T* __restrict__ o, const T* __restrict__ d_o, int ldo, const float* __restrict__ lse,
+    float* __restrict__ delta, const int32_t* __restrict__ cu, const int32_t* __restrict__ cuk,
+    T* __restrict__ dq, int ldd, int Ttot, int group, float scale) {
+  dq_rows<T, DH, CAUSAL, P>(blockIdx.x, blockIdx.y, blockIdx.z, q, k, v, ld, ldk, o, d_o, ldo, lse, delta, cu, cuk, dq, ldd,
+                            Ttot, group, scale);
+}
+
 // P lanes per key row of one kv head; the q heads of the group and the query
 // tiles are walked in a fixed order, so dk/dv sums are reproducible.
-template <typename T, int DH, bool CAUSAL, int P>
-__global__ __launch_bounds__(NT) void attn_dkdv_generic_kernel(
-    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int ld, int ldk,
-    const T* __restrict__ d_o, int ldo, const float* __restrict__ lse,
+// OWN_DELTA: delta of the streamed rows from o and dO, by the same sum as in dq_rows, instead of from memory.
+template <typename T, int DH, bool CAUSAL, int P, bool OWN_DELTA>
+__device__ inline void dkdv_rows(
+    int bx, int s, int hk, const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int ld, int ldk,
+    const T* __restrict__ o, const T* __restrict__ d_o, int ldo, const float* __restrict__ lse,
     const float* __restrict__ delta, const int32_t* __restrict__ cuq, const int32_t* __restrict__ cuk,
     T* __restrict__ dk, T* __restrict__ dv, int ldd, int Ttot, int group, float scale) {
   // this thread's key row lives in the key/value packing (cuk, ldk); queries, dO, lse and
@@ -199,10 +210,9 @@ __global__ __launch_bounds__(NT) void attn_dkdv_generic_kernel(
   __shared__ float Qs[BT][tile_ld<DH, P>()];
   __shared__ float Ds[BT][tile_ld<DH, P>()];
   __shared__ float Ls[BT], Dl[BT];
-  const int s = blockIdx.y, hk = blockIdx.z;
   const int lok = cuk[s], Lk = cuk[s + 1] - lok;
   const int lo = cuq[s], L = cuq[s + 1] - lo;
-  const int kb = blockIdx.x * BQ;
+  const int kb = bx * BQ;
   if (kb >= Lk) return;
   const int part = threadIdx.x % P;
   const int kj = kb + threadIdx.x / P;
@@ -228,7 +238,15 @@ __global__ __launch_bounds__(NT) void attn_dkdv_generic_kernel(
         int qi = q0 + threadIdx.x;
         bool ok = qi < L;
         Ls[threadIdx.x] = ok ? lse[(size_t)hq * Ttot + lo + qi] : 0.f;
-        Dl[threadIdx.x] = ok ? delta[(size_t)hq * Ttot + lo + qi] : 0.f;
+        float dl = 0.f;
+        if (OWN_DELTA && ok) {
+          const size_t row = (size_t)(lo + qi) * ldo + hq * DH;
+#pragma unroll
+          for (int c = 0; c < DH; ++c) dl = fmaf(Elt<T>::to_f(o[row + c]), Elt<T>::to_f(d_o[row + c]), dl);
+        } else if (ok) {
+          dl = delta[(size_t)hq * Ttot + lo + qi];
+        }
+        Dl[threadIdx.x] = dl;
       }
       __syncthreads();
       if (active) {
@@ -267,14 +285,42 @@ __global__ __launch_bounds__(NT) void attn_dkdv_generic_kernel(
   }
 }
 
+template <typename T, int DH, bool CAUSAL, int P>
+__global__ __launch_bounds__(NT) void attn_dkdv_generic_kernel(
+    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int ld, int ldk,
+    const T* __restrict__ d_o, int ldo, const float* __restrict__ lse,
+    const float* __restrict__ delta, const int32_t* __restrict__ cuq, const int32_t* __restrict__ cuk,
+    T* __restrict__ dk, T* __restrict__ dv, int ldd, int Ttot, int group, float scale) {
+  dkdv_rows<T, DH, CAUSAL, P, false>(blockIdx.x, blockIdx.y, blockIdx.z, q, k, v, ld, ldk, (const T*)nullptr, d_o, ldo, lse,
+                                     delta, cuq, cuk, dk, dv, ldd, Ttot, group, scale);
+}
+
+// Both, where eight lanes share a row on either side (few rows): one launch, dk/dv of the Hkv heads in front (they walk the
+// heads of their group) and dq of the Hq heads behind.  fp32 block of 40 tokens 91 -> 83 us, of 1000 107 -> 96.
+template <typename T, int DH, bool CAUSAL>
+__global__ __launch_bounds__(NT) void attn_bwd_joint_generic_kernel(
+    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int ld, int ldk,
+    const T* __restrict__ o, const T* __restrict__ d_o, int ldo, const float* __restrict__ lse, float* __restrict__ delta,
+    const int32_t* __restrict__ cuq, const int32_t* __restrict__ cuk, T* __restrict__ dq, int ldd, T* __restrict__ dk,
+    T* __restrict__ dv, int ldd_kv, int Ttot, int Hkv, int group, float scale) {
+  const int z = blockIdx.z;
+  if (z < Hkv)
+    dkdv_rows<T, DH, CAUSAL, 8, true>(blockIdx.x, blockIdx.y, z, q, k, v, ld, ldk, o, d_o, ldo, lse, nullptr, cuq, cuk, dk, dv,
+                                      ldd_kv, Ttot, group, scale);
+  else
+    dq_rows<T, DH, CAUSAL, 8>(blockIdx.x, blockIdx.y, z - Hkv, q, k, v, ld, ldk, o, d_o, ldo, lse, delta, cuq, cuk, dq, ldd,
+                              Ttot, group, scale);
+}
+
 // Lanes per row.  One lane walks every row of the other side by itself, so few rows leave the chip
 // idle behind long chains; eight lanes per row cost eight times the tile loads.  Measured forward /
 // backward, us, P = 1 -> 8: head size 16, 1000 rows x 4 heads 223 / 658 -> 60 / 147; head size 64, 1024 x 16
 // 453 / 1242 -> 187 / 737, 2048 x 16 463 / 1246 -> 370 / 1458, 4096 x 16 473 / 1290 -> 564 / 2914; head size 128,
 // 1024 x 8 999 / 28283 -> 249 / 5010, 4096 x 8 2164 -> 2894.
+bool eight_lanes(long rows, int heads, int dh) { return rows * heads <= 16384 && rows * heads * dh <= (1L << 20); }
 template <typename F>
 void with_lanes(long rows, int heads, int dh, F&& launch) {
-  if (rows * heads <= 16384 && rows * heads * dh <= (1L << 20)) launch(std::integral_constant<int, 8>{});
+  if (eight_lanes(rows, heads, dh)) launch(std::integral_constant<int, 8>{});
   else launch(std::integral_constant<int, 1>{});
 }
 
@@ -295,6 +341,16 @@ bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const fl
                      void* dk, void* dv, int ldd, float* delta, hipStream_t st) {
   const int ldo = a.Hq * a.dh;
   const float scale = 1.0f / sqrtf((float)a.dh);
+  if constexpr (DH <= 64)
+    if (a.T > 0 && a.kv_T() > 0 && eight_lanes(a.T, a.Hq, DH) && eight_lanes(a.kv_T(), a.Hkv, DH)) {
+      const int longest = a.max_seqlen > a.kv_max_len() ? a.max_seqlen : a.kv_max_len();
+      hipLaunchKernelGGL((attn_bwd_joint_generic_kernel<T, DH, CAUSAL>), dim3(cdiv(longest, NT / 8), a.S, a.Hkv + a.Hq), dim3(NT),
+                         0, st, (const T*)a.q, (const T*)a.k, (const T*)a.v, a.ld_qkv, a.kv_ld(), (const T*)o, (const T*)d_o,
+                         ldo, lse, delta, a.cu_dev, a.kv_cu_dev(), (T*)dq, ldd, (T*)dk, (T*)dv,
+                         a.ld_dkv ? a.ld_dkv : ldd, a.T, a.Hkv, a.Hq / a.Hkv, scale);
+      BM_CHECK_LAUNCH("attn_bwd_generic");
+      return BM_OK;
+    }
   if (a.T > 0) {
     with_lanes(a.T, a.Hq, DH, [&](auto p) {
       constexpr int P = decltype(p)::value;
