@@ -196,29 +196,41 @@ __global__ __launch_bounds__(MOE_CHUNK) void moe_slot_kernel(
 }
 
 // ---- row movement ------------------------------------------------------------------------------
-// dst[row] = scale(row) * src[row_token[row]]  (zeros for padding rows); scale = row_gate or 1
+// dst[row] = scale(row) * src[row_token[row]]  (zeros for padding rows); scale = row_gate or 1.  A wavefront takes a row, so
+// that its token is looked up once and its loads are in flight together (a thread per 16 bytes, each with a
+// look-up in front of its load: 82000 x 2048 bf16 92 us; this: 83, 4.5 TB/s).
 template <typename T>
-__global__ void moe_gather_kernel(const T* __restrict__ src, const int32_t* __restrict__ row_token,
-                                  const float* __restrict__ row_gate, T* __restrict__ dst, int rows,
-                                  int d, int n_src) {
-  constexpr int VEC = Elt<T>::VEC;
-  const int per = d / VEC;
-  const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (long)rows * per) return;
-  const int row = (int)(gid / per), c = (int)(gid % per) * VEC;
+__global__ __launch_bounds__(256) void moe_gather_kernel(const T* __restrict__ src, const int32_t* __restrict__ row_token,
+                                                         const float* __restrict__ row_gate, T* __restrict__ dst, int rows,
+                                                         int d, int n_src) {
+  constexpr int VEC = Elt<T>::VEC, AHEAD = 4;
+  const int lane = threadIdx.x & 63;
+  const int row = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+  if (row >= rows) return;
   const int t = row_token[row];
-  float v[VEC];
+  const bool live = t >= 0 && t < n_src;
+  const bool scaled = live && row_gate;
+  const float g = scaled ? row_gate[row] : 1.f;
+  const T* from = src + (size_t)(live ? t : 0) * d;
+  T* to = dst + (size_t)row * d;
+  for (int c0 = lane * VEC; c0 < d; c0 += AHEAD * WAVE * VEC) {
+    float v[AHEAD][VEC];
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) v[e] = 0.f;
-  if (t >= 0 && t < n_src) {
-    load16(src + (size_t)t * d + c, v);
-    if (row_gate) {
-      const float g = row_gate[row];
+    for (int i = 0; i < AHEAD; ++i) {
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) v[e] *= g;
+      for (int e = 0; e < VEC; ++e) v[i][e] = 0.f;
+      const int c = c0 + i * WAVE * VEC;
+      if (live && c < d) load16(from + c, v[i]);
+    }
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i) {
+      const int c = c0 + i * WAVE * VEC;
+      if (scaled)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) v[i][e] *= g;
+      if (c < d) store16(to + c, v[i]);
     }
   }
-  store16(dst + (size_t)row * d + c, v);
 }
 
 // out[t] = (res ? res[t] : 0) + sum_j w(t,j) * rows[slot[t,j]],  w = gate or 1; choices in order
@@ -354,14 +366,12 @@ bm_status moe_layout(const MoeTables& m, int T, int E, int k, void* scratch, hip
 
 bm_status moe_gather(int dtype, const void* src, const MoeTables& m, int use_gate, void* dst, int d, int T,
                      hipStream_t st) {
-  const int vec = dtype == BM_DTYPE_BF16 ? 8 : 4;
-  const long n = (long)m.cap * (d / vec);
   const float* rg = use_gate ? m.row_gate : nullptr;
   if (dtype == BM_DTYPE_BF16)
-    hipLaunchKernelGGL(moe_gather_kernel<bf16_t>, dim3(cdiv(n, 256)), dim3(256), 0, st, (const bf16_t*)src,
+    hipLaunchKernelGGL(moe_gather_kernel<bf16_t>, dim3(cdiv(m.cap, 4)), dim3(256), 0, st, (const bf16_t*)src,
                        m.row_token, rg, (bf16_t*)dst, m.cap, d, T);
   else
-    hipLaunchKernelGGL(moe_gather_kernel<float>, dim3(cdiv(n, 256)), dim3(256), 0, st, (const float*)src,
+    hipLaunchKernelGGL(moe_gather_kernel<float>, dim3(cdiv(m.cap, 4)), dim3(256), 0, st, (const float*)src,
                        m.row_token, rg, (float*)dst, m.cap, d, T);
   BM_CHECK_LAUNCH("moe_gather");
   return BM_OK;
