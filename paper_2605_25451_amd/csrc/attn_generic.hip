@@ -33,6 +33,34 @@ template <int P> __device__ inline float lanes_max(float v) {
   return v;
 }
 
+// BT rows of two matrices from row r0 of `rows` (>= 1) into LDS, `scale` on the first; rows past the last one are zeros.  The
+// loads carry no condition (their rows are clamped), so that several are in flight: with a branch around every
+// load, here and for a lane's own row, each waited for the one before it.  us, forward / backward: 300 rows, 4 heads of 16, 22 /
+// 25 -> 15 / 21; 16 heads of 64 70 / 156 -> 43 / 93; 5 x 200 rows, 8 heads of 128 335 / 803 -> 156 / 373; 4 x 1024 rows, 4 heads of 32,
+// 183 / 542 -> 84 / 279 (5 x 200, 8 heads of 72, forward 76 -> 79).
+template <int DH, int LD, typename T>
+__device__ inline void load_tiles(const T* __restrict__ a, int lda, const T* __restrict__ b, int ldb, int r0, int rows, float scale,
+                                  float (*A)[LD], float (*B)[LD]) {
+  constexpr int N = BT * DH / NT, U = N % 4 == 0 ? 4 : N;
+  static_assert(BT * DH % NT == 0, "whole trips");
+#pragma unroll 1
+  for (int it = 0; it < N; it += U) {
+    float x[U], y[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int idx = (it + u) * NT + threadIdx.x, r = min(r0 + idx / DH, rows - 1);
+      x[u] = Elt<T>::to_f(a[(size_t)r * lda + idx % DH]);
+      y[u] = Elt<T>::to_f(b[(size_t)r * ldb + idx % DH]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int idx = (it + u) * NT + threadIdx.x, r = idx / DH;
+      A[r][idx % DH] = r0 + r < rows ? x[u] * scale : 0.f;
+      B[r][idx % DH] = r0 + r < rows ? y[u] : 0.f;
+    }
+  }
+}
+
 template <typename T, int DH, bool CAUSAL, int P>
 __global__ __launch_bounds__(NT) void attn_fwd_generic_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int ld, int ldk,
@@ -52,18 +80,13 @@ __global__ __launch_bounds__(NT) void attn_fwd_generic_kernel(
   float qr[DH], acc[DH];
 #pragma unroll
   for (int c = 0; c < DH; ++c) {
-    qr[c] = active ? Elt<T>::to_f(q[(size_t)(lo + qi) * ld + hq * DH + c]) * scale : 0.f;
+    qr[c] = Elt<T>::to_f(q[(size_t)(lo + min(qi, L - 1)) * ld + hq * DH + c]) * scale;
     acc[c] = 0.f;
   }
   float m = -INFINITY, l = 0.f;
   const int kend = CAUSAL ? min(Lk, q0 + BQ) : Lk;
   for (int k0 = 0; k0 < kend; k0 += BT) {
-    for (int idx = threadIdx.x; idx < BT * DH; idx += NT) {
-      int r = idx / DH, c = idx % DH, kj = k0 + r;
-      bool ok = kj < Lk;
-      Ks[r][c] = ok ? Elt<T>::to_f(k[(size_t)(lok + kj) * ldk + hk * DH + c]) : 0.f;
-      Vs[r][c] = ok ? Elt<T>::to_f(v[(size_t)(lok + kj) * ldk + hk * DH + c]) : 0.f;
-    }
+    load_tiles<DH>(k + (size_t)lok * ldk + hk * DH, ldk, v + (size_t)lok * ldk + hk * DH, ldk, k0, Lk, 1.f, Ks, Vs);
     __syncthreads();
     if (active) {
       float sc[BT / P];
@@ -134,28 +157,22 @@ __device__ inline void dq_rows(
   const int part = threadIdx.x % P;
   const int qi = q0 + threadIdx.x / P;
   const bool active = qi < L;
+  const int qrow = min(qi, L - 1);
   float qr[DH], dor[DH], acc[DH];
 #pragma unroll
   for (int c = 0; c < DH; ++c) {
-    qr[c] = active ? Elt<T>::to_f(q[(size_t)(lo + qi) * ld + hq * DH + c]) * scale : 0.f;
-    dor[c] = active ? Elt<T>::to_f(d_o[(size_t)(lo + qi) * ldo + hq * DH + c]) : 0.f;
+    qr[c] = Elt<T>::to_f(q[(size_t)(lo + qrow) * ld + hq * DH + c]) * scale;
+    dor[c] = Elt<T>::to_f(d_o[(size_t)(lo + qrow) * ldo + hq * DH + c]);
     acc[c] = 0.f;
   }
-  const float my_lse = active ? lse[(size_t)hq * Ttot + lo + qi] : 0.f;
+  const float my_lse = lse[(size_t)hq * Ttot + lo + qrow];
   float my_delta = 0.f;
-  if (active) {
 #pragma unroll
-    for (int c = 0; c < DH; ++c) my_delta = fmaf(Elt<T>::to_f(o[(size_t)(lo + qi) * ldo + hq * DH + c]), dor[c], my_delta);
-    if (part == 0) delta[(size_t)hq * Ttot + lo + qi] = my_delta;
-  }
+  for (int c = 0; c < DH; ++c) my_delta = fmaf(Elt<T>::to_f(o[(size_t)(lo + qrow) * ldo + hq * DH + c]), dor[c], my_delta);
+  if (active && part == 0) delta[(size_t)hq * Ttot + lo + qi] = my_delta;
   const int kend = CAUSAL ? min(Lk, q0 + BQ) : Lk;
   for (int k0 = 0; k0 < kend; k0 += BT) {
-    for (int idx = threadIdx.x; idx < BT * DH; idx += NT) {
-      int r = idx / DH, c = idx % DH, kj = k0 + r;
-      bool ok = kj < Lk;
-      Ks[r][c] = ok ? Elt<T>::to_f(k[(size_t)(lok + kj) * ldk + hk * DH + c]) : 0.f;
-      Vs[r][c] = ok ? Elt<T>::to_f(v[(size_t)(lok + kj) * ldk + hk * DH + c]) : 0.f;
-    }
+    load_tiles<DH>(k + (size_t)lok * ldk + hk * DH, ldk, v + (size_t)lok * ldk + hk * DH, ldk, k0, Lk, 1.f, Ks, Vs);
     __syncthreads();
     if (active) {
       for (int j = part; j < BT; j += P) {
@@ -217,23 +234,19 @@ __device__ inline void dkdv_rows(
   const int part = threadIdx.x % P;
   const int kj = kb + threadIdx.x / P;
   const bool active = kj < Lk;
+  const int krow = min(kj, Lk - 1);
   float kr[DH], vr[DH], dkr[DH], dvr[DH];
 #pragma unroll
   for (int c = 0; c < DH; ++c) {
-    kr[c] = active ? Elt<T>::to_f(k[(size_t)(lok + kj) * ldk + hk * DH + c]) : 0.f;
-    vr[c] = active ? Elt<T>::to_f(v[(size_t)(lok + kj) * ldk + hk * DH + c]) : 0.f;
+    kr[c] = Elt<T>::to_f(k[(size_t)(lok + krow) * ldk + hk * DH + c]);
+    vr[c] = Elt<T>::to_f(v[(size_t)(lok + krow) * ldk + hk * DH + c]);
     dkr[c] = 0.f; dvr[c] = 0.f;
   }
   const int qstart = CAUSAL ? (kb / BT) * BT : 0;
   for (int g = 0; g < group; ++g) {
     const int hq = hk * group + g;
     for (int q0 = qstart; q0 < L; q0 += BT) {
-      for (int idx = threadIdx.x; idx < BT * DH; idx += NT) {
-        int r = idx / DH, c = idx % DH, qi = q0 + r;
-        bool ok = qi < L;
-        Qs[r][c] = ok ? Elt<T>::to_f(q[(size_t)(lo + qi) * ld + hq * DH + c]) * scale : 0.f;
-        Ds[r][c] = ok ? Elt<T>::to_f(d_o[(size_t)(lo + qi) * ldo + hq * DH + c]) : 0.f;
-      }
+      load_tiles<DH>(q + (size_t)lo * ld + hq * DH, ld, d_o + (size_t)lo * ldo + hq * DH, ldo, q0, L, scale, Qs, Ds);
       if (threadIdx.x < BT) {
         int qi = q0 + threadIdx.x;
         bool ok = qi < L;
@@ -313,8 +326,8 @@ __global__ __launch_bounds__(NT) void attn_bwd_joint_generic_kernel(
 }
 
 // Lanes per row.  One lane walks every row of the other side by itself, so few rows leave the chip
-// idle behind long chains; eight lanes per row cost eight times the tile loads.  Measured forward /
-// backward, us, P = 1 -> 8: head size 16, 1000 rows x 4 heads 223 / 658 -> 60 / 147; head size 64, 1024 x 16
+// idle behind long chains; eight lanes per row cost eight times the tile loads.  Measured (with a branch around
+// every load, see load_tiles) forward / backward, us, P = 1 -> 8: head size 16, 1000 rows x 4 heads 223 / 658 -> 60 / 147; head size 64, 1024 x 16
 // 453 / 1242 -> 187 / 737, 2048 x 16 463 / 1246 -> 370 / 1458, 4096 x 16 473 / 1290 -> 564 / 2914; head size 128,
 // 1024 x 8 999 / 28283 -> 249 / 5010, 4096 x 8 2164 -> 2894.
 bool eight_lanes(long rows, int heads, int dh) { return rows * heads <= 16384 && rows * heads * dh <= (1L << 20); }
