@@ -37,6 +37,7 @@ Dims make_dims(const bm_block_desc& c, int T, int S) {
 }
 
 struct Saved {
+  int32_t* tok_seq;   // sequence of every token (RoPE, adaLN)
   float *stats1, *stats2, *lse, *mod;
   char *qkv, *o, *x1, *up, *attn, *m;
   MoeTables moe;      // routing tables of the forward pass
@@ -75,12 +76,12 @@ Saved layout_saved(const Dims& m, void* base) {
     s.attn = a.take<char>(T * m.d * m.es);
     s.m = a.take<char>(T * m.d * m.es);
   }
+  s.tok_seq = a.take<int32_t>(T * sizeof(int32_t));
   s.bytes = a.off;
   return s;
 }
 
 struct FwdScratch {
-  int32_t* tok_seq;
   char *h, *a, *sc;
   float* logits;          // experts: [T, E]
   char *xp, *moe_ws;      // experts: [cap, d] routed inputs; layout scratch
@@ -92,7 +93,6 @@ FwdScratch layout_fwd(const Dims& m, int dtype, void* base) {
   Arena a(base);
   FwdScratch s;
   const size_t T = m.T;
-  s.tok_seq = a.take<int32_t>(T * sizeof(int32_t));
   s.h = a.take<char>(T * m.d * m.es);
   s.a = a.take<char>((m.E > 0 ? (size_t)m.cap : T) * m.F * m.es);
   s.sc = m.ada ? a.take<char>((size_t)m.S * m.d * m.es) : nullptr;
@@ -109,8 +109,8 @@ FwdScratch layout_fwd(const Dims& m, int dtype, void* base) {
 }
 
 struct BwdScratch {
-  int32_t* tok_seq;
   char *a, *dup, *da, *h, *dh, *dx1, *dgated, *d_o, *dqkv;
+  char *seg_ws[2];                                // adaLN: the per-sequence sums of the two gates
   char *attn_ws, *norm_ws, *norm1_ws, *gemm_ws;   // norm1_ws: norm 1, whose column sums wait for the same flush as norm 2's
   char *colsum_ws[5];                             // up, down, o, qkv, ada: the column sums of the bias gradients
   size_t attn_ws_bytes, gemm_ws_bytes;
@@ -142,7 +142,6 @@ BwdScratch layout_bwd(const Dims& m, int dtype, void* base) {
   Arena a(base);
   BwdScratch s;
   const size_t T = m.T;
-  s.tok_seq = a.take<int32_t>(T * sizeof(int32_t));
   const size_t R = m.E > 0 ? (size_t)m.cap : T;     // rows of the FFN activations
   s.a = a.take<char>(R * m.F * m.es);
   s.dup = a.take<char>(R * m.UP * m.es);
@@ -155,7 +154,8 @@ BwdScratch layout_bwd(const Dims& m, int dtype, void* base) {
   s.attn_ws_bytes = attention_backward_scratch_bytes(m.Hq, m.Hkv, m.dh, m.T);
   s.attn_ws = a.take<char>(s.attn_ws_bytes);
   s.norm_ws = a.take<char>(norm_backward_scratch_bytes(m.T, m.d));
-  s.norm1_ws = m.ada ? s.norm_ws : a.take<char>(norm_backward_scratch_bytes(m.T, m.d));
+  s.norm1_ws = a.take<char>(norm_backward_scratch_bytes(m.T, m.d));
+  for (int i = 0; i < 2; ++i) s.seg_ws[i] = m.ada ? a.take<char>(segment_scratch_bytes()) : nullptr;
   const int widths[5] = {m.F, m.d, m.d, m.QKV, 6 * m.d};
   for (int i = 0; i < 5; ++i) s.colsum_ws[i] = a.take<char>(colsum_scratch_bytes(m.T, widths[i]));
   s.gemm_ws_bytes = max_gemm_tn_scratch(m, dtype) + gemm_rows_scratch_bytes(m.T, m.d, dtype);   // gemm_nn_tn: both at once
@@ -347,8 +347,8 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
   hipStream_t st = (hipStream_t)hip_stream;
   const int dt = c.dtype;
 
-  // token -> sequence map: read by the rotary embedding and by the per-sequence modulation only
-  if (c.rope || m.ada) BM_RETURN_IF(launch_tok_seq(cu_dev, S, T, ws.tok_seq, st));
+  // token -> sequence map: read by the rotary embedding and by the per-sequence modulation only, here and in the backward
+  if (c.rope || m.ada) BM_RETURN_IF(launch_tok_seq(cu_dev, S, T, sv.tok_seq, st));
   if (m.ada) {
     BM_RETURN_IF(silu_forward(dt, cond, ws.sc, (long)S * m.d, st));
     GemmEpilogue e; e.bias = w->b_ada; e.out_fp32 = 1;
@@ -356,7 +356,7 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
                       ws.gemm_ws, ws.gemm_ws_bytes, st));
   }
   // attention half
-  { ProfScope _p(PROF_NORM, 2.0 * T * m.d * (double)m.es, st); BM_RETURN_IF(norm_forward(norm_args(c, m, 1, w, sv.mod, ws.tok_seq), x, ws.h, sv.stats1, 1, st)); }
+  { ProfScope _p(PROF_NORM, 2.0 * T * m.d * (double)m.es, st); BM_RETURN_IF(norm_forward(norm_args(c, m, 1, w, sv.mod, sv.tok_seq), x, ws.h, sv.stats1, 1, st)); }
   {
     GemmEpilogue e; e.bias = c.linear_bias ? w->b_qkv : nullptr;
     BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.QKV, m.d, ws.h, m.d, w->w_qkv, m.d, sv.qkv, m.QKV, e,
@@ -364,7 +364,7 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
   }
   if (c.rope)
     { ProfScope _p(PROF_ELEMENTWISE, 2.0 * T * (m.Hq + m.Hkv) * m.dh * (double)m.es, st); BM_RETURN_IF(rope_inplace(dt, sv.qkv, m.QKV, T, m.Hq + m.Hkv, m.dh, c.rope_base, cu_dev,
-                              ws.tok_seq, 1.0f, st)); }
+                              sv.tok_seq, 1.0f, st)); }
   AttnArgs at;
   at.dtype = dt; at.causal = c.mask == BM_MASK_CAUSAL; at.Hq = m.Hq; at.Hkv = m.Hkv; at.dh = m.dh;
   at.q = sv.qkv; at.k = sv.qkv + (size_t)m.QD * m.es; at.v = sv.qkv + (size_t)(m.QD + m.Hkv * m.dh) * m.es;
@@ -376,7 +376,7 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
     if (m.ada) {
       BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.d, m.QD, sv.o, m.QD, w->w_o, m.QD, sv.attn, m.d, e,
                         ws.gemm_ws, ws.gemm_ws_bytes, st));
-      { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(gate_mul(dt, sv.attn, sv.mod + 2 * m.d, 6 * m.d, ws.tok_seq, x, sv.x1, T, m.d, st)); }
+      { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(gate_mul(dt, sv.attn, sv.mod + 2 * m.d, 6 * m.d, sv.tok_seq, x, sv.x1, T, m.d, st)); }
     } else {
       e.residual = x;
       BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.d, m.QD, sv.o, m.QD, w->w_o, m.QD, sv.x1, m.d, e,
@@ -384,7 +384,7 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
     }
   }
   // MLP half
-  { ProfScope _p(PROF_NORM, 2.0 * T * m.d * (double)m.es, st); BM_RETURN_IF(norm_forward(norm_args(c, m, 2, w, sv.mod, ws.tok_seq), sv.x1, ws.h, sv.stats2, 1, st)); }
+  { ProfScope _p(PROF_NORM, 2.0 * T * m.d * (double)m.es, st); BM_RETURN_IF(norm_forward(norm_args(c, m, 2, w, sv.mod, sv.tok_seq), sv.x1, ws.h, sv.stats2, 1, st)); }
   if (m.E > 0) {
     // mixture of experts: route, sort the routed rows by expert, run the expert FFNs as
     // grouped GEMMs over the sorted rows, and sum each token's k gated outputs
@@ -434,7 +434,7 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
     if (m.ada) {
       BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.d, m.F, ws.a, m.F, w->w_down, m.F, sv.m, m.d, e,
                         ws.gemm_ws, ws.gemm_ws_bytes, st));
-      { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(gate_mul(dt, sv.m, sv.mod + 5 * m.d, 6 * m.d, ws.tok_seq, sv.x1, y, T, m.d, st)); }
+      { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(gate_mul(dt, sv.m, sv.mod + 5 * m.d, 6 * m.d, sv.tok_seq, sv.x1, y, T, m.d, st)); }
     } else {
       e.residual = sv.x1;
       BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.d, m.F, ws.a, m.F, w->w_down, m.F, y, m.d, e,
@@ -471,9 +471,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   const GemmEpilogue none;
   const int d = m.d;
   ColumnSums sums;
-
-  // token -> sequence map: read by the rotary embedding and by the per-sequence modulation only
-  if (c.rope || m.ada) BM_RETURN_IF(launch_tok_seq(cu_dev, S, T, ws.tok_seq, st));
+  SegmentSums segments;
 
   // ---- y = x1 + [g2 *] m,  m = a W_down^T + b_down
   const void* dm = dy;
@@ -481,7 +479,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     // gate gradient (per-sequence sum of dy * m) and the gated upstream gradient in one pass over dy
     { ProfScope _p(PROF_ELEMENTWISE, 3.0 * T * d * (double)m.es, st);
       BM_RETURN_IF(segment_gate(dt, dy, sv.m, sv.mod + 5 * d, 6 * d, ws.dgated, cu_dev, S, d, ws.dmod + 5 * d, 6 * d,
-                                ws.norm_ws, st)); }
+                                ws.seg_ws[0], &segments, st)); }
     dm = ws.dgated;
   }
   const bool fused_sums = c.linear_bias && !m.ada;
@@ -517,10 +515,10 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
       BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.E, ws.dlogits, m.E, w->w_router, d, ws.dh, d, e, ws.gemm_ws,
                         ws.gemm_ws_bytes, st));
     }
-    NormArgs n2 = norm_args(c, m, 2, w, sv.mod, ws.tok_seq);
+    NormArgs n2 = norm_args(c, m, 2, w, sv.mod, sv.tok_seq);
     { ProfScope _p(PROF_NORM, 5.0 * T * m.d * (double)m.es, st);
       BM_RETURN_IF(norm_backward(n2, sv.x1, sv.stats2, ws.dh, dy, ws.dx1, ws.h, (float*)grads->norm2_g,
-                                 (float*)grads->norm2_b, nullptr, nullptr, ws.dmod, cu_dev, S, ws.norm_ws, &sums, st)); }
+                                 (float*)grads->norm2_b, nullptr, nullptr, ws.dmod, cu_dev, S, ws.norm_ws, &sums, nullptr, st)); }
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(moe_gather(dt, ws.h, sv.moe, 0, ws.xp, d, T, st)); }
     g.c_stride = (long)m.UP * d;
     BM_RETURN_IF(gemm_grouped(GEMM_TN, dt, m.UP, d, m.cap, ws.dup, m.UP, ws.xp, d, grads->w_up, d, g, st));
@@ -549,12 +547,12 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   if (c.linear_bias && !fused_sums)
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, dm, d, T, d, (float*)grads->b_down, ws.colsum_ws[1], &sums, st)); }
 
-  NormArgs n2 = norm_args(c, m, 2, w, sv.mod, ws.tok_seq);
+  NormArgs n2 = norm_args(c, m, 2, w, sv.mod, sv.tok_seq);
   { ProfScope _p(PROF_NORM, 5.0 * T * m.d * (double)m.es, st);
     BM_RETURN_IF(norm_backward(n2, sv.x1, sv.stats2, ws.dh, dy, ws.dx1, ws.h, (float*)grads->norm2_g,
                                (float*)grads->norm2_b, fused_sums ? (float*)grads->b_down : nullptr,
                                fused_sums ? (float*)grads->b_o : nullptr, ws.dmod, cu_dev, S,
-                               ws.norm_ws, &sums, st)); }
+                               ws.norm_ws, &sums, &segments, st)); }
   }
 
   // ---- x1 = x + [g1 *] attn,  attn = o W_o^T + b_o
@@ -562,7 +560,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   if (m.ada) {
     { ProfScope _p(PROF_ELEMENTWISE, 3.0 * T * d * (double)m.es, st);
       BM_RETURN_IF(segment_gate(dt, ws.dx1, sv.attn, sv.mod + 2 * d, 6 * d, ws.dgated, cu_dev, S, d, ws.dmod + 2 * d,
-                                6 * d, ws.norm_ws, st)); }
+                                6 * d, ws.seg_ws[1], &segments, st)); }
     dattn = ws.dgated;
   }
   // (the weight gradient of the output projection is small: it shares a launch with the one of
@@ -592,10 +590,10 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
                                   ws.attn_ws_bytes, st));
   if (c.rope)
     { ProfScope _p(PROF_ELEMENTWISE, 2.0 * T * (m.Hq + m.Hkv) * m.dh * (double)m.es, st); BM_RETURN_IF(rope_inplace(dt, ws.dqkv, m.QKV, T, m.Hq + m.Hkv, m.dh, c.rope_base, cu_dev,
-                              ws.tok_seq, -1.0f, st)); }
+                              sv.tok_seq, -1.0f, st)); }
 
   // ---- qkv = h W_qkv^T + b_qkv,  h = N1(x)
-  NormArgs n1 = norm_args(c, m, 1, w, sv.mod, ws.tok_seq);
+  NormArgs n1 = norm_args(c, m, 1, w, sv.mod, sv.tok_seq);
   if (c.linear_bias)
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, ws.dqkv, m.QKV, T, m.QKV, (float*)grads->b_qkv, ws.colsum_ws[3], &sums, st)); }
   // the weight gradient of the output projection goes with the input gradient here, where that is one launch, or with
@@ -615,7 +613,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   { ProfScope _p(PROF_NORM, 5.0 * T * m.d * (double)m.es, st);
     BM_RETURN_IF(norm_backward(n1, x, sv.stats1, ws.dh, ws.dx1, dx, ws.h, (float*)grads->norm1_g,
                                (float*)grads->norm1_b, nullptr, nullptr, ws.dmod, cu_dev, S,
-                               ws.norm1_ws, &sums, st)); }
+                               ws.norm1_ws, &sums, &segments, st)); }
   if (o_done)
     BM_RETURN_IF(gemm(GEMM_TN, dt, m.QKV, d, T, ws.dqkv, m.QKV, ws.h, d, grads->w_qkv, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
   else
@@ -624,17 +622,14 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
 
   // ---- adaLN: mod = silu(cond) W_ada^T + b_ada
   if (m.ada) {
-    const long nmod = (long)S * 6 * d;
-    BM_RETURN_IF(cast_from_f32(dt, ws.dmod, ws.dmod_e, nmod, st));
-    BM_RETURN_IF(silu_forward(dt, cond, ws.sc, (long)S * d, st));
+    const int S8 = (int)align_up(S, 8);
+    BM_RETURN_IF(flush_segment_sums(&segments, st));
+    BM_RETURN_IF(ada_operands(dt, ws.dmod, cond, ws.dmod_e, ws.dmod_t, ws.sc, ws.dsc, S, S8, 6 * d, d, st));
     BM_RETURN_IF(gemm(GEMM_TN, dt, 6 * d, d, S, ws.dmod_e, 6 * d, ws.sc, d, grads->w_ada, d, none,
                       ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, ws.dmod_e, 6 * d, S, 6 * d, (float*)grads->b_ada, ws.colsum_ws[4], &sums, st)); }
     // d silu(cond) = dmod W_ada: a few rows against a long reduction, so it runs as a weight-gradient
     // style product on the transposed dmod (rows padded to 8), whose k range splits over the chip
-    const int S8 = (int)align_up(S, 8);
-    BM_RETURN_IF(cast_transpose_from_f32(dt, ws.dmod, ws.dmod_t, S, 6 * d, S8, st));
-    BM_RETURN_IF(fill_zero(ws.dsc, (size_t)S8 * d * sizeof(float), st));
     BM_RETURN_IF(gemm(GEMM_TN, dt, S8, d, 6 * d, ws.dmod_t, S8, w->w_ada, d, ws.dsc, d, none, ws.gemm_ws,
                       ws.gemm_ws_bytes, st));
     BM_RETURN_IF(silu_backward_f32(dt, cond, ws.dsc, dcond, (long)S * d, st));

@@ -303,6 +303,20 @@ struct ColumnSums {
 };
 bm_status flush_column_sums(ColumnSums* sums, hipStream_t st);
 
+// The same for the per-sequence sums of the adaLN gradients whose rows are shared by several workgroups: the flush writes
+// out[s, off_q + n] = sum over r < parts of partial[s, r, q, n].
+struct SegmentSums {
+  static constexpr int MAX = 8;
+  struct Target { const float* partial; float* out; int S, parts, planes, N, ld_out, off0, off1; } target[MAX];
+  int count = 0;
+  bm_status add(const Target& t) {
+    if (count == MAX) { set_error("more than %d segment sums in one list", MAX); return BM_ERR_INVALID_ARG; }
+    target[count++] = t;
+    return BM_OK;
+  }
+};
+bm_status flush_segment_sums(SegmentSums* sums, hipStream_t st);
+
 struct NormArgs {
   int dtype, kind;          // BM_NORM_*
   int T, d;
@@ -318,11 +332,12 @@ bm_status norm_forward(const NormArgs& a, const void* x, void* h, float* stats, 
                        hipStream_t st);
 size_t norm_backward_scratch_bytes(int T, int d);
 // dx = dres + dN/dx(dh);  dgamma/dbeta fp32 += (LayerNorm/RMSNorm) and dsum_res/dsum_out when `sums` is flushed
-// adaLN: dmod[:, shift_off..] = segsum(dh), dmod[:, scale_off..] = segsum(dh * xhat) (overwrite, fp32)
+// adaLN: dmod[:, shift_off..] = segsum(dh), dmod[:, scale_off..] = segsum(dh * xhat) (overwrite, fp32), whole when
+// `segments` is flushed (null otherwise)
 bm_status norm_backward(const NormArgs& a, const void* x, const float* stats, const void* dh,
                         const void* dres, void* dx, void* h_out, float* dgamma, float* dbeta,
                         float* dsum_res, float* dsum_out, float* dmod, const int32_t* cu_dev, int S,
-                        void* scratch, ColumnSums* sums, hipStream_t st);
+                        void* scratch, ColumnSums* sums, SegmentSums* segments, hipStream_t st);
 
 // RoPE in place on the first n_heads heads of each row of qkv; sign=+1 fwd, -1 bwd
 bm_status rope_inplace(int dtype, void* qkv, int ld, int T, int n_heads, int dh, float base,
@@ -337,11 +352,11 @@ size_t colsum_scratch_bytes(int T, int N);
 bm_status colsum_accumulate(int dtype, const void* a, int lda, int T, int N, float* out,
                             void* scratch, ColumnSums* sums, hipStream_t st);
 // out[s, n] = sum_{t in s} a[t,n] * b[t,n] (fp32, overwrite) and, when gated != nullptr,
-// gated[t, n] = a[t, n] * gate[s, n]; rows are N wide; scratch: segment_scratch_bytes()
+// gated[t, n] = a[t, n] * gate[s, n]; rows are N wide; scratch: segment_scratch_bytes(), until `sums` is flushed
 size_t segment_scratch_bytes();
 bm_status segment_gate(int dtype, const void* a, const void* b, const float* gate, int ld_gate, void* gated,
                        const int32_t* cu_dev, int S, int N, float* out, int ld_out, void* scratch,
-                       hipStream_t st);
+                       SegmentSums* sums, hipStream_t st);
 // out[t, n] = (residual ? residual[t,n] : 0) + a[t, n] * gate[tok_seq[t], n]
 bm_status gate_mul(int dtype, const void* a, const float* gate, int ld_gate,
                    const int32_t* tok_seq, const void* residual, void* out, int T, int N,
@@ -350,11 +365,10 @@ bm_status gate_mul(int dtype, const void* a, const float* gate, int ld_gate,
 bm_status silu_forward(int dtype, const void* in, void* out, long n, hipStream_t st);
 bm_status silu_backward_f32(int dtype, const void* in, const float* g, void* out, long n,
                             hipStream_t st);
-// fp32 -> storage dtype
-bm_status cast_from_f32(int dtype, const float* in, void* out, long n, hipStream_t st);
-// fp32 [rows, cols] -> storage dtype [cols, ld_out], columns rows..ld_out-1 zero
-bm_status cast_transpose_from_f32(int dtype, const float* in, void* out, int rows, int cols, int ld_out,
-                                  hipStream_t st);
+// operands of the adaLN projection's backward from dmod [S, W] and cond [S, d]: e, t (transposed, S8 >= S columns), sc (nullable)
+// and the cleared accumulator acc [S8, d]; W >= d
+bm_status ada_operands(int dtype, const float* dmod, const void* cond, void* e, void* t, void* sc, float* acc, int S, int S8,
+                       int W, int d, hipStream_t st);
 
 }  // namespace bm
 

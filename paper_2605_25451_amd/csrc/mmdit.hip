@@ -114,7 +114,8 @@ struct MBwd {
   char *d_o_j, *dqkv_j;         // joint order
   char *a, *dup, *da, *h, *dh, *dgated, *d_o, *dqkv, *dmod_e, *dmod_t, *sc;   // per-stream temporaries, reused
   float* gain_part[2];          // per stream: per-workgroup partial sums of the q/k gain gradients
-  char *attn_ws, *norm_ws, *gemm_ws;
+  char *attn_ws, *norm1_ws, *gemm_ws;
+  char *norm_ws[2], *seg_ws[2][2];   // per stream: norm 2, the sums of both gates
   char *colsum_ws[2][5];        // per stream: the column sums of the up, down, o, qkv and ada bias gradients
   size_t attn_ws_bytes, gemm_ws_bytes;
   size_t bytes;
@@ -162,7 +163,11 @@ MBwd layout_bwd(const MDims& m, int dtype, void* base) {
   for (int s = 0; s < 2; ++s) w.gain_part[s] = a.take<float>((size_t)QKN_BLOCKS * 2 * m.dh * sizeof(float));
   w.attn_ws_bytes = attention_backward_scratch_bytes(m.H, m.H, m.dh, m.T);
   w.attn_ws = a.take<char>(w.attn_ws_bytes);
-  w.norm_ws = a.take<char>(norm_backward_scratch_bytes(m.Tmax, m.d));
+  w.norm1_ws = a.take<char>(norm_backward_scratch_bytes(m.Tmax, m.d));
+  for (int s = 0; s < 2; ++s) {
+    w.norm_ws[s] = a.take<char>(norm_backward_scratch_bytes(m.Tmax, m.d));
+    for (int i = 0; i < 2; ++i) w.seg_ws[s][i] = a.take<char>(segment_scratch_bytes());
+  }
   const int widths[5] = {m.F, m.d, m.d, m.QKV, 6 * m.d};
   for (int s = 0; s < 2; ++s)
     for (int i = 0; i < 5; ++i) w.colsum_ws[s][i] = a.take<char>(colsum_scratch_bytes(m.Tmax, widths[i]));
@@ -614,6 +619,7 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
   const int dt = c.dtype, d = m.d;
   const GemmEpilogue none;
   ColumnSums sums;
+  SegmentSums segments;
 
   BM_RETURN_IF(build_tables(m, ws.tb, cu_dev, st));
 
@@ -628,7 +634,7 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
     // y = x1 + g2 * m,  m = a W_down^T + b_down
     { ProfScope _p(PROF_ELEMENTWISE, 3.0 * T * d * (double)m.es, st);
       BM_RETURN_IF(segment_gate(dt, dy[s], q.m, q.mod + 5 * d, 6 * d, ws.dgated, cu_dev[s], S, d, dmod + 5 * d, 6 * d,
-                                ws.norm_ws, st)); }
+                                ws.seg_ws[s][0], &segments, st)); }
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.F, d, ws.dgated, d, p.w_down, m.F, ws.da, m.F, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, (double)T * 4.0 * m.F * (double)m.es, st);
       BM_RETURN_IF(act_backward(dt, BM_ACT_GELU, q.up, ws.da, ws.dup, ws.a, (float*)g.b_up, ws.colsum_ws[s][0], T, m.F, &sums, st)); }
@@ -640,12 +646,13 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.F, ws.dup, m.F, p.w_up, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_NORM, 5.0 * T * d * (double)m.es, st);
       BM_RETURN_IF(norm_backward(ada_norm_args(c, T, 2, q.mod, tok), q.x1, q.stats2, ws.dh, dy[s], ws.dx1[s], ws.h,
-                                 nullptr, nullptr, nullptr, nullptr, dmod, cu_dev[s], S, ws.norm_ws, &sums, st)); }
+                                 nullptr, nullptr, nullptr, nullptr, dmod, cu_dev[s], S, ws.norm_ws[s], &sums, &segments,
+                                 st)); }
     BM_RETURN_IF(gemm(GEMM_TN, dt, m.F, d, T, ws.dup, m.F, ws.h, d, g.w_up, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     // x1 = x + g1 * attn,  attn = o W_o^T + b_o
     { ProfScope _p(PROF_ELEMENTWISE, 3.0 * T * d * (double)m.es, st);
       BM_RETURN_IF(segment_gate(dt, ws.dx1[s], q.attn, q.mod + 2 * d, 6 * d, ws.dgated, cu_dev[s], S, d, dmod + 2 * d,
-                                6 * d, ws.norm_ws, st)); }
+                                6 * d, ws.seg_ws[s][1], &segments, st)); }
     BM_RETURN_IF(gemm(GEMM_TN, dt, d, m.QD, T, ws.dgated, d, q.o, m.QD, g.w_o, m.QD, none, ws.gemm_ws,
                       ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
@@ -661,7 +668,6 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
                                   ws.dqkv_j + (size_t)2 * m.QD * m.es, m.QKV, ws.attn_ws, ws.attn_ws_bytes, st));
 
   // ---- per stream: back out of the joint order, qkv projection, norm 1, modulation
-  BM_RETURN_IF(silu_forward(dt, cond, ws.sc, (long)S * d, st));
   for (int s = 0; s < 2; ++s) {
     const bm_block_params& p = w->stream[s];
     const bm_block_params& g = grads->stream[s];
@@ -682,20 +688,21 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.QKV, ws.dqkv, m.QKV, p.w_qkv, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_NORM, 5.0 * T * d * (double)m.es, st);
       BM_RETURN_IF(norm_backward(ada_norm_args(c, T, 1, q.mod, tok), x[s], q.stats1, ws.dh, ws.dx1[s], dx[s], ws.h,
-                                 nullptr, nullptr, nullptr, nullptr, dmod, cu_dev[s], S, ws.norm_ws, &sums, st)); }
+                                 nullptr, nullptr, nullptr, nullptr, dmod, cu_dev[s], S, ws.norm1_ws, &sums, &segments,
+                                 st)); }
     BM_RETURN_IF(gemm(GEMM_TN, dt, m.QKV, d, T, ws.dqkv, m.QKV, ws.h, d, g.w_qkv, d, none, ws.gemm_ws,
                       ws.gemm_ws_bytes, st));
     // mod = silu(cond) W_ada^T + b_ada
-    BM_RETURN_IF(cast_from_f32(dt, dmod, ws.dmod_e, (long)S * 6 * d, st));
+    const int S8 = (int)align_up(S, 8);
+    BM_RETURN_IF(flush_segment_sums(&segments, st));
+    // (both streams read the same conditioning rows: silu(cond) is there already)
+    BM_RETURN_IF(ada_operands(dt, dmod, cond, ws.dmod_e, ws.dmod_t, s == 0 ? ws.sc : nullptr, ws.dsc[s], S, S8, 6 * d, d, st));
     BM_RETURN_IF(gemm(GEMM_TN, dt, 6 * d, d, S, ws.dmod_e, 6 * d, ws.sc, d, g.w_ada, d, none, ws.gemm_ws,
                       ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
       BM_RETURN_IF(colsum_accumulate(dt, ws.dmod_e, 6 * d, S, 6 * d, (float*)g.b_ada, ws.colsum_ws[s][4], &sums, st)); }
     // d silu(cond) = dmod W_ada as a weight-gradient style product on the transposed dmod
     // (few rows, long reduction: the k range splits over the chip)
-    const int S8 = (int)align_up(S, 8);
-    BM_RETURN_IF(cast_transpose_from_f32(dt, dmod, ws.dmod_t, S, 6 * d, S8, st));
-    BM_RETURN_IF(fill_zero(ws.dsc[s], (size_t)S8 * d * sizeof(float), st));
     BM_RETURN_IF(gemm(GEMM_TN, dt, S8, d, 6 * d, ws.dmod_t, S8, p.w_ada, d, ws.dsc[s], d, none, ws.gemm_ws,
                       ws.gemm_ws_bytes, st));
   }
