@@ -406,6 +406,8 @@ constexpr int NUM_CU = 256;
 // Measured on 527 shapes (blocks of 1024 to 4096 columns at 300 to 16384 rows, shapes drawn over the same range, and
 // gradients of 8 to 128 conditions; every tile, splits 1-32): the plan it picks takes 1.2 % longer than the best one on
 // average, 23 % at worst.
+// (Fitted before the slices of 256x256 weight gradients were cut along k and their C went through whole lines, which took
+// 1-7 % off those tiles: the choices are the same, on a few shapes near a line 256x256 would now win by that much.)
 struct TileKind { int bm, bn, slots; double t_min, t_full, power, t_fixed, t_cut, f_tn, hidden; };
 constexpr TileKind TILE_KINDS[] = {
   {256, 256, NUM_CU, 0.87, 1.36, 0.6, 5.5, 3.6, 1.13, 0.23},
