@@ -186,7 +186,9 @@ bm_status bm_attention_forward(int32_t dtype, int32_t mask, int32_t Hq, int32_t 
                                void* o, float* lse, void* hip_stream);
 
 /* Gradients dq,dk,dv (rows of one packed buffer with row stride ld_dqkv, fully
- * overwritten) from do:[T,Hq*dh], the forward's q,k,v,o and lse.
+ * overwritten) from do:[T,Hq*dh], the forward's q,k,v,o and lse.  The gradients lie apart from the
+ * inputs, except that (in rows of the same stride) dq, dk or dv may take the place of o; dq that of q or do in bf16
+ * with head sizes of 64, 72 and 128; and dk and dv those of k and v in fp32.  Such a call takes a launch more.
  * scratch: bm_attention_backward_scratch_bytes(...) bytes. */
 size_t    bm_attention_backward_scratch_bytes(int32_t Hq, int32_t Hkv, int32_t dh, int32_t T);
 bm_status bm_attention_backward(int32_t dtype, int32_t mask, int32_t Hq, int32_t Hkv, int32_t dh,

@@ -51,7 +51,8 @@ size_t bm_cp_attention_backward_scratch_bytes(int32_t n_q_heads, int32_t n_kv_he
                                               int32_t Tq, int32_t Tk);
 
 /* dq_part [Tq, ld_dq], dk_part / dv_part [Tk, ld_dkv] are overwritten (rows of sequences that are
- * empty on the other side become zero). */
+ * empty on the other side become zero).  They lie apart from the inputs, but for what bm_attention_backward
+ * allows. */
 bm_status bm_cp_attention_backward(int32_t dtype, int32_t mask, int32_t n_q_heads, int32_t n_kv_heads,
                                    int32_t head_dim, const void* q, int32_t ld_q, const void* k,
                                    const void* v, int32_t ld_kv, const void* o, const void* d_o,

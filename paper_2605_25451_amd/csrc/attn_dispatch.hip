@@ -39,9 +39,29 @@ size_t attention_backward_scratch_bytes(int Hq, int Hkv, int dh, int T) {
   return attention_backward_scratch_bytes(Hq, Hkv, dh, T, T);
 }
 
-bm_status attention_backward(const AttnArgs& a, const void* o, const void* d_o, const float* lse,
+// does a gradient's memory, first to last row, touch an input's?
+static bool in_place(const AttnArgs& a, const void* o, const void* d_o, const void* dq, const void* dk, const void* dv,
+                     int ld_dqkv) {
+  struct Span { uintptr_t begin, end; };
+  auto span = [&](const void* p, int rows, int ld, int heads) {
+    const uintptr_t b = reinterpret_cast<uintptr_t>(p);
+    return Span{b, rows > 0 ? b + ((size_t)(rows - 1) * ld + (size_t)heads * a.dh) * elt_size(a.dtype) : b};
+  };
+  const int wide = a.Hq * a.dh, ld_dkv = a.ld_dkv ? a.ld_dkv : ld_dqkv;
+  const Span in[] = {span(a.q, a.T, a.ld_qkv, a.Hq), span(o, a.T, wide, a.Hq), span(d_o, a.T, wide, a.Hq),
+                     span(a.k, a.kv_T(), a.kv_ld(), a.Hkv), span(a.v, a.kv_T(), a.kv_ld(), a.Hkv)};
+  const Span out[] = {span(dq, a.T, ld_dqkv, a.Hq), span(dk, a.kv_T(), ld_dkv, a.Hkv), span(dv, a.kv_T(), ld_dkv, a.Hkv)};
+  for (const Span& x : in)
+    for (const Span& y : out)
+      if (x.begin < y.end && y.begin < x.end) return true;
+  return false;
+}
+
+bm_status attention_backward(const AttnArgs& args, const void* o, const void* d_o, const float* lse,
                              void* dq, void* dk, void* dv, int ld_dqkv, void* scratch,
                              size_t scratch_bytes, hipStream_t st) {
+  AttnArgs a = args;
+  a.in_place = in_place(a, o, d_o, dq, dk, dv, ld_dqkv);
   ProfScope prof(PROF_ATTN_BWD, 10.0 * a.dh * a.Hq * attn_pairs(a), st);
   if (attention_mfma_supported(a))
     return attention_backward_mfma(a, o, d_o, lse, dq, dk, dv, ld_dqkv, scratch, scratch_bytes, st);

@@ -355,7 +355,7 @@ bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const fl
   const int ldo = a.Hq * a.dh;
   const float scale = 1.0f / sqrtf((float)a.dh);
   if constexpr (DH <= 64)
-    if (a.T > 0 && a.kv_T() > 0 && eight_lanes(a.T, a.Hq, DH) && eight_lanes(a.kv_T(), a.Hkv, DH)) {
+    if (!a.in_place && a.T > 0 && a.kv_T() > 0 && eight_lanes(a.T, a.Hq, DH) && eight_lanes(a.kv_T(), a.Hkv, DH)) {
       const int longest = a.max_seqlen > a.kv_max_len() ? a.max_seqlen : a.kv_max_len();
       hipLaunchKernelGGL((attn_bwd_joint_generic_kernel<T, DH, CAUSAL>), dim3(cdiv(longest, NT / 8), a.S, a.Hkv + a.Hq), dim3(NT),
                          0, st, (const T*)a.q, (const T*)a.k, (const T*)a.v, a.ld_qkv, a.kv_ld(), (const T*)o, (const T*)d_o,

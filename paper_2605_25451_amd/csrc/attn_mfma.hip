@@ -2063,7 +2063,7 @@ bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const fl
   const int Tk = a.kv_T();
   const int kv_wgs = ktiles * a.Hkv * gsplit;
   const int qtiles = count_tiles(a.cu_host, a.S, query_rows);
-  int q_wgs = qtiles * (DH > 64 && !alt ? (a.Hq + 1) / 2 : a.Hq);
+  const int q_wgs = qtiles * (DH > 64 && !alt ? (a.Hq + 1) / 2 : a.Hq);
   // One launch or two?  One, where dQ takes the same workgroups anyway: head size 64, and 256-row query tiles (60 packs of
   // 1500 to 36000 tokens: 57 faster, 3 % on average, 12 % at best, the slowest -1.6 %).  The 128 rows of two heads side by
   // side are slower than two workgroups on a CU, so that is for packs whose workgroups all run at once, or nearly so where a
@@ -2074,36 +2074,48 @@ bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const fl
   // 147 both; causal 1100 (288 of dK/dV, 432) 91 -> 82; 1500 (384, 576) 168 -> 170, causal 117 -> 121.
   const int both = kv_wgs + q_wgs;
   const int at_once = wide ? NUM_CU * 5 / 4 : a.causal && qtiles >= 3 * a.S ? NUM_CU * 3 / 2 : NUM_CU;
-  const bool together = DH <= 64 || alt || both <= at_once || (kv_wgs > NUM_CU && both <= 2 * NUM_CU);
-  if (!together) q_wgs = 0;
+  const bool same_wgs = DH <= 64 || alt;
+  const bool together = !a.in_place && (same_wgs || both <= at_once || (kv_wgs > NUM_CU && both <= 2 * NUM_CU));
   // a key tile runs as long as its sequence has queries, a query tile as long as it has keys
   const SeqOrder ord_kv = make_seq_order(a.kv_cu_host(), a.cu_host, a.S, key_rows, !a.causal);
   const SeqOrder ord_q = make_seq_order(a.cu_host, a.kv_cu_host(), a.S, query_rows, !a.causal);
-  auto launch = [&](auto kern, int threads) {
-    hipLaunchKernelGGL(kern, dim3(kv_wgs + q_wgs), dim3(threads), 0, st, (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v,
-                       a.ld_qkv, a.kv_ld(), (const bf16_t*)d_o, ldo, lse, (const float*)delta, a.cu_dev, a.kv_cu_dev(), a.S,
-                       (bf16_t*)dq, ldd, (bf16_t*)dk, (bf16_t*)dv, ldd_kv, a.T, Tk, a.Hkv, a.Hq / a.Hkv, scale, sl2, gsplit, part,
-                       kv_wgs, ord_kv, ord_q);
-  };
-  if (kv_wgs + q_wgs > 0) {
+  // workgroups of dK/dV, then of dQ
+  auto launch = [&](int kv, int q) {
+    auto go = [&](auto kern, int threads) {
+      hipLaunchKernelGGL(kern, dim3(kv + q), dim3(threads), 0, st, (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v,
+                         a.ld_qkv, a.kv_ld(), (const bf16_t*)d_o, ldo, lse, (const float*)delta, a.cu_dev, a.kv_cu_dev(), a.S,
+                         (bf16_t*)dq, ldd, (bf16_t*)dk, (bf16_t*)dv, ldd_kv, a.T, Tk, a.Hkv, a.Hq / a.Hkv, scale, sl2, gsplit, part,
+                         kv, ord_kv, ord_q);
+    };
+    if (kv + q == 0) return;
     if constexpr (DH <= 64) {
-      launch(a.causal ? fa_bwd_joint_kernel<DH, true> : fa_bwd_joint_kernel<DH, false>, 256);
+      go(a.causal ? fa_bwd_joint_kernel<DH, true> : fa_bwd_joint_kernel<DH, false>, 256);
     } else if constexpr (DH == 128) {
-      if (wide && alt) launch(a.causal ? fa_bwd_joint512_kernel<DH, true, true, true> : fa_bwd_joint512_kernel<DH, false, true, true>, 512);
-      else if (wide) launch(a.causal ? fa_bwd_joint512_kernel<DH, true, true, false> : fa_bwd_joint512_kernel<DH, false, true, false>, 512);
-      else if (alt) launch(a.causal ? fa_bwd_joint512_kernel<DH, true, false, true> : fa_bwd_joint512_kernel<DH, false, false, true>, 512);
-      else launch(a.causal ? fa_bwd_joint512_kernel<DH, true, false, false> : fa_bwd_joint512_kernel<DH, false, false, false>, 512);
+      if (wide && alt) go(a.causal ? fa_bwd_joint512_kernel<DH, true, true, true> : fa_bwd_joint512_kernel<DH, false, true, true>, 512);
+      else if (wide) go(a.causal ? fa_bwd_joint512_kernel<DH, true, true, false> : fa_bwd_joint512_kernel<DH, false, true, false>, 512);
+      else if (alt) go(a.causal ? fa_bwd_joint512_kernel<DH, true, false, true> : fa_bwd_joint512_kernel<DH, false, false, true>, 512);
+      else go(a.causal ? fa_bwd_joint512_kernel<DH, true, false, false> : fa_bwd_joint512_kernel<DH, false, false, false>, 512);
     } else {
-      launch(a.causal ? fa_bwd_joint512_kernel<DH, true, false, false> : fa_bwd_joint512_kernel<DH, false, false, false>, 512);
+      go(a.causal ? fa_bwd_joint512_kernel<DH, true, false, false> : fa_bwd_joint512_kernel<DH, false, false, false>, 512);
+    }
+  };
+  if (together) {
+    launch(kv_wgs, q_wgs);
+  } else {
+    launch(kv_wgs, 0);
+    if constexpr (DH > 64) {
+      if (alt) {
+        launch(0, q_wgs);
+      } else if (qtiles > 0) {
+        auto kern = a.causal ? fa_bwd_dq_kernel<DH, true> : fa_bwd_dq_kernel<DH, false>;
+        hipLaunchKernelGGL(kern, dim3(qtiles * a.Hq), dim3(256), 0, st, (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v,
+                           a.ld_qkv, a.kv_ld(), (const bf16_t*)d_o, ldo, lse, (const float*)delta, a.cu_dev, a.kv_cu_dev(), a.S,
+                           (bf16_t*)dq, ldd, a.T, a.Hq, a.Hq / a.Hkv, scale, sl2, ord_q);
+      }
+    } else {
+      launch(0, q_wgs);
     }
   }
-  if constexpr (DH > 64)
-    if (!together && qtiles > 0) {
-      auto kern = a.causal ? fa_bwd_dq_kernel<DH, true> : fa_bwd_dq_kernel<DH, false>;
-      hipLaunchKernelGGL(kern, dim3(qtiles * a.Hq), dim3(256), 0, st, (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v,
-                         a.ld_qkv, a.kv_ld(), (const bf16_t*)d_o, ldo, lse, (const float*)delta, a.cu_dev, a.kv_cu_dev(), a.S,
-                         (bf16_t*)dq, ldd, a.T, a.Hq, a.Hq / a.Hkv, scale, sl2, ord_q);
-    }
   if (gsplit > 1 && ktiles > 0) {
     const long n4 = (long)Tk * a.Hkv * a.dh / 4;
     hipLaunchKernelGGL(fa_dkdv_reduce_kernel, dim3(cdiv(n4, 256)), dim3(256), 0, st, part, gsplit, Tk,

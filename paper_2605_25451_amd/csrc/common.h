@@ -266,6 +266,9 @@ struct AttnArgs {
   const int32_t* cu_k_dev = nullptr;
   const int32_t* cu_k_host = nullptr;
   int Tk = 0, ld_kv = 0, max_klen = 0, ld_dkv = 0;
+  // backward: a gradient lies in memory that an input takes up (set by attention_backward).  dK/dV and dQ tiles then do not
+  // run side by side: either would read what the other has already overwritten.
+  bool in_place = false;
   const int32_t* kv_cu_dev() const { return cu_k_dev ? cu_k_dev : cu_dev; }
   const int32_t* kv_cu_host() const { return cu_k_dev ? cu_k_host : cu_host; }
   int kv_T() const { return cu_k_dev ? Tk : T; }
