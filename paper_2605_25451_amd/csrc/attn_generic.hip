@@ -37,11 +37,12 @@ template <int P> __device__ inline float lanes_max(float v) {
 // loads carry no condition (their rows are clamped), so that several are in flight: with a branch around every
 // load, here and for a lane's own row, each waited for the one before it.  us, forward / backward: 300 rows, 4 heads of 16, 22 /
 // 25 -> 15 / 21; 16 heads of 64 70 / 156 -> 43 / 93; 5 x 200 rows, 8 heads of 128 335 / 803 -> 156 / 373; 4 x 1024 rows, 4 heads of 32,
-// 183 / 542 -> 84 / 279 (5 x 200, 8 heads of 72, forward 76 -> 79).
+// 183 / 542 -> 84 / 279.  More than four pairs at once cost registers: all 18 of head size 72 left the forward one wavefront
+// per SIMD, and it was slower than with the branches (16 x 1024 rows 923 -> 1045); by sixes 768, 5 x 200 rows of 8 heads 74 -> 40 / 326 -> 190.
 template <int DH, int LD, typename T>
 __device__ inline void load_tiles(const T* __restrict__ a, int lda, const T* __restrict__ b, int ldb, int r0, int rows, float scale,
                                   float (*A)[LD], float (*B)[LD]) {
-  constexpr int N = BT * DH / NT, U = N % 4 == 0 ? 4 : N;
+  constexpr int N = BT * DH / NT, U = N % 4 == 0 ? 4 : N % 6 == 0 ? 6 : N;
   static_assert(BT * DH % NT == 0, "whole trips");
 #pragma unroll 1
   for (int it = 0; it < N; it += U) {
