@@ -1,5 +1,5 @@
 """Registers and stack of the built kernels, read from the library's own code objects (no GPU): what a change of the source
-can lose without any result changing."""
+can lose without any result changing.  A SIMD has 512 registers per lane for its wavefronts."""
 import functools
 import struct
 
@@ -42,6 +42,22 @@ def metadata(elf):
             p = body + (desc + 3) // 4 * 4
 
 
+def functions(elf):
+    """Names of the functions in the symbol table."""
+    sections, = struct.unpack_from("<Q", elf, 0x28)
+    entry, count = struct.unpack_from("<HH", elf, 0x3A)
+    heads = [struct.unpack_from("<IIQQQQIIQQ", elf, sections + i * entry) for i in range(count)]
+    found = set()
+    for _, kind, _, _, offset, size, link, _, _, step in heads:
+        if kind == 2:                                        # SHT_SYMTAB
+            strings = heads[link][4]
+            for p in range(offset, offset + size, step):
+                name, info = struct.unpack_from("<IB", elf, p)
+                if info & 15 == 2:                           # STT_FUNC
+                    found.add(elf[strings + name:elf.index(b"\0", strings + name)])
+    return found
+
+
 @functools.lru_cache(None)
 def kernels():
     with open(build.LIB, "rb") as f:
@@ -57,8 +73,23 @@ def registers(part):
     return max(got)
 
 
+def test_kernels_call_no_function():
+    """What several kernels share is inlined: a call holds the registers of the largest caller and moves its rows through
+    the stack."""
+    with open(build.LIB, "rb") as f:
+        blob = f.read()
+    for elf in code_objects(blob):
+        names = {n.encode() for k in metadata(elf) for n in (k[".name"],)}
+        assert functions(elf) <= names, functions(elf) - names
+
+
+@pytest.mark.parametrize("storage", ["f", "DF16b"])
+@pytest.mark.parametrize("causal", [0, 1])
+def test_dq_of_head_size_32_keeps_two_wavefronts_per_simd(storage, causal):
+    assert registers(GENERIC % ("dq", storage, 32, causal) + "Li8E") <= 256
+
+
 @pytest.mark.parametrize("storage", ["f", "DF16b"])
 @pytest.mark.parametrize("causal", [0, 1])
 def test_attention_of_head_size_72_keeps_two_wavefronts_per_simd(storage, causal):
-    # 512 registers per lane and SIMD
     assert registers(GENERIC % ("fwd", storage, 72, causal)) <= 256
