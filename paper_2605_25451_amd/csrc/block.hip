@@ -18,7 +18,8 @@ namespace {
 struct Dims {
   int T, S, d, Hq, Hkv, dh, F, QKV, UP, QD;
   size_t es;   // element size
-  bool ada;
+  int norm;
+  bool ada, bias, positions;   // positions: kernels ask for the sequence of a token
   int E, k, cap;   // mixture of experts: experts, choices per token, padded row capacity (0 = dense)
 };
 
@@ -30,7 +31,10 @@ Dims make_dims(const bm_block_desc& c, int T, int S) {
   m.QKV = (m.Hq + 2 * m.Hkv) * m.dh;
   m.UP = m.F * (c.act == BM_ACT_SWIGLU ? 2 : 1);
   m.es = elt_size(c.dtype);
+  m.norm = c.norm;
   m.ada = c.norm == BM_NORM_ADALN;
+  m.bias = c.linear_bias != 0;
+  m.positions = m.ada || c.rope != 0;
   m.E = c.n_experts; m.k = c.top_k;
   m.cap = m.E > 0 ? moe_row_capacity(T, m.E, m.k) : 0;
   return m;
@@ -76,7 +80,7 @@ Saved layout_saved(const Dims& m, void* base) {
     s.attn = a.take<char>(T * m.d * m.es);
     s.m = a.take<char>(T * m.d * m.es);
   }
-  s.tok_seq = a.take<int32_t>(T * sizeof(int32_t));
+  s.tok_seq = m.positions ? a.take<int32_t>(T * sizeof(int32_t)) : nullptr;
   s.bytes = a.off;
   return s;
 }
@@ -153,12 +157,14 @@ BwdScratch layout_bwd(const Dims& m, int dtype, void* base) {
   s.dqkv = a.take<char>(T * m.QKV * m.es);
   s.attn_ws_bytes = attention_backward_scratch_bytes(m.Hq, m.Hkv, m.dh, m.T);
   s.attn_ws = a.take<char>(s.attn_ws_bytes);
-  s.norm_ws = a.take<char>(norm_backward_scratch_bytes(m.T, m.d));
-  s.norm1_ws = a.take<char>(norm_backward_scratch_bytes(m.T, m.d));
+  // without a gate in between, norm 2 also sums the columns of the down and output gradients
+  s.norm_ws = a.take<char>(norm_backward_scratch_bytes(m.norm, m.bias && !m.ada, m.T, m.d));
+  s.norm1_ws = a.take<char>(norm_backward_scratch_bytes(m.norm, false, m.T, m.d));
   for (int i = 0; i < 2; ++i) s.seg_ws[i] = m.ada ? a.take<char>(segment_scratch_bytes()) : nullptr;
-  const int widths[5] = {m.F, m.d, m.d, m.QKV, 6 * m.d};
-  for (int i = 0; i < 5; ++i) s.colsum_ws[i] = a.take<char>(colsum_scratch_bytes(m.T, widths[i]));
-  s.gemm_ws_bytes = max_gemm_tn_scratch(m, dtype) + gemm_rows_scratch_bytes(m.T, m.d, dtype);   // gemm_nn_tn: both at once
+  const int widths[5] = {m.bias ? m.F : 0, m.bias && m.ada ? m.d : 0, m.bias && m.ada ? m.d : 0, m.bias ? m.QKV : 0, m.ada ? 6 * m.d : 0};
+  for (int i = 0; i < 5; ++i) s.colsum_ws[i] = widths[i] ? a.take<char>(colsum_scratch_bytes(m.T, widths[i])) : nullptr;
+  const size_t tn = max_gemm_tn_scratch(m, dtype), rows = gemm_rows_scratch_bytes(m.T, m.d, dtype);
+  s.gemm_ws_bytes = std::max(std::max(tn, rows), gemm_nn_tn_scratch_bytes(rows, tn, dtype));
   s.gemm_ws = a.take<char>(s.gemm_ws_bytes);
   s.dyp = nullptr; s.xp = nullptr; s.dlogits = nullptr; s.dh2e = nullptr;
   if (m.E > 0) {
@@ -348,7 +354,7 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
   const int dt = c.dtype;
 
   // token -> sequence map: read by the rotary embedding and by the per-sequence modulation only, here and in the backward
-  if (c.rope || m.ada) BM_RETURN_IF(launch_tok_seq(cu_dev, S, T, sv.tok_seq, st));
+  if (m.positions) BM_RETURN_IF(launch_tok_seq(cu_dev, S, T, sv.tok_seq, st));
   if (m.ada) {
     BM_RETURN_IF(silu_forward(dt, cond, ws.sc, (long)S * m.d, st));
     GemmEpilogue e; e.bias = w->b_ada; e.out_fp32 = 1;
@@ -482,7 +488,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
                                 ws.seg_ws[0], &segments, st)); }
     dm = ws.dgated;
   }
-  const bool fused_sums = c.linear_bias && !m.ada;
+  const bool fused_sums = m.bias && !m.ada;
   if (m.E > 0) {
     // ---- mixture of experts (dm = dy: no gate sits on this branch)
     GemmGroups g;

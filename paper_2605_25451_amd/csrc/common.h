@@ -166,6 +166,8 @@ bm_status gemm_nn_tn(int dtype, const GemmCall& nn, const GemmCall& tn, void* sc
 // one launch, with its status in *rc; or false and nothing launched: separate launches are the better choice
 bool gemm_nn_tn_joint(int dtype, const GemmCall& nn, const GemmCall& tn, void* scratch, size_t scratch_bytes, hipStream_t st,
                       bm_status* rc);
+// room for both, given what either is given on its own
+size_t gemm_nn_tn_scratch_bytes(size_t nn, size_t tn, int dtype);
 bool gemm_mfma_nn_tn(const GemmCall& nn, const GemmCall& tn, void* scratch, size_t scratch_bytes, hipStream_t st, bm_status* rc);
 bool gemm_generic_nn_tn(int dtype, const GemmCall& nn, const GemmCall& tn, hipStream_t st, bm_status* rc);
 
@@ -333,7 +335,8 @@ struct NormArgs {
 // h = N(x); stats[2T] = (mean, rstd) written when write_stats
 bm_status norm_forward(const NormArgs& a, const void* x, void* h, float* stats, int write_stats,
                        hipStream_t st);
-size_t norm_backward_scratch_bytes(int T, int d);
+// sums: with dsum_res and dsum_out
+size_t norm_backward_scratch_bytes(int kind, bool sums, int T, int d);
 // dx = dres + dN/dx(dh);  dgamma/dbeta fp32 += (LayerNorm/RMSNorm) and dsum_res/dsum_out when `sums` is flushed
 // adaLN: dmod[:, shift_off..] = segsum(dh), dmod[:, scale_off..] = segsum(dh * xhat) (overwrite, fp32), whole when
 // `segments` is flushed (null otherwise)

@@ -556,8 +556,17 @@ static int norm_bwd_blocks(int T, int d) {
   return b < cap ? b : cap;
 }
 
-size_t norm_backward_scratch_bytes(int T, int d) {
-  return align_up((size_t)norm_bwd_blocks(T, d) * 4 * d * sizeof(float), 256) + segment_scratch_bytes();
+// partial rows per workgroup
+static int norm_bwd_rows(int kind, bool sums) {
+  return (kind == BM_NORM_LAYERNORM ? 2 : kind == BM_NORM_RMSNORM ? 1 : 0) + (sums ? 2 : 0);
+}
+
+static size_t norm_bwd_partial_bytes(int kind, bool sums, int T, int d) {
+  return align_up((size_t)norm_bwd_blocks(T, d) * norm_bwd_rows(kind, sums) * d * sizeof(float), 256);
+}
+
+size_t norm_backward_scratch_bytes(int kind, bool sums, int T, int d) {
+  return norm_bwd_partial_bytes(kind, sums, T, d) + (kind == BM_NORM_ADALN ? segment_scratch_bytes() : 0);
 }
 
 template <typename T, int KIND, bool SUMS>
@@ -618,7 +627,7 @@ bm_status norm_backward(const NormArgs& a, const void* x, const float* stats, co
     SegArgs p{};
     p.a = dh; p.b = x; p.stats = stats; p.cu = cu_dev; p.out = dmod; p.ld_out = a.ld_mod;
     p.off0 = a.shift_off; p.off1 = a.scale_off; p.rows = a.T; p.N = a.d;
-    char* seg_ws = (char*)scratch + align_up((size_t)nb * 4 * a.d * sizeof(float), 256);
+    char* seg_ws = (char*)scratch + norm_bwd_partial_bytes(a.kind, sums, a.T, a.d);
     BM_RETURN_IF(seg_launch<1>(a.dtype, p, S, seg_ws, segments, st));
   }
   int np = 0;

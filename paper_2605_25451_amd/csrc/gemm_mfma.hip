@@ -722,6 +722,9 @@ bool joint_plan(const GemmCall& nn, const GemmCall& tn, size_t scratch_bytes, Pl
   return found;
 }
 
+// all partial tiles of such a grid
+constexpr size_t JOINT_PARTIAL_BYTES = (size_t)TILE_KINDS[3].slots * 128 * 128 * sizeof(float) + 256;
+
 GemmParams plain_params(const GemmCall& g, const Plan& pl, float* partial) {
   GemmParams p;
   p.A = (const bf16_t*)g.A; p.B = (const bf16_t*)g.B; p.C = g.C; p.bias = nullptr; p.residual = nullptr;
@@ -751,6 +754,10 @@ bm_status launch_joint(const GemmParams& nn, const GemmParams& tn, hipStream_t s
 }
 
 }  // namespace
+
+size_t gemm_nn_tn_scratch_bytes(size_t nn, size_t tn, int dtype) {
+  return dtype == BM_DTYPE_BF16 ? std::min(nn + tn, JOINT_PARTIAL_BYTES) : 0;
+}
 
 bool gemm_mfma_nn_tn(const GemmCall& nn, const GemmCall& tn, void* scratch, size_t scratch_bytes, hipStream_t st,
                      bm_status* rc) {

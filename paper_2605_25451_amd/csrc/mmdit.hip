@@ -163,9 +163,9 @@ MBwd layout_bwd(const MDims& m, int dtype, void* base) {
   for (int s = 0; s < 2; ++s) w.gain_part[s] = a.take<float>((size_t)QKN_BLOCKS * 2 * m.dh * sizeof(float));
   w.attn_ws_bytes = attention_backward_scratch_bytes(m.H, m.H, m.dh, m.T);
   w.attn_ws = a.take<char>(w.attn_ws_bytes);
-  w.norm1_ws = a.take<char>(norm_backward_scratch_bytes(m.Tmax, m.d));
+  w.norm1_ws = a.take<char>(norm_backward_scratch_bytes(BM_NORM_ADALN, false, m.Tmax, m.d));
   for (int s = 0; s < 2; ++s) {
-    w.norm_ws[s] = a.take<char>(norm_backward_scratch_bytes(m.Tmax, m.d));
+    w.norm_ws[s] = a.take<char>(norm_backward_scratch_bytes(BM_NORM_ADALN, false, m.Tmax, m.d));
     for (int i = 0; i < 2; ++i) w.seg_ws[s][i] = a.take<char>(segment_scratch_bytes());
   }
   const int widths[5] = {m.F, m.d, m.d, m.QKV, 6 * m.d};
