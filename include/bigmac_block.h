@@ -279,6 +279,15 @@ bm_status bm_probe_gemm_plan(int32_t layout, int32_t M, int32_t N, int32_t K, si
 bm_status bm_probe_attention_plan(int32_t mask, int32_t Hq, int32_t Hkv, int32_t dh, const int32_t* cu_q_host,
                                   const int32_t* cu_k_host, int32_t S, int32_t* fwd_rows /* host */,
                                   int32_t* dq_rows /* host */, int32_t* dkdv_rows /* host */);
+/* ... and its backward behind the row sums: 1 where the dK/dV and dQ tiles share a launch, 2 where they do not, and the
+ * workgroups of each; 0 as above. */
+bm_status bm_probe_attention_backward_plan(int32_t mask, int32_t Hq, int32_t Hkv, int32_t dh, const int32_t* cu_q_host,
+                                           const int32_t* cu_k_host, int32_t S, int32_t* launches /* host */,
+                                           int32_t* dkdv_wgs /* host */, int32_t* dq_wgs /* host */);
+/* The products of a dense block's backward that may share a launch (host only).  k_ranges[2 i], k_ranges[2 i + 1]: the k ranges of the
+ * input gradient and of the weight gradient of pair i -- 0: up and down projection, 1: output and up, 2: QKV and output -- or
+ * 0, 0 where they are launched apart. */
+bm_status bm_probe_block_backward_plan(const bm_block_desc* desc, int32_t T, int32_t S, int32_t* k_ranges /* host [6] */);
 
 /* ---- nested schedule (host only; Sec. 3.1 and the BuildSchedule figure) ------------ */
 

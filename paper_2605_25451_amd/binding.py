@@ -160,6 +160,10 @@ def lib() -> C.CDLL:
         l.bm_probe_gemm_plan.restype = C.c_int
         l.bm_probe_attention_plan.argtypes = [i32] * 4 + [vp, vp, i32, pi32, pi32, pi32]
         l.bm_probe_attention_plan.restype = C.c_int
+        l.bm_probe_attention_backward_plan.argtypes = l.bm_probe_attention_plan.argtypes
+        l.bm_probe_attention_backward_plan.restype = C.c_int
+        l.bm_probe_block_backward_plan.argtypes = [C.POINTER(BlockDesc), i32, i32, pi32]
+        l.bm_probe_block_backward_plan.restype = C.c_int
         l.bm_probe_read.restype = C.c_int
         l.bm_probe_fill.restype = C.c_int
         l.bm_probe_mfma.restype = C.c_int
@@ -497,14 +501,29 @@ def probe_gemm_plan(layout, M, N, K, scratch_bytes=None):
     return m.value, n.value, r.value
 
 
-def probe_attention_plan(mask, Hq, Hkv, dh, cu_q_host, cu_k_host=None):
-    """Rows per workgroup of the forward, dQ and dK/dV kernels."""
+def _probe_attention(fn, mask, Hq, Hkv, dh, cu_q_host, cu_k_host):
     q = _host_cu(cu_q_host)
     k = None if cu_k_host is None else _host_cu(cu_k_host)
-    f, d, w = C.c_int32(), C.c_int32(), C.c_int32()
-    _check(lib().bm_probe_attention_plan(mask, Hq, Hkv, dh, q.ctypes.data, None if k is None else k.ctypes.data, len(q) - 1,
-                                         C.byref(f), C.byref(d), C.byref(w)))
-    return f.value, d.value, w.value
+    out = [C.c_int32() for _ in range(3)]
+    _check(fn(mask, Hq, Hkv, dh, q.ctypes.data, None if k is None else k.ctypes.data, len(q) - 1, *map(C.byref, out)))
+    return tuple(v.value for v in out)
+
+
+def probe_attention_plan(mask, Hq, Hkv, dh, cu_q_host, cu_k_host=None):
+    """Rows per workgroup of the forward, dQ and dK/dV kernels."""
+    return _probe_attention(lib().bm_probe_attention_plan, mask, Hq, Hkv, dh, cu_q_host, cu_k_host)
+
+
+def probe_attention_backward_plan(mask, Hq, Hkv, dh, cu_q_host, cu_k_host=None):
+    """(launches of dK/dV and dQ, workgroups of dK/dV, workgroups of dQ)."""
+    return _probe_attention(lib().bm_probe_attention_backward_plan, mask, Hq, Hkv, dh, cu_q_host, cu_k_host)
+
+
+def probe_block_backward_plan(desc: BlockDesc, T, S):
+    """Per pair of products that may share a launch: the k ranges of input and weight gradient, (0, 0) if launched apart."""
+    out = (C.c_int32 * 6)()
+    _check(lib().bm_probe_block_backward_plan(C.byref(desc), T, S, out))
+    return [(out[i], out[i + 1]) for i in (0, 2, 4)]
 
 
 def profile_begin():

@@ -115,6 +115,12 @@ bool gemm_nn_tn_joint(int dtype, const GemmCall& nn, const GemmCall& tn, void* s
                                 : gemm_generic_nn_tn(dtype, nn, tn, st, rc);
 }
 
+void gemm_nn_tn_ranges(int dtype, const GemmCall& nn, const GemmCall& tn, size_t scratch_bytes, int* nn_ranges, int* tn_ranges) {
+  *nn_ranges = *tn_ranges = 0;
+  if (dtype == BM_DTYPE_BF16) gemm_mfma_nn_tn_ranges(nn, tn, scratch_bytes, nn_ranges, tn_ranges);
+  else if (gemm_generic_nn_tn_shares(dtype, nn, tn)) *nn_ranges = *tn_ranges = 1;
+}
+
 bm_status gemm_nn_tn(int dtype, const GemmCall& nn, const GemmCall& tn, void* scratch, size_t scratch_bytes, hipStream_t st) {
   bm_status rc;
   if (gemm_nn_tn_joint(dtype, nn, tn, scratch, scratch_bytes, st, &rc)) return rc;

@@ -7,6 +7,7 @@ namespace bm {
 bool attention_mfma_supported(const AttnArgs& a);
 bm_status attention_forward_mfma(const AttnArgs& a, void* o, float* lse, hipStream_t st);
 void attention_mfma_plan(const AttnArgs& a, int* fwd_rows, int* dq_rows, int* dkdv_rows);
+void attention_mfma_backward_plan(const AttnArgs& a, int* launches, int* dkdv_wgs, int* dq_wgs);
 size_t attention_backward_mfma_scratch_bytes(int Hq, int Hkv, int dh, int Tq, int Tk);
 bm_status attention_backward_mfma(const AttnArgs& a, const void* o, const void* d_o, const float* lse,
                                   void* dq, void* dk, void* dv, int ld_dqkv, void* scratch,
@@ -72,19 +73,37 @@ bm_status attention_backward(const AttnArgs& args, const void* o, const void* d_
 
 using namespace bm;
 
+static bm_status probe_args(int32_t mask, int32_t Hq, int32_t Hkv, int32_t dh, const int32_t* cu_q_host, const int32_t* cu_k_host,
+                            int32_t S, AttnArgs* a) {
+  BM_ARG_CHECK(mask == 0 || mask == 1, "attention plan: mask %d", mask);
+  BM_ARG_CHECK(Hq > 0 && Hkv > 0 && dh > 0 && Hq % Hkv == 0, "attention plan: bad head counts %d/%d", Hq, Hkv);
+  BM_ARG_CHECK(S >= 1 && cu_q_host, "attention plan: NULL offsets or no sequence");
+  a->dtype = BM_DTYPE_BF16; a->causal = mask; a->Hq = Hq; a->Hkv = Hkv; a->dh = dh; a->S = S;
+  a->ld_qkv = (Hq + 2 * Hkv) * dh;
+  a->cu_host = cu_q_host; a->T = cu_q_host[S];
+  static const int32_t on_device = 0;               // only says that the keys have a packing of their own
+  if (cu_k_host) { a->cu_k_dev = &on_device; a->cu_k_host = cu_k_host; a->Tk = cu_k_host[S]; a->ld_kv = a->ld_qkv; }
+  return BM_OK;
+}
+
 extern "C" bm_status bm_probe_attention_plan(int32_t mask, int32_t Hq, int32_t Hkv, int32_t dh, const int32_t* cu_q_host,
                                              const int32_t* cu_k_host, int32_t S, int32_t* fwd_rows, int32_t* dq_rows,
                                              int32_t* dkdv_rows) {
-  BM_ARG_CHECK(mask == 0 || mask == 1, "bm_probe_attention_plan: mask %d", mask);
-  BM_ARG_CHECK(Hq > 0 && Hkv > 0 && dh > 0 && Hq % Hkv == 0, "bm_probe_attention_plan: bad head counts %d/%d", Hq, Hkv);
-  BM_ARG_CHECK(S >= 1 && cu_q_host && fwd_rows && dq_rows && dkdv_rows, "bm_probe_attention_plan: NULL pointer or no sequence");
+  BM_ARG_CHECK(fwd_rows && dq_rows && dkdv_rows, "bm_probe_attention_plan: NULL pointer");
   AttnArgs a{};
-  a.dtype = BM_DTYPE_BF16; a.causal = mask; a.Hq = Hq; a.Hkv = Hkv; a.dh = dh; a.S = S;
-  a.ld_qkv = (Hq + 2 * Hkv) * dh;
-  a.cu_host = cu_q_host; a.T = cu_q_host[S];
-  static const int32_t on_device = 0;               // only says that the keys have a packing of their own
-  if (cu_k_host) { a.cu_k_dev = &on_device; a.cu_k_host = cu_k_host; a.Tk = cu_k_host[S]; a.ld_kv = a.ld_qkv; }
+  BM_RETURN_IF(probe_args(mask, Hq, Hkv, dh, cu_q_host, cu_k_host, S, &a));
   *fwd_rows = *dq_rows = *dkdv_rows = 0;
   if (attention_mfma_supported(a)) attention_mfma_plan(a, fwd_rows, dq_rows, dkdv_rows);
+  return BM_OK;
+}
+
+extern "C" bm_status bm_probe_attention_backward_plan(int32_t mask, int32_t Hq, int32_t Hkv, int32_t dh, const int32_t* cu_q_host,
+                                                      const int32_t* cu_k_host, int32_t S, int32_t* launches,
+                                                      int32_t* dkdv_wgs, int32_t* dq_wgs) {
+  BM_ARG_CHECK(launches && dkdv_wgs && dq_wgs, "bm_probe_attention_backward_plan: NULL pointer");
+  AttnArgs a{};
+  BM_RETURN_IF(probe_args(mask, Hq, Hkv, dh, cu_q_host, cu_k_host, S, &a));
+  *launches = *dkdv_wgs = *dq_wgs = 0;
+  if (attention_mfma_supported(a)) attention_mfma_backward_plan(a, launches, dkdv_wgs, dq_wgs);
   return BM_OK;
 }

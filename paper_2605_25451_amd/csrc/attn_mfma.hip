@@ -1751,7 +1751,7 @@ __device__ inline void dq_tile(unsigned char* lds, int tid, int tile_id, int hq,
   }
 }
 
-// head sizes above 64, two workgroups per CU: packs whose dK/dV tiles alone fill the chip (see bwd_launch)
+// head sizes above 64, two workgroups per CU: packs whose dK/dV tiles alone fill the chip (see bwd_plan)
 template <int DH, bool CAUSAL>
 __global__ __launch_bounds__(256, 2) void fa_bwd_dq_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld,
@@ -2042,6 +2042,38 @@ bool dkdv_wide(const AttnArgs& a) {
   return wide >= 3 * NUM_CU || (!a.causal && wide <= NUM_CU && narrow > NUM_CU);
 }
 
+// What a backward pass launches behind delta: tiles, workgroups, and whether dK/dV and dQ share a grid.
+struct BwdPlan { bool wide, alt, together; int key_rows, query_rows, gsplit, kv_wgs, qtiles, q_wgs; };
+
+BwdPlan bwd_plan(const AttnArgs& a) {
+  BwdPlan p;
+  p.wide = a.dh == 128 && dkdv_wide(a);
+  p.alt = a.dh == 128 && queries_alternating(a);
+  p.key_rows = p.wide ? WIDE_KEYS : BK_KEYS;
+  p.query_rows = p.alt ? AQ : FQ;
+  const int ktiles = count_tiles(a.kv_cu_host(), a.S, p.key_rows);
+  p.gsplit = ktiles > 0 ? dkdv_group_split(ktiles, a.Hkv, a.Hq / a.Hkv) : 1;
+  p.kv_wgs = ktiles * a.Hkv * p.gsplit;
+  p.qtiles = count_tiles(a.cu_host, a.S, p.query_rows);
+  const bool same_wgs = a.dh <= 64 || p.alt;              // dQ takes the workgroups of dK/dV
+  p.q_wgs = p.qtiles * (same_wgs ? a.Hq : (a.Hq + 1) / 2);
+  // One launch or two?  One, where dQ takes the same workgroups anyway: head size 64, and 256-row query tiles (60 packs of
+  // 1500 to 36000 tokens: 57 faster, 3 % on average, 12 % at best, the slowest -1.6 %).  Where both parts fill whole rounds there is nothing to
+  // gain: 32 / 8 heads, 8192 queries and keys 3217 -> 3172, causal 1729 -> 1733; the four pairs of a rank 14668 -> 14612, in seven runs +1.0 %
+  // to -0.8 %.  The 128 rows of two heads side by
+  // side are slower than two workgroups on a CU, so that is for packs whose workgroups all run at once, or nearly so where a
+  // causal mask makes most of them short or the wide dK/dV ones are few and long, and for those whose dQ fits into what
+  // a second round of dK/dV leaves idle.
+  // Two launches -> one, us: 16 / 4 heads, 777 tokens (168 workgroups) 83 -> 55; 24 heads, 1100 tokens (324) 92 -> 103, causal
+  // 86 -> 61; 32 heads, 777 (336) 69 -> 80, causal 69 -> 48; causal 8 x 256 (384) 50 -> 52.5; wide 500 + 700 (320) 89 -> 78, 1300 (368)
+  // 147 both; causal 1100 (288 of dK/dV, 432) 91 -> 82; 1500 (384, 576) 168 -> 170, causal 117 -> 121.
+  const int both = p.kv_wgs + p.q_wgs;
+  const int at_once = p.wide ? NUM_CU * 5 / 4 : a.causal && p.qtiles >= 3 * a.S ? NUM_CU * 3 / 2 : NUM_CU;
+  p.together = !a.in_place && (same_wgs || both <= at_once || (p.kv_wgs > NUM_CU && both <= 2 * NUM_CU));
+  if (!p.together && !same_wgs) p.q_wgs = p.qtiles * a.Hq;   // a kernel of its own, two workgroups per CU
+  return p;
+}
+
 template <int DH>
 bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const float* lse, void* dq,
                      void* dk, void* dv, int ldd, float* delta, hipStream_t st) {
@@ -2053,32 +2085,14 @@ bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const fl
   if (n > 0)
     hipLaunchKernelGGL((fa_delta_kernel<DH>), dim3(cdiv(n * DeltaLanes<DH>::N, 256)), dim3(256), 0, st, (const bf16_t*)o,
                        (const bf16_t*)d_o, ldo, delta, a.T, a.Hq);
-  const bool wide = DH == 128 && dkdv_wide(a);
-  const int key_rows = wide ? WIDE_KEYS : BK_KEYS;
-  const bool alt = DH == 128 && queries_alternating(a);
-  const int query_rows = alt ? AQ : FQ;
-  const int ktiles = count_tiles(a.kv_cu_host(), a.S, key_rows);
-  const int gsplit = ktiles > 0 ? dkdv_group_split(ktiles, a.Hkv, a.Hq / a.Hkv) : 1;
+  const BwdPlan p = bwd_plan(a);
+  const bool wide = p.wide, alt = p.alt;
+  const int gsplit = p.gsplit;
   float* part = delta + align_up((size_t)a.Hq * a.T, 64);      // after the delta plane
   const int Tk = a.kv_T();
-  const int kv_wgs = ktiles * a.Hkv * gsplit;
-  const int qtiles = count_tiles(a.cu_host, a.S, query_rows);
-  const int q_wgs = qtiles * (DH > 64 && !alt ? (a.Hq + 1) / 2 : a.Hq);
-  // One launch or two?  One, where dQ takes the same workgroups anyway: head size 64, and 256-row query tiles (60 packs of
-  // 1500 to 36000 tokens: 57 faster, 3 % on average, 12 % at best, the slowest -1.6 %).  The 128 rows of two heads side by
-  // side are slower than two workgroups on a CU, so that is for packs whose workgroups all run at once, or nearly so where a
-  // causal mask makes most of them short or the wide dK/dV ones are few and long, and for those whose dQ fits into what
-  // a second round of dK/dV leaves idle.
-  // Two launches -> one, us: 16 / 4 heads, 777 tokens (168 workgroups) 83 -> 55; 24 heads, 1100 tokens (324) 92 -> 103, causal
-  // 86 -> 61; 32 heads, 777 (336) 69 -> 80, causal 69 -> 48; causal 8 x 256 (384) 50 -> 52.5; wide 500 + 700 (320) 89 -> 78, 1300 (368)
-  // 147 both; causal 1100 (288 of dK/dV, 432) 91 -> 82; 1500 (384, 576) 168 -> 170, causal 117 -> 121.
-  const int both = kv_wgs + q_wgs;
-  const int at_once = wide ? NUM_CU * 5 / 4 : a.causal && qtiles >= 3 * a.S ? NUM_CU * 3 / 2 : NUM_CU;
-  const bool same_wgs = DH <= 64 || alt;
-  const bool together = !a.in_place && (same_wgs || both <= at_once || (kv_wgs > NUM_CU && both <= 2 * NUM_CU));
   // a key tile runs as long as its sequence has queries, a query tile as long as it has keys
-  const SeqOrder ord_kv = make_seq_order(a.kv_cu_host(), a.cu_host, a.S, key_rows, !a.causal);
-  const SeqOrder ord_q = make_seq_order(a.cu_host, a.kv_cu_host(), a.S, query_rows, !a.causal);
+  const SeqOrder ord_kv = make_seq_order(a.kv_cu_host(), a.cu_host, a.S, p.key_rows, !a.causal);
+  const SeqOrder ord_q = make_seq_order(a.cu_host, a.kv_cu_host(), a.S, p.query_rows, !a.causal);
   // workgroups of dK/dV, then of dQ
   auto launch = [&](int kv, int q) {
     auto go = [&](auto kern, int threads) {
@@ -2099,24 +2113,24 @@ bm_status bwd_launch(const AttnArgs& a, const void* o, const void* d_o, const fl
       go(a.causal ? fa_bwd_joint512_kernel<DH, true, false, false> : fa_bwd_joint512_kernel<DH, false, false, false>, 512);
     }
   };
-  if (together) {
-    launch(kv_wgs, q_wgs);
+  if (p.together) {
+    launch(p.kv_wgs, p.q_wgs);
   } else {
-    launch(kv_wgs, 0);
-    if constexpr (DH > 64) {
-      if (alt) {
-        launch(0, q_wgs);
-      } else if (qtiles > 0) {
+    launch(p.kv_wgs, 0);
+    bool same_wgs = true;
+    if constexpr (DH > 64) same_wgs = alt;
+    if (same_wgs) {
+      launch(0, p.q_wgs);
+    } else if constexpr (DH > 64) {
+      if (p.q_wgs > 0) {
         auto kern = a.causal ? fa_bwd_dq_kernel<DH, true> : fa_bwd_dq_kernel<DH, false>;
-        hipLaunchKernelGGL(kern, dim3(qtiles * a.Hq), dim3(256), 0, st, (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v,
+        hipLaunchKernelGGL(kern, dim3(p.q_wgs), dim3(256), 0, st, (const bf16_t*)a.q, (const bf16_t*)a.k, (const bf16_t*)a.v,
                            a.ld_qkv, a.kv_ld(), (const bf16_t*)d_o, ldo, lse, (const float*)delta, a.cu_dev, a.kv_cu_dev(), a.S,
                            (bf16_t*)dq, ldd, a.T, a.Hq, a.Hq / a.Hkv, scale, sl2, ord_q);
       }
-    } else {
-      launch(0, q_wgs);
     }
   }
-  if (gsplit > 1 && ktiles > 0) {
+  if (gsplit > 1 && p.kv_wgs > 0) {
     const long n4 = (long)Tk * a.Hkv * a.dh / 4;
     hipLaunchKernelGGL(fa_dkdv_reduce_kernel, dim3(cdiv(n4, 256)), dim3(256), 0, st, part, gsplit, Tk,
                        a.Hkv * a.dh, (bf16_t*)dk, (bf16_t*)dv, ldd_kv);
@@ -2143,6 +2157,13 @@ void attention_mfma_plan(const AttnArgs& a, int* fwd_rows, int* dq_rows, int* dk
   *fwd_rows = alt ? AQ : FQ;
   *dq_rows = alt && a.dh == 128 ? AQ : FQ;
   *dkdv_rows = a.dh == 128 && dkdv_wide(a) ? WIDE_KEYS : BK_KEYS;
+}
+
+void attention_mfma_backward_plan(const AttnArgs& a, int* launches, int* dkdv_wgs, int* dq_wgs) {
+  const BwdPlan p = bwd_plan(a);
+  *launches = p.together ? 1 : 2;
+  *dkdv_wgs = p.kv_wgs;
+  *dq_wgs = p.q_wgs;
 }
 
 size_t attention_backward_mfma_scratch_bytes(int Hq, int Hkv, int dh, int Tq, int Tk) {

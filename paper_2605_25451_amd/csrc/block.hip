@@ -187,6 +187,10 @@ BwdScratch layout_bwd(const Dims& m, int dtype, void* base) {
   return s;
 }
 
+// C[M,N] = A[M,K] B[K,N] and C[M,N] += A[K,M]^T B[K,N] of contiguous rows
+GemmCall input_grad(int M, int N, int K, const void* A, const void* B, void* C) { return {M, N, K, A, K, B, N, C, N}; }
+GemmCall weight_grad(int M, int N, int K, const void* A, const void* B, void* C) { return {M, N, K, A, M, B, N, C, N}; }
+
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 bm_status check_desc(const bm_block_desc* c) {
@@ -546,8 +550,8 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
                                 c.linear_bias ? (float*)grads->b_up : nullptr, ws.colsum_ws[0], T, m.F, &sums, st)); }
   }
   // ---- up = h2 W_up^T + b_up,  h2 = N2(x1): its input gradient beside the weight gradient of the down projection
-  BM_RETURN_IF(gemm_nn_tn(dt, GemmCall{T, d, m.UP, ws.dup, m.UP, w->w_up, d, ws.dh, d},
-                          GemmCall{d, m.F, T, dm, d, ws.a, m.F, grads->w_down, m.F}, ws.gemm_ws, ws.gemm_ws_bytes, st));
+  BM_RETURN_IF(gemm_nn_tn(dt, input_grad(T, d, m.UP, ws.dup, w->w_up, ws.dh), weight_grad(d, m.F, T, dm, ws.a, grads->w_down),
+                          ws.gemm_ws, ws.gemm_ws_bytes, st));
   // bias gradients of the down and output projections are column sums of the two
   // gradients the norm backward below touches anyway (not so when a gate sits between)
   if (c.linear_bias && !fused_sums)
@@ -574,13 +578,12 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   if (c.linear_bias && !fused_sums)
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, dattn, d, T, d, (float*)grads->b_o, ws.colsum_ws[2], &sums, st)); }
   {
-    const GemmCall d_o{T, m.QD, d, dattn, d, w->w_o, m.QD, ws.d_o, m.QD};
+    const GemmCall d_o = input_grad(T, m.QD, d, dattn, w->w_o, ws.d_o);
     if (m.E > 0)
       BM_RETURN_IF(gemm(GEMM_NN, dt, d_o.M, d_o.N, d_o.K, d_o.A, d_o.lda, d_o.B, d_o.ldb, d_o.C, d_o.ldc, none, ws.gemm_ws,
                         ws.gemm_ws_bytes, st));
     else   // beside the weight gradient of the up projection, whose input ws.h holds until norm 1
-      BM_RETURN_IF(gemm_nn_tn(dt, d_o, GemmCall{m.UP, d, T, ws.dup, m.UP, ws.h, d, grads->w_up, d}, ws.gemm_ws,
-                              ws.gemm_ws_bytes, st));
+      BM_RETURN_IF(gemm_nn_tn(dt, d_o, weight_grad(m.UP, d, T, ws.dup, ws.h, grads->w_up), ws.gemm_ws, ws.gemm_ws_bytes, st));
   }
 
   // ---- attention
@@ -610,8 +613,8 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   bool o_done = false;
   if (!o_with_qkv) {
     bm_status rc;
-    o_done = gemm_nn_tn_joint(dt, GemmCall{T, d, m.QKV, ws.dqkv, m.QKV, w->w_qkv, d, ws.dh, d},
-                              GemmCall{d, m.QD, T, dattn, d, sv.o, m.QD, grads->w_o, m.QD}, ws.gemm_ws, ws.gemm_ws_bytes, st, &rc);
+    o_done = gemm_nn_tn_joint(dt, input_grad(T, d, m.QKV, ws.dqkv, w->w_qkv, ws.dh),
+                              weight_grad(d, m.QD, T, dattn, sv.o, grads->w_o), ws.gemm_ws, ws.gemm_ws_bytes, st, &rc);
     if (o_done) BM_RETURN_IF(rc);
   }
   if (!o_done)
@@ -641,5 +644,26 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     BM_RETURN_IF(silu_backward_f32(dt, cond, ws.dsc, dcond, (long)S * d, st));
   }
   { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(flush_column_sums(&sums, st)); }
+  return BM_OK;
+}
+
+extern "C" bm_status bm_probe_block_backward_plan(const bm_block_desc* desc, int32_t T, int32_t S, int32_t* k_ranges) {
+  BM_RETURN_IF(check_desc(desc));
+  BM_ARG_CHECK(T >= 1 && S >= 1 && S <= T && k_ranges, "bm_probe_block_backward_plan: bad T=%d S=%d or NULL output", T, S);
+  BM_RETURN_IF(check_extent(*desc, T, S));
+  if (desc->n_experts > 0) { set_error("bm_probe_block_backward_plan: a block of experts"); return BM_ERR_UNSUPPORTED; }
+  const Dims m = make_dims(*desc, T, S);
+  const int dt = desc->dtype, d = m.d;
+  const size_t bytes = layout_bwd(m, dt, nullptr).gemm_ws_bytes;
+  void* const none = nullptr;
+  gemm_nn_tn_ranges(dt, input_grad(T, d, m.UP, none, none, none), weight_grad(d, m.F, T, none, none, none), bytes, k_ranges, k_ranges + 1);
+  gemm_nn_tn_ranges(dt, input_grad(T, m.QD, d, none, none, none), weight_grad(m.UP, d, T, none, none, none), bytes, k_ranges + 2,
+                    k_ranges + 3);
+  k_ranges[4] = k_ranges[5] = 0;
+  void* const some = (void*)256;                       // a workspace that is there and aligned; nothing is launched
+  if (!gemm_tn_pair_shares_launch(dt, T, m.QKV, d, none, m.QKV, none, d, none, d, d, m.QD, none, d, none, m.QD, none, m.QD, some,
+                                  bytes, nullptr))
+    gemm_nn_tn_ranges(dt, input_grad(T, d, m.QKV, none, none, none), weight_grad(d, m.QD, T, none, none, none), bytes, k_ranges + 4,
+                      k_ranges + 5);
   return BM_OK;
 }

@@ -169,6 +169,10 @@ bool gemm_nn_tn_joint(int dtype, const GemmCall& nn, const GemmCall& tn, void* s
 // room for both, given what either is given on its own
 size_t gemm_nn_tn_scratch_bytes(size_t nn, size_t tn, int dtype);
 bool gemm_mfma_nn_tn(const GemmCall& nn, const GemmCall& tn, void* scratch, size_t scratch_bytes, hipStream_t st, bm_status* rc);
+bool gemm_generic_nn_tn_shares(int dtype, const GemmCall& nn, const GemmCall& tn);
+// the k ranges of either where they share a launch, else 0
+void gemm_nn_tn_ranges(int dtype, const GemmCall& nn, const GemmCall& tn, size_t scratch_bytes, int* nn_ranges, int* tn_ranges);
+bool gemm_mfma_nn_tn_ranges(const GemmCall& nn, const GemmCall& tn, size_t scratch_bytes, int* nn_ranges, int* tn_ranges);
 bool gemm_generic_nn_tn(int dtype, const GemmCall& nn, const GemmCall& tn, hipStream_t st, bm_status* rc);
 
 // Grouped GEMM for the mixture-of-experts FFN: the rows of the activation matrices are

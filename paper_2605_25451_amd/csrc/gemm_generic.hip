@@ -396,13 +396,18 @@ bm_status gemm_generic_grouped(int layout, int dtype, int M, int N, int K, const
   return launch_grouped<float>(layout, M, N, K, A, lda, B, ldb, C, ldc, gg, st);
 }
 
+static bool wide_nn(const GemmCall& g) { return g.K % 4 == 0 && aligned_rows(g.A, g.lda, sizeof(float)); }
+
 // both products as the separate launches would run them: 16x16 tiles, one k range
+bool gemm_generic_nn_tn_shares(int dtype, const GemmCall& nn, const GemmCall& tn) {
+  return dtype == BM_DTYPE_FP32 && generic_splits(nn.M, nn.N, nn.K) == 1 && generic_splits(tn.M, tn.N, tn.K) == 1 &&
+         choose_kernel(GEMM_NN, nn.M, nn.N, nn.K, 1, false, wide_nn(nn)) == 1 &&
+         choose_kernel(GEMM_TN, tn.M, tn.N, tn.K, 1, false, tn.K % 4 == 0) == 1;
+}
+
 bool gemm_generic_nn_tn(int dtype, const GemmCall& nn, const GemmCall& tn, hipStream_t st, bm_status* rc) {
-  if (dtype != BM_DTYPE_FP32) return false;
-  const bool wide0 = nn.K % 4 == 0 && aligned_rows(nn.A, nn.lda, sizeof(float)), wide1 = tn.K % 4 == 0;
-  if (generic_splits(nn.M, nn.N, nn.K) > 1 || generic_splits(tn.M, tn.N, tn.K) > 1 ||
-      choose_kernel(GEMM_NN, nn.M, nn.N, nn.K, 1, false, wide0) != 1 ||
-      choose_kernel(GEMM_TN, tn.M, tn.N, tn.K, 1, false, wide1) != 1) return false;
+  if (!gemm_generic_nn_tn_shares(dtype, nn, tn)) return false;
+  const bool wide0 = wide_nn(nn), wide1 = tn.K % 4 == 0;
   ProfScope prof(PROF_GEMM_NN, 2.0 * nn.M * nn.N * nn.K + 2.0 * tn.M * tn.N * tn.K, st);       // the class of the first
   const int wgs0 = cdiv(nn.M, 16) * cdiv(nn.N, 16), wgs1 = cdiv(tn.M, 16) * cdiv(tn.N, 16);
   auto kern = wide0 ? (wide1 ? gemm_direct_joint_kernel<float, true, true> : gemm_direct_joint_kernel<float, true, false>)

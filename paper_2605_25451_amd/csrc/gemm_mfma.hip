@@ -687,7 +687,9 @@ namespace {
 // there on larger tiles are the better ones).
 bool joint_plan(const GemmCall& nn, const GemmCall& tn, size_t scratch_bytes, Plan* pn, Plan* pt) {
   const TileKind& tk = TILE_KINDS[3];
-  if (nn.K % BK) return false;
+  const GemmEpilogue none;
+  if (!gemm_mfma_supported(GEMM_NN, BM_DTYPE_BF16, nn.M, nn.N, nn.K, nn.lda, nn.ldb, nn.ldc, none) ||
+      !gemm_mfma_supported(GEMM_TN, BM_DTYPE_BF16, tn.M, tn.N, tn.K, tn.lda, tn.ldb, tn.ldc, none) || nn.K % BK) return false;
   const long tiles0 = (long)cdiv(nn.M, 128) * cdiv(nn.N, 128), tiles1 = (long)cdiv(tn.M, 128) * cdiv(tn.N, 128);
   if (tiles0 + tiles1 > tk.slots) return false;
   double apart0, apart1;
@@ -759,11 +761,15 @@ size_t gemm_nn_tn_scratch_bytes(size_t nn, size_t tn, int dtype) {
   return dtype == BM_DTYPE_BF16 ? std::min(nn + tn, JOINT_PARTIAL_BYTES) : 0;
 }
 
+bool gemm_mfma_nn_tn_ranges(const GemmCall& nn, const GemmCall& tn, size_t scratch_bytes, int* nn_ranges, int* tn_ranges) {
+  Plan pn, pt;
+  if (!joint_plan(nn, tn, scratch_bytes, &pn, &pt)) return false;
+  *nn_ranges = pn.splits; *tn_ranges = pt.splits;
+  return true;
+}
+
 bool gemm_mfma_nn_tn(const GemmCall& nn, const GemmCall& tn, void* scratch, size_t scratch_bytes, hipStream_t st,
                      bm_status* rc) {
-  const GemmEpilogue none;
-  if (!gemm_mfma_supported(GEMM_NN, BM_DTYPE_BF16, nn.M, nn.N, nn.K, nn.lda, nn.ldb, nn.ldc, none) ||
-      !gemm_mfma_supported(GEMM_TN, BM_DTYPE_BF16, tn.M, tn.N, tn.K, tn.lda, tn.ldb, tn.ldc, none)) return false;
   if (!scratch || reinterpret_cast<uintptr_t>(scratch) % 16) scratch_bytes = 0;
   Plan pn, pt;
   if (!joint_plan(nn, tn, scratch_bytes, &pn, &pt)) return false;

@@ -1,0 +1,43 @@
+"""Which launches the backward of the GPU tests' cases takes (no GPU): a line of a rule that moves past a case shows here."""
+import numpy as np
+import pytest
+
+import test_gpu_joint_attention as attention
+import test_gpu_joint_gradients as gradients
+from paper_2605_25451_amd import binding as bm
+from paper_2605_25451_amd import synth
+
+
+@pytest.mark.parametrize("Hq,Hkv,dh,causal,lq,lk,plan", attention.CASES)
+def test_attention(Hq, Hkv, dh, causal, lq, lk, plan):
+    cuq, cuk = (None if l is None else np.concatenate([[0], np.cumsum(l)]).astype(np.int32) for l in (lq, lk))
+    assert bm.probe_attention_backward_plan(causal, Hq, Hkv, dh, cuq, cuk) == plan
+
+
+@pytest.mark.parametrize("cfg,lens,plan", gradients.CASES)
+def test_gradients(cfg, lens, plan):
+    assert bm.probe_block_backward_plan(bm.make_desc(cfg), sum(lens), len(lens)) == plan
+
+
+def test_every_variant_of_the_joint_products_has_a_case():
+    """(input gradient split, weight gradient split, rows end inside a slice)"""
+    seen = {(a > 1, b > 1, sum(lens) % 64 != 0) for cfg, lens, plan in gradients.CASES if cfg.dtype == synth.DTYPE_BF16
+            for a, b in plan if (a, b) != gradients.APART}
+    assert len(seen) == 8
+
+
+def test_full_packs_are_launched_apart():
+    assert bm.probe_block_backward_plan(bm.make_desc(synth.vit_large()), 16384, 28) == [(0, 0)] * 3
+    assert bm.probe_block_backward_plan(bm.make_desc(synth.decoder_7b()), 8192, 8) == [(0, 0)] * 3
+
+
+def test_bad_arguments():
+    desc = bm.make_desc(synth.vit_large())
+    for T, S in ((0, 1), (4, 5), (4, 0)):
+        with pytest.raises(bm.BmError):
+            bm.probe_block_backward_plan(desc, T, S)
+    with pytest.raises(bm.BmError):
+        bm.probe_block_backward_plan(bm.make_desc(synth.decoder_moe()), 64, 1)
+    with pytest.raises(bm.BmError):
+        bm.probe_attention_backward_plan(2, 4, 4, 64, [0, 8])
+    assert bm.probe_attention_backward_plan(0, 4, 4, 16, [0, 8]) == (0, 0, 0)
