@@ -257,10 +257,13 @@ __device__ inline void gemm_epilogue_f32(const GemmParams& p, f32x4 (&acc)[FM][F
       if (i + AHEAD < STRIPS) request(std::integral_constant<int, i + AHEAD>{}, FULL);
     });
   };
-  // few rows (decoding): wavefronts past them store nothing, others one strip.  4 rows x 280 x 5160, NN, 14 k ranges: all strips 12.6 us,
-  // this 12.2.  (A test in front of every strip keeps them from overlapping: 64 x 64 x 4000, TN, 12.0 -> 13.2.)
+  // Partial tiles of few rows (decoding): wavefronts past them store nothing, others one strip.  4 rows x 280 x 5160, NN, 14 k ranges: all
+  // strips 12.6 us, this 12.2; 128 x 80 x 7475, TN, 24 ranges, 15.1 -> 14.1.  (A test in front of every strip keeps them from overlapping:
+  // 64 x 64 x 4000, TN, 12.0 -> 13.2; the same for EPI_ADD: a block of 1000 rows 289.0 -> 290.4.)
   if (full) {
     finish(std::true_type{}, std::integral_constant<int, FM>{});
+  } else if (EPI != EPI_PARTIAL) {
+    finish(std::false_type{}, std::integral_constant<int, FM>{});
   } else if (row_of(0) < p.M && col0 < p.N) {
     if (row_of(1) < p.M) finish(std::false_type{}, std::integral_constant<int, FM>{});
     else finish(std::false_type{}, std::integral_constant<int, 1>{});
