@@ -227,6 +227,7 @@ bm_status bm_attention_backward_static(int32_t dtype, int32_t mask, int32_t Hq, 
  * bm_profile_end synchronises with those events and returns, per class, the
  * summed elapsed milliseconds, the summed algorithmic work (flops for GEMM and
  * attention classes, bytes for the HBM-bound classes) and the number of launches.
+ * A launch that an input and a weight gradient share counts, with the work of both, as BM_PROF_GEMM_NN.
  * Outputs are host arrays of BM_PROF_CLASSES entries.  Not thread safe; measuring
  * tool only (it serialises neighbouring kernels at the event boundaries). */
 enum { BM_PROF_GEMM_NT = 0, BM_PROF_GEMM_NN = 1, BM_PROF_GEMM_TN = 2, BM_PROF_ATTN_FWD = 3,

@@ -313,7 +313,9 @@ __global__ __launch_bounds__(NT) void attn_dkdv_generic_kernel(
 }
 
 // Both, where eight lanes share a row on either side (few rows): one launch, dk/dv of the Hkv heads in front (they walk the
-// heads of their group) and dq of the Hq heads behind.  fp32 block of 40 tokens 91 -> 83 us, of 1000 107 -> 96.
+// heads of their group) and dq of the Hq heads behind.  fp32 block of 40 tokens 91 -> 83 us, of 1000 107 -> 96.  On more rows the sums of delta
+// that every dk/dv tile forms for itself cost more than the launch: two launches -> one, 4 heads of 64, 797 rows ahead, 1597 580 -> 621,
+// 3997 2864 -> 3090; 4 heads of 16, 3997 rows 367 -> 410 (causal 415 -> 283); 8 / 1 heads of 64, 708 rows 1235 -> 1419.
 template <typename T, int DH, bool CAUSAL>
 __global__ __launch_bounds__(NT) void attn_bwd_joint_generic_kernel(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, int ld, int ldk,
@@ -330,10 +332,11 @@ __global__ __launch_bounds__(NT) void attn_bwd_joint_generic_kernel(
 }
 
 // Lanes per row.  One lane walks every row of the other side by itself, so few rows leave the chip
-// idle behind long chains; eight lanes per row cost eight times the tile loads.  Measured (with a branch around
-// every load, see load_tiles) forward / backward, us, P = 1 -> 8: head size 16, 1000 rows x 4 heads 223 / 658 -> 60 / 147; head size 64, 1024 x 16
-// 453 / 1242 -> 187 / 737, 2048 x 16 463 / 1246 -> 370 / 1458, 4096 x 16 473 / 1290 -> 564 / 2914; head size 128,
-// 1024 x 8 999 / 28283 -> 249 / 5010, 4096 x 8 2164 -> 2894.
+// idle behind long chains; eight lanes per row cost eight times the tile loads.  The line was drawn where every load stood behind a branch
+// (16 heads of 64, 2048 rows, forward / backward 463 / 1246 -> 370 / 1458, 4096 rows 473 / 1290 -> 564 / 2914).  With the loads of today eight
+// lanes are ahead well beyond it: us, forward / backward, P = 1 -> 8: 4 heads of 16, 1000 rows 198 / 456 -> 40 / 53, 8192 1582 / 3662 ->
+// 533 / 1477; 16 heads of 64, 1024 686 / 2060 -> 158 / 838, 2048 1370 / 4101 -> 600 / 3203, 4096 2706 / 8040 -> 2508 / 12769; 8 heads of 128, 1024
+// 1876 / 7531 -> 344 / 2386, 2048 3741 / 14945 -> 1340 / 9368, 4096 7476 / 29918 -> 5280 / 37396.  The line has not been moved.
 bool eight_lanes(long rows, int heads, int dh) { return rows * heads <= 16384 && rows * heads * dh <= (1L << 20); }
 template <typename F>
 void with_lanes(long rows, int heads, int dh, F&& launch) {

@@ -1962,8 +1962,9 @@ __device__ inline void dq_alt_tile(
 // pair), dQ with turns (ALT) or as the 128 rows of two heads side by side -- the same sequence and tile, so that both
 // halves of the workgroup make the same steps and meet at the same barriers; with an odd number of heads the last
 // workgroup's second half repeats the first and stores nothing.  Two launches -> one, us: 32 heads, 300 tokens 39 -> 27, causal
-// documents of 8192 tokens 537 -> 526; 32 / 8 heads, 777 causal tokens 76 -> 55, heavy-tailed documents 3515 -> 3267; two-stream
-// samples of 1170 tokens, 24 heads, 1112 -> 1069.
+// documents of 8192 tokens 561 -> 534; 32 / 8 heads, 777 causal tokens 76 -> 55, 39000 tokens of heavy-tailed documents 9349 -> 8839;
+// 16 two-stream samples of 1170 tokens, 24 heads, 1104 -> 1028.  The kernels with turns hold more than the 102 scalar registers there
+// are (5 to 16 spill into lanes of a vector register; apart, dQ spilled two).
 template <int DH, bool CAUSAL, bool WIDE, bool ALT>
 __global__ __launch_bounds__(512, 2) void fa_bwd_joint512_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v, int ld, int ldk,

@@ -333,7 +333,7 @@ __global__ __launch_bounds__(256) void gemm_mfma_kernel(GemmParams p) {
 
 // An input gradient (NN, whole slices) and a weight gradient (TN) that do not depend on one another in one grid: on few
 // rows each alone leaves half of the chip's slots idle and costs a launch.  Blocks of a vision encoder, three such pairs
-// each: 256 rows 218 -> 202 us, 577 rows 278 -> 258, 1500 rows 367 -> 341, 3000 rows 539 -> 519.
+// each: 256 rows 207 -> 193 us, 577 rows 260 -> 241, 1500 rows 340 -> 323, 3000 rows 500 -> 485.
 template <int EPI_NN, int EPI_TN, bool KTAIL>
 __global__ __launch_bounds__(256) void gemm_joint_kernel(GemmParams nn, GemmParams tn, int nn_wgs) {
   if ((int)blockIdx.x < nn_wgs) small_tile<false, true, EPI_NN, false>(nn, blockIdx.x);
@@ -406,8 +406,10 @@ constexpr int NUM_CU = 256;
 // Measured on 527 shapes (blocks of 1024 to 4096 columns at 300 to 16384 rows, shapes drawn over the same range, and
 // gradients of 8 to 128 conditions; every tile, splits 1-32): the plan it picks takes 1.2 % longer than the best one on
 // average, 23 % at worst.
-// (Fitted before the slices of 256x256 weight gradients were cut along k and their C went through whole lines, which took
-// 1-7 % off those tiles: the choices are the same, on a few shapes near a line 256x256 would now win by that much.)
+// The constants of weight gradients are those of a kernel that is gone: slices of 256x256 tiles are cut along k by now (a lone one takes
+// 0.96 / 0.87 = 1.10 of an NT slice, f_tn says 1.13) and C goes through whole lines, which took 1-7 % off all fp32 epilogues.  So on shapes
+// near a line the plan, the shared launch of two weight gradients and joint_plan still price a 256x256 tile a few per cent too
+// high and may take a choice that is that much slower than the best; the table has not been refitted.
 struct TileKind { int bm, bn, slots; double t_min, t_full, power, t_fixed, t_cut, f_tn, hidden; };
 constexpr TileKind TILE_KINDS[] = {
   {256, 256, NUM_CU, 0.87, 1.36, 0.6, 5.5, 3.6, 1.13, 0.23},

@@ -159,22 +159,6 @@ __device__ inline TileJob locate_tile(GemmParams& p, int pid) {
   return t;
 }
 
-// ---- epilogue of one wavefront: FM x FN accumulator blocks of 16x16.  The MFMAs run with swapped
-// operands, so block (i,j) holds C^T: lane = row m = l%16, registers = 4 consecutive columns
-// n = 4*(l/16) + e.  Each wavefront transposes its own 16-row strips through LDS and then writes
-// whole rows, 16 bytes per lane.
-//
-// What the epilogue combines with the product -- the old C of a weight gradient, the residual, the
-// saved g and u of the SwiGLU backward -- is requested two strips ahead, the first two strips before
-// the tile's last MFMAs (`last`): fetched in front of each store instead, a tile pays one memory
-// latency per store instruction, 32 of them in a row (four wavefronts of 128x128: dW 22016x4096 over
-// 777 rows 296 -> 247 us, over 8192 rows 1301 -> 1271 us).  Addresses are clamped into the matrix, so
-// that the requests carry no condition.
-//   row_of(i)   first row of strip i;  col0  the wavefront's first column
-//   acol0       SwiGLU forward: its first column of a
-//   stage       epilogue_stage_floats() of LDS of its own; free to write once `last` has returned
-//   full        the tile lies inside C, so no store carries a condition (a conditional store makes the
-//               wait for the next strip's operands wait for the stores as well)
 // The accumulators behind the last MFMAs, readable: the compiler does not know that the asm statements are MFMAs and
 // leaves no wait states between them and what reads their results, and arithmetic on the results (a conversion, a copy to
 // the other half of the register file) may move in front of the wait unless it depends on it.
@@ -193,8 +177,8 @@ template <int FN> constexpr int epilogue_stage_floats() { return 2 * 16 * (FN * 
 // fp32 outputs of weight gradients and k ranges (EPI_ADD, EPI_PARTIAL): 4 columns per lane, so that a load or store
 // instruction covers 4 rows of 256 contiguous bytes (with 8 columns per lane every instruction touched half of each
 // 32 bytes and the caches took twice the requests); two strips of LDS in turn; the old C four strips ahead, the last two
-// of them once the fragments are dead.  The epilogue of a lone 256x256 tile 6.0 -> 4.2 us, with all CUs at work
-// 16-19 -> 15-18 (HBM); 22016x4096 over 8192 rows 1152 -> 1109 us, over 777 241 -> 235, 4096x11008 over 777 134 -> 128.
+// of them once the fragments are dead.  The epilogue of a lone 256x256 tile, until its last store is issued, 6.0 -> 4.2 us, with all CUs at
+// work 16-19 -> 15-18; 22016x4096 over 8192 rows 1152 -> 1109 us, over 777 241 -> 235, 4096x11008 over 777 134 -> 128.
 // One lane offset serves all rows of a tile that lies inside C: with an address per row the ragged and the full path
 // together spill.
 template <int EPI, int FM, int FN, typename RowOf, typename Last>
@@ -270,6 +254,22 @@ __device__ inline void gemm_epilogue_f32(const GemmParams& p, f32x4 (&acc)[FM][F
   }
 }
 
+// ---- epilogue of one wavefront: FM x FN accumulator blocks of 16x16.  The MFMAs run with swapped
+// operands, so block (i,j) holds C^T: lane = row m = l%16, registers = 4 consecutive columns
+// n = 4*(l/16) + e.  Each wavefront transposes its own 16-row strips through LDS and then writes
+// whole rows, 16 bytes per lane (fp32 outputs: above).
+//
+// What the epilogue combines with the product -- the residual, the saved g and u of the SwiGLU
+// backward -- is requested two strips ahead (the old C of a weight gradient four), the first two strips before
+// the tile's last MFMAs (`last`): fetched in front of each store instead, a tile pays one memory
+// latency per store instruction, 32 of them in a row (four wavefronts of 128x128, the old C: dW 22016x4096
+// over 777 rows 296 -> 247 us, over 8192 rows 1301 -> 1271 us).  Addresses are clamped into the matrix, so
+// that the requests carry no condition.
+//   row_of(i)   first row of strip i;  col0  the wavefront's first column
+//   acol0       SwiGLU forward: its first column of a
+//   stage       epilogue_stage_floats() of LDS of its own; free to write once `last` has returned
+//   full        the tile lies inside C, so no store carries a condition (a conditional store makes the
+//               wait for the next strip's operands wait for the stores as well)
 template <int EPI, int FM, int FN, typename RowOf, typename Last>
 __device__ inline void gemm_epilogue(const GemmParams& p, f32x4 (&acc)[FM][FN], float* stage, int lane, int col0,
                                      int acol0, int split, long c_off, bool full, RowOf row_of, Last last) {
