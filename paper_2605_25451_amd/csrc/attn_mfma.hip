@@ -2060,7 +2060,7 @@ BwdPlan bwd_plan(const AttnArgs& a) {
   p.q_wgs = p.qtiles * (same_wgs ? a.Hq : (a.Hq + 1) / 2);
   // One launch or two?  One, where dQ takes the same workgroups anyway: head size 64, and 256-row query tiles (60 packs of
   // 1500 to 36000 tokens: 57 faster, 3 % on average, 12 % at best, the slowest -1.6 %).  Where both parts fill whole rounds there is nothing to
-  // gain: 32 / 8 heads, 8192 queries and keys 3217 -> 3172, causal 1729 -> 1733; the four pairs of a rank 14668 -> 14612, in seven runs +1.0 %
+  // gain: 32 / 8 heads, 8192 queries and keys 3217 -> 3172, causal 1729 -> 1733; the four pairs of a rank 14668 -> 14612, in eight runs +1.0 %
   // to -0.8 %.  The 128 rows of two heads side by
   // side are slower than two workgroups on a CU, so that is for packs whose workgroups all run at once, or nearly so where a
   // causal mask makes most of them short or the wide dK/dV ones are few and long, and for those whose dQ fits into what
