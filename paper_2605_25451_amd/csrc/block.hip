@@ -191,6 +191,24 @@ BwdScratch layout_bwd(const Dims& m, int dtype, void* base) {
 GemmCall input_grad(int M, int N, int K, const void* A, const void* B, void* C) { return {M, N, K, A, K, B, N, C, N}; }
 GemmCall weight_grad(int M, int N, int K, const void* A, const void* B, void* C) { return {M, N, K, A, M, B, N, C, N}; }
 
+// The products of a backward pass: input gradients of up, o, qkv; weight gradients of down, up, o, qkv
+struct BackwardGemms { GemmCall nn[3], tn[4]; };
+BackwardGemms backward_gemms(const Dims& m) {
+  const int T = m.T, d = m.d;
+  void* const no = nullptr;
+  return {{input_grad(T, d, m.UP, no, no, no), input_grad(T, m.QD, d, no, no, no), input_grad(T, d, m.QKV, no, no, no)},
+          {weight_grad(d, m.F, T, no, no, no), weight_grad(m.UP, d, T, no, no, no), weight_grad(d, m.QD, T, no, no, no),
+           weight_grad(m.QKV, d, T, no, no, no)}};
+}
+// All weight gradients in one launch at the end: what they read has to be there until then.  The gradient of the activation's
+// output is spent by then and takes the rewritten output of norm 1 and, where a gate sits in front of the output
+// projection, that projection's gradient.
+bool weight_grads_last(const Dims& m, int dtype, size_t gemm_ws_bytes) {
+  if (m.E > 0 || m.F < m.d * (m.ada ? 2 : 1)) return false;
+  const BackwardGemms g = backward_gemms(m);
+  return gemm_tn_group_pays(dtype, g.nn, g.tn, gemm_ws_bytes);
+}
+
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
 bm_status check_desc(const bm_block_desc* c) {
@@ -482,6 +500,10 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   const int d = m.d;
   ColumnSums sums;
   SegmentSums segments;
+  const bool weights_last = weight_grads_last(m, dt, ws.gemm_ws_bytes);
+  auto gemm_nn = [&](const GemmCall& g) {
+    return gemm(GEMM_NN, dt, g.M, g.N, g.K, g.A, g.lda, g.B, g.ldb, g.C, g.ldc, none, ws.gemm_ws, ws.gemm_ws_bytes, st);
+  };
 
   // ---- y = x1 + [g2 *] m,  m = a W_down^T + b_down
   const void* dm = dy;
@@ -550,8 +572,9 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
                                 c.linear_bias ? (float*)grads->b_up : nullptr, ws.colsum_ws[0], T, m.F, &sums, st)); }
   }
   // ---- up = h2 W_up^T + b_up,  h2 = N2(x1): its input gradient beside the weight gradient of the down projection
-  BM_RETURN_IF(gemm_nn_tn(dt, input_grad(T, d, m.UP, ws.dup, w->w_up, ws.dh), weight_grad(d, m.F, T, dm, ws.a, grads->w_down),
-                          ws.gemm_ws, ws.gemm_ws_bytes, st));
+  const GemmCall dh = input_grad(T, d, m.UP, ws.dup, w->w_up, ws.dh);
+  if (weights_last) BM_RETURN_IF(gemm_nn(dh));
+  else BM_RETURN_IF(gemm_nn_tn(dt, dh, weight_grad(d, m.F, T, dm, ws.a, grads->w_down), ws.gemm_ws, ws.gemm_ws_bytes, st));
   // bias gradients of the down and output projections are column sums of the two
   // gradients the norm backward below touches anyway (not so when a gate sits between)
   if (c.linear_bias && !fused_sums)
@@ -568,10 +591,11 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   // ---- x1 = x + [g1 *] attn,  attn = o W_o^T + b_o
   const void* dattn = ws.dx1;
   if (m.ada) {
+    char* gated = weights_last ? ws.da + (size_t)T * d * m.es : ws.dgated;
     { ProfScope _p(PROF_ELEMENTWISE, 3.0 * T * d * (double)m.es, st);
-      BM_RETURN_IF(segment_gate(dt, ws.dx1, sv.attn, sv.mod + 2 * d, 6 * d, ws.dgated, cu_dev, S, d, ws.dmod + 2 * d,
+      BM_RETURN_IF(segment_gate(dt, ws.dx1, sv.attn, sv.mod + 2 * d, 6 * d, gated, cu_dev, S, d, ws.dmod + 2 * d,
                                 6 * d, ws.seg_ws[1], &segments, st)); }
-    dattn = ws.dgated;
+    dattn = gated;
   }
   // (the weight gradient of the output projection is small: it shares a launch with the one of
   // the QKV projection at the end; dattn and the saved o stay untouched until then)
@@ -579,9 +603,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, dattn, d, T, d, (float*)grads->b_o, ws.colsum_ws[2], &sums, st)); }
   {
     const GemmCall d_o = input_grad(T, m.QD, d, dattn, w->w_o, ws.d_o);
-    if (m.E > 0)
-      BM_RETURN_IF(gemm(GEMM_NN, dt, d_o.M, d_o.N, d_o.K, d_o.A, d_o.lda, d_o.B, d_o.ldb, d_o.C, d_o.ldc, none, ws.gemm_ws,
-                        ws.gemm_ws_bytes, st));
+    if (m.E > 0 || weights_last) BM_RETURN_IF(gemm_nn(d_o));
     else   // beside the weight gradient of the up projection, whose input ws.h holds until norm 1
       BM_RETURN_IF(gemm_nn_tn(dt, d_o, weight_grad(m.UP, d, T, ws.dup, ws.h, grads->w_up), ws.gemm_ws, ws.gemm_ws_bytes, st));
   }
@@ -607,11 +629,11 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, ws.dqkv, m.QKV, T, m.QKV, (float*)grads->b_qkv, ws.colsum_ws[3], &sums, st)); }
   // the weight gradient of the output projection goes with the input gradient here, where that is one launch, or with
   // the weight gradient of the QKV projection behind norm 1
-  const bool o_with_qkv = gemm_tn_pair_shares_launch(dt, T, m.QKV, d, ws.dqkv, m.QKV, ws.h, d, grads->w_qkv, d,
+  const bool o_with_qkv = !weights_last && gemm_tn_pair_shares_launch(dt, T, m.QKV, d, ws.dqkv, m.QKV, ws.h, d, grads->w_qkv, d,
                                                      d, m.QD, dattn, d, sv.o, m.QD, grads->w_o, m.QD, ws.gemm_ws,
                                                      ws.gemm_ws_bytes, st);
   bool o_done = false;
-  if (!o_with_qkv) {
+  if (!weights_last && !o_with_qkv) {
     bm_status rc;
     o_done = gemm_nn_tn_joint(dt, input_grad(T, d, m.QKV, ws.dqkv, w->w_qkv, ws.dh),
                               weight_grad(d, m.QD, T, dattn, sv.o, grads->w_o), ws.gemm_ws, ws.gemm_ws_bytes, st, &rc);
@@ -619,11 +641,17 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   }
   if (!o_done)
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.QKV, ws.dqkv, m.QKV, w->w_qkv, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
+  char* h1 = weights_last ? ws.da : ws.h;
   { ProfScope _p(PROF_NORM, 5.0 * T * m.d * (double)m.es, st);
-    BM_RETURN_IF(norm_backward(n1, x, sv.stats1, ws.dh, ws.dx1, dx, ws.h, (float*)grads->norm1_g,
+    BM_RETURN_IF(norm_backward(n1, x, sv.stats1, ws.dh, ws.dx1, dx, h1, (float*)grads->norm1_g,
                                (float*)grads->norm1_b, nullptr, nullptr, ws.dmod, cu_dev, S,
                                ws.norm1_ws, &sums, &segments, st)); }
-  if (o_done)
+  if (weights_last) {
+    const GemmCall all[4] = {weight_grad(d, m.F, T, dm, ws.a, grads->w_down), weight_grad(m.UP, d, T, ws.dup, ws.h, grads->w_up),
+                             weight_grad(d, m.QD, T, dattn, sv.o, grads->w_o),
+                             weight_grad(m.QKV, d, T, ws.dqkv, h1, grads->w_qkv)};
+    BM_RETURN_IF(gemm_tn_group(all, 4, ws.gemm_ws, ws.gemm_ws_bytes, st));
+  } else if (o_done)
     BM_RETURN_IF(gemm(GEMM_TN, dt, m.QKV, d, T, ws.dqkv, m.QKV, ws.h, d, grads->w_qkv, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
   else
     BM_RETURN_IF(gemm_tn_pair(dt, T, m.QKV, d, ws.dqkv, m.QKV, ws.h, d, grads->w_qkv, d,
@@ -655,6 +683,7 @@ extern "C" bm_status bm_probe_block_backward_plan(const bm_block_desc* desc, int
   const Dims m = make_dims(*desc, T, S);
   const int dt = desc->dtype, d = m.d;
   const size_t bytes = layout_bwd(m, dt, nullptr).gemm_ws_bytes;
+  if (weight_grads_last(m, dt, bytes)) { for (int i = 0; i < 6; ++i) k_ranges[i] = 0; return BM_OK; }
   void* const none = nullptr;
   gemm_nn_tn_ranges(dt, input_grad(T, d, m.UP, none, none, none), weight_grad(d, m.F, T, none, none, none), bytes, k_ranges, k_ranges + 1);
   gemm_nn_tn_ranges(dt, input_grad(T, m.QD, d, none, none, none), weight_grad(m.UP, d, T, none, none, none), bytes, k_ranges + 2,

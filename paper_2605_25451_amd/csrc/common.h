@@ -204,7 +204,17 @@ bool gemm_tn_pair_shares_launch(int dtype, int K, int M0, int N0, const void* A0
 size_t gemm_mfma_tn_pair_scratch_bytes(int K, int M0, int N0, int M1, int N1);
 bool gemm_mfma_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const void* B0, int ldb0, void* C0, int ldc0,
                        int M1, int N1, const void* A1, int lda1, const void* B1, int ldb1, void* C1, int ldc1,
-                       void* scratch, size_t scratch_bytes, hipStream_t st, bm_status* rc);
+                       void* scratch, size_t scratch_bytes, hipStream_t st, bm_status* rc, double* time = nullptr);
+// All weight gradients of a block (the same rows, at most 4) in one launch; scratch as for any of them alone.  `pays`:
+// expected to be faster than launches that follow one another, where nn[i] and tn[i] (i < 2: up/down, o/up) can share
+// one and so can either nn[2] and tn[2] (qkv/o) or tn[2] and tn[3] (o/qkv).
+bool gemm_tn_group_pays(int dtype, const GemmCall nn[3], const GemmCall tn[4], size_t scratch_bytes);
+bm_status gemm_tn_group(const GemmCall* tn, int n, void* scratch, size_t scratch_bytes, hipStream_t st);
+bm_status gemm_mfma_tn_group(const GemmCall* tn, int n, void* scratch, size_t scratch_bytes, hipStream_t st);
+// expected times in us; < 0: not supported or not the choice
+double gemm_mfma_tn_group_time(const GemmCall* tn, int n, size_t scratch_bytes);
+double gemm_mfma_nn_tn_time(const GemmCall& nn, const GemmCall& tn, size_t scratch_bytes);
+double gemm_mfma_time(int layout, const GemmCall& w, size_t scratch_bytes);
 // epi (MFMA path only, the caller checks gemm_mfma_grouped_supported): the SwiGLU epilogues of
 // GemmEpilogue, forward on NT (N a multiple of 256) and backward on NN (N a multiple of 256)
 bm_status gemm_grouped(int layout, int dtype, int M, int N, int K, const void* A, int lda,

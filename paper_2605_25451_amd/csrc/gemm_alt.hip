@@ -298,14 +298,13 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_kernel(GemmParams p) {
 // The first 32 k of a slice are re-filled while its last 32 are read, and the other way round.  (K-contiguous operands
 // are cut along the rows because half a slice of theirs would be half of every 128-byte line.)
 template <int EPI, bool CUT>
-__global__ __launch_bounds__(THREADS, 2) void gemm_alt256_tn_kernel(GemmParams p) {
+__device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJob& job) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using Reg = Region<256, true>;
   constexpr uint32_t B0 = Reg::BYTES, BUF = 2 * Reg::BYTES;
   constexpr int HL = Reg::LOADS;                                             // loads of half a slice, A and B
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 2, wn = wave & 3;                                   // wm is the group
-  const TileJob job = locate_tile<256, 256>(p, blockIdx.x);
   if (job.kbeg >= job.kend) return;
   const int m0 = job.m0, n0 = job.n0, n = (job.kend - job.kbeg + BK - 1) / BK;
   const int k_left = job.kend - job.kbeg - (n - 1) * BK;                     // of the last slice
@@ -396,6 +395,37 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_tn_kernel(GemmParams p
                              // group 0 writes its strips over the buffers group 1 has just read
                              if (wm == 0) end_phase();
                            });
+}
+
+template <int EPI, bool CUT>
+__global__ __launch_bounds__(THREADS, 2) void gemm_alt256_tn_kernel(GemmParams p) {
+  alt256_tn_tile<EPI, CUT>(p, locate_tile<256, 256>(p, blockIdx.x));
+}
+
+// Several weight gradients in one grid.
+template <bool CUT>
+__global__ __launch_bounds__(THREADS, 2) void gemm_alt256_tn_parts_kernel(TnParts g) {
+  // One round of tiles with one k range lies in one list, of which every XCD takes a run: an XCD that took a run of every
+  // part would fetch twice the panels (a block of 1024 columns, 5477 rows: 161 -> 146 us).  Over several rounds a
+  // run of every part is better: then all XCDs walk the same operands at a time (the stage of four microbatches
+  // 155.2 -> 154.7 ms).
+  const int pid = blockIdx.x, id = pid < g.one_list ? xcd_run(pid, g.one_list) : pid;
+  int i = 0;
+  while (i + 1 < g.n && id >= g.part[i + 1].first_wg) ++i;
+  const TnParts::Part& q = g.part[i];
+  GemmParams p{};
+  p.A = q.A; p.B = q.B; p.C = q.C; p.partial = q.partial;
+  p.M = q.M; p.N = q.N; p.K = q.K; p.lda = q.lda; p.ldb = q.ldb; p.ldc = q.ldc;
+  p.tiles_m = q.tiles_m; p.tiles_n = q.tiles_n; p.splits = q.splits; p.k_per_split = q.k_per_split;
+  p.xcd_split = q.xcd_split;
+  if (p.splits > 1) {
+    alt256_tn_tile<EPI_PARTIAL, CUT>(p, locate_tile<256, 256>(p, id - q.first_wg));
+  } else {
+    int tm, tn, t = id - q.first_wg;
+    if (g.one_list == 0) t = xcd_run(t, q.tiles_m * q.tiles_n);
+    grouped_tile<4>(t, q.tiles_m, q.tiles_n, &tm, &tn);
+    alt256_tn_tile<EPI_ADD, CUT>(p, tile_job<256, 256>(p, 0, tm, tn));
+  }
 }
 
 // ---- 128x256 and 256x128 tiles: each wavefront owns 64x64 and a slice is one phase per group.  LDS holds
@@ -508,10 +538,22 @@ bm_status launch_one(const GemmParams& p, hipStream_t st) {
     BM_CHECK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     attr_done.store(true, std::memory_order_relaxed);
   }
-  int wgs = p.tiles_m * p.tiles_n * p.splits * p.grid_groups;
-  if (p.pair_wgs0 > 0) wgs = p.pair_wgs0 + p.second.tiles_m * p.second.tiles_n * p.second.splits;
-  hipLaunchKernelGGL(kern, dim3(wgs), dim3(THREADS), lds, st, p);
+  hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n * p.splits * p.grid_groups), dim3(THREADS), lds, st, p);
   BM_CHECK_LAUNCH("gemm_alt");
+  return BM_OK;
+}
+
+template <bool CUT>
+bm_status launch_parts(const TnParts& g, hipStream_t st) {
+  constexpr size_t lds = (size_t)2 * (256 + 256) * BK * sizeof(bf16_t);
+  auto kern = gemm_alt256_tn_parts_kernel<CUT>;
+  static std::atomic<bool> attr_done{false};
+  if (!attr_done.load(std::memory_order_relaxed)) {
+    BM_CHECK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    attr_done.store(true, std::memory_order_relaxed);
+  }
+  hipLaunchKernelGGL(kern, dim3(g.wgs()), dim3(THREADS), lds, st, g);
+  BM_CHECK_LAUNCH("gemm_alt_tn_parts");
   return BM_OK;
 }
 
@@ -543,6 +585,12 @@ bm_status launch_gemm_alt(int layout, int bm, int bn, const GemmParams& p, hipSt
   if (bm == 256 && bn == 256) return launch_tile<256, 256>(layout, p, st);
   if (bm == 256 && bn == 128) return launch_tile<256, 128>(layout, p, st);
   return launch_tile<128, 256>(layout, p, st);
+}
+
+bm_status launch_gemm_alt_tn_parts(const TnParts& g, hipStream_t st) {
+  bool cut = false;
+  for (int i = 0; i < g.n; ++i) cut = cut || g.part[i].K % BK;
+  return cut ? launch_parts<true>(g, st) : launch_parts<false>(g, st);
 }
 
 }  // namespace bm

@@ -340,9 +340,8 @@ __global__ __launch_bounds__(256) void gemm_joint_kernel(GemmParams nn, GemmPara
   else small_tile<true, true, EPI_TN, KTAIL>(tn, blockIdx.x - nn_wgs);
 }
 
-__global__ void splitk_reduce_kernel(const float* __restrict__ partial, int splits, int M, int N,
-                                     float* __restrict__ C, int ldc) {
-  const long i = ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4;
+__device__ inline void splitk_reduce(const float* __restrict__ partial, int splits, int M, int N, float* __restrict__ C,
+                                     int ldc, long i) {
   if (i >= (long)M * N) return;
   const int m = (int)(i / N), n = (int)(i % N);
   float4 s = {0.f, 0.f, 0.f, 0.f};
@@ -352,6 +351,15 @@ __global__ void splitk_reduce_kernel(const float* __restrict__ partial, int spli
   }
   float* c = C + (size_t)m * ldc + n;
   c[0] += s.x; c[1] += s.y; c[2] += s.z; c[3] += s.w;
+}
+__global__ void splitk_reduce_kernel(const float* __restrict__ partial, int splits, int M, int N,
+                                     float* __restrict__ C, int ldc) {
+  splitk_reduce(partial, splits, M, N, C, ldc, ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4);
+}
+// the split parts of a shared grid; blockIdx.y is the part
+__global__ void splitk_reduce_parts_kernel(TnParts g) {
+  const TnParts::Part& q = g.part[blockIdx.y];
+  if (q.splits > 1) splitk_reduce(q.partial, q.splits, q.M, q.N, q.C, q.ldc, ((long)blockIdx.x * blockDim.x + threadIdx.x) * 4);
 }
 
 // C = sum of the k ranges' partial products (+bias) (+residual), in range order
@@ -576,7 +584,7 @@ bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, con
     return BM_ERR_INVALID_ARG;
   }
   p.tile_group = nullptr; p.group_rows = nullptr; p.b_group_stride = 0; p.c_group_stride = 0;
-  p.grid_groups = 1; p.pair_wgs0 = 0; p.second = {};
+  p.grid_groups = 1;
   p.xcd_split = xcd_split_possible(pl.tiles_m * pl.tiles_n, pl.splits) ? 1 : 0;
   BM_RETURN_IF(pl.bm == 128 && pl.bn == 128 ? launch_small(layout, p, st) : launch_gemm_alt(layout, pl.bm, pl.bn, p, st));
   if (pl.splits > 1 && layout == GEMM_TN) {
@@ -614,13 +622,42 @@ size_t gemm_mfma_tn_pair_scratch_bytes(int K, int M0, int N0, int M1, int N1) {
   return align_up((size_t)sp * M0 * N0 * sizeof(float), 256) + (size_t)sp * M1 * N1 * sizeof(float);
 }
 
+namespace {
+
+TnParts::Part tn_part(const GemmCall& w, const Plan& pl, float* partial, int first_wg) {
+  TnParts::Part q;
+  q.A = (const bf16_t*)w.A; q.B = (const bf16_t*)w.B; q.C = (float*)w.C; q.partial = partial;
+  q.M = w.M; q.N = w.N; q.K = w.K; q.lda = w.lda; q.ldb = w.ldb; q.ldc = w.ldc;
+  q.tiles_m = pl.tiles_m; q.tiles_n = pl.tiles_n; q.splits = pl.splits; q.k_per_split = pl.k_per_split;
+  // (split tiles are pinned to XCDs by the id of a workgroup in its grid)
+  q.xcd_split = first_wg % 8 == 0 && xcd_split_possible(pl.tiles_m * pl.tiles_n, pl.splits) ? 1 : 0;
+  q.first_wg = first_wg;
+  return q;
+}
+
+bm_status launch_tn_parts(const TnParts& g, hipStream_t st) {
+  BM_RETURN_IF(launch_gemm_alt_tn_parts(g, st));
+  long longest = 0, last = g.n - 1;                            // unsplit parts come first
+  for (int i = 0; i < g.n; ++i)
+    if (g.part[i].splits > 1) { longest = std::max(longest, (long)g.part[i].M * g.part[i].N); last = std::min<long>(last, i); }
+  if (longest == 0) return BM_OK;
+  TnParts split = g;
+  split.n = g.n - (int)last;
+  for (int i = 0; i < split.n; ++i) split.part[i] = g.part[last + i];
+  hipLaunchKernelGGL(splitk_reduce_parts_kernel, dim3(cdiv(longest / 4, 256), split.n), dim3(256), 0, st, split);
+  BM_CHECK_LAUNCH("splitk_reduce");
+  return BM_OK;
+}
+
+}  // namespace
+
 // Two weight gradients C_i[M_i,N_i] += A_i[K,M_i]^T B_i[K,N_i] over the same K in ONE grid, when
 // both plans use 256x256 tiles and whole slices: a gradient whose tiles x splits do not fill
 // the chip (1024x1024 next to 3072x1024 in a ViT-L block) no longer has the machine to itself.
 // Returns false (nothing launched) when the pair does not qualify; the caller then runs two GEMMs.
 bool gemm_mfma_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const void* B0, int ldb0, void* C0, int ldc0,
                        int M1, int N1, const void* A1, int lda1, const void* B1, int ldb1, void* C1, int ldc1,
-                       void* scratch, size_t scratch_bytes, hipStream_t st, bm_status* rc) {
+                       void* scratch, size_t scratch_bytes, hipStream_t st, bm_status* rc, double* time) {
   // rc == nullptr: only answer whether the pair qualifies
   const GemmEpilogue none;
   if (rc) *rc = BM_OK;
@@ -647,6 +684,7 @@ bool gemm_mfma_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const vo
     if (sp > 1) together += output_time(TILE_KINDS[0], GEMM_TN, sp, mn0, 0.0) + output_time(TILE_KINDS[0], GEMM_TN, sp, mn1, 0.0);
     else together += output_time(TILE_KINDS[0], GEMM_TN, 1, mn0 + mn1, together);
     if (together >= t0 + t1) return false;
+    if (time) *time = together;
   }
   const size_t part0 = a.splits > 1 ? align_up((size_t)a.splits * M0 * N0 * sizeof(float), 256) : 0;
   const size_t part1 = b.splits > 1 ? (size_t)b.splits * M1 * N1 * sizeof(float) : 0;
@@ -655,30 +693,113 @@ bool gemm_mfma_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const vo
   const bool xa = xcd_split_possible(a.tiles_m * a.tiles_n, a.splits), xb = xcd_split_possible(b.tiles_m * b.tiles_n, b.splits);
   if (xb && wgs0 % 8) return false;               // the second problem's XCD pinning needs an aligned start
   if (!rc) return true;
-  GemmParams p;
-  p.A = (const bf16_t*)A0; p.B = (const bf16_t*)B0; p.C = C0; p.bias = nullptr; p.residual = nullptr;
-  p.partial = (float*)scratch;
-  p.M = M0; p.N = N0; p.K = K; p.lda = lda0; p.ldb = ldb0; p.ldc = ldc0;
-  p.tiles_m = a.tiles_m; p.tiles_n = a.tiles_n; p.splits = a.splits; p.k_per_split = a.k_per_split;
-  p.out_fp32 = 0; p.xcd_split = xa ? 1 : 0;
-  p.tile_group = nullptr; p.group_rows = nullptr; p.b_group_stride = 0; p.c_group_stride = 0; p.grid_groups = 1;
-  p.pair_wgs0 = wgs0;
-  p.second.A = (const bf16_t*)A1; p.second.B = (const bf16_t*)B1; p.second.C = C1;
-  p.second.partial = (float*)((char*)scratch + part0);
-  p.second.M = M1; p.second.N = N1; p.second.lda = lda1; p.second.ldb = ldb1; p.second.ldc = ldc1;
-  p.second.tiles_m = b.tiles_m; p.second.tiles_n = b.tiles_n; p.second.splits = b.splits;
-  p.second.k_per_split = b.k_per_split; p.second.xcd_split = xb ? 1 : 0;
-  *rc = launch_gemm_alt(GEMM_TN, 256, 256, p, st);
-  if (*rc != BM_OK) return true;
-  if (a.splits > 1)
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(cdiv((long)M0 * N0 / 4, 256)), dim3(256), 0, st, p.partial, a.splits,
-                       M0, N0, (float*)C0, ldc0);
-  if (b.splits > 1)
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3(cdiv((long)M1 * N1 / 4, 256)), dim3(256), 0, st, p.second.partial,
-                       b.splits, M1, N1, (float*)C1, ldc1);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) *rc = hip_fail(e, "splitk_reduce");
+  TnParts g;
+  g.n = 2;
+  g.one_list = 0;
+  g.part[0] = tn_part(GemmCall{M0, N0, K, A0, lda0, B0, ldb0, C0, ldc0}, a, (float*)scratch, 0);
+  g.part[1] = tn_part(GemmCall{M1, N1, K, A1, lda1, B1, ldb1, C1, ldc1}, b, (float*)((char*)scratch + part0), wgs0);
+  *rc = launch_tn_parts(g, st);
   return true;
+}
+
+// ---- all weight gradients of a block in one grid
+//
+// They are ready one after the other, and alone each leaves CUs idle or splits its k range: a block of 1024 columns is
+// 48 + 16 + 64 + 64 tiles of 256x256.  Together those are one round of 192 without partial tiles; where a round has room
+// for more, all are split alike, and the one gradient that would otherwise open a round of its own is split over its
+// CUs.  A slice of 192 tiles takes 1.19 us, of 256 tiles 1.37 (power), so the idle quarter costs little.  Forward and backward of a block:
+// vision encoder of 1024 columns, 3000 rows 508 -> 457 us, 5477 rows 816 -> 745, 16384 rows 1688 -> 1650; generator of 1152 columns,
+// 8192 rows 1364 -> 1274; 256 columns, 8000 rows 242 -> 213; decoder of 2048 columns, 6000 rows 2180 -> 2111.
+namespace {
+
+struct TnGroupPlan { int split_part, splits, per; };          // the part that is split: NO_PART, ALL_PARTS or its index
+constexpr int NO_PART = -1, ALL_PARTS = -2;
+
+// `longer` workgroups of per0 slices each, then `shorter` ones of per1
+double two_lengths_time(const TileKind& tk, bool cut, long longer, int per0, long shorter, int per1) {
+  if (shorter == 0) return grid_time(tk, GEMM_TN, cut, longer, per0);
+  const double fixed = tk.t_fixed + (cut ? tk.t_cut : 0.0);
+  const double t0 = per0 * tk.t_full * tk.f_tn + fixed, t1 = per1 * tk.t_full * tk.f_tn + fixed;
+  const long rest = longer % tk.slots;
+  if (rest) shorter = std::max(0L, shorter - (tk.slots - rest) * (long)(t0 / t1));       // beside the last of the long ones
+  return cdiv(longer, (long)tk.slots) * t0 + (shorter ? grid_time(tk, GEMM_TN, cut, shorter, per1) : 0.0);
+}
+
+bool tn_group_plan(const GemmCall* w, int n, size_t scratch_bytes, TnGroupPlan* plan, double* time) {
+  const TileKind& tk = TILE_KINDS[0];
+  const GemmEpilogue none;
+  if (n < 2 || n > TnParts::MAX) return false;
+  const int K = w[0].K, slices = cdiv(K, BK);
+  const bool cut = K % BK;
+  long tiles[TnParts::MAX], all = 0;
+  double mn = 0.0;
+  for (int i = 0; i < n; ++i) {
+    if (w[i].K != K || !gemm_mfma_supported(GEMM_TN, BM_DTYPE_BF16, w[i].M, w[i].N, K, w[i].lda, w[i].ldb, w[i].ldc, none)) return false;
+    tiles[i] = (long)cdiv(w[i].M, 256) * cdiv(w[i].N, 256);
+    all += tiles[i];
+    mn += (double)w[i].M * w[i].N;
+  }
+  double best = grid_time(tk, GEMM_TN, cut, all, slices);
+  best += output_time(tk, GEMM_TN, 1, mn, best);
+  *plan = TnGroupPlan{NO_PART, 1, slices};
+  for (int sp = 2; sp <= std::min<long>(std::min<long>(slices / 4, 32), NUM_CU / all); ++sp) {
+    const int per = cdiv(slices, sp);
+    if (cdiv(slices, per) != sp) continue;
+    if (sp * mn * sizeof(float) + 256.0 * n > (double)scratch_bytes) break;
+    const double t = grid_time(tk, GEMM_TN, cut, all * sp, per) + output_time(tk, GEMM_TN, sp, mn, 0.0);
+    if (t < best) { best = t; *plan = TnGroupPlan{ALL_PARTS, sp, per}; }
+  }
+  for (int i = 0; i < n; ++i) {
+    const double mni = (double)w[i].M * w[i].N;
+    for (int sp = 2; sp <= split_cap(GEMM_TN, w[i].M, w[i].N, K); ++sp) {
+      const int per = cdiv(slices, sp);
+      if (cdiv(slices, per) != sp) continue;
+      if (sp * mni * sizeof(float) > (double)scratch_bytes) break;
+      double t = two_lengths_time(tk, cut, all - tiles[i], slices, tiles[i] * sp, per);
+      t += output_time(tk, GEMM_TN, 1, mn - mni, t) + output_time(tk, GEMM_TN, sp, mni, t);
+      if (t < best) { best = t; *plan = TnGroupPlan{i, sp, per}; }
+    }
+  }
+  if (time) *time = best;
+  return true;
+}
+
+}  // namespace
+
+double gemm_mfma_tn_group_time(const GemmCall* w, int n, size_t scratch_bytes) {
+  TnGroupPlan plan;
+  double t;
+  return tn_group_plan(w, n, scratch_bytes, &plan, &t) ? t : -1.0;
+}
+
+bm_status gemm_mfma_tn_group(const GemmCall* w, int n, void* scratch, size_t scratch_bytes, hipStream_t st) {
+  TnGroupPlan plan;
+  if (!tn_group_plan(w, n, scratch ? scratch_bytes : 0, &plan, nullptr)) {
+    set_error("gemm: these weight gradients share no launch");
+    return BM_ERR_UNSUPPORTED;
+  }
+  TnParts g;
+  g.n = 0;
+  int first = 0;
+  size_t part = 0;
+  auto add = [&](int i, int splits, int per) {
+    const Plan pl{256, 256, cdiv(w[i].M, 256), cdiv(w[i].N, 256), splits, per * BK};
+    g.part[g.n++] = tn_part(w[i], pl, (float*)((char*)scratch + part), first);
+    first += pl.tiles_m * pl.tiles_n * splits;
+    if (splits > 1) part += align_up((size_t)splits * w[i].M * w[i].N * sizeof(float), 256);
+  };
+  for (int i = 0; i < n; ++i)
+    if (i != plan.split_part && plan.split_part != ALL_PARTS) add(i, 1, cdiv(w[i].K, BK));
+  g.one_list = first <= NUM_CU ? first : 0;
+  for (int i = 0; i < n; ++i)                                 // the shorter workgroups last
+    if (i == plan.split_part || plan.split_part == ALL_PARTS) add(i, plan.splits, plan.per);
+  return launch_tn_parts(g, st);
+}
+
+double gemm_mfma_time(int layout, const GemmCall& w, size_t scratch_bytes) {
+  double t;
+  make_plan(layout, w.M, w.N, w.K, scratch_bytes, true, &t);
+  return t;
 }
 
 namespace {
@@ -687,7 +808,7 @@ namespace {
 // in one round, by the same model: the longest chain of slices at the rate of a nearly empty chip, or all slices at the
 // rate of a full one.  false: separate launches are expected to be as fast (or the pair has more tiles than slots: from
 // there on larger tiles are the better ones).
-bool joint_plan(const GemmCall& nn, const GemmCall& tn, size_t scratch_bytes, Plan* pn, Plan* pt) {
+bool joint_plan(const GemmCall& nn, const GemmCall& tn, size_t scratch_bytes, Plan* pn, Plan* pt, double* time = nullptr) {
   const TileKind& tk = TILE_KINDS[3];
   const GemmEpilogue none;
   if (!gemm_mfma_supported(GEMM_NN, BM_DTYPE_BF16, nn.M, nn.N, nn.K, nn.lda, nn.ldb, nn.ldc, none) ||
@@ -723,6 +844,7 @@ bool joint_plan(const GemmCall& nn, const GemmCall& tn, size_t scratch_bytes, Pl
       }
     }
   }
+  if (time) *time = best;
   return found;
 }
 
@@ -738,7 +860,6 @@ GemmParams plain_params(const GemmCall& g, const Plan& pl, float* partial) {
   p.out_fp32 = 0;
   p.xcd_split = xcd_split_possible(pl.tiles_m * pl.tiles_n, pl.splits) ? 1 : 0;
   p.tile_group = nullptr; p.group_rows = nullptr; p.b_group_stride = 0; p.c_group_stride = 0; p.grid_groups = 1;
-  p.pair_wgs0 = 0; p.second = {};
   return p;
 }
 
@@ -761,6 +882,12 @@ bm_status launch_joint(const GemmParams& nn, const GemmParams& tn, hipStream_t s
 
 size_t gemm_nn_tn_scratch_bytes(size_t nn, size_t tn, int dtype) {
   return dtype == BM_DTYPE_BF16 ? std::min(nn + tn, JOINT_PARTIAL_BYTES) : 0;
+}
+
+double gemm_mfma_nn_tn_time(const GemmCall& nn, const GemmCall& tn, size_t scratch_bytes) {
+  Plan pn, pt;
+  double t;
+  return joint_plan(nn, tn, scratch_bytes, &pn, &pt, &t) ? t : -1.0;
 }
 
 bool gemm_mfma_nn_tn_ranges(const GemmCall& nn, const GemmCall& tn, size_t scratch_bytes, int* nn_ranges, int* tn_ranges) {
@@ -818,7 +945,7 @@ bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int 
   p.bias = nullptr; p.residual = nullptr; p.partial = nullptr;
   p.M = M; p.N = N; p.K = K; p.lda = lda; p.ldb = ldb; p.ldc = ldc;
   p.tiles_m = cdiv(M, 128); p.tiles_n = cdiv(N, 128); p.splits = 1; p.k_per_split = cdiv(K, BK) * BK;
-  p.out_fp32 = 0; p.xcd_split = 0; p.pair_wgs0 = 0; p.second = {};
+  p.out_fp32 = 0; p.xcd_split = 0;
   p.tile_group = layout == GEMM_TN ? nullptr : g.tile_group;
   p.group_rows = layout == GEMM_TN ? g.group_rows : nullptr;
   p.b_group_stride = g.b_stride; p.c_group_stride = g.c_stride;

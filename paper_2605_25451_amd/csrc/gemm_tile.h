@@ -32,13 +32,17 @@ struct GemmParams {
   const int32_t* group_rows;
   long b_group_stride, c_group_stride;
   int grid_groups;              // host: workgroups = tiles * splits * grid_groups (>= 1)
-  // paired launch: workgroups pair_wgs0.. of the grid work on a second problem of the same
-  // kind and the same K (two weight gradients that each leave CUs idle share one grid)
-  int pair_wgs0;                // 0: one problem
-  struct Second {
-    const bf16_t* A; const bf16_t* B; void* C; float* partial;
-    int M, N, lda, ldb, ldc, tiles_m, tiles_n, splits, k_per_split, xcd_split;
-  } second;
+};
+
+// Weight gradients that share a grid: the parts' workgroups lie behind one another, first those of parts with one k range.
+struct TnParts {
+  static constexpr int MAX = 4;
+  struct Part {
+    const bf16_t *A, *B; float *C, *partial;
+    int M, N, K, lda, ldb, ldc, tiles_m, tiles_n, splits, k_per_split, xcd_split, first_wg;
+  } part[MAX];
+  int n, one_list;              // one_list: workgroups of the parts with one k range, if their tiles lie in one list
+  int wgs() const { const Part& l = part[n - 1]; return l.first_wg + l.tiles_m * l.tiles_n * l.splits; }
 };
 
 // acc += a b^T with v_mfma_f32_16x16x32_bf16.  Written as an asm statement that ties the
@@ -66,11 +70,14 @@ __device__ inline void static_for(F&& f) {
   }
 }
 
-// XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs, so give
-// each XCD a contiguous run of tiles, walked in column-major groups of GROUP_M
-// tile rows (operand reuse in that XCD's L2).
+// XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs, so give each XCD a contiguous run of the tiles (the
+// first total % 8 of them one tile more), walked in column-major groups of GROUP_M tile rows (operand reuse in that XCD's L2).
+__device__ inline int xcd_run(int pid, int total) {
+  const int xcd = pid % 8;
+  return xcd * (total / 8) + min(xcd, total % 8) + pid / 8;
+}
+template <int GROUP_M>
 __device__ inline void grouped_tile(int id, int tiles_m, int tiles_n, int* tm, int* tn) {
-  constexpr int GROUP_M = 8;
   const int per_group = GROUP_M * tiles_n;
   const int g = id / per_group;
   const int first_m = g * GROUP_M;
@@ -89,22 +96,11 @@ __device__ inline void split_tile_of_block(int pid, int tiles, int splits, int t
   const int G = 8 / splits;
   const int xcd = pid & 7, local = pid >> 3;
   *split = xcd / G;
-  grouped_tile((xcd % G) * (tiles / G) + local, tiles_m, tiles_n, tm, tn);
+  grouped_tile<8>((xcd % G) * (tiles / G) + local, tiles_m, tiles_n, tm, tn);
 }
 
 __device__ inline void tile_of_block(int pid, int total, int tiles_m, int tiles_n, int* tm, int* tn) {
-  constexpr int XCDS = 8, GROUP_M = 4;     // measured: 4 tile rows per group is a little ahead of 8, 2 and 16
-  // workgroup pid runs on XCD pid % 8: give every XCD one contiguous run of tiles (the first
-  // total % 8 of them one tile more)
-  const int xcd = pid % XCDS;
-  const int id = xcd * (total / XCDS) + min(xcd, total % XCDS) + pid / XCDS;
-  const int per_group = GROUP_M * tiles_n;
-  const int g = id / per_group;
-  const int first_m = g * GROUP_M;
-  const int gsize = min(tiles_m - first_m, GROUP_M);
-  const int in = id % per_group;
-  *tm = first_m + in % gsize;
-  *tn = in / gsize;
+  grouped_tile<4>(xcd_run(pid, total), tiles_m, tiles_n, tm, tn);     // measured: 4 tile rows per group is a little ahead of 8, 2 and 16
 }
 
 // What the epilogue does with the product, fixed at compile time: one straight run of instructions
@@ -117,7 +113,7 @@ enum { EPI_PLAIN = 0,     // C = acc (+bias), bf16 or fp32
 
 
 // Where a workgroup's tile lies: operands (B of the tile's group), first row and column, k range.
-// `p` is taken over by the second problem of a paired launch.  kbeg == kend: nothing to do.
+// kbeg == kend: nothing to do.
 // All values are workgroup-uniform.
 struct TileJob {
   const bf16_t *A, *B;
@@ -126,20 +122,9 @@ struct TileJob {
 };
 
 template <int BM, int BN>
-__device__ inline TileJob locate_tile(GemmParams& p, int pid) {
+__device__ inline TileJob tile_job(const GemmParams& p, int split, int tm, int tn) {
   TileJob t;
-  if (p.pair_wgs0 > 0 && pid >= p.pair_wgs0) {
-    pid -= p.pair_wgs0;
-    p.A = p.second.A; p.B = p.second.B; p.C = p.second.C; p.partial = p.second.partial;
-    p.M = p.second.M; p.N = p.second.N; p.lda = p.second.lda; p.ldb = p.second.ldb; p.ldc = p.second.ldc;
-    p.tiles_m = p.second.tiles_m; p.tiles_n = p.second.tiles_n; p.splits = p.second.splits;
-    p.k_per_split = p.second.k_per_split; p.xcd_split = p.second.xcd_split;
-  }
-  const int tiles = p.tiles_m * p.tiles_n;
-  int tm;
-  t.split = pid / tiles;
-  if (p.xcd_split) split_tile_of_block(pid, tiles, p.splits, p.tiles_m, p.tiles_n, &t.split, &tm, &t.tn);
-  else tile_of_block(pid % tiles, tiles, p.tiles_m, p.tiles_n, &tm, &t.tn);
+  t.split = split; t.tn = tn;
   t.m0 = tm * BM; t.n0 = t.tn * BN;
   t.kbeg = t.split * p.k_per_split;
   t.kend = min(p.K, t.kbeg + p.k_per_split);
@@ -157,6 +142,15 @@ __device__ inline TileJob locate_tile(GemmParams& p, int pid) {
     else t.B += (long)g * p.b_group_stride;
   }
   return t;
+}
+
+template <int BM, int BN>
+__device__ inline TileJob locate_tile(const GemmParams& p, int pid) {
+  const int tiles = p.tiles_m * p.tiles_n;
+  int split = pid / tiles, tm, tn;
+  if (p.xcd_split) split_tile_of_block(pid, tiles, p.splits, p.tiles_m, p.tiles_n, &split, &tm, &tn);
+  else tile_of_block(pid % tiles, tiles, p.tiles_m, p.tiles_n, &tm, &tn);
+  return tile_job<BM, BN>(p, split, tm, tn);
 }
 
 // The accumulators behind the last MFMAs, readable: the compiler does not know that the asm statements are MFMAs and
@@ -407,5 +401,7 @@ __device__ inline void gemm_epilogue(const GemmParams& p, f32x4 (&acc)[FM][FN], 
 
 // gemm_alt.hip: the tile (256x256, 128x256 or 256x128) of a plan
 bm_status launch_gemm_alt(int layout, int bm, int bn, const GemmParams& p, hipStream_t st);
+// weight gradients in one grid of 256x256 tiles
+bm_status launch_gemm_alt_tn_parts(const TnParts& g, hipStream_t st);
 
 }  // namespace bm
