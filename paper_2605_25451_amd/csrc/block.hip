@@ -72,6 +72,7 @@ Saved layout_saved(const Dims& m, void* base) {
     s.moe.row_gate = a.take<float>((size_t)m.cap * sizeof(float));
     s.moe.tile_group = a.take<int32_t>((size_t)(m.cap / MOE_PAD) * sizeof(int32_t));
     s.moe.expert_rows = a.take<int32_t>((size_t)(m.E + 1) * sizeof(int32_t));
+    s.moe.row_tiles = a.take<int32_t>((size_t)(moe_row_tiles_cap(m.cap, m.E) + 1) * sizeof(int32_t));
     s.moe_y = a.take<char>((size_t)m.cap * m.d * m.es);
   }
   s.mod = nullptr; s.attn = nullptr; s.m = nullptr;
@@ -423,6 +424,7 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
     }
     GemmGroups g;
     g.tile_group = sv.moe.tile_group; g.routed_rows = (long)T * m.k;
+    g.row_tiles = sv.moe.row_tiles; g.row_tiles_cap = moe_row_tiles_cap(m.cap, m.E);
     {
       ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
       BM_RETURN_IF(moe_route(ws.logits, T, m.E, m.k, sv.moe.probs, sv.moe.idx, sv.moe.gate, st));
@@ -519,6 +521,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     // ---- mixture of experts (dm = dy: no gate sits on this branch)
     GemmGroups g;
     g.tile_group = sv.moe.tile_group; g.group_rows = sv.moe.expert_rows; g.n_groups = m.E;
+    g.row_tiles = sv.moe.row_tiles; g.row_tiles_cap = moe_row_tiles_cap(m.cap, m.E);
     g.routed_rows = (long)T * m.k;
     {
       ProfScope _p(PROF_ELEMENTWISE, 0.0, st);

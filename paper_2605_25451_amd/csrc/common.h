@@ -186,6 +186,8 @@ constexpr int MOE_PAD = 128;
 struct GemmGroups {
   const int32_t* tile_group = nullptr;   // dev [rows / MOE_PAD]     (NT, NN)
   const int32_t* group_rows = nullptr;   // dev [n_groups + 1]       (TN)
+  const int32_t* row_tiles = nullptr;    // dev [1 + row_tiles_cap]  (NT, NN): their number, then for each twice its first row block,
+  int row_tiles_cap = 0;                 //   plus one where it holds the next block of the same group as well
   int n_groups = 0;
   long b_stride = 0;                     // elements between the B matrices of two groups (NT, NN)
   long c_stride = 0;                     // elements between the C matrices of two groups (TN)
@@ -240,8 +242,10 @@ struct MoeTables {
   float* row_gate = nullptr;      // [cap] gate of a row
   int32_t* tile_group = nullptr;  // [cap / MOE_PAD] expert of a row block, -1 past the end
   int32_t* expert_rows = nullptr; // [E + 1] padded segment offsets
+  int32_t* row_tiles = nullptr;   // [1 + moe_row_tiles_cap] see GemmGroups
 };
 int moe_row_capacity(int T, int E, int k);
+inline int moe_row_tiles_cap(int cap, int E) { return (cap / MOE_PAD + E) / 2; }
 size_t moe_layout_scratch_bytes(int T, int E);
 bm_status moe_check(int E, int k, int d, int dtype);
 bm_status moe_route(const float* logits, int T, int E, int k, float* probs, int32_t* idx, float* gate,

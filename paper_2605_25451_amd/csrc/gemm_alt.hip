@@ -170,7 +170,7 @@ __device__ inline void clear(f32x4 (&acc)[FM][FN]) {
 // of A with B, and its second half, are re-filled as soon as both groups have read them: loads are
 // in flight for more than a slice (4 to 5 phases of 512 clocks).
 template <bool B_TR, int EPI, bool CUT>
-__global__ __launch_bounds__(THREADS, 2) void gemm_alt256_kernel(GemmParams p) {
+__device__ __forceinline__ void alt256_tile(const GemmParams& p, const TileJob& job) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using RegA = Region<128, false>;
   using RegB = Region<256, B_TR>;
@@ -178,7 +178,6 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_kernel(GemmParams p) {
   constexpr int LATE = RegA::LOADS, EARLY = RegA::LOADS + RegB::LOADS;      // loads of a slice's two parts
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 2, wn = wave & 3;                                   // wm is the group
-  const TileJob job = locate_tile<256, 256>(p, blockIdx.x);
   if (job.kbeg >= job.kend) return;
   const int m0 = job.m0, n0 = job.n0, n = (job.kend - job.kbeg + BK - 1) / BK;
   const int k_left = job.kend - job.kbeg - (n - 1) * BK;                     // of the last slice
@@ -431,7 +430,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_tn_parts_kernel(TnPart
 // ---- 128x256 and 256x128 tiles: each wavefront owns 64x64 and a slice is one phase per group.  LDS holds
 // three slices; the loads of slice j+2 go out while slice j is read.
 template <int BM, int BN, bool A_TR, bool B_TR, int EPI, bool CUT>
-__global__ __launch_bounds__(THREADS, 2) void gemm_alt128_kernel(GemmParams p) {
+__device__ __forceinline__ void alt128_tile(const GemmParams& p, const TileJob& job) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using RegA = Region<BM, A_TR>;
   using RegB = Region<BN, B_TR>;
@@ -440,7 +439,6 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt128_kernel(GemmParams p) {
   constexpr int WN = BN / 64;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave / WN, wn = wave % WN, group = wave >> 2;
-  const TileJob job = locate_tile<BM, BN>(p, blockIdx.x);
   if (job.kbeg >= job.kend) return;
   const int m0 = job.m0, n0 = job.n0, n = (job.kend - job.kbeg + BK - 1) / BK;
   const int k_left = job.kend - job.kbeg - (n - 1) * BK;
@@ -525,6 +523,37 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt128_kernel(GemmParams p) {
                            });
 }
 
+template <bool B_TR, int EPI, bool CUT>
+__global__ __launch_bounds__(THREADS, 2) void gemm_alt256_kernel(GemmParams p) {
+  alt256_tile<B_TR, EPI, CUT>(p, locate_tile<256, 256>(p, blockIdx.x));
+}
+
+template <int BM, int BN, bool A_TR, bool B_TR, int EPI, bool CUT>
+__global__ __launch_bounds__(THREADS, 2) void gemm_alt128_kernel(GemmParams p) {
+  alt128_tile<BM, BN, A_TR, B_TR, EPI, CUT>(p, locate_tile<BM, BN>(p, blockIdx.x));
+}
+
+// Grouped NT and NN (experts): two row blocks of a group share a 256x256 tile, the last one of an odd number takes 128x256.  How many
+// tiles there are is known on the device only; the XCDs share those, not the capacity, whose end is empty (a tenth of
+// it with 128 experts of 512 rows, all in the last XCD's run).  8192 tokens, 8 of 128 experts, against one 128x256 tile per row
+// block: up 1536x2048 with SwiGLU 575 -> 460 us, its input gradient 565 -> 440, down 2048x768 330 -> 255, its input gradient with
+// SwiGLU 350 -> 305; the outputs are the same bit for bit.  Bound by HBM (1.4 GB of weights and rows, 290 us) next to the MFMAs (300).
+template <bool B_TR, int EPI, bool CUT>
+__global__ __launch_bounds__(THREADS, 2) void gemm_alt_groups_kernel(GemmParams p) {
+  const int row_tiles = p.row_tiles[0], total = row_tiles * p.tiles_n;
+  if ((int)blockIdx.x >= total) return;
+  int tm, tn;
+  grouped_tile<4>(xcd_run(blockIdx.x, total), row_tiles, p.tiles_n, &tm, &tn);
+  const int tile = p.row_tiles[1 + tm], block = tile >> 1;
+  TileJob job;
+  job.A = p.A; job.B = p.B + (long)p.tile_group[block] * p.b_group_stride;
+  job.m0 = block * MOE_PAD; job.n0 = tn * 256; job.tn = tn;
+  job.kbeg = 0; job.kend = p.K; job.split = 0; job.c_off = 0;
+  p.M = job.m0 + (tile & 1 ? 2 : 1) * MOE_PAD;
+  if (tile & 1) alt256_tile<B_TR, EPI, CUT>(p, job);
+  else alt128_tile<MOE_PAD, 256, false, B_TR, EPI, CUT>(p, job);
+}
+
 template <int BM, int BN, bool A_TR, bool B_TR, int EPI, bool CUT>
 bm_status launch_one(const GemmParams& p, hipStream_t st) {
   constexpr bool LARGE = BM == 256 && BN == 256;
@@ -541,6 +570,24 @@ bm_status launch_one(const GemmParams& p, hipStream_t st) {
   hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n * p.splits * p.grid_groups), dim3(THREADS), lds, st, p);
   BM_CHECK_LAUNCH("gemm_alt");
   return BM_OK;
+}
+
+template <bool B_TR, int EPI, bool CUT>
+bm_status launch_groups(const GemmParams& p, hipStream_t st) {
+  constexpr size_t lds = (size_t)3 * (128 + 256) * BK * sizeof(bf16_t);
+  auto kern = gemm_alt_groups_kernel<B_TR, EPI, CUT>;
+  static std::atomic<bool> attr_done{false};
+  if (!attr_done.load(std::memory_order_relaxed)) {
+    BM_CHECK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    attr_done.store(true, std::memory_order_relaxed);
+  }
+  hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n), dim3(THREADS), lds, st, p);
+  BM_CHECK_LAUNCH("gemm_alt_groups");
+  return BM_OK;
+}
+template <bool B_TR, int EPI>
+bm_status launch_groups_cut(const GemmParams& p, hipStream_t st) {
+  return p.K % BK ? launch_groups<B_TR, EPI, true>(p, st) : launch_groups<B_TR, EPI, false>(p, st);
 }
 
 template <bool CUT>
@@ -585,6 +632,11 @@ bm_status launch_gemm_alt(int layout, int bm, int bn, const GemmParams& p, hipSt
   if (bm == 256 && bn == 256) return launch_tile<256, 256>(layout, p, st);
   if (bm == 256 && bn == 128) return launch_tile<256, 128>(layout, p, st);
   return launch_tile<128, 256>(layout, p, st);
+}
+
+bm_status launch_gemm_alt_groups(int layout, const GemmParams& p, hipStream_t st) {
+  if (layout == GEMM_NT) return p.swf_a ? launch_groups_cut<false, EPI_SWIGLU_FWD>(p, st) : launch_groups_cut<false, EPI_PLAIN>(p, st);
+  return p.sw_up ? launch_groups_cut<true, EPI_SWIGLU_BWD>(p, st) : launch_groups_cut<true, EPI_PLAIN>(p, st);
 }
 
 bm_status launch_gemm_alt_tn_parts(const TnParts& g, hipStream_t st) {

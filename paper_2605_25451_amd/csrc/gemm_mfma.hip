@@ -583,7 +583,7 @@ bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, con
     set_error("gemm: the SwiGLU forward epilogue needs the NT layout, N a multiple of 256 and no bias");
     return BM_ERR_INVALID_ARG;
   }
-  p.tile_group = nullptr; p.group_rows = nullptr; p.b_group_stride = 0; p.c_group_stride = 0;
+  p.tile_group = nullptr; p.group_rows = nullptr; p.row_tiles = nullptr; p.b_group_stride = 0; p.c_group_stride = 0;
   p.grid_groups = 1;
   p.xcd_split = xcd_split_possible(pl.tiles_m * pl.tiles_n, pl.splits) ? 1 : 0;
   BM_RETURN_IF(pl.bm == 128 && pl.bn == 128 ? launch_small(layout, p, st) : launch_gemm_alt(layout, pl.bm, pl.bn, p, st));
@@ -859,7 +859,7 @@ GemmParams plain_params(const GemmCall& g, const Plan& pl, float* partial) {
   p.tiles_m = pl.tiles_m; p.tiles_n = pl.tiles_n; p.splits = pl.splits; p.k_per_split = pl.k_per_split;
   p.out_fp32 = 0;
   p.xcd_split = xcd_split_possible(pl.tiles_m * pl.tiles_n, pl.splits) ? 1 : 0;
-  p.tile_group = nullptr; p.group_rows = nullptr; p.b_group_stride = 0; p.c_group_stride = 0; p.grid_groups = 1;
+  p.tile_group = nullptr; p.group_rows = nullptr; p.row_tiles = nullptr; p.b_group_stride = 0; p.c_group_stride = 0; p.grid_groups = 1;
   return p;
 }
 
@@ -935,7 +935,7 @@ bool gemm_mfma_grouped_supported(int layout, int dtype, int M, int N, int K, int
   return K >= 64 && K % 8 == 0 && N % 8 == 0 && ldc % 8 == 0 && M % MOE_PAD == 0;
 }
 
-// 128x128 tiles: a row tile is one MOE_PAD block, so it never straddles two groups.
+// A row tile is one MOE_PAD block or two of the same group.
 bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int lda, const void* B,
                             int ldb, void* C, int ldc, const GemmGroups& g, hipStream_t st,
                             const GemmEpilogue* epi) {
@@ -948,10 +948,11 @@ bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int 
   p.out_fp32 = 0; p.xcd_split = 0;
   p.tile_group = layout == GEMM_TN ? nullptr : g.tile_group;
   p.group_rows = layout == GEMM_TN ? g.group_rows : nullptr;
+  p.row_tiles = layout == GEMM_TN ? nullptr : g.row_tiles;
   p.b_group_stride = g.b_stride; p.c_group_stride = g.c_stride;
   p.grid_groups = layout == GEMM_TN ? g.n_groups : 1;
   if (epi) {
-    // the SwiGLU epilogues ride on the 128x256 tiles (a tile gathers its weight rows per expert
+    // the SwiGLU epilogues ride on tiles of 256 columns (a tile gathers its weight rows per expert
     // exactly as the dense kernel does per matrix)
     const bool fwd = epi->swiglu_fwd_a != nullptr, bwd = epi->swiglu_up != nullptr;
     if (epi->bias || epi->residual || epi->out_fp32 || fwd == bwd || N % 256 || (fwd && layout != GEMM_NT) ||
@@ -962,15 +963,13 @@ bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int 
     p.sw_up = (const bf16_t*)epi->swiglu_up; p.sw_dup = (bf16_t*)epi->swiglu_dup; p.sw_a = (bf16_t*)epi->swiglu_a;
     p.swf_a = (bf16_t*)epi->swiglu_fwd_a;
   }
-  if ((layout == GEMM_TN ? p.group_rows == nullptr || g.n_groups < 1 : p.tile_group == nullptr)) {
+  if ((layout == GEMM_TN ? p.group_rows == nullptr || g.n_groups < 1 : p.tile_group == nullptr || p.row_tiles == nullptr)) {
     set_error("grouped gemm: group tables are NULL");
     return BM_ERR_INVALID_ARG;
   }
-  // row tiles are pinned to 128 rows (one MOE_PAD block); 256 columns per tile where the output is
-  // wide enough: per flop a 128x256 tile writes and reads a quarter less LDS than two 128x128 ones
   if (layout != GEMM_TN && N >= 256) {
-    p.tiles_n = cdiv(N, 256);
-    return launch_gemm_alt(layout, 128, 256, p, st);
+    p.tiles_m = g.row_tiles_cap; p.tiles_n = cdiv(N, 256);
+    return launch_gemm_alt_groups(layout, p, st);
   }
   if (layout != GEMM_TN) return launch_small(layout, p, st);
   // weight gradient: rows are the contraction index, so the output tile is free; a group's

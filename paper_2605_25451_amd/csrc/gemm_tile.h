@@ -30,6 +30,7 @@ struct GemmParams {
   // grouped problems (see GemmGroups); all null / zero otherwise
   const int32_t* tile_group;
   const int32_t* group_rows;
+  const int32_t* row_tiles;
   long b_group_stride, c_group_stride;
   int grid_groups;              // host: workgroups = tiles * splits * grid_groups (>= 1)
 };
@@ -401,6 +402,8 @@ __device__ inline void gemm_epilogue(const GemmParams& p, f32x4 (&acc)[FM][FN], 
 
 // gemm_alt.hip: the tile (256x256, 128x256 or 256x128) of a plan
 bm_status launch_gemm_alt(int layout, int bm, int bn, const GemmParams& p, hipStream_t st);
+// grouped NT and NN on the row tiles that p lists; tiles_m: their capacity
+bm_status launch_gemm_alt_groups(int layout, const GemmParams& p, hipStream_t st);
 // weight gradients in one grid of 256x256 tiles
 bm_status launch_gemm_alt_tn_parts(const TnParts& g, hipStream_t st);
 

@@ -113,9 +113,10 @@ __global__ __launch_bounds__(MOE_CHUNK) void moe_count_kernel(const int32_t* __r
 __global__ __launch_bounds__(256) void moe_offsets_kernel(const int32_t* __restrict__ counts, int nblk, int E,
                                                           int32_t* __restrict__ base,
                                                           int32_t* __restrict__ expert_rows,
-                                                          int32_t* __restrict__ tile_group, int n_tiles) {
+                                                          int32_t* __restrict__ tile_group, int n_tiles,
+                                                          int32_t* __restrict__ row_tiles) {
   static_assert(MOE_MAX_E <= 256, "one thread per expert");
-  __shared__ int wave_rows[4];
+  __shared__ int wave_rows[4], wave_tiles[4];
   const int e = threadIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int run = 0;
   if (e < E) {
@@ -132,20 +133,24 @@ __global__ __launch_bounds__(256) void moe_offsets_kernel(const int32_t* __restr
     }
   }
   const int padded = (run + MOE_PAD - 1) / MOE_PAD * MOE_PAD;
-  int sum = padded;                                       // inclusive over the wavefront
+  const int own_tiles = (padded / MOE_PAD + 1) / 2;       // of two row blocks, the last of one where they are odd
+  int sum = padded, tiles = own_tiles;                    // inclusive over the wavefront
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
-    const int below = __shfl_up(sum, off, WAVE);
-    if (lane >= off) sum += below;
+    const int below = __shfl_up(sum, off, WAVE), tiles_below = __shfl_up(tiles, off, WAVE);
+    if (lane >= off) { sum += below; tiles += tiles_below; }
   }
-  if (lane == 63) wave_rows[wave] = sum;
+  if (lane == 63) { wave_rows[wave] = sum; wave_tiles[wave] = tiles; }
   __syncthreads();
-  int start = sum - padded, all = 0;
+  int start = sum - padded, all = 0, tile0 = tiles - own_tiles, all_tiles = 0;
 #pragma unroll
   for (int w = 0; w < 4; ++w) {
-    if (w < wave) start += wave_rows[w];
-    all += wave_rows[w];
+    if (w < wave) { start += wave_rows[w]; tile0 += wave_tiles[w]; }
+    all += wave_rows[w]; all_tiles += wave_tiles[w];
   }
+  if (e == 0) row_tiles[0] = all_tiles;
+  for (int t = 0; t < own_tiles; ++t)
+    row_tiles[1 + tile0 + t] = 2 * (start / MOE_PAD + 2 * t) + (2 * t + 1 < padded / MOE_PAD ? 1 : 0);
   if (e < E) {
     expert_rows[e] = start;
     for (int tile = start / MOE_PAD; tile < (start + padded) / MOE_PAD && tile < n_tiles; ++tile) tile_group[tile] = e;
@@ -380,7 +385,7 @@ bm_status moe_layout(const MoeTables& m, int T, int E, int k, void* scratch, hip
   int32_t* base = (int32_t*)((char*)scratch + align_up((size_t)nblk * E * sizeof(int32_t), 256));
   hipLaunchKernelGGL(moe_count_kernel, dim3(nblk), dim3(MOE_CHUNK), 0, st, m.idx, T, E, k, counts);
   hipLaunchKernelGGL(moe_offsets_kernel, dim3(1), dim3(256), 0, st, counts, nblk, E, base, m.expert_rows,
-                     m.tile_group, m.cap / MOE_PAD);
+                     m.tile_group, m.cap / MOE_PAD, m.row_tiles);
   hipLaunchKernelGGL(moe_fill_i32_kernel, dim3(cdiv(m.cap, 256)), dim3(256), 0, st, m.row_token, -1, (long)m.cap);
   hipLaunchKernelGGL(moe_slot_kernel, dim3(nblk), dim3(MOE_CHUNK), 0, st, m.idx, m.gate, T, E, k, base,
                      m.expert_rows, m.slot, m.row_token, m.row_gate, m.cap);
