@@ -270,7 +270,8 @@ bm_status bm_probe_lds(int32_t what, int32_t iters, const void* src_dev, size_t 
                        void* hip_stream);
 bm_status bm_probe_issue(int32_t n_valu, int32_t iters, float* out_dev, void* hip_stream);
 /* What bm_gemm launches for a bf16 product with contiguous rows and that many scratch bytes (host only, nothing
- * is launched): rows and columns of an output tile and the number of k ranges; all 0 where the product goes
+ * is launched): rows and columns of an output tile and the number of k ranges (384 rows: tiles of
+ * 256 rows and, for the last rows, of 128); all 0 where the product goes
  * to the kernels for any shape instead. */
 bm_status bm_probe_gemm_plan(int32_t layout, int32_t M, int32_t N, int32_t K, size_t scratch_bytes,
                              int32_t* tile_m /* host */, int32_t* tile_n /* host */, int32_t* k_ranges /* host */);

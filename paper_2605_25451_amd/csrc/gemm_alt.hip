@@ -533,6 +533,22 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt128_kernel(GemmParams p) {
   alt128_tile<BM, BN, A_TR, B_TR, EPI, CUT>(p, locate_tile<BM, BN>(p, blockIdx.x));
 }
 
+// Rows on tiles of two heights: the 256x256 tiles that fill whole rounds, and the rows that are left on 128x256, which end a
+// round earlier than another one of 256x256 would (see mixed_rows()).
+template <bool B_TR, int EPI, bool CUT>
+__global__ __launch_bounds__(THREADS, 2) void gemm_alt_mixed_kernel(GemmParams p) {
+  const int big = p.big_rows * p.tiles_n;
+  int tm, tn;
+  if ((int)blockIdx.x < big) {
+    tile_of_block(blockIdx.x, big, p.big_rows, p.tiles_n, &tm, &tn);
+    alt256_tile<B_TR, EPI, CUT>(p, tile_job<256, 256>(p, 0, tm, tn));
+  } else {
+    const int rows = p.tiles_m - p.big_rows;
+    tile_of_block((int)blockIdx.x - big, rows * p.tiles_n, rows, p.tiles_n, &tm, &tn);
+    alt128_tile<128, 256, false, B_TR, EPI, CUT>(p, tile_job<128, 256>(p, 0, 2 * p.big_rows + tm, tn));
+  }
+}
+
 // Grouped NT and NN (experts): two row blocks of a group share a 256x256 tile, the last one of an odd number takes 128x256.  How many
 // tiles there are is known on the device only; the XCDs share those, not the capacity, whose end is empty (a tenth of
 // it with 128 experts of 512 rows, all in the last XCD's run).  8192 tokens, 8 of 128 experts, against one 128x256 tile per row
@@ -572,22 +588,25 @@ bm_status launch_one(const GemmParams& p, hipStream_t st) {
   return BM_OK;
 }
 
-template <bool B_TR, int EPI, bool CUT>
-bm_status launch_groups(const GemmParams& p, hipStream_t st) {
+// kernels that hold both a 256x256 and a 128x256 tile
+template <bool GROUPS, bool B_TR, int EPI, bool CUT>
+bm_status launch_two_heights(const GemmParams& p, hipStream_t st) {
   constexpr size_t lds = (size_t)3 * (128 + 256) * BK * sizeof(bf16_t);
-  auto kern = gemm_alt_groups_kernel<B_TR, EPI, CUT>;
+  void (*kern)(GemmParams);
+  if constexpr (GROUPS) kern = gemm_alt_groups_kernel<B_TR, EPI, CUT>;
+  else kern = gemm_alt_mixed_kernel<B_TR, EPI, CUT>;
   static std::atomic<bool> attr_done{false};
   if (!attr_done.load(std::memory_order_relaxed)) {
     BM_CHECK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     attr_done.store(true, std::memory_order_relaxed);
   }
   hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n), dim3(THREADS), lds, st, p);
-  BM_CHECK_LAUNCH("gemm_alt_groups");
+  BM_CHECK_LAUNCH("gemm_alt_two_heights");
   return BM_OK;
 }
-template <bool B_TR, int EPI>
-bm_status launch_groups_cut(const GemmParams& p, hipStream_t st) {
-  return p.K % BK ? launch_groups<B_TR, EPI, true>(p, st) : launch_groups<B_TR, EPI, false>(p, st);
+template <bool GROUPS, bool B_TR, int EPI>
+bm_status launch_two_heights_cut(const GemmParams& p, hipStream_t st) {
+  return p.K % BK ? launch_two_heights<GROUPS, B_TR, EPI, true>(p, st) : launch_two_heights<GROUPS, B_TR, EPI, false>(p, st);
 }
 
 template <bool CUT>
@@ -635,8 +654,18 @@ bm_status launch_gemm_alt(int layout, int bm, int bn, const GemmParams& p, hipSt
 }
 
 bm_status launch_gemm_alt_groups(int layout, const GemmParams& p, hipStream_t st) {
-  if (layout == GEMM_NT) return p.swf_a ? launch_groups_cut<false, EPI_SWIGLU_FWD>(p, st) : launch_groups_cut<false, EPI_PLAIN>(p, st);
-  return p.sw_up ? launch_groups_cut<true, EPI_SWIGLU_BWD>(p, st) : launch_groups_cut<true, EPI_PLAIN>(p, st);
+  if (layout == GEMM_NT)
+    return p.swf_a ? launch_two_heights_cut<true, false, EPI_SWIGLU_FWD>(p, st) : launch_two_heights_cut<true, false, EPI_PLAIN>(p, st);
+  return p.sw_up ? launch_two_heights_cut<true, true, EPI_SWIGLU_BWD>(p, st) : launch_two_heights_cut<true, true, EPI_PLAIN>(p, st);
+}
+
+bm_status launch_gemm_alt_mixed(int layout, const GemmParams& p, hipStream_t st) {
+  if (layout == GEMM_NT) {
+    if (p.swf_a) return launch_two_heights_cut<false, false, EPI_SWIGLU_FWD>(p, st);
+    return p.residual ? launch_two_heights_cut<false, false, EPI_RES>(p, st) : launch_two_heights_cut<false, false, EPI_PLAIN>(p, st);
+  }
+  if (p.sw_up) return launch_two_heights_cut<false, true, EPI_SWIGLU_BWD>(p, st);
+  return p.residual ? launch_two_heights_cut<false, true, EPI_RES>(p, st) : launch_two_heights_cut<false, true, EPI_PLAIN>(p, st);
 }
 
 bm_status launch_gemm_alt_tn_parts(const TnParts& g, hipStream_t st) {

@@ -398,7 +398,8 @@ __global__ __launch_bounds__(256) void splitk_finish_kernel(const float* __restr
   }
 }
 
-struct Plan { int bm, bn, tiles_m, tiles_n, splits, k_per_split; };
+// big_rows > 0: that many rows of 256x256 tiles, the other rows on 128x256 (tiles_m counts both)
+struct Plan { int bm, bn, tiles_m, tiles_n, splits, k_per_split, big_rows = 0; };
 
 constexpr int NUM_CU = 256;
 
@@ -467,6 +468,43 @@ int split_cap(int layout, int M, int N, int K) {
   return cap < 1 ? 1 : (int)std::min<long>(cap, 32);
 }
 
+// Rows on tiles of two heights: as many 256-row tiles as fill whole rounds (or all that the rows fill), the other rows on
+// 128-row tiles, which run beside the last of the former and behind them.  us against the best of the four tiles: NT 5477x3072x1024
+// 46 -> 40, 5477x4096x1024 51 -> 46, 777x22016x4096 161 -> 143, 8192x4608x1152 83 -> 76, 6352x6144x4096 244 -> 230, NN 1783x12288x3072 128 -> 110,
+// 8192x11008x4096 527 -> 516.  Of 160 products drawn from 384 to 16384 rows none that it takes is slower.
+void mixed_rows(int layout, int M, int N, int K, Plan* best, double* best_t) {
+  const TileKind &big = TILE_KINDS[0], &low = TILE_KINDS[1];
+  const int tiles_n = cdiv(N, 256), slices = cdiv(K, BK);
+  if (N < 256 || M < 256 + 128) return;
+  const bool cut = K % BK;
+  const double f = layout == GEMM_NT ? 1.0 : 1.05, fixed_cut = cut ? 1.0 : 0.0;
+  const double t_big = slices * big.t_full * f + big.t_fixed + fixed_cut * big.t_cut;
+  const double t_low = slices * low.t_full * f + low.t_fixed + fixed_cut * low.t_cut;
+  auto consider = [&](long rows) {
+    const long low_rows = cdiv(M - rows * 256, 128L);
+    if (rows < 1 || rows * 256 >= M || low_rows < 1) return;
+    const long wgs = rows * tiles_n, rest = wgs % NUM_CU;
+    long lows = low_rows * tiles_n;
+    double t = wgs / NUM_CU * t_big;
+    if (rest) {
+      // the last round of the big ones, with low ones on the CUs they leave
+      const long beside = std::min(lows, (NUM_CU - rest) * std::max(1L, (long)(t_big / t_low)));
+      t += beside > 0 && rest + beside >= NUM_CU * 3 / 4 ? t_big : grid_time(big, layout, cut, std::min<long>(NUM_CU, rest + beside), slices);
+      lows -= beside;
+    }
+    if (lows > 0) t += grid_time(low, layout, cut, lows, slices);
+    if (t < *best_t) {
+      *best_t = t;
+      *best = Plan{256, 256, (int)(rows + low_rows), tiles_n, 1, slices * BK, (int)rows};
+    }
+  };
+  const long full = M / 256, rounds = full * tiles_n / NUM_CU;
+  consider(full);
+  if (rounds >= 1) consider(rounds * NUM_CU / tiles_n);
+  if (rounds >= 2) consider((rounds - 1) * NUM_CU / tiles_n);
+  else if (tiles_n < NUM_CU) consider(full / 2);
+}
+
 Plan make_plan(int layout, int M, int N, int K, size_t partial_bytes, bool may_split, double* time = nullptr) {
   Plan best{};
   double best_t = 1e30;
@@ -489,6 +527,7 @@ Plan make_plan(int layout, int M, int N, int K, size_t partial_bytes, bool may_s
       }
     }
   }
+  if (layout != GEMM_TN) mixed_rows(layout, M, N, K, &best, &best_t);
   if (time) *time = best_t;
   return best;
 }
@@ -560,7 +599,7 @@ size_t gemm_mfma_scratch_bytes(int layout, int M, int N, int K) {
 
 void gemm_mfma_plan(int layout, int M, int N, int K, size_t scratch_bytes, int* bm, int* bn, int* splits) {
   const Plan pl = make_plan(layout, M, N, K, scratch_bytes, true);
-  *bm = pl.bm; *bn = pl.bn; *splits = pl.splits;
+  *bm = pl.big_rows > 0 ? 256 + 128 : pl.bm; *bn = pl.bn; *splits = pl.splits;
 }
 
 bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, const void* B, int ldb,
@@ -586,7 +625,9 @@ bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, con
   p.tile_group = nullptr; p.group_rows = nullptr; p.row_tiles = nullptr; p.b_group_stride = 0; p.c_group_stride = 0;
   p.grid_groups = 1;
   p.xcd_split = xcd_split_possible(pl.tiles_m * pl.tiles_n, pl.splits) ? 1 : 0;
-  BM_RETURN_IF(pl.bm == 128 && pl.bn == 128 ? launch_small(layout, p, st) : launch_gemm_alt(layout, pl.bm, pl.bn, p, st));
+  p.big_rows = pl.big_rows;
+  BM_RETURN_IF(pl.big_rows > 0 ? launch_gemm_alt_mixed(layout, p, st)
+               : pl.bm == 128 && pl.bn == 128 ? launch_small(layout, p, st) : launch_gemm_alt(layout, pl.bm, pl.bn, p, st));
   if (pl.splits > 1 && layout == GEMM_TN) {
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3(cdiv((long)M * N / 4, 256)), dim3(256), 0, st,
                        (const float*)scratch, pl.splits, M, N, (float*)C, ldc);
@@ -783,7 +824,7 @@ bm_status gemm_mfma_tn_group(const GemmCall* w, int n, void* scratch, size_t scr
   int first = 0;
   size_t part = 0;
   auto add = [&](int i, int splits, int per) {
-    const Plan pl{256, 256, cdiv(w[i].M, 256), cdiv(w[i].N, 256), splits, per * BK};
+    const Plan pl{256, 256, cdiv(w[i].M, 256), cdiv(w[i].N, 256), splits, per * BK, 0};
     g.part[g.n++] = tn_part(w[i], pl, (float*)((char*)scratch + part), first);
     first += pl.tiles_m * pl.tiles_n * splits;
     if (splits > 1) part += align_up((size_t)splits * w[i].M * w[i].N * sizeof(float), 256);

@@ -32,6 +32,7 @@ struct GemmParams {
   const int32_t* group_rows;
   const int32_t* row_tiles;
   long b_group_stride, c_group_stride;
+  int big_rows;                 // of launch_gemm_alt_mixed: rows of 256x256 tiles, before tiles_m - big_rows of 128x256
   int grid_groups;              // host: workgroups = tiles * splits * grid_groups (>= 1)
 };
 
@@ -402,6 +403,8 @@ __device__ inline void gemm_epilogue(const GemmParams& p, f32x4 (&acc)[FM][FN], 
 
 // gemm_alt.hip: the tile (256x256, 128x256 or 256x128) of a plan
 bm_status launch_gemm_alt(int layout, int bm, int bn, const GemmParams& p, hipStream_t st);
+// NT and NN: the first big_rows x 256 rows on 256x256 tiles, the others on 128x256
+bm_status launch_gemm_alt_mixed(int layout, const GemmParams& p, hipStream_t st);
 // grouped NT and NN on the row tiles that p lists; tiles_m: their capacity
 bm_status launch_gemm_alt_groups(int layout, const GemmParams& p, hipStream_t st);
 // weight gradients in one grid of 256x256 tiles
