@@ -429,15 +429,17 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
       ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
       BM_RETURN_IF(moe_route(ws.logits, T, m.E, m.k, sv.moe.probs, sv.moe.idx, sv.moe.gate, st));
       BM_RETURN_IF(moe_layout(sv.moe, T, m.E, m.k, ws.moe_ws, st));
-      BM_RETURN_IF(moe_gather(dt, ws.h, sv.moe, 0, ws.xp, m.d, T, st));
     }
     g.b_stride = (long)m.UP * m.d;
     if (c.act == BM_ACT_SWIGLU && m.UP % 256 == 0 &&
         gemm_mfma_grouped_supported(GEMM_NT, dt, m.cap, m.UP, m.d, m.d, m.d, m.UP)) {
-      // the activation rides in the epilogue of the experts' up projections
+      // the activation rides in the epilogue of the experts' up projections, which read the tokens' rows where they lie
       GemmEpilogue e; e.swiglu_fwd_a = ws.a;
-      BM_RETURN_IF(gemm_grouped(GEMM_NT, dt, m.cap, m.UP, m.d, ws.xp, m.d, w->w_up, m.d, sv.up, m.UP, g, st, &e));
+      GemmGroups from = g;
+      from.source = sv.moe.row_token; from.src_rows = T;
+      BM_RETURN_IF(gemm_grouped(GEMM_NT, dt, m.cap, m.UP, m.d, ws.h, m.d, w->w_up, m.d, sv.up, m.UP, from, st, &e));
     } else {
+      { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(moe_gather(dt, ws.h, sv.moe, 0, ws.xp, m.d, T, st)); }
       BM_RETURN_IF(gemm_grouped(GEMM_NT, dt, m.cap, m.UP, m.d, ws.xp, m.d, w->w_up, m.d, sv.up, m.UP, g, st));
       { ProfScope _p(PROF_ELEMENTWISE, (double)m.cap * (m.UP + m.F) * (double)m.es, st); BM_RETURN_IF(act_forward(dt, c.act, sv.up, ws.a, m.cap, m.F, st)); }
     }
@@ -523,24 +525,40 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     g.tile_group = sv.moe.tile_group; g.group_rows = sv.moe.expert_rows; g.n_groups = m.E;
     g.row_tiles = sv.moe.row_tiles; g.row_tiles_cap = moe_row_tiles_cap(m.cap, m.E);
     g.routed_rows = (long)T * m.k;
+    // The fused path reads dy and h2 where they lie, by the token of a routed row, and the gate goes into the epilogue (into the
+    // activation as well, so that the weight gradient of the down projection has it); else both are copied into expert order.
+    GemmEpilogue swb; swb.swiglu_up = sv.up; swb.swiglu_dup = ws.dup; swb.swiglu_a = ws.a;
+    const bool fused = c.act == BM_ACT_SWIGLU && m.F % 256 == 0 &&
+                       gemm_mfma_grouped_supported(GEMM_NN, dt, m.cap, m.F, d, d, m.F, m.F);
+    const bool in_place = fused && T <= MOE_SOURCE_ROWS && gemm_mfma_reads_source_rows(GEMM_NN, m.cap, m.F, &swb) &&
+                          gemm_mfma_grouped_supported(GEMM_TN, dt, d, m.F, m.cap, d, m.F, m.F) &&
+                          gemm_mfma_reads_source_rows(GEMM_TN, d, m.F, nullptr) &&
+                          gemm_mfma_grouped_supported(GEMM_TN, dt, m.UP, d, m.cap, m.UP, d, d) &&
+                          gemm_mfma_reads_source_rows(GEMM_TN, m.UP, d, nullptr);
+    GemmGroups from_dy = g, from_h = g;
+    if (in_place) {
+      from_dy.source = from_h.source = sv.moe.row_token;
+      from_dy.src_rows = from_h.src_rows = T;
+      from_dy.row_scale = sv.moe.row_gate;
+      from_h.source_operand = 1;
+    }
+    const void* dyp = in_place ? dm : ws.dyp;
     {
       ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
-      BM_RETURN_IF(moe_gather(dt, dm, sv.moe, 1, ws.dyp, d, T, st));            // gate * dy of the row's token
+      if (!in_place) BM_RETURN_IF(moe_gather(dt, dm, sv.moe, 1, ws.dyp, d, T, st));            // gate * dy of the row's token
       BM_RETURN_IF(moe_router_backward(dt, dm, sv.moe_y, sv.moe, ws.dlogits, T, m.E, m.k, d, st));
     }
-    g.b_stride = (long)d * m.F;
-    if (c.act == BM_ACT_SWIGLU && m.F % 256 == 0 &&
-        gemm_mfma_grouped_supported(GEMM_NN, dt, m.cap, m.F, d, d, m.F, m.F)) {
+    from_dy.b_stride = (long)d * m.F;
+    if (fused) {
       // SwiGLU backward in the epilogue of the experts' input-gradient GEMM: dA never goes to memory
-      GemmEpilogue e; e.swiglu_up = sv.up; e.swiglu_dup = ws.dup; e.swiglu_a = ws.a;
-      BM_RETURN_IF(gemm_grouped(GEMM_NN, dt, m.cap, m.F, d, ws.dyp, d, w->w_down, m.F, ws.da, m.F, g, st, &e));
+      BM_RETURN_IF(gemm_grouped(GEMM_NN, dt, m.cap, m.F, d, dyp, d, w->w_down, m.F, ws.da, m.F, from_dy, st, &swb));
     } else {
-      BM_RETURN_IF(gemm_grouped(GEMM_NN, dt, m.cap, m.F, d, ws.dyp, d, w->w_down, m.F, ws.da, m.F, g, st));
+      BM_RETURN_IF(gemm_grouped(GEMM_NN, dt, m.cap, m.F, d, dyp, d, w->w_down, m.F, ws.da, m.F, from_dy, st));
       { ProfScope _p(PROF_ELEMENTWISE, (double)m.cap * (2.0 * m.UP + 2.0 * m.F) * (double)m.es, st);
         BM_RETURN_IF(act_backward(dt, c.act, sv.up, ws.da, ws.dup, ws.a, nullptr, nullptr, m.cap, m.F, nullptr, st)); }
     }
-    g.c_stride = (long)d * m.F;
-    BM_RETURN_IF(gemm_grouped(GEMM_TN, dt, d, m.F, m.cap, ws.dyp, d, ws.a, m.F, grads->w_down, m.F, g, st));
+    from_dy.c_stride = (long)d * m.F;
+    BM_RETURN_IF(gemm_grouped(GEMM_TN, dt, d, m.F, m.cap, dyp, d, ws.a, m.F, grads->w_down, m.F, from_dy, st));
     g.b_stride = (long)m.UP * d;
     char* dxp = ws.dyp;                                  // the routed output gradient is spent
     BM_RETURN_IF(gemm_grouped(GEMM_NN, dt, m.cap, d, m.UP, ws.dup, m.UP, w->w_up, d, dxp, d, g, st));
@@ -554,9 +572,9 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     { ProfScope _p(PROF_NORM, 5.0 * T * m.d * (double)m.es, st);
       BM_RETURN_IF(norm_backward(n2, sv.x1, sv.stats2, ws.dh, dy, ws.dx1, ws.h, (float*)grads->norm2_g,
                                  (float*)grads->norm2_b, nullptr, nullptr, ws.dmod, cu_dev, S, ws.norm_ws, &sums, nullptr, st)); }
-    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(moe_gather(dt, ws.h, sv.moe, 0, ws.xp, d, T, st)); }
-    g.c_stride = (long)m.UP * d;
-    BM_RETURN_IF(gemm_grouped(GEMM_TN, dt, m.UP, d, m.cap, ws.dup, m.UP, ws.xp, d, grads->w_up, d, g, st));
+    if (!in_place) { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(moe_gather(dt, ws.h, sv.moe, 0, ws.xp, d, T, st)); }
+    from_h.c_stride = (long)m.UP * d;
+    BM_RETURN_IF(gemm_grouped(GEMM_TN, dt, m.UP, d, m.cap, ws.dup, m.UP, in_place ? ws.h : ws.xp, d, grads->w_up, d, from_h, st));
     BM_RETURN_IF(gemm(GEMM_TN, dt, m.E, d, T, ws.dlogits, m.E, ws.h, d, grads->w_router, d, none, ws.gemm_ws,
                       ws.gemm_ws_bytes, st));
   } else {

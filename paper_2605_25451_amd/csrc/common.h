@@ -188,6 +188,12 @@ struct GemmGroups {
   const int32_t* group_rows = nullptr;   // dev [n_groups + 1]       (TN)
   const int32_t* row_tiles = nullptr;    // dev [1 + row_tiles_cap]  (NT, NN): their number, then for each twice its first row block,
   int row_tiles_cap = 0;                 //   plus one where it holds the next block of the same group as well
+  // Rows read where they lie instead of from a sorted copy (gemm_mfma_reads_source_rows): the source row, of src_rows, of each row of A
+  // (NT, NN) or of each k row of A (source_operand 0) or B (1) (TN, groups of at most MOE_SOURCE_ROWS).  Rows without one read
+  // some row of their group; what they are multiplied with has to be zero, or their results are never read.
+  const int32_t* source = nullptr;
+  int src_rows = 0, source_operand = 0;
+  const float* row_scale = nullptr;      // dev [rows]: factor of every row of A, with the SwiGLU backward epilogue (its activation included)
   int n_groups = 0;
   long b_stride = 0;                     // elements between the B matrices of two groups (NT, NN)
   long c_stride = 0;                     // elements between the C matrices of two groups (TN)
@@ -222,6 +228,8 @@ double gemm_mfma_time(int layout, const GemmCall& w, size_t scratch_bytes);
 bm_status gemm_grouped(int layout, int dtype, int M, int N, int K, const void* A, int lda,
                        const void* B, int ldb, void* C, int ldc, const GemmGroups& g, hipStream_t st,
                        const GemmEpilogue* epi = nullptr);
+constexpr int MOE_SOURCE_ROWS = 8192;
+bool gemm_mfma_reads_source_rows(int layout, int M, int N, const GemmEpilogue* epi);
 bool gemm_mfma_grouped_supported(int layout, int dtype, int M, int N, int K, int lda, int ldb, int ldc);
 bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int lda, const void* B,
                             int ldb, void* C, int ldc, const GemmGroups& g, hipStream_t st,

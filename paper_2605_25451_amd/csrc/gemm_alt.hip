@@ -45,6 +45,12 @@ __device__ inline void load_to_lds(const bf16_t* base, uint32_t off, uint32_t ld
                :: "s"(lds), "v"(off), "s"(base) : "memory", "m0");
 }
 
+// the source of a row, or that of the first row where there is none (the rows that fill up a group)
+__device__ inline int source_row(const int32_t* source, int row, int src_rows) {
+  const int s = source[row];
+  return (uint32_t)s < (uint32_t)src_rows ? s : min(max(source[0], 0), src_rows - 1);
+}
+
 // LDS layouts of a region of R rows x 64 k (the swizzles keep fragment reads free of bank conflicts):
 //   k-contiguous operand  [row][64 k]: 16-byte chunk c of row r sits at c ^ ((r >> 1) & 7)
 //   transposed operand    [k][R rows]: chunk c of k-row k sits at c ^ ((k & 3) << 2) ^ (((k >> 3) & 1) << 1)
@@ -67,7 +73,9 @@ struct Region {
   // half > 0 (k-contiguous only): rows are gathered from two ranges F rows apart -- within every run of
   // 2*half tile rows the first half come from f0.. and the second from F + f0.. (gate and up rows of a
   // SwiGLU weight); offsets are then relative to the matrix's first row.
-  __device__ inline void init(int ld, int row0, int rows_left, int wave, int lane, int half = 0, int F = 0, int f0 = 0) {
+  // source (k-contiguous only): where the tile's rows lie in a matrix of src_rows rows; offsets are then relative to its first row
+  __device__ inline void init(int ld, int row0, int rows_left, int wave, int lane, int half = 0, int F = 0, int f0 = 0,
+                              const int32_t* source = nullptr, int src_rows = 0) {
 #pragma unroll
     for (int i = 0; i < LOADS; ++i) {
       int r, c;
@@ -79,6 +87,7 @@ struct Region {
       } else {
         int row = min(row0 + r, rows_left - 1);
         if (half > 0) row = (r / half & 1) * F + f0 + (r / (2 * half)) * half + r % half;
+        if (source) row = source_row(source, row, src_rows);
         off[i] = ((uint32_t)row * (uint32_t)ld + (uint32_t)c * 8u) * 2u;
       }
     }
@@ -98,6 +107,23 @@ struct Region {
       }
       load_to_lds(base, o, lds + (i * 8 + wave) * 1024);
     }
+  }
+};
+
+// The same for a transposed operand whose k rows are read from their source rows: those of the tile's k range lie in LDS, and
+// the ones of a load are fetched a phase ahead of it.
+template <int R, int FIRST, int COUNT>
+struct SourceLoads {
+  using Reg = Region<R, true>;
+  int row[COUNT];
+  __device__ inline void fetch(const int32_t* rows, int j, int wave, int lane) {
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i) row[i] = rows[j * BK + ((FIRST + i) * 8 + wave) * Reg::RPL + lane / Reg::CPR];
+  }
+  // col: byte offset of this lane's chunk in a row, the same in every load
+  __device__ inline void load(const bf16_t* base, uint32_t row_bytes, uint32_t col, uint32_t lds, int wave) const {
+#pragma unroll
+    for (int i = 0; i < COUNT; ++i) load_to_lds(base, (uint32_t)row[i] * row_bytes + col, lds + ((FIRST + i) * 8 + wave) * 1024);
   }
 };
 
@@ -169,7 +195,7 @@ __device__ inline void clear(f32x4 (&acc)[FM][FN]) {
 // two phases per group (first and second half of A); LDS holds two slices, and a slice's first half
 // of A with B, and its second half, are re-filled as soon as both groups have read them: loads are
 // in flight for more than a slice (4 to 5 phases of 512 clocks).
-template <bool B_TR, int EPI, bool CUT>
+template <bool B_TR, int EPI, bool CUT, bool SOURCE = false>
 __device__ __forceinline__ void alt256_tile(const GemmParams& p, const TileJob& job) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using RegA = Region<128, false>;
@@ -185,11 +211,12 @@ __device__ __forceinline__ void alt256_tile(const GemmParams& p, const TileJob& 
 
   RegA ra0, ra1;
   RegB rb;
-  ra0.init(p.lda, 0, p.M - m0, wave, lane);
-  ra1.init(p.lda, 128, p.M - m0, wave, lane);
+  const int32_t* source = SOURCE && p.source ? p.source + m0 : nullptr;
+  ra0.init(p.lda, 0, p.M - m0, wave, lane, 0, 0, 0, source, p.src_rows);
+  ra1.init(p.lda, 128, p.M - m0, wave, lane, 0, 0, 0, source, p.src_rows);
   if (SWF) rb.init(p.ldb, 0, 256, wave, lane, 32, p.N / 2, job.tn * 128);
   else rb.init(p.ldb, 0, p.N - n0, wave, lane);
-  const bf16_t* a_base = job.A + (size_t)m0 * p.lda + job.kbeg;
+  const bf16_t* a_base = job.A + (source ? (size_t)0 : (size_t)m0 * p.lda) + job.kbeg;
   const bf16_t* b_base = B_TR ? job.B + (size_t)job.kbeg * p.ldb + n0
                               : job.B + (SWF ? (size_t)0 : (size_t)n0 * p.ldb) + job.kbeg;
   const size_t a_step = BK, b_step = B_TR ? (size_t)BK * p.ldb : (size_t)BK;
@@ -296,7 +323,10 @@ __device__ __forceinline__ void alt256_tile(const GemmParams& p, const TileJob& 
 // with all CUs at work 1.45 and 1.33 (power).  12288x4096 over 8192 rows 621 -> 604 us, 22016x4096 over 777 247 -> 241.
 // The first 32 k of a slice are re-filled while its last 32 are read, and the other way round.  (K-contiguous operands
 // are cut along the rows because half a slice of theirs would be half of every 128-byte line.)
-template <int EPI, bool CUT>
+// SOURCE: 1 or 2 where the k rows of A or B are read from their source rows (whole slices only).  The table of source rows costs a tile
+// about a microsecond in front of its first loads and four LDS reads a slice; a sorted copy costs its own pass and 268 MB to
+// be read back (65536 rows of 2048): up 1536x2048 with the pass 870 -> 755 us, down 2048x768 500 -> 405.
+template <int EPI, bool CUT, int SOURCE = 0>
 __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJob& job) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using Reg = Region<256, true>;
@@ -314,11 +344,43 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
   const bf16_t* a_base = job.A + (size_t)job.kbeg * p.lda + m0;
   const bf16_t* b_base = job.B + (size_t)job.kbeg * p.ldb + n0;
   const size_t a_step = (size_t)BK * p.lda, b_step = (size_t)BK * p.ldb;
-  auto load_half = [&](auto half_t, int j, uint32_t buf) {
+  // source rows of the tile's k range in LDS behind the slices, and those of the next loads of either half of a slice
+  int32_t* rows = reinterpret_cast<int32_t*>(smem + 2 * BUF);
+  SourceLoads<256, 0, HL / 2> next0;
+  SourceLoads<256, HL / 2, HL / 2> next1;
+  const uint32_t src_bytes = (uint32_t)(SOURCE == 1 ? p.lda : p.ldb) * 2u;
+  uint32_t src_col = 0;
+  if (SOURCE) {
+    int r, c;
+    Reg::place(0, wave, lane, &r, &c);
+    const int first = SOURCE == 1 ? m0 : n0, left = (SOURCE == 1 ? p.M : p.N) - first;
+    src_col = (uint32_t)(c * 8 < left ? c * 8 : 0) * 2u;
+  }
+  const bf16_t* src_base = SOURCE == 1 ? job.A + m0 : job.B + n0;
+  auto load_b = [&](auto half_t, int j, uint32_t buf) {
     constexpr int FIRST = decltype(half_t)::value * (HL / 2);
     const int left = CUT && j == n - 1 ? k_left : BK;
     rb.template load<CUT, FIRST, HL / 2>(b_base + (size_t)j * b_step, p.ldb, left, buf + B0, wave, lane);
+  };
+  auto load_a = [&](auto half_t, int j, uint32_t buf) {
+    constexpr int FIRST = decltype(half_t)::value * (HL / 2);
+    const int left = CUT && j == n - 1 ? k_left : BK;
     ra.template load<CUT, FIRST, HL / 2>(a_base + (size_t)j * a_step, p.lda, left, buf, wave, lane);
+  };
+  auto load_source = [&](auto half_t, uint32_t buf) {
+    const uint32_t at = buf + (SOURCE == 1 ? 0 : B0);
+    if constexpr (decltype(half_t)::value == 0) next0.load(src_base, src_bytes, src_col, at, wave);
+    else next1.load(src_base, src_bytes, src_col, at, wave);
+  };
+  auto fetch_rows = [&](auto half_t, int j) {
+    if constexpr (SOURCE != 0) {
+      if constexpr (decltype(half_t)::value == 0) next0.fetch(rows, j, wave, lane);
+      else next1.fetch(rows, j, wave, lane);
+    }
+  };
+  auto load_half = [&](auto half_t, int j, uint32_t buf) {
+    if constexpr (SOURCE == 2) load_source(half_t, buf); else load_b(half_t, j, buf);
+    if constexpr (SOURCE == 1) load_source(half_t, buf); else load_a(half_t, j, buf);
   };
 
   // rows wm*64.. of each half of A: the second half lies 128 rows on in every k row
@@ -356,6 +418,7 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
     const uint32_t buf = (j & 1) * BUF;
     read(Int<0>{}, buf);
     if (COME >= 1) load_half(Int<1>{}, j + 1, buf ^ BUF);
+    if (COME >= 2) fetch_rows(Int<0>{}, j + 2);
     wait_fragments();
     if (CUT && COME == 0 && k_left < BK) cut(0);
     wait_loads<COME >= 1 ? 2 * HL : 0>();
@@ -364,7 +427,7 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
     wait_loads<COME >= 1 ? 2 * HL : 0>();
     end_phase();
     read(Int<1>{}, buf);
-    if (COME >= 2) load_half(Int<0>{}, j + 2, buf);
+    if (COME >= 2) { load_half(Int<0>{}, j + 2, buf); fetch_rows(Int<1>{}, j + 2); }
     wait_fragments();
     if (CUT && COME == 0 && k_left < BK) cut(1);
     if (COME == 0) { end_phase(); return; }                 // the last MFMAs belong to the epilogue
@@ -374,12 +437,32 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
     wait_loads<COME >= 2 ? 2 * HL : HL>();
     end_phase();
   };
-  load_half(Int<0>{}, 0, 0);
-  load_half(Int<1>{}, 0, 0);
-  if (n > 1) load_half(Int<0>{}, 1, BUF);
-  clear(acc);                                               // under the latency of the first loads
-  if (n > 1) wait_loads<2 * HL>();
-  else wait_loads<0>();
+  if constexpr (SOURCE != 0) {
+    // the other operand's first slice is on its way while the table is filled
+    if constexpr (SOURCE == 2) { load_a(Int<0>{}, 0, 0); load_a(Int<1>{}, 0, 0); }
+    else { load_b(Int<0>{}, 0, 0); load_b(Int<1>{}, 0, 0); }
+    for (int i = threadIdx.x; i < n * BK; i += THREADS) rows[i] = source_row(p.source + job.kbeg, i, p.src_rows);
+    __syncthreads();
+    fetch_rows(Int<0>{}, 0);
+    fetch_rows(Int<1>{}, 0);
+    load_source(Int<0>{}, 0);
+    load_source(Int<1>{}, 0);
+    if (n > 1) {
+      fetch_rows(Int<0>{}, 1);
+      load_half(Int<0>{}, 1, BUF);
+      fetch_rows(Int<1>{}, 1);
+    }
+    clear(acc);
+    if (n > 1) wait_loads<HL + HL / 2>();
+    else wait_loads<0>();
+  } else {
+    load_half(Int<0>{}, 0, 0);
+    load_half(Int<1>{}, 0, 0);
+    if (n > 1) load_half(Int<0>{}, 1, BUF);
+    clear(acc);                                             // under the latency of the first loads
+    if (n > 1) wait_loads<2 * HL>();
+    else wait_loads<0>();
+  }
   end_phase();
   if (wm == 1) end_phase();                                 // group 1 stays one phase behind
   const bool full = m0 + 256 <= p.M && n0 + 256 <= p.N;
@@ -399,6 +482,14 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
 template <int EPI, bool CUT>
 __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_tn_kernel(GemmParams p) {
   alt256_tn_tile<EPI, CUT>(p, locate_tile<256, 256>(p, blockIdx.x));
+}
+
+// Grouped weight gradients with one operand read from its source rows.
+template <int SOURCE>
+__global__ __launch_bounds__(THREADS, 2) void gemm_alt256_tn_source_kernel(GemmParams p) {
+  TileJob job = locate_tile<256, 256>(p, blockIdx.x);
+  job.kend = min(job.kend, job.kbeg + MOE_SOURCE_ROWS);
+  alt256_tn_tile<EPI_ADD, false, SOURCE>(p, job);
 }
 
 // Several weight gradients in one grid.
@@ -429,7 +520,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_tn_parts_kernel(TnPart
 
 // ---- 128x256 and 256x128 tiles: each wavefront owns 64x64 and a slice is one phase per group.  LDS holds
 // three slices; the loads of slice j+2 go out while slice j is read.
-template <int BM, int BN, bool A_TR, bool B_TR, int EPI, bool CUT>
+template <int BM, int BN, bool A_TR, bool B_TR, int EPI, bool CUT, bool SOURCE = false>
 __device__ __forceinline__ void alt128_tile(const GemmParams& p, const TileJob& job) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   using RegA = Region<BM, A_TR>;
@@ -446,10 +537,12 @@ __device__ __forceinline__ void alt128_tile(const GemmParams& p, const TileJob& 
 
   RegA ra;
   RegB rb;
-  ra.init(p.lda, 0, p.M - m0, wave, lane);
+  const int32_t* source = SOURCE && p.source ? p.source + m0 : nullptr;
+  ra.init(p.lda, 0, p.M - m0, wave, lane, 0, 0, 0, source, p.src_rows);
   if (SWF) rb.init(p.ldb, 0, BN, wave, lane, 32, p.N / 2, job.tn * (BN / 2));
   else rb.init(p.ldb, 0, p.N - n0, wave, lane);
-  const bf16_t* a_base = A_TR ? job.A + (size_t)job.kbeg * p.lda + m0 : job.A + (size_t)m0 * p.lda + job.kbeg;
+  const bf16_t* a_base = A_TR ? job.A + (size_t)job.kbeg * p.lda + m0
+                              : job.A + (source ? (size_t)0 : (size_t)m0 * p.lda) + job.kbeg;
   const bf16_t* b_base = B_TR ? job.B + (size_t)job.kbeg * p.ldb + n0
                               : job.B + (SWF ? (size_t)0 : (size_t)n0 * p.ldb) + job.kbeg;
   const size_t a_step = A_TR ? (size_t)BK * p.lda : (size_t)BK, b_step = B_TR ? (size_t)BK * p.ldb : (size_t)BK;
@@ -566,8 +659,9 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt_groups_kernel(GemmParams 
   job.m0 = block * MOE_PAD; job.n0 = tn * 256; job.tn = tn;
   job.kbeg = 0; job.kend = p.K; job.split = 0; job.c_off = 0;
   p.M = job.m0 + (tile & 1 ? 2 : 1) * MOE_PAD;
-  if (tile & 1) alt256_tile<B_TR, EPI, CUT>(p, job);
-  else alt128_tile<MOE_PAD, 256, false, B_TR, EPI, CUT>(p, job);
+  constexpr bool SOURCE = EPI == EPI_SWIGLU_FWD || EPI == EPI_SWIGLU_BWD;
+  if (tile & 1) alt256_tile<B_TR, EPI, CUT, SOURCE>(p, job);
+  else alt128_tile<MOE_PAD, 256, false, B_TR, EPI, CUT, SOURCE>(p, job);
 }
 
 template <int BM, int BN, bool A_TR, bool B_TR, int EPI, bool CUT>
@@ -623,6 +717,21 @@ bm_status launch_parts(const TnParts& g, hipStream_t st) {
   return BM_OK;
 }
 
+template <int SOURCE>
+bm_status launch_source(const GemmParams& p, hipStream_t st) {
+  constexpr size_t lds = (size_t)2 * (256 + 256) * BK * sizeof(bf16_t) + MOE_SOURCE_ROWS * sizeof(int32_t);
+  static_assert(lds <= 160 * 1024, "the source rows lie behind the slices");
+  auto kern = gemm_alt256_tn_source_kernel<SOURCE>;
+  static std::atomic<bool> attr_done{false};
+  if (!attr_done.load(std::memory_order_relaxed)) {
+    BM_CHECK_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+    attr_done.store(true, std::memory_order_relaxed);
+  }
+  hipLaunchKernelGGL(kern, dim3(p.tiles_m * p.tiles_n * p.grid_groups), dim3(THREADS), lds, st, p);
+  BM_CHECK_LAUNCH("gemm_alt_tn_source");
+  return BM_OK;
+}
+
 template <int BM, int BN, bool A_TR, bool B_TR, int EPI>
 bm_status launch_cut(const GemmParams& p, hipStream_t st) {
   if (p.K % BK) return launch_one<BM, BN, A_TR, B_TR, EPI, true>(p, st);
@@ -666,6 +775,10 @@ bm_status launch_gemm_alt_mixed(int layout, const GemmParams& p, hipStream_t st)
   }
   if (p.sw_up) return launch_two_heights_cut<false, true, EPI_SWIGLU_BWD>(p, st);
   return p.residual ? launch_two_heights_cut<false, true, EPI_RES>(p, st) : launch_two_heights_cut<false, true, EPI_PLAIN>(p, st);
+}
+
+bm_status launch_gemm_alt_tn_source(int operand, const GemmParams& p, hipStream_t st) {
+  return operand == 0 ? launch_source<1>(p, st) : launch_source<2>(p, st);
 }
 
 bm_status launch_gemm_alt_tn_parts(const TnParts& g, hipStream_t st) {

@@ -622,7 +622,7 @@ bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, con
     set_error("gemm: the SwiGLU forward epilogue needs the NT layout, N a multiple of 256 and no bias");
     return BM_ERR_INVALID_ARG;
   }
-  p.tile_group = nullptr; p.group_rows = nullptr; p.row_tiles = nullptr; p.b_group_stride = 0; p.c_group_stride = 0;
+  p.tile_group = nullptr; p.group_rows = nullptr; p.row_tiles = nullptr; p.source = nullptr; p.src_rows = 0; p.row_scale = nullptr; p.b_group_stride = 0; p.c_group_stride = 0;
   p.grid_groups = 1;
   p.xcd_split = xcd_split_possible(pl.tiles_m * pl.tiles_n, pl.splits) ? 1 : 0;
   p.big_rows = pl.big_rows;
@@ -900,7 +900,7 @@ GemmParams plain_params(const GemmCall& g, const Plan& pl, float* partial) {
   p.tiles_m = pl.tiles_m; p.tiles_n = pl.tiles_n; p.splits = pl.splits; p.k_per_split = pl.k_per_split;
   p.out_fp32 = 0;
   p.xcd_split = xcd_split_possible(pl.tiles_m * pl.tiles_n, pl.splits) ? 1 : 0;
-  p.tile_group = nullptr; p.group_rows = nullptr; p.row_tiles = nullptr; p.b_group_stride = 0; p.c_group_stride = 0; p.grid_groups = 1;
+  p.tile_group = nullptr; p.group_rows = nullptr; p.row_tiles = nullptr; p.source = nullptr; p.src_rows = 0; p.row_scale = nullptr; p.b_group_stride = 0; p.c_group_stride = 0; p.grid_groups = 1;
   return p;
 }
 
@@ -976,6 +976,10 @@ bool gemm_mfma_grouped_supported(int layout, int dtype, int M, int N, int K, int
   return K >= 64 && K % 8 == 0 && N % 8 == 0 && ldc % 8 == 0 && M % MOE_PAD == 0;
 }
 
+bool gemm_mfma_reads_source_rows(int layout, int M, int N, const GemmEpilogue* epi) {
+  return layout == GEMM_TN ? M >= 256 && N >= 256 : N >= 256 && epi && (epi->swiglu_fwd_a || epi->swiglu_up);
+}
+
 // A row tile is one MOE_PAD block or two of the same group.
 bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int lda, const void* B,
                             int ldb, void* C, int ldc, const GemmGroups& g, hipStream_t st,
@@ -990,6 +994,11 @@ bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int 
   p.tile_group = layout == GEMM_TN ? nullptr : g.tile_group;
   p.group_rows = layout == GEMM_TN ? g.group_rows : nullptr;
   p.row_tiles = layout == GEMM_TN ? nullptr : g.row_tiles;
+  p.source = g.source; p.src_rows = g.src_rows; p.row_scale = g.row_scale;
+  if (g.source && !gemm_mfma_reads_source_rows(layout, M, N, epi)) {
+    set_error("grouped gemm: rows of this product are not read from their source");
+    return BM_ERR_UNSUPPORTED;
+  }
   p.b_group_stride = g.b_stride; p.c_group_stride = g.c_stride;
   p.grid_groups = layout == GEMM_TN ? g.n_groups : 1;
   if (epi) {
@@ -1017,6 +1026,7 @@ bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int 
   // k range is short (a few slices), which makes the per-tile fixed cost count: large tiles
   if (M >= 256 && N >= 256) {
     p.tiles_m = cdiv(M, 256); p.tiles_n = cdiv(N, 256);
+    if (g.source) return launch_gemm_alt_tn_source(g.source_operand, p, st);
     return launch_gemm_alt(GEMM_TN, 256, 256, p, st);                     // k ranges are whole slices
   }
   return launch_small(GEMM_TN, p, st);

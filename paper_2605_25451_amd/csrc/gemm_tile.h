@@ -32,6 +32,10 @@ struct GemmParams {
   const int32_t* group_rows;
   const int32_t* row_tiles;
   long b_group_stride, c_group_stride;
+  // rows read where they lie instead of from a sorted copy: the source row (of src_rows) of each row of A (grouped NT and NN) or of
+  // each k row of one operand (grouped TN); what is out of range reads the first row of its tile or group
+  const int32_t* source; int src_rows;
+  const float* row_scale;       // SwiGLU backward: a factor of every row of the product
   int big_rows;                 // of launch_gemm_alt_mixed: rows of 256x256 tiles, before tiles_m - big_rows of 128x256
   int grid_groups;              // host: workgroups = tiles * splits * grid_groups (>= 1)
 };
@@ -283,6 +287,7 @@ __device__ inline void gemm_epilogue(const GemmParams& p, f32x4 (&acc)[FM][FN], 
   const int rcol = (lane % LPR) * 8, rrow = lane / LPR;
   const int gn = col0 + rcol;
   u32x4 pre[2][TPS][2];
+  float scale[2][TPS];
   auto request = [&](auto i_t) {
     constexpr int i = decltype(i_t)::value;
     if (i >= FM) return;
@@ -293,6 +298,7 @@ __device__ inline void gemm_epilogue(const GemmParams& p, f32x4 (&acc)[FM][FN], 
         const bf16_t* up = p.sw_up + (size_t)gm * (2 * p.N) + gc;
         pre[i & 1][t][0] = *reinterpret_cast<const u32x4*>(up);
         pre[i & 1][t][1] = *reinterpret_cast<const u32x4*>(up + p.N);
+        scale[i & 1][t] = p.row_scale ? p.row_scale[gm] : 1.f;
       } else if (EPI == EPI_RES) {
         pre[i & 1][t][0] = *reinterpret_cast<const u32x4*>(p.residual + (size_t)gm * p.ldc + gc);
       }
@@ -361,14 +367,15 @@ __device__ inline void gemm_epilogue(const GemmParams& p, f32x4 (&acc)[FM][FN], 
           const size_t up_idx = (size_t)gm * (2 * p.N) + gn;
           union { u32x4 u; bf16_t h[8]; } sg{pre[i & 1][t][0]}, su{pre[i & 1][t][1]};
           float dg[8], du[8], av[8];
+          const float sc = scale[i & 1][t];                    // on the activation as well: it is only read for the weight gradient
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             const float g = (float)sg.h[e], u = (float)su.h[e];
             const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
-            const float sl = g * sig;                          // silu(g)
+            const float sl = sc * (g * sig);                   // silu(g)
             av[e] = sl * u;
             du[e] = out[e] * sl;
-            dg[e] = out[e] * u * sig * (1.0f + g * (1.0f - sig));
+            dg[e] = sc * out[e] * u * sig * (1.0f + g * (1.0f - sig));
           }
           store16(p.sw_dup + up_idx, dg);
           store16(p.sw_dup + up_idx + p.N, du);
@@ -407,6 +414,8 @@ bm_status launch_gemm_alt(int layout, int bm, int bn, const GemmParams& p, hipSt
 bm_status launch_gemm_alt_mixed(int layout, const GemmParams& p, hipStream_t st);
 // grouped NT and NN on the row tiles that p lists; tiles_m: their capacity
 bm_status launch_gemm_alt_groups(int layout, const GemmParams& p, hipStream_t st);
+// grouped weight gradients whose A (operand 0) or B (1) is read from its source rows; no group longer than MOE_SOURCE_ROWS
+bm_status launch_gemm_alt_tn_source(int operand, const GemmParams& p, hipStream_t st);
 // weight gradients in one grid of 256x256 tiles
 bm_status launch_gemm_alt_tn_parts(const TnParts& g, hipStream_t st);
 

@@ -159,9 +159,10 @@ __global__ __launch_bounds__(256) void moe_offsets_kernel(const int32_t* __restr
   for (int tile = all / MOE_PAD + threadIdx.x; tile < n_tiles; tile += 256) tile_group[tile] = -1;
 }
 
-__global__ void moe_fill_i32_kernel(int32_t* __restrict__ p, int32_t v, long n) {
-  const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = v;
+// rows that fill up a segment have no token and no weight
+__global__ void moe_clear_rows_kernel(int32_t* __restrict__ row_token, float* __restrict__ row_gate, int n) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < n) { row_token[i] = -1; row_gate[i] = 0.f; }
 }
 
 // slot of every (token, choice): segment offset + tokens of earlier chunks + rank inside the
@@ -386,7 +387,7 @@ bm_status moe_layout(const MoeTables& m, int T, int E, int k, void* scratch, hip
   hipLaunchKernelGGL(moe_count_kernel, dim3(nblk), dim3(MOE_CHUNK), 0, st, m.idx, T, E, k, counts);
   hipLaunchKernelGGL(moe_offsets_kernel, dim3(1), dim3(256), 0, st, counts, nblk, E, base, m.expert_rows,
                      m.tile_group, m.cap / MOE_PAD, m.row_tiles);
-  hipLaunchKernelGGL(moe_fill_i32_kernel, dim3(cdiv(m.cap, 256)), dim3(256), 0, st, m.row_token, -1, (long)m.cap);
+  hipLaunchKernelGGL(moe_clear_rows_kernel, dim3(cdiv(m.cap, 256)), dim3(256), 0, st, m.row_token, m.row_gate, m.cap);
   hipLaunchKernelGGL(moe_slot_kernel, dim3(nblk), dim3(MOE_CHUNK), 0, st, m.idx, m.gate, T, E, k, base,
                      m.expert_rows, m.slot, m.row_token, m.row_gate, m.cap);
   BM_CHECK_LAUNCH("moe_layout");
