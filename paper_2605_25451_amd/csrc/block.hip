@@ -192,6 +192,9 @@ BwdScratch layout_bwd(const Dims& m, int dtype, void* base) {
 GemmCall input_grad(int M, int N, int K, const void* A, const void* B, void* C) { return {M, N, K, A, K, B, N, C, N}; }
 GemmCall weight_grad(int M, int N, int K, const void* A, const void* B, void* C) { return {M, N, K, A, M, B, N, C, N}; }
 
+// the column sums that a GELU backward in an epilogue leaves, a row for every 16
+bool gelu_sum_rows_fit(int T, int F) { return (size_t)cdiv(T, 16) * F * sizeof(float) <= colsum_scratch_bytes(T, F); }
+
 // The products of a backward pass: input gradients of up, o, qkv; weight gradients of down, up, o, qkv
 struct BackwardGemms { GemmCall nn[3], tn[4]; };
 BackwardGemms backward_gemms(const Dims& m) {
@@ -456,9 +459,10 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
       e.swiglu_fwd_a = ws.a;
       BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.UP, m.d, ws.h, m.d, w->w_up, m.d, sv.up, m.UP, e, ws.gemm_ws, ws.gemm_ws_bytes, st));
     } else {
+      if (c.act == BM_ACT_GELU && gemm_fuses_gelu(GEMM_NT, dt, T, m.UP, m.d)) e.gelu_a = ws.a;
       BM_RETURN_IF(gemm(GEMM_NT, dt, T, m.UP, m.d, ws.h, m.d, w->w_up, m.d, sv.up, m.UP, e,
                         ws.gemm_ws, ws.gemm_ws_bytes, st));
-      { ProfScope _p(PROF_ELEMENTWISE, (double)T * (m.UP + m.F) * (double)m.es, st); BM_RETURN_IF(act_forward(dt, c.act, sv.up, ws.a, T, m.F, st)); }
+      if (!e.gelu_a) { ProfScope _p(PROF_ELEMENTWISE, (double)T * (m.UP + m.F) * (double)m.es, st); BM_RETURN_IF(act_forward(dt, c.act, sv.up, ws.a, T, m.F, st)); }
     }
   }
   {
@@ -586,6 +590,12 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     // SwiGLU backward rides in the epilogue of this GEMM: dA never goes to memory
     down_in.swiglu_up = sv.up; down_in.swiglu_dup = ws.dup; down_in.swiglu_a = ws.a;
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.F, d, dm, d, w->w_down, m.F, ws.da, m.F, down_in, ws.gemm_ws, ws.gemm_ws_bytes, st));
+  } else if (c.act == BM_ACT_GELU && gemm_fuses_gelu(GEMM_NN, dt, T, m.F, d) && gelu_sum_rows_fit(T, m.F)) {
+    GemmEpilogue e;
+    e.gelu_up = sv.up; e.gelu_dup = ws.dup; e.gelu_act = ws.a;
+    e.gelu_sums = c.linear_bias ? (float*)ws.colsum_ws[0] : nullptr;
+    BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.F, d, dm, d, w->w_down, m.F, ws.da, m.F, e, ws.gemm_ws, ws.gemm_ws_bytes, st));
+    if (c.linear_bias) BM_RETURN_IF(sums.add(e.gelu_sums, cdiv(T, 16), m.F, m.F, (float*)grads->b_up));
   } else {
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.F, d, dm, d, w->w_down, m.F, ws.da, m.F, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, (double)T * (2.0 * m.UP + 2.0 * m.F) * (double)m.es, st);

@@ -101,6 +101,28 @@ __device__ inline float wave_max(float v) {
   return v;
 }
 
+// Phi(z) = (1 + erf(z / sqrt 2)) / 2 and phi(z) = exp(-z^2/2) / sqrt(2 pi) from ONE
+// exponential: erfc(x) = (a1 t + ... + a5 t^5) exp(-x^2), t = 1 / (1 + p x), x >= 0
+// (Abramowitz & Stegun 7.1.26, absolute error below 1.5e-7, i.e. fp32 rounding level),
+// and exp(-x^2) with x = |z| / sqrt 2 is the exponential of the density.
+__device__ inline void normal_cdf_pdf(float z, float* cdf, float* pdf) {
+  const float x = fabsf(z) * 0.70710678118654752f;
+  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, x, 1.0f));
+  const float e = __builtin_amdgcn_exp2f(-x * x * 1.4426950408889634f);
+  float poly = fmaf(t, 1.061405429f, -1.453152027f);
+  poly = fmaf(t, poly, 1.421413741f);
+  poly = fmaf(t, poly, -0.284496736f);
+  poly = fmaf(t, poly, 0.254829592f);
+  const float half_erfc = 0.5f * t * poly * e;
+  *cdf = z >= 0.f ? 1.0f - half_erfc : half_erfc;
+  *pdf = e * 0.39894228040143268f;
+}
+__device__ inline float gelu_f(float z) {
+  float cdf, pdf;
+  normal_cdf_pdf(z, &cdf, &pdf);
+  return z * cdf;
+}
+
 // ---------------------------------------------------------------- host helpers
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
@@ -138,6 +160,14 @@ struct GemmEpilogue {
   // a[M, N/2] = silu(g) u, taken from the ROUNDED g and u (what a separate pass over C would read).
   // A tile gathers its weight rows from both halves, so that g and u of a column meet in one wavefront.
   void* swiglu_fwd_a = nullptr;     // [M, N/2]
+  // GELU in the epilogue, where gemm_fuses_gelu() says so (C contiguous): few fp32 rows.
+  // NT: gelu_a[M, N] = gelu(C).
+  void* gelu_a = nullptr;
+  // NN: dA[M, N] is not stored; gelu_dup = dA gelu'(up), gelu_act = gelu(up) and, with gelu_sums, the column sums of
+  // every 16 rows of gelu_dup: [cdiv(M, 16), N]
+  const void* gelu_up = nullptr;
+  void *gelu_dup = nullptr, *gelu_act = nullptr;
+  float* gelu_sums = nullptr;
 };
 
 // gemm_scratch_bytes: what a product can make use of; NT and NN also run in less, TN and the generic
@@ -158,6 +188,9 @@ inline size_t gemm_rows_scratch_bytes(int rows, int N, int dtype) {
 bm_status gemm(int layout, int dtype, int M, int N, int K, const void* A, int lda, const void* B,
                int ldb, void* C, int ldc, const GemmEpilogue& epi, void* scratch,
                size_t scratch_bytes, hipStream_t st);
+
+// contiguous rows, 16-byte aligned operands
+bool gemm_fuses_gelu(int layout, int dtype, int M, int N, int K);
 
 // An input gradient C[M,N] = A[M,K] B[K,N] and a weight gradient C[M,N] += A[K,M]^T B[K,N] (fp32 C) that do not depend on
 // one another: one launch where few rows leave the chip idle, else one after the other.  Scratch as for both.

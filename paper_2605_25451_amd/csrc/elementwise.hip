@@ -346,18 +346,18 @@ __global__ __launch_bounds__(NormBwdWaves<NV>::N * 64) void norm_bwd_kernel(
   }
 }
 
-// out[c] += sum over parts of partial[p*stride + c] for every target of the list (blockIdx.y); 64 columns per
-// workgroup, sixteen groups of parts combined through LDS in a fixed order.  Bound by the latency of its loads, about
-// 4 us whatever the sizes, so a backward pass collects its targets and runs one launch (a block with biases: four before,
+// out[c] += sum over parts of partial[p*stride + c] for every target of the list (blockIdx.y); 32 columns per
+// workgroup, 32 groups of parts combined through LDS in a fixed order (64 columns and 16 groups: 768 parts of 1024 to 4096 columns
+// 13 us, this 9.5).  Bound by the latency of its loads, 4 us at the least, so a backward pass collects its targets and runs one launch (a block with biases: four before,
 // one image of 577 tokens 300 -> 289 us, 40 tokens in fp32 111 -> 99).
-constexpr int PR_GROUPS = 16;
-__global__ __launch_bounds__(64 * PR_GROUPS) void partial_reduce_kernel(ColumnSums sums) {
-  __shared__ float sm[PR_GROUPS][64];
+constexpr int PR_GROUPS = 32, PR_COLS = 32;
+__global__ __launch_bounds__(PR_COLS * PR_GROUPS) void partial_reduce_kernel(ColumnSums sums) {
+  __shared__ float sm[PR_GROUPS][PR_COLS];
   const ColumnSums::Target t = sums.target[blockIdx.y];
-  if ((int)blockIdx.x * 64 >= t.n) return;
+  if ((int)blockIdx.x * PR_COLS >= t.n) return;
   const float* __restrict__ partial = t.partial;
-  const int c = blockIdx.x * 64 + (threadIdx.x & 63);
-  const int g = threadIdx.x >> 6;
+  const int c = blockIdx.x * PR_COLS + threadIdx.x % PR_COLS;
+  const int g = threadIdx.x / PR_COLS;
   // eight independent loads in flight per thread: the partials come from L2 or further away and
   // the loop is bound by that latency, not by bandwidth
   float s[8];
@@ -373,7 +373,7 @@ __global__ __launch_bounds__(64 * PR_GROUPS) void partial_reduce_kernel(ColumnSu
     for (int u = 0; u < 8; ++u)
       if (p + u * PR_GROUPS < t.parts) s[u] += partial[(size_t)(p + u * PR_GROUPS) * t.stride + c];
   }
-  sm[g][threadIdx.x & 63] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+  sm[g][threadIdx.x % PR_COLS] = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
   __syncthreads();
   if (g == 0 && c < t.n) {
     const int l = threadIdx.x;
@@ -390,7 +390,7 @@ bm_status flush_column_sums(ColumnSums* sums, hipStream_t st) {
   int widest = 0;
   auto launch = [&] {
     if (now.count > 0)
-      hipLaunchKernelGGL(partial_reduce_kernel, dim3(cdiv(widest, 64), now.count), dim3(64 * PR_GROUPS), 0, st, now);
+      hipLaunchKernelGGL(partial_reduce_kernel, dim3(cdiv(widest, PR_COLS), now.count), dim3(PR_COLS * PR_GROUPS), 0, st, now);
     now.count = widest = 0;
   };
   for (int i = 0; i < sums->count; ++i) {
@@ -711,27 +711,6 @@ bm_status rope_inplace(int dtype, void* qkv, int ld, int T, int n_heads, int dh,
 }
 
 // ------------------------------------------------------------------ activations
-// Phi(z) = (1 + erf(z / sqrt 2)) / 2 and phi(z) = exp(-z^2/2) / sqrt(2 pi) from ONE
-// exponential: erfc(x) = (a1 t + ... + a5 t^5) exp(-x^2), t = 1 / (1 + p x), x >= 0
-// (Abramowitz & Stegun 7.1.26, absolute error below 1.5e-7, i.e. fp32 rounding level),
-// and exp(-x^2) with x = |z| / sqrt 2 is the exponential of the density.
-__device__ inline void normal_cdf_pdf(float z, float* cdf, float* pdf) {
-  const float x = fabsf(z) * 0.70710678118654752f;
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, x, 1.0f));
-  const float e = __builtin_amdgcn_exp2f(-x * x * 1.4426950408889634f);
-  float poly = fmaf(t, 1.061405429f, -1.453152027f);
-  poly = fmaf(t, poly, 1.421413741f);
-  poly = fmaf(t, poly, -0.284496736f);
-  poly = fmaf(t, poly, 0.254829592f);
-  const float half_erfc = 0.5f * t * poly * e;
-  *cdf = z >= 0.f ? 1.0f - half_erfc : half_erfc;
-  *pdf = e * 0.39894228040143268f;
-}
-__device__ inline float gelu_f(float z) {
-  float cdf, pdf;
-  normal_cdf_pdf(z, &cdf, &pdf);
-  return z * cdf;
-}
 __device__ inline float sigmoid_f(float z) { return 1.0f / (1.0f + expf(-z)); }
 
 template <typename T, int ACT>
