@@ -108,17 +108,37 @@ bm_status gemm_tn_pair(int dtype, int K, int M0, int N0, const void* A0, int lda
   return gemm(GEMM_TN, dtype, M1, N1, K, A1, lda1, B1, ldb1, C1, ldc1, none, scratch, scratch_bytes, st);
 }
 
-bool gemm_tn_group_pays(int dtype, const GemmCall nn[3], const GemmCall tn[4], size_t scratch_bytes) {
+// the time of a shared launch to compare with; < 0: separate launches
+static double tn_group_time(int dtype, const GemmCall* tn, int n, size_t scratch_bytes) {
   // Under 1024 rows the launches that an input gradient shares are as good (800 rows of 512 to 4096 columns within 1 % either
   // way).  Over long packs a gradient that comes right behind its operands finds more of them in the caches, and the clock gives
   // back what idle CUs in a last round cost: decoder of 4096 columns, grouped queries, 8000 rows 8935 -> 8790 us, 16384
   // 17389 -> 17348, 32768 34670 -> 34830.
-  if (dtype != BM_DTYPE_BF16 || tn[0].K < 1024 || tn[0].K > 16384) return false;
+  if (dtype != BM_DTYPE_BF16 || tn[0].K < 1024 || tn[0].K > 16384) return -1.0;
+  const double together = gemm_mfma_tn_group_time(tn, n, scratch_bytes);
+  if (together < 0.0) return -1.0;
+  // The model prices 256x256 tiles of weight gradients high (see TILE_KINDS).  With 0.93 of it no block of 56 measured, 512 to
+  // 4096 columns and 1024 to 16384 rows, is slower than by separate launches, and what it turns down is level; the few
+  // tiles of narrow blocks leave CUs idle, where shared launches of 128x128 tiles are level for longer.
+  long tiles = 0;
+  for (int i = 0; i < n; ++i) tiles += (long)cdiv(tn[i].M, 256) * cdiv(tn[i].N, 256);
+  return (tiles < 64 ? 1.0 : 0.93) * together;
+}
+
+bool gemm_tn_group_pays(int dtype, const GemmCall* tn, int n, size_t scratch_bytes) {
+  const double together = tn_group_time(dtype, tn, n, scratch_bytes);
+  double apart = 0.0;
+  if (together >= 0.0)
+    for (int i = 0; i < n; ++i) apart += gemm_mfma_time(GEMM_TN, tn[i], scratch_bytes);
+  return together >= 0.0 && together < apart;
+}
+
+bool gemm_tn_group_pays(int dtype, const GemmCall nn[3], const GemmCall tn[4], size_t scratch_bytes) {
+  const double together = tn_group_time(dtype, tn, 4, scratch_bytes);
+  if (together < 0.0) return false;
   const GemmEpilogue none;
   for (int i = 0; i < 3; ++i)
     if (!gemm_mfma_supported(GEMM_NN, dtype, nn[i].M, nn[i].N, nn[i].K, nn[i].lda, nn[i].ldb, nn[i].ldc, none)) return false;
-  const double together = gemm_mfma_tn_group_time(tn, 4, scratch_bytes);
-  if (together < 0.0) return false;
   double apart = 0.0, inputs = 0.0, t_nn[3], t_tn[4];
   for (int i = 0; i < 3; ++i) inputs += t_nn[i] = gemm_mfma_time(GEMM_NN, nn[i], scratch_bytes);
   for (int i = 0; i < 4; ++i) t_tn[i] = gemm_mfma_time(GEMM_TN, tn[i], scratch_bytes);
@@ -134,12 +154,7 @@ bool gemm_tn_group_pays(int dtype, const GemmCall nn[3], const GemmCall tn[4], s
     apart += t_nn[2] + pair;
   else
     apart += beside(2) + t_tn[3];
-  // The model prices 256x256 tiles of weight gradients high (see TILE_KINDS).  With 0.93 of it no block of 56 measured, 512 to
-  // 4096 columns and 1024 to 16384 rows, is slower than by separate launches, and what it turns down is level; the few
-  // tiles of narrow blocks leave CUs idle, where shared launches of 128x128 tiles are level for longer.
-  long tiles = 0;
-  for (int i = 0; i < 4; ++i) tiles += (long)cdiv(tn[i].M, 256) * cdiv(tn[i].N, 256);
-  return inputs + (tiles < 64 ? 1.0 : 0.93) * together < apart;
+  return inputs + together < apart;
 }
 
 bm_status gemm_tn_group(const GemmCall* tn, int n, void* scratch, size_t scratch_bytes, hipStream_t st) {

@@ -163,7 +163,11 @@ BwdScratch layout_bwd(const Dims& m, int dtype, void* base) {
   s.norm1_ws = a.take<char>(norm_backward_scratch_bytes(m.norm, false, m.T, m.d));
   for (int i = 0; i < 2; ++i) s.seg_ws[i] = m.ada ? a.take<char>(segment_scratch_bytes()) : nullptr;
   const int widths[5] = {m.bias ? m.F : 0, m.bias && m.ada ? m.d : 0, m.bias && m.ada ? m.d : 0, m.bias ? m.QKV : 0, m.ada ? 6 * m.d : 0};
-  for (int i = 0; i < 5; ++i) s.colsum_ws[i] = widths[i] ? a.take<char>(colsum_scratch_bytes(m.T, widths[i])) : nullptr;
+  for (int i = 0; i < 5; ++i) {
+    size_t bytes = widths[i] ? colsum_scratch_bytes(m.T, widths[i]) : 0;
+    if (i == 1 || i == 2) bytes = widths[i] ? std::max(bytes, segment_columns_bytes()) : 0;       // down, o: beside the gates
+    s.colsum_ws[i] = bytes ? a.take<char>(bytes) : nullptr;
+  }
   const size_t tn = max_gemm_tn_scratch(m, dtype), rows = gemm_rows_scratch_bytes(m.T, m.d, dtype);
   s.gemm_ws_bytes = std::max(std::max(tn, rows), gemm_nn_tn_scratch_bytes(rows, tn, dtype));
   s.gemm_ws = a.take<char>(s.gemm_ws_bytes);
@@ -518,8 +522,9 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   if (m.ada) {
     // gate gradient (per-sequence sum of dy * m) and the gated upstream gradient in one pass over dy
     { ProfScope _p(PROF_ELEMENTWISE, 3.0 * T * d * (double)m.es, st);
-      BM_RETURN_IF(segment_gate(dt, dy, sv.m, sv.mod + 5 * d, 6 * d, ws.dgated, cu_dev, S, d, ws.dmod + 5 * d, 6 * d,
-                                ws.seg_ws[0], &segments, st)); }
+      BM_RETURN_IF(segment_gate(dt, dy, sv.m, sv.mod + 5 * d, 6 * d, ws.dgated, cu_dev, S, T, d, ws.dmod + 5 * d, 6 * d,
+                                ws.seg_ws[0], &segments, c.linear_bias ? (float*)grads->b_down : nullptr, ws.colsum_ws[1], &sums,
+                                st)); }
     dm = ws.dgated;
   }
   const bool fused_sums = m.bias && !m.ada;
@@ -607,9 +612,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   if (weights_last) BM_RETURN_IF(gemm_nn(dh));
   else BM_RETURN_IF(gemm_nn_tn(dt, dh, weight_grad(d, m.F, T, dm, ws.a, grads->w_down), ws.gemm_ws, ws.gemm_ws_bytes, st));
   // bias gradients of the down and output projections are column sums of the two
-  // gradients the norm backward below touches anyway (not so when a gate sits between)
-  if (c.linear_bias && !fused_sums)
-    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, dm, d, T, d, (float*)grads->b_down, ws.colsum_ws[1], &sums, st)); }
+  // gradients the norm backward below touches anyway (when a gate sits between: of what its backward writes)
 
   NormArgs n2 = norm_args(c, m, 2, w, sv.mod, sv.tok_seq);
   { ProfScope _p(PROF_NORM, 5.0 * T * m.d * (double)m.es, st);
@@ -624,14 +627,13 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
   if (m.ada) {
     char* gated = weights_last ? ws.da + (size_t)T * d * m.es : ws.dgated;
     { ProfScope _p(PROF_ELEMENTWISE, 3.0 * T * d * (double)m.es, st);
-      BM_RETURN_IF(segment_gate(dt, ws.dx1, sv.attn, sv.mod + 2 * d, 6 * d, gated, cu_dev, S, d, ws.dmod + 2 * d,
-                                6 * d, ws.seg_ws[1], &segments, st)); }
+      BM_RETURN_IF(segment_gate(dt, ws.dx1, sv.attn, sv.mod + 2 * d, 6 * d, gated, cu_dev, S, T, d, ws.dmod + 2 * d,
+                                6 * d, ws.seg_ws[1], &segments, c.linear_bias ? (float*)grads->b_o : nullptr, ws.colsum_ws[2], &sums,
+                                st)); }
     dattn = gated;
   }
   // (the weight gradient of the output projection is small: it shares a launch with the one of
   // the QKV projection at the end; dattn and the saved o stay untouched until then)
-  if (c.linear_bias && !fused_sums)
-    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(colsum_accumulate(dt, dattn, d, T, d, (float*)grads->b_o, ws.colsum_ws[2], &sums, st)); }
   {
     const GemmCall d_o = input_grad(T, m.QD, d, dattn, w->w_o, ws.d_o);
     if (m.E > 0 || weights_last) BM_RETURN_IF(gemm_nn(d_o));

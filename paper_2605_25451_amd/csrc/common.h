@@ -248,8 +248,9 @@ bool gemm_mfma_tn_pair(int K, int M0, int N0, const void* A0, int lda0, const vo
                        void* scratch, size_t scratch_bytes, hipStream_t st, bm_status* rc, double* time = nullptr);
 // All weight gradients of a block (the same rows, at most 4) in one launch; scratch as for any of them alone.  `pays`:
 // expected to be faster than launches that follow one another, where nn[i] and tn[i] (i < 2: up/down, o/up) can share
-// one and so can either nn[2] and tn[2] (qkv/o) or tn[2] and tn[3] (o/qkv).
+// one and so can either nn[2] and tn[2] (qkv/o) or tn[2] and tn[3] (o/qkv); the second form: where none of them do.
 bool gemm_tn_group_pays(int dtype, const GemmCall nn[3], const GemmCall tn[4], size_t scratch_bytes);
+bool gemm_tn_group_pays(int dtype, const GemmCall* tn, int n, size_t scratch_bytes);
 bm_status gemm_tn_group(const GemmCall* tn, int n, void* scratch, size_t scratch_bytes, hipStream_t st);
 bm_status gemm_mfma_tn_group(const GemmCall* tn, int n, void* scratch, size_t scratch_bytes, hipStream_t st);
 // expected times in us; < 0: not supported or not the choice
@@ -417,11 +418,14 @@ size_t colsum_scratch_bytes(int T, int N);
 bm_status colsum_accumulate(int dtype, const void* a, int lda, int T, int N, float* out,
                             void* scratch, ColumnSums* sums, hipStream_t st);
 // out[s, n] = sum_{t in s} a[t,n] * b[t,n] (fp32, overwrite) and, when gated != nullptr,
-// gated[t, n] = a[t, n] * gate[s, n]; rows are N wide; scratch: segment_scratch_bytes(), until `sums` is flushed
+// gated[t, n] = a[t, n] * gate[s, n]; rows are N wide; scratch: segment_scratch_bytes(), until `sums` is flushed.
+// bias_grad (nullable): += the column sums of gated when `columns` is flushed, with columns_ws until then
+// (segment_columns_bytes() and colsum_scratch_bytes(T, N), the larger)
 size_t segment_scratch_bytes();
+size_t segment_columns_bytes();
 bm_status segment_gate(int dtype, const void* a, const void* b, const float* gate, int ld_gate, void* gated,
-                       const int32_t* cu_dev, int S, int N, float* out, int ld_out, void* scratch,
-                       SegmentSums* sums, hipStream_t st);
+                       const int32_t* cu_dev, int S, int T, int N, float* out, int ld_out, void* scratch,
+                       SegmentSums* sums, float* bias_grad, void* columns_ws, ColumnSums* columns, hipStream_t st);
 // out[t, n] = (residual ? residual[t,n] : 0) + a[t, n] * gate[tok_seq[t], n]
 bm_status gate_mul(int dtype, const void* a, const float* gate, int ld_gate,
                    const int32_t* tok_seq, const void* residual, void* out, int T, int N,

@@ -416,7 +416,7 @@ bm_status flush_column_sums(ColumnSums* sums, hipStream_t st) {
 // rows round-robin, are combined through LDS in a fixed order, and the parts of a sequence are
 // added in a fixed order by seg_reduce_kernel, one launch for a whole backward pass (parts == 1 writes the result
 // directly).
-//   MODE 0 (gate):   sum0[s] = sum_t a*b;  optionally gated[t] = a[t] * gate[s]
+//   MODE 0 (gate):   sum0[s] = sum_t a*b;  optionally gated[t] = a[t] * gate[s], and its column sums (a bias gradient)
 //   MODE 1 (adaLN):  sum0[s] = sum_t dh,  sum1[s] = sum_t dh * xhat   (xhat from x and the row statistics)
 struct SegArgs {
   const void *a, *b;              // MODE 0: a, b.  MODE 1: dh, x
@@ -426,6 +426,7 @@ struct SegArgs {
   const int32_t* cu;
   float* out; int ld_out, off0, off1;   // out[s, off_p + n]
   float* partial;                 // [S*parts][planes][N] when parts > 1
+  float* columns;                 // MODE 0, nullable: [S*parts][N] column sums of the rows of gated
   int parts, rows, N;
 };
 
@@ -433,7 +434,7 @@ template <typename T, int MODE>
 __global__ __launch_bounds__(256) void seg_sums_kernel(SegArgs p) {
   constexpr int VEC = Elt<T>::VEC;
   constexpr int P = MODE == 0 ? 1 : 2;
-  __shared__ float sm[P][4][WAVE * VEC];
+  __shared__ float sm[2][4][WAVE * VEC];
   const int s = blockIdx.x / p.parts, part = blockIdx.x % p.parts;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int col = (blockIdx.y * WAVE + lane) * VEC;
@@ -443,9 +444,9 @@ __global__ __launch_bounds__(256) void seg_sums_kernel(SegArgs p) {
   const int rb = t0 + part * per, re = min(t1, rb + per);
   const T* a = (const T*)p.a;
   const T* b = (const T*)p.b;
-  float acc[P][VEC], g[VEC];
+  float acc[2][VEC], g[VEC];
 #pragma unroll
-  for (int e = 0; e < VEC; ++e) { acc[0][e] = 0.f; acc[P - 1][e] = 0.f; g[e] = 0.f; }
+  for (int e = 0; e < VEC; ++e) { acc[0][e] = 0.f; acc[1][e] = 0.f; g[e] = 0.f; }
   if (MODE == 0 && p.gated && live) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) g[e] = p.gate[(size_t)s * p.ld_gate + col + e];
@@ -461,7 +462,10 @@ __global__ __launch_bounds__(256) void seg_sums_kernel(SegArgs p) {
         if (p.gated) {
           float o[VEC];
 #pragma unroll
-          for (int e = 0; e < VEC; ++e) o[e] = va[e] * g[e];
+          for (int e = 0; e < VEC; ++e) {
+            o[e] = va[e] * g[e];
+            acc[1][e] += Elt<T>::to_f(Elt<T>::from_f(o[e]));
+          }
           store16((T*)p.gated + (size_t)t * p.N + col, o);
         }
       } else {
@@ -469,16 +473,23 @@ __global__ __launch_bounds__(256) void seg_sums_kernel(SegArgs p) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
           acc[0][e] += va[e];
-          acc[P - 1][e] += va[e] * ((vb[e] - mean) * rstd);
+          acc[1][e] += va[e] * ((vb[e] - mean) * rstd);
         }
       }
     }
   }
 #pragma unroll
-  for (int q = 0; q < P; ++q)
+  for (int q = 0; q < 2; ++q)
 #pragma unroll
     for (int e = 0; e < VEC; ++e) sm[q][wave][lane * VEC + e] = acc[q][e];
   __syncthreads();
+  if (MODE == 0 && p.columns && wave == 1 && live) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      const int c = lane * VEC + e;
+      p.columns[(size_t)blockIdx.x * p.N + col + e] = sm[1][0][c] + sm[1][1][c] + sm[1][2][c] + sm[1][3][c];
+    }
+  }
   if (wave == 0 && live) {
 #pragma unroll
     for (int q = 0; q < P; ++q) {
@@ -526,6 +537,7 @@ static int seg_parts(int S, int N, int vec) {
 // upper bound for any S: parts > 1 only while S * column blocks < 1024, and then
 // S * parts * N <= 2048 * 64 * VEC elements per plane
 size_t segment_scratch_bytes() { return (size_t)2048 * 512 * 2 * sizeof(float); }
+size_t segment_columns_bytes() { return (size_t)2048 * 512 * sizeof(float); }
 
 template <int MODE>
 static bm_status seg_launch(int dtype, SegArgs p, int S, void* scratch, SegmentSums* sums, hipStream_t st) {
@@ -542,12 +554,17 @@ static bm_status seg_launch(int dtype, SegArgs p, int S, void* scratch, SegmentS
 }
 
 bm_status segment_gate(int dtype, const void* a, const void* b, const float* gate, int ld_gate, void* gated,
-                       const int32_t* cu_dev, int S, int N, float* out, int ld_out, void* scratch,
-                       SegmentSums* sums, hipStream_t st) {
+                       const int32_t* cu_dev, int S, int T, int N, float* out, int ld_out, void* scratch,
+                       SegmentSums* sums, float* bias_grad, void* columns_ws, ColumnSums* columns, hipStream_t st) {
   SegArgs p{};
   p.a = a; p.b = b; p.gate = gate; p.ld_gate = ld_gate; p.gated = gated; p.cu = cu_dev;
   p.out = out; p.ld_out = ld_out; p.off0 = 0; p.off1 = 0; p.N = N;
-  return seg_launch<0>(dtype, p, S, scratch, sums, st);
+  const long rows = (long)S * (scratch ? seg_parts(S, N, dtype == BM_DTYPE_BF16 ? 8 : 4) : 1);
+  const bool here = bias_grad && rows * N * (long)sizeof(float) <= (long)segment_columns_bytes();
+  if (here) p.columns = (float*)columns_ws;
+  BM_RETURN_IF(seg_launch<0>(dtype, p, S, scratch, sums, st));
+  if (here) return columns->add(p.columns, (int)rows, N, N, bias_grad);
+  return bias_grad ? colsum_accumulate(dtype, gated, N, T, N, bias_grad, columns_ws, columns, st) : BM_OK;
 }
 
 static int norm_bwd_blocks(int T, int d) {

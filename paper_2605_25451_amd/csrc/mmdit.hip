@@ -170,7 +170,7 @@ MBwd layout_bwd(const MDims& m, int dtype, void* base) {
   }
   const int widths[5] = {m.F, m.d, m.d, m.QKV, 6 * m.d};
   for (int s = 0; s < 2; ++s)
-    for (int i = 0; i < 5; ++i) w.colsum_ws[s][i] = a.take<char>(colsum_scratch_bytes(m.Tmax, widths[i]));
+    for (int i = 0; i < 5; ++i) w.colsum_ws[s][i] = a.take<char>(std::max(colsum_scratch_bytes(m.Tmax, widths[i]), i == 1 || i == 2 ? segment_columns_bytes() : 0));
   w.gemm_ws_bytes = std::max(max_gemm_scratch(m, dtype), gemm_rows_scratch_bytes(m.Tmax, m.d, dtype));
   w.gemm_ws = a.take<char>(w.gemm_ws_bytes);
   w.bytes = a.off;
@@ -623,6 +623,21 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
 
   BM_RETURN_IF(build_tables(m, ws.tb, cu_dev, st));
 
+  // Weight gradients of a stream in one launch where that pays: those of the MLP and the output projection, and for the stream that
+  // is last in both halves also the QKV projection's, at its end.  Their operands then have to stay: the gradient of the
+  // activation's output, spent early, takes the gated gradient of the attention branch and the output of norm 1.
+  auto weight_grad = [](int M, int N, int K, const void* A, const void* B, void* C) { return GemmCall{M, N, K, A, M, B, N, C, N}; };
+  bool together[2];
+  for (int s = 0; s < 2; ++s) {
+    const int T = m.Ts[s];
+    void* const no = nullptr;
+    const GemmCall all[4] = {weight_grad(d, m.F, T, no, no, no), weight_grad(m.F, d, T, no, no, no), weight_grad(d, m.QD, T, no, no, no),
+                             weight_grad(m.QKV, d, T, no, no, no)};
+    together[s] = m.F >= 2 * d && gemm_tn_group_pays(dt, all, s == 0 ? 3 : 4, ws.gemm_ws_bytes);
+  }
+  char* const gated1 = ws.da;
+  char* const h1 = ws.da + (size_t)m.Tmax * d * m.es;
+
   // ---- per stream: MLP half and output projection, down to the attention output gradient
   for (int s = 0; s < 2; ++s) {
     const bm_block_params& p = w->stream[s];
@@ -633,31 +648,36 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
     float* dmod = ws.dmod[s];
     // y = x1 + g2 * m,  m = a W_down^T + b_down
     { ProfScope _p(PROF_ELEMENTWISE, 3.0 * T * d * (double)m.es, st);
-      BM_RETURN_IF(segment_gate(dt, dy[s], q.m, q.mod + 5 * d, 6 * d, ws.dgated, cu_dev[s], S, d, dmod + 5 * d, 6 * d,
-                                ws.seg_ws[s][0], &segments, st)); }
+      BM_RETURN_IF(segment_gate(dt, dy[s], q.m, q.mod + 5 * d, 6 * d, ws.dgated, cu_dev[s], S, T, d, dmod + 5 * d, 6 * d,
+                                ws.seg_ws[s][0], &segments, (float*)g.b_down, ws.colsum_ws[s][1], &sums, st)); }
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.F, d, ws.dgated, d, p.w_down, m.F, ws.da, m.F, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, (double)T * 4.0 * m.F * (double)m.es, st);
       BM_RETURN_IF(act_backward(dt, BM_ACT_GELU, q.up, ws.da, ws.dup, ws.a, (float*)g.b_up, ws.colsum_ws[s][0], T, m.F, &sums, st)); }
-    BM_RETURN_IF(gemm(GEMM_TN, dt, d, m.F, T, ws.dgated, d, ws.a, m.F, g.w_down, m.F, none, ws.gemm_ws,
+    if (!together[s])
+      BM_RETURN_IF(gemm(GEMM_TN, dt, d, m.F, T, ws.dgated, d, ws.a, m.F, g.w_down, m.F, none, ws.gemm_ws,
                       ws.gemm_ws_bytes, st));
-    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
-      BM_RETURN_IF(colsum_accumulate(dt, ws.dgated, d, T, d, (float*)g.b_down, ws.colsum_ws[s][1], &sums, st)); }
     // up = h2 W_up^T + b_up,  h2 = LN0(x1)(1 + scale2) + shift2
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.F, ws.dup, m.F, p.w_up, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_NORM, 5.0 * T * d * (double)m.es, st);
       BM_RETURN_IF(norm_backward(ada_norm_args(c, T, 2, q.mod, tok), q.x1, q.stats2, ws.dh, dy[s], ws.dx1[s], ws.h,
                                  nullptr, nullptr, nullptr, nullptr, dmod, cu_dev[s], S, ws.norm_ws[s], &sums, &segments,
                                  st)); }
-    BM_RETURN_IF(gemm(GEMM_TN, dt, m.F, d, T, ws.dup, m.F, ws.h, d, g.w_up, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
+    if (!together[s])
+      BM_RETURN_IF(gemm(GEMM_TN, dt, m.F, d, T, ws.dup, m.F, ws.h, d, g.w_up, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     // x1 = x + g1 * attn,  attn = o W_o^T + b_o
+    char* gated = together[s] ? gated1 : ws.dgated;
     { ProfScope _p(PROF_ELEMENTWISE, 3.0 * T * d * (double)m.es, st);
-      BM_RETURN_IF(segment_gate(dt, ws.dx1[s], q.attn, q.mod + 2 * d, 6 * d, ws.dgated, cu_dev[s], S, d, dmod + 2 * d,
-                                6 * d, ws.seg_ws[s][1], &segments, st)); }
-    BM_RETURN_IF(gemm(GEMM_TN, dt, d, m.QD, T, ws.dgated, d, q.o, m.QD, g.w_o, m.QD, none, ws.gemm_ws,
-                      ws.gemm_ws_bytes, st));
-    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
-      BM_RETURN_IF(colsum_accumulate(dt, ws.dgated, d, T, d, (float*)g.b_o, ws.colsum_ws[s][2], &sums, st)); }
-    BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.QD, d, ws.dgated, d, p.w_o, m.QD, ws.d_o, m.QD, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
+      BM_RETURN_IF(segment_gate(dt, ws.dx1[s], q.attn, q.mod + 2 * d, 6 * d, gated, cu_dev[s], S, T, d, dmod + 2 * d,
+                                6 * d, ws.seg_ws[s][1], &segments, (float*)g.b_o, ws.colsum_ws[s][2], &sums, st)); }
+    if (!together[s]) {
+      BM_RETURN_IF(gemm(GEMM_TN, dt, d, m.QD, T, gated, d, q.o, m.QD, g.w_o, m.QD, none, ws.gemm_ws,
+                        ws.gemm_ws_bytes, st));
+    } else if (s == 0) {
+      const GemmCall three[3] = {weight_grad(d, m.F, T, ws.dgated, ws.a, g.w_down), weight_grad(m.F, d, T, ws.dup, ws.h, g.w_up),
+                                 weight_grad(d, m.QD, T, gated, q.o, g.w_o)};
+      BM_RETURN_IF(gemm_tn_group(three, 3, ws.gemm_ws, ws.gemm_ws_bytes, st));
+    }
+    BM_RETURN_IF(gemm(GEMM_NN, dt, T, m.QD, d, gated, d, p.w_o, m.QD, ws.d_o, m.QD, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
     { ProfScope _p(PROF_ELEMENTWISE, 2.0 * T * m.QD * (double)m.es, st);
       BM_RETURN_IF(row_scatter(dt, ws.d_o, ws.tb.jpos[s], ws.d_o_j, T, m.QD, st)); }
   }
@@ -686,12 +706,19 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
       BM_RETURN_IF(colsum_accumulate(dt, ws.dqkv, m.QKV, T, m.QKV, (float*)g.b_qkv, ws.colsum_ws[s][3], &sums, st));
     }
     BM_RETURN_IF(gemm(GEMM_NN, dt, T, d, m.QKV, ws.dqkv, m.QKV, p.w_qkv, d, ws.dh, d, none, ws.gemm_ws, ws.gemm_ws_bytes, st));
+    char* hn = together[1] ? h1 : ws.h;              // the last stream's norm 2 output stays for its gradient
     { ProfScope _p(PROF_NORM, 5.0 * T * d * (double)m.es, st);
-      BM_RETURN_IF(norm_backward(ada_norm_args(c, T, 1, q.mod, tok), x[s], q.stats1, ws.dh, ws.dx1[s], dx[s], ws.h,
+      BM_RETURN_IF(norm_backward(ada_norm_args(c, T, 1, q.mod, tok), x[s], q.stats1, ws.dh, ws.dx1[s], dx[s], hn,
                                  nullptr, nullptr, nullptr, nullptr, dmod, cu_dev[s], S, ws.norm1_ws, &sums, &segments,
                                  st)); }
-    BM_RETURN_IF(gemm(GEMM_TN, dt, m.QKV, d, T, ws.dqkv, m.QKV, ws.h, d, g.w_qkv, d, none, ws.gemm_ws,
-                      ws.gemm_ws_bytes, st));
+    if (s == 1 && together[1]) {
+      const GemmCall all[4] = {weight_grad(d, m.F, T, ws.dgated, ws.a, g.w_down), weight_grad(m.F, d, T, ws.dup, ws.h, g.w_up),
+                               weight_grad(d, m.QD, T, gated1, q.o, g.w_o), weight_grad(m.QKV, d, T, ws.dqkv, hn, g.w_qkv)};
+      BM_RETURN_IF(gemm_tn_group(all, 4, ws.gemm_ws, ws.gemm_ws_bytes, st));
+    } else {
+      BM_RETURN_IF(gemm(GEMM_TN, dt, m.QKV, d, T, ws.dqkv, m.QKV, hn, d, g.w_qkv, d, none, ws.gemm_ws,
+                        ws.gemm_ws_bytes, st));
+    }
     // mod = silu(cond) W_ada^T + b_ada
     const int S8 = (int)align_up(S, 8);
     BM_RETURN_IF(flush_segment_sums(&segments, st));

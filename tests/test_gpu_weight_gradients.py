@@ -65,3 +65,28 @@ def test_tied_accumulators_add_up():
     assert float((both - want).norm() / want.norm()) <= 1e-5
     for k in ("w_o", "w_qkv"):
         assert float((run.grads[k] - g[k]).norm() / g[k].norm()) <= 1e-5, k
+
+
+@pytest.mark.parametrize("text,image", [([500, 800], [1100, 900]), ([40, 33], [1000, 1111]), ([1024, 1024], [70, 9])],
+                         ids=["both", "image", "text"])
+def test_two_stream_block(text, image):
+    """Streams long enough for a shared launch, both and either of them, with rows that end inside tiles and whole ones."""
+    import test_gpu_mmdit as mmdit
+    cfg = synth.scaled(synth.dit_block(), hidden=1024, n_q_heads=8, n_kv_heads=8, head_dim=128, mlp_hidden=2048)
+    case = synth.make_two_stream_case(cfg, text, image, 75, 1, "two_stream_weights")
+    print("two-stream weight gradients", flush=True)
+    mmdit.compare(case, mmdit.run_hip(case), mmdit.run_oracle(case))
+
+
+def test_bias_sums_of_more_sequences_than_fit():
+    """The sums of the gated gradients beside the gates: a row per part of a sequence; more of them than the workspace has go a
+    way of their own."""
+    from paper_2605_25451_amd.runner import CaseOnDevice
+    case = synth.make_case(synth.dit_block(), [1] * 900 + [3] * 40, 29, name="many")
+    dev = CaseOnDevice(case)
+    dev.step()
+    y, dx, grads, dcond = dev.results()
+    ref = bo.block_fwd_bwd(case.cfg, case.params, case.x, case.cu_seqlens, case.dy, cond=case.cond)
+    assert rel(dx, ref[1]) <= 2e-2
+    for k, g in ref[2].items():
+        assert rel(grads[k], g) <= 2e-2, k
