@@ -539,7 +539,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     GemmEpilogue swb; swb.swiglu_up = sv.up; swb.swiglu_dup = ws.dup; swb.swiglu_a = ws.a;
     const bool fused = c.act == BM_ACT_SWIGLU && m.F % 256 == 0 &&
                        gemm_mfma_grouped_supported(GEMM_NN, dt, m.cap, m.F, d, d, m.F, m.F);
-    const bool in_place = fused && T <= MOE_SOURCE_ROWS && gemm_mfma_reads_source_rows(GEMM_NN, m.cap, m.F, &swb) &&
+    const bool in_place = fused && T <= MOE_SOURCE_ROWS && m.F <= 32 * d && gemm_mfma_reads_source_rows(GEMM_NN, m.cap, m.F, &swb) &&
                           gemm_mfma_grouped_supported(GEMM_TN, dt, d, m.F, m.cap, d, m.F, m.F) &&
                           gemm_mfma_reads_source_rows(GEMM_TN, d, m.F, nullptr) &&
                           gemm_mfma_grouped_supported(GEMM_TN, dt, m.UP, d, m.cap, m.UP, d, d) &&
@@ -549,14 +549,11 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
       from_dy.source = from_h.source = sv.moe.row_token;
       from_dy.src_rows = from_h.src_rows = T;
       from_dy.row_scale = sv.moe.row_gate;
+      from_dy.row_dot = (float*)ws.xp;                 // (the sorted copies have no use then)
       from_h.source_operand = 1;
     }
     const void* dyp = in_place ? dm : ws.dyp;
-    {
-      ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
-      if (!in_place) BM_RETURN_IF(moe_gather(dt, dm, sv.moe, 1, ws.dyp, d, T, st));            // gate * dy of the row's token
-      BM_RETURN_IF(moe_router_backward(dt, dm, sv.moe_y, sv.moe, ws.dlogits, T, m.E, m.k, d, st));
-    }
+    if (!in_place) { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(moe_gather(dt, dm, sv.moe, 1, ws.dyp, d, T, st)); }   // gate * dy of the row's token
     from_dy.b_stride = (long)d * m.F;
     if (fused) {
       // SwiGLU backward in the epilogue of the experts' input-gradient GEMM: dA never goes to memory
@@ -566,6 +563,9 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
       { ProfScope _p(PROF_ELEMENTWISE, (double)m.cap * (2.0 * m.UP + 2.0 * m.F) * (double)m.es, st);
         BM_RETURN_IF(act_backward(dt, c.act, sv.up, ws.da, ws.dup, ws.a, nullptr, nullptr, m.cap, m.F, nullptr, st)); }
     }
+    // the gradient of a gate: <dy, y of its row>, or what the epilogue above has left of <dA, a>, the same sum without a pass over y
+    { ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
+      BM_RETURN_IF(moe_router_backward(dt, dm, sv.moe_y, from_dy.row_dot, m.F / 64, sv.moe, ws.dlogits, T, m.E, m.k, d, st)); }
     from_dy.c_stride = (long)d * m.F;
     BM_RETURN_IF(gemm_grouped(GEMM_TN, dt, d, m.F, m.cap, dyp, d, ws.a, m.F, grads->w_down, m.F, from_dy, st));
     g.b_stride = (long)m.UP * d;

@@ -227,6 +227,7 @@ struct GemmGroups {
   const int32_t* source = nullptr;
   int src_rows = 0, source_operand = 0;
   const float* row_scale = nullptr;      // dev [rows]: factor of every row of A, with the SwiGLU backward epilogue (its activation included)
+  float* row_dot = nullptr;              // dev [rows, N / 64] with it: what the row's product with the activation sums to, without the factor
   int n_groups = 0;
   long b_stride = 0;                     // elements between the B matrices of two groups (NT, NN)
   long c_stride = 0;                     // elements between the C matrices of two groups (TN)
@@ -297,7 +298,9 @@ bm_status moe_gather(int dtype, const void* src, const MoeTables& m, int use_gat
                      hipStream_t st);
 bm_status moe_combine(int dtype, const void* rows, const MoeTables& m, int use_gate, const void* res,
                       void* out, int T, int k, int d, hipStream_t st);
-bm_status moe_router_backward(int dtype, const void* dm, const void* y_rows, const MoeTables& m,
+// the gradient of a gate is <dm, y_rows> of its routed row, or the sum of the row's `parts` values of row_dot (then dm and y_rows are
+// not read)
+bm_status moe_router_backward(int dtype, const void* dm, const void* y_rows, const float* row_dot, int parts, const MoeTables& m,
                               void* dlogits, int T, int E, int k, int d, hipStream_t st);
 
 // generic (any shape, fp32 arithmetic) and MFMA (bf16) back ends

@@ -622,7 +622,7 @@ bm_status gemm_mfma(int layout, int M, int N, int K, const void* A, int lda, con
     set_error("gemm: the SwiGLU forward epilogue needs the NT layout, N a multiple of 256 and no bias");
     return BM_ERR_INVALID_ARG;
   }
-  p.tile_group = nullptr; p.group_rows = nullptr; p.row_tiles = nullptr; p.source = nullptr; p.src_rows = 0; p.row_scale = nullptr; p.b_group_stride = 0; p.c_group_stride = 0;
+  p.tile_group = nullptr; p.group_rows = nullptr; p.row_tiles = nullptr; p.source = nullptr; p.src_rows = 0; p.row_scale = nullptr; p.row_dot = nullptr; p.b_group_stride = 0; p.c_group_stride = 0;
   p.grid_groups = 1;
   p.xcd_split = xcd_split_possible(pl.tiles_m * pl.tiles_n, pl.splits) ? 1 : 0;
   p.big_rows = pl.big_rows;
@@ -900,7 +900,7 @@ GemmParams plain_params(const GemmCall& g, const Plan& pl, float* partial) {
   p.tiles_m = pl.tiles_m; p.tiles_n = pl.tiles_n; p.splits = pl.splits; p.k_per_split = pl.k_per_split;
   p.out_fp32 = 0;
   p.xcd_split = xcd_split_possible(pl.tiles_m * pl.tiles_n, pl.splits) ? 1 : 0;
-  p.tile_group = nullptr; p.group_rows = nullptr; p.row_tiles = nullptr; p.source = nullptr; p.src_rows = 0; p.row_scale = nullptr; p.b_group_stride = 0; p.c_group_stride = 0; p.grid_groups = 1;
+  p.tile_group = nullptr; p.group_rows = nullptr; p.row_tiles = nullptr; p.source = nullptr; p.src_rows = 0; p.row_scale = nullptr; p.row_dot = nullptr; p.b_group_stride = 0; p.c_group_stride = 0; p.grid_groups = 1;
   return p;
 }
 
@@ -994,7 +994,7 @@ bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int 
   p.tile_group = layout == GEMM_TN ? nullptr : g.tile_group;
   p.group_rows = layout == GEMM_TN ? g.group_rows : nullptr;
   p.row_tiles = layout == GEMM_TN ? nullptr : g.row_tiles;
-  p.source = g.source; p.src_rows = g.src_rows; p.row_scale = g.row_scale;
+  p.source = g.source; p.src_rows = g.src_rows; p.row_scale = g.row_scale; p.row_dot = g.row_dot;
   if (g.source && !gemm_mfma_reads_source_rows(layout, M, N, epi)) {
     set_error("grouped gemm: rows of this product are not read from their source");
     return BM_ERR_UNSUPPORTED;

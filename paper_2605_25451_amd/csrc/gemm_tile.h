@@ -35,7 +35,8 @@ struct GemmParams {
   // rows read where they lie instead of from a sorted copy: the source row (of src_rows) of each row of A (grouped NT and NN) or of
   // each k row of one operand (grouped TN); what is out of range reads the first row of its tile or group
   const int32_t* source; int src_rows;
-  const float* row_scale;       // SwiGLU backward: a factor of every row of the product
+  const float* row_scale;       // SwiGLU backward: a factor of every row of the product ...
+  float* row_dot;               // ... and [rows, N / 64]: the product times the activation, both without it, summed over 64 columns
   int big_rows;                 // of launch_gemm_alt_mixed: rows of 256x256 tiles, before tiles_m - big_rows of 128x256
   int grid_groups;              // host: workgroups = tiles * splits * grid_groups (>= 1)
 };
@@ -368,14 +369,21 @@ __device__ inline void gemm_epilogue(const GemmParams& p, f32x4 (&acc)[FM][FN], 
           union { u32x4 u; bf16_t h[8]; } sg{pre[i & 1][t][0]}, su{pre[i & 1][t][1]};
           float dg[8], du[8], av[8];
           const float sc = scale[i & 1][t];                    // on the activation as well: it is only read for the weight gradient
+          float dot = 0.f;
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             const float g = (float)sg.h[e], u = (float)su.h[e];
             const float sig = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
+            dot += out[e] * (g * sig * u);
             const float sl = sc * (g * sig);                   // silu(g)
             av[e] = sl * u;
             du[e] = out[e] * sl;
             dg[e] = sc * out[e] * u * sig * (1.0f + g * (1.0f - sig));
+          }
+          if (p.row_dot) {
+#pragma unroll
+            for (int off = 1; off < LPR; off <<= 1) dot += __shfl_xor(dot, off, WAVE);
+            if (lane % LPR == 0) p.row_dot[(size_t)gm * (p.N / TN_) + col0 / TN_] = dot;
           }
           store16(p.sw_dup + up_idx, dg);
           store16(p.sw_dup + up_idx + p.N, du);

@@ -296,12 +296,14 @@ __global__ void moe_combine_kernel(const T* __restrict__ rows, const int32_t* __
 
 // ---- router backward (one wavefront per token) ------------------------------------------------
 // dgate[t,j] = <dm[t], y_rows[slot[t,j]]>; then through the gate normalisation and the
-// softmax: dlogit_e = p_e (dp_e - sum_e' p_e' dp_e'), dp nonzero on the chosen experts only
+// softmax: dlogit_e = p_e (dp_e - sum_e' p_e' dp_e'), dp nonzero on the chosen experts only.
+// <dm, y> = <dm W_down, a>, which the SwiGLU backward's epilogue has in registers: with its partial sums (row_dot) 65536 rows
+// of 2048 columns are not read (96 -> 14 us)
 template <typename T>
 __global__ __launch_bounds__(256) void moe_router_bwd_kernel(
-    const T* __restrict__ dm, const T* __restrict__ y_rows, const int32_t* __restrict__ slot,
-    const int32_t* __restrict__ idx, const float* __restrict__ gate, const float* __restrict__ probs,
-    T* __restrict__ dlogits, int Tn, int E, int k, int d, int cap) {
+    const T* __restrict__ dm, const T* __restrict__ y_rows, const float* __restrict__ row_dot, int parts,
+    const int32_t* __restrict__ slot, const int32_t* __restrict__ idx, const float* __restrict__ gate,
+    const float* __restrict__ probs, T* __restrict__ dlogits, int Tn, int E, int k, int d, int cap) {
   constexpr int VEC = Elt<T>::VEC;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int t = blockIdx.x * 4 + wave;
@@ -314,7 +316,9 @@ __global__ __launch_bounds__(256) void moe_router_bwd_kernel(
     const int s = slot[(size_t)t * k + j];
     if (s < 0 || s >= cap) continue;
     float part = 0.f;
-    for (int c = lane * VEC; c < d; c += WAVE * VEC) {
+    if (row_dot)
+      for (int c = lane; c < parts; c += WAVE) part += row_dot[(size_t)s * parts + c];
+    else for (int c = lane * VEC; c < d; c += WAVE * VEC) {
       float a[VEC], b[VEC];
       load16(dm + (size_t)t * d + c, a);
       load16(y_rows + (size_t)s * d + c, b);
@@ -428,14 +432,14 @@ bm_status moe_combine(int dtype, const void* rows, const MoeTables& m, int use_g
   return BM_OK;
 }
 
-bm_status moe_router_backward(int dtype, const void* dm, const void* y_rows, const MoeTables& m,
+bm_status moe_router_backward(int dtype, const void* dm, const void* y_rows, const float* row_dot, int parts, const MoeTables& m,
                               void* dlogits, int T, int E, int k, int d, hipStream_t st) {
   if (dtype == BM_DTYPE_BF16)
     hipLaunchKernelGGL(moe_router_bwd_kernel<bf16_t>, dim3(cdiv(T, 4)), dim3(256), 0, st, (const bf16_t*)dm,
-                       (const bf16_t*)y_rows, m.slot, m.idx, m.gate, m.probs, (bf16_t*)dlogits, T, E, k, d, m.cap);
+                       (const bf16_t*)y_rows, row_dot, parts, m.slot, m.idx, m.gate, m.probs, (bf16_t*)dlogits, T, E, k, d, m.cap);
   else
     hipLaunchKernelGGL(moe_router_bwd_kernel<float>, dim3(cdiv(T, 4)), dim3(256), 0, st, (const float*)dm,
-                       (const float*)y_rows, m.slot, m.idx, m.gate, m.probs, (float*)dlogits, T, E, k, d, m.cap);
+                       (const float*)y_rows, row_dot, parts, m.slot, m.idx, m.gate, m.probs, (float*)dlogits, T, E, k, d, m.cap);
   BM_CHECK_LAUNCH("moe_router_backward");
   return BM_OK;
 }
