@@ -264,6 +264,8 @@ bm_status gemm_grouped(int layout, int dtype, int M, int N, int K, const void* A
                        const void* B, int ldb, void* C, int ldc, const GemmGroups& g, hipStream_t st,
                        const GemmEpilogue* epi = nullptr);
 constexpr int MOE_SOURCE_ROWS = 8192;
+// the kernels reach a source row by a 32-bit byte offset from the first one
+inline bool source_rows_in_reach(long src_rows, int width) { return src_rows * width * (long)sizeof(bf16_t) <= (1L << 32); }
 bool gemm_mfma_reads_source_rows(int layout, int M, int N, const GemmEpilogue* epi);
 bool gemm_mfma_grouped_supported(int layout, int dtype, int M, int N, int K, int lda, int ldb, int ldc);
 bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int lda, const void* B,
