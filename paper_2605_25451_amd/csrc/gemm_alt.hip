@@ -652,7 +652,9 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt_groups_kernel(GemmParams 
   const int row_tiles = p.row_tiles[0], total = row_tiles * p.tiles_n;
   if ((int)blockIdx.x >= total) return;
   int tm, tn;
-  grouped_tile<4>(xcd_run(blockIdx.x, total), row_tiles, p.tiles_n, &tm, &tn);
+  const int id = xcd_run(blockIdx.x, total);
+  if (p.walk_rows == 2) grouped_tile<2>(id, row_tiles, p.tiles_n, &tm, &tn);
+  else grouped_tile<4>(id, row_tiles, p.tiles_n, &tm, &tn);
   const int tile = p.row_tiles[1 + tm], block = tile >> 1;
   TileJob job;
   job.A = p.A; job.B = p.B + (long)p.tile_group[block] * p.b_group_stride;

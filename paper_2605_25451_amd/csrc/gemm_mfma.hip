@@ -1019,6 +1019,10 @@ bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int 
   }
   if (layout != GEMM_TN && N >= 256) {
     p.tiles_m = g.row_tiles_cap; p.tiles_n = cdiv(N, 256);
+    // Up to 512 rows an expert has two row tiles on average: walked two at a time, an XCD's CUs read the weights of half as many
+    // experts at once, and of more of each one's columns.  128 experts, a pass with two and with four: 512 rows each
+    // 4248 and 4274 us, 312 3491 and 3503, 16 to 156 level, eight at a time as four.  More rows share a weight panel among four.
+    p.walk_rows = g.n_groups > 0 && g.routed_rows <= 512L * g.n_groups ? 2 : 4;
     return launch_gemm_alt_groups(layout, p, st);
   }
   if (layout != GEMM_TN) return launch_small(layout, p, st);

@@ -38,6 +38,7 @@ struct GemmParams {
   const float* row_scale;       // SwiGLU backward: a factor of every row of the product ...
   float* row_dot;               // ... and [rows, N / 64]: the product times the activation, both without it, summed over 64 columns
   int big_rows;                 // of launch_gemm_alt_mixed: rows of 256x256 tiles, before tiles_m - big_rows of 128x256
+  int walk_rows;                // of launch_gemm_alt_groups: row tiles that are walked side by side, 2 or 4
   int grid_groups;              // host: workgroups = tiles * splits * grid_groups (>= 1)
 };
 
