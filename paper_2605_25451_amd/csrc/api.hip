@@ -84,10 +84,17 @@ size_t gemm_tn_pair_scratch_bytes(int K, int M0, int N0, int M1, int N1, int dty
   return both > one ? both : one;
 }
 
+// Accumulators that share memory (tied weights) are added to one after the other, never by one launch.  NULL: not known yet.
+static bool accumulators_overlap(const void* C0, int M0, int ldc0, const void* C1, int M1, int ldc1) {
+  const char *a = (const char*)C0, *b = (const char*)C1;
+  return a && b && a < b + (size_t)M1 * ldc1 * sizeof(float) && b < a + (size_t)M0 * ldc0 * sizeof(float);
+}
+
 bool gemm_tn_pair_shares_launch(int dtype, int K, int M0, int N0, const void* A0, int lda0, const void* B0, int ldb0,
                                 void* C0, int ldc0, int M1, int N1, const void* A1, int lda1, const void* B1, int ldb1,
                                 void* C1, int ldc1, void* scratch, size_t scratch_bytes, hipStream_t st) {
   return dtype == BM_DTYPE_BF16 && K > 0 && M0 > 0 && N0 > 0 && M1 > 0 && N1 > 0 &&
+         !accumulators_overlap(C0, M0, ldc0, C1, M1, ldc1) &&
          gemm_mfma_tn_pair(K, M0, N0, A0, lda0, B0, ldb0, C0, ldc0, M1, N1, A1, lda1, B1, ldb1, C1, ldc1, scratch,
                            scratch_bytes, st, nullptr);
 }
@@ -160,19 +167,15 @@ bool gemm_tn_group_pays(int dtype, const GemmCall nn[3], const GemmCall tn[4], s
 bm_status gemm_tn_group(const GemmCall* tn, int n, void* scratch, size_t scratch_bytes, hipStream_t st) {
   double flops = 0.0;
   for (int i = 0; i < n; ++i) flops += 2.0 * tn[i].M * tn[i].N * tn[i].K;
-  // accumulators that share memory (tied weights) are added to one after the other
   for (int i = 0; i < n; ++i)
-    for (int j = 0; j < i; ++j) {
-      const char *a = (const char*)tn[i].C, *b = (const char*)tn[j].C;
-      const size_t an = (size_t)tn[i].M * tn[i].ldc * sizeof(float), bn = (size_t)tn[j].M * tn[j].ldc * sizeof(float);
-      if (a < b + bn && b < a + an) {
+    for (int j = 0; j < i; ++j)
+      if (accumulators_overlap(tn[i].C, tn[i].M, tn[i].ldc, tn[j].C, tn[j].M, tn[j].ldc)) {
         const GemmEpilogue none;
         for (int k = 0; k < n; ++k)
           BM_RETURN_IF(gemm(GEMM_TN, BM_DTYPE_BF16, tn[k].M, tn[k].N, tn[k].K, tn[k].A, tn[k].lda, tn[k].B, tn[k].ldb, tn[k].C,
                             tn[k].ldc, none, scratch, scratch_bytes, st));
         return BM_OK;
       }
-    }
   ProfScope prof(PROF_GEMM_TN, flops, st);
   return gemm_mfma_tn_group(tn, n, scratch, scratch_bytes, st);
 }

@@ -36,3 +36,40 @@ def test_tied_gradients_add_up(cfg, lens):
     assert torch.equal(biases, want)
     for k in ("norm1_b", "norm2_b", "b_up", "b_qkv"):
         assert torch.equal(run.grads[k], g[k]), k
+
+
+VIT_256 = synth.scaled(synth.vit_large(), hidden=256, n_q_heads=4, n_kv_heads=4, mlp_hidden=512)
+
+
+@pytest.mark.parametrize("lens", [[500, 268], [156, 100]], ids=["3_ranges", "1_range"])
+def test_tied_qkv_and_output_weights_add_up(lens):
+    """The weight gradients of the QKV and output projections share a launch; with accumulators that overlap, here the last
+    rows of w_qkv's and the first ones of w_o's, they have one each."""
+    import torch
+    from paper_2605_25451_amd import binding as bm
+    from paper_2605_25451_amd.runner import CaseOnDevice
+    dev = CaseOnDevice(synth.make_case(VIT_256, lens, 5, name="tied_qkv_o"))
+    run = dev.runner
+
+    def weight_gradient_launches():             # alone or with each other: one beside an input gradient counts as that
+        bm.profile_begin()
+        dev.step()
+        _, flops, count = bm.profile_end()["gemm_tn"]
+        torch.cuda.synchronize()
+        return count, flops
+    print("separate accumulators", flush=True)
+    apart = weight_gradient_launches()
+    g = {k: v.clone() for k, v in run.grads.items()}
+    d, qkv = VIT_256.hidden, VIT_256.qkv_dim
+    both = torch.zeros(qkv + d // 2, d, device="cuda")
+    run.g = bm.make_params(dict(run.grads, w_qkv=both[:qkv], w_o=both[qkv - d // 2:]))
+    run.zero_grads()
+    print("tied accumulators", flush=True)
+    assert weight_gradient_launches() != apart
+    want = torch.zeros_like(both)
+    want[:qkv] += g["w_qkv"]
+    want[qkv - d // 2:] += g["w_o"]
+    # the same products with their k ranges cut elsewhere: 2-norm error of an fp32 sum over 768 rows, 2^-24 * sqrt(768) = 1.7e-6
+    assert float((both - want).norm() / want.norm()) <= 1e-5
+    for k in ("w_up", "w_down", "b_qkv", "b_o"):
+        assert torch.equal(run.grads[k], g[k]), k
