@@ -326,6 +326,8 @@ __device__ __forceinline__ void alt256_tile(const GemmParams& p, const TileJob& 
 // SOURCE: 1 or 2 where the k rows of A or B are read from their source rows (whole slices only).  The table of source rows costs a tile
 // about a microsecond in front of its first loads and four LDS reads a slice; a sorted copy costs its own pass and 268 MB to
 // be read back (65536 rows of 2048): up 1536x2048 with the pass 870 -> 755 us, down 2048x768 500 -> 405.
+// The rows that fill up a group stand at its end and read a row of a token: they are zeroed in the fragments, or an infinity of that
+// token would meet their zeros as a NaN.
 template <int EPI, bool CUT, int SOURCE = 0>
 __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJob& job) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -404,13 +406,14 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
 #pragma unroll
     for (int q = 0; q < 4; ++q) af[4 + q] = fa.read(smem, q, KS, buf + 128 * 2);
   };
-  auto cut = [&](int ks) {
-    const u32x4 mask = cut_mask(ks, k_left, lane);
+  auto cut = [&](int ks, int left) {
+    const u32x4 mask = cut_mask(ks, left, lane);
 #pragma unroll
     for (int q = 0; q < 4; ++q) cut_fragment(bf[q], mask);
 #pragma unroll
     for (int q = 0; q < 8; ++q) cut_fragment(af[q], mask);
   };
+  int routed = 0;                                           // SOURCE: k rows of the tile before those that fill up its group
   // COME: slices that follow this one (2: two or more, 0: this is the last).  A wait names the half slice that is read
   // next: everything older than the two halves requested since must have landed.
   auto slice = [&](auto come_t, int j) {
@@ -420,7 +423,9 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
     if (COME >= 1) load_half(Int<1>{}, j + 1, buf ^ BUF);
     if (COME >= 2) fetch_rows(Int<0>{}, j + 2);
     wait_fragments();
-    if (CUT && COME == 0 && k_left < BK) cut(0);
+    const int left = SOURCE ? routed - j * BK : k_left;     // (a group is filled up by less than two slices)
+    const bool ends = SOURCE ? COME <= 1 && left < BK : CUT && COME == 0 && k_left < BK;
+    if (ends) cut(0, left);
     wait_loads<COME >= 1 ? 2 * HL : 0>();
     end_phase();
     multiply();
@@ -429,7 +434,7 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
     read(Int<1>{}, buf);
     if (COME >= 2) { load_half(Int<0>{}, j + 2, buf); fetch_rows(Int<1>{}, j + 2); }
     wait_fragments();
-    if (CUT && COME == 0 && k_left < BK) cut(1);
+    if (ends) cut(1, left);
     if (COME == 0) { end_phase(); return; }                 // the last MFMAs belong to the epilogue
     wait_loads<COME >= 2 ? 2 * HL : HL>();
     end_phase();
@@ -442,6 +447,10 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
     if constexpr (SOURCE == 2) { load_a(Int<0>{}, 0, 0); load_a(Int<1>{}, 0, 0); }
     else { load_b(Int<0>{}, 0, 0); load_b(Int<1>{}, 0, 0); }
     for (int i = threadIdx.x; i < n * BK; i += THREADS) rows[i] = source_row(p.source + job.kbeg, i, p.src_rows);
+    routed = n * BK - MOE_PAD;
+#pragma unroll
+    for (int i = 0; i < MOE_PAD; i += WAVE)
+      routed += __popcll(__ballot((uint32_t)p.source[job.kend - MOE_PAD + i + lane] < (uint32_t)p.src_rows));
     __syncthreads();
     fetch_rows(Int<0>{}, 0);
     fetch_rows(Int<1>{}, 0);

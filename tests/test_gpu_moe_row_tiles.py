@@ -17,3 +17,28 @@ pytestmark = pytest.mark.gpu
 def test_row_tiles(E, k, lens, F):
     cfg = moe.moe_cfg(synth.DTYPE_BF16, 512, 4, 2, 128, F, E, k, 0.2)
     moe.test_bf16_choice_is_admissible_and_everything_matches_under_it("moe_tiles", cfg, lens, 71)
+
+
+def test_infinity_beside_rows_that_fill_up_an_expert():
+    """The first token of an expert has an infinite gradient: the rows that fill up the expert's last block read that token's row and
+    add nothing, so the expert's weight gradients are infinite where the token reaches and never NaN."""
+    import torch
+    from paper_2605_25451_amd.runner import CaseOnDevice
+    E, d, F, hit = 3, 512, 256, 5
+    dev = CaseOnDevice(synth.make_case(moe.moe_cfg(synth.DTYPE_BF16, d, 4, 2, 128, F, E, 2, 0.2), [333, 167], 72, name="moe_inf"))
+    dev.forward()
+    chosen, _ = dev.moe_routing()
+    rows = [int((chosen == e).sum()) for e in range(E)]
+    mine = [int(e) for e in chosen[0]]                          # the token in front of theirs
+    assert all(rows[e] % 128 for e in mine)
+    dev.dy[0, hit] = float("inf")
+    print("infinite gradient", rows, flush=True)
+    dev.backward()
+    torch.cuda.synchronize()
+    down, up = dev.runner.grads["w_down"].view(E, d, F), dev.runner.grads["w_up"].view(E, 2 * F, d)
+    reached = torch.zeros(d, 1, dtype=torch.bool, device="cuda")
+    reached[hit] = True
+    for e in range(E):
+        assert torch.equal(torch.isinf(down[e]), (reached if e in mine else reached & False).expand(d, F)), e
+        assert not torch.isnan(down[e]).any() and not torch.isnan(up[e]).any(), e
+        assert bool(torch.isinf(up[e]).all()) == (e in mine) and bool(torch.isfinite(up[e]).all()) == (e not in mine), e
