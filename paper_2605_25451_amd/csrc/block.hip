@@ -443,10 +443,8 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
       // the activation rides in the epilogue of the experts' up projections, which read the tokens' rows where they lie
       GemmEpilogue e; e.swiglu_fwd_a = ws.a;
       GemmGroups from = g;
-      const bool in_place = source_rows_in_reach(T, m.d);
-      if (in_place) { from.source = sv.moe.row_token; from.src_rows = T; }
-      else { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(moe_gather(dt, ws.h, sv.moe, 0, ws.xp, m.d, T, st)); }
-      BM_RETURN_IF(gemm_grouped(GEMM_NT, dt, m.cap, m.UP, m.d, in_place ? ws.h : ws.xp, m.d, w->w_up, m.d, sv.up, m.UP, from, st, &e));
+      from.source = sv.moe.row_token; from.src_rows = T;
+      BM_RETURN_IF(gemm_grouped(GEMM_NT, dt, m.cap, m.UP, m.d, ws.h, m.d, w->w_up, m.d, sv.up, m.UP, from, st, &e));
     } else {
       { ProfScope _p(PROF_ELEMENTWISE, 0.0, st); BM_RETURN_IF(moe_gather(dt, ws.h, sv.moe, 0, ws.xp, m.d, T, st)); }
       BM_RETURN_IF(gemm_grouped(GEMM_NT, dt, m.cap, m.UP, m.d, ws.xp, m.d, w->w_up, m.d, sv.up, m.UP, g, st));
@@ -541,7 +539,7 @@ extern "C" bm_status bm_block_backward(const bm_block_desc* desc, const bm_block
     GemmEpilogue swb; swb.swiglu_up = sv.up; swb.swiglu_dup = ws.dup; swb.swiglu_a = ws.a;
     const bool fused = c.act == BM_ACT_SWIGLU && m.F % 256 == 0 &&
                        gemm_mfma_grouped_supported(GEMM_NN, dt, m.cap, m.F, d, d, m.F, m.F);
-    const bool in_place = fused && T <= MOE_SOURCE_ROWS && source_rows_in_reach(T, d) && m.F <= 32 * d && gemm_mfma_reads_source_rows(GEMM_NN, m.cap, m.F, &swb) &&
+    const bool in_place = fused && T <= MOE_SOURCE_ROWS && m.F <= 32 * d && gemm_mfma_reads_source_rows(GEMM_NN, m.cap, m.F, &swb) &&
                           gemm_mfma_grouped_supported(GEMM_TN, dt, d, m.F, m.cap, d, m.F, m.F) &&
                           gemm_mfma_reads_source_rows(GEMM_TN, d, m.F, nullptr) &&
                           gemm_mfma_grouped_supported(GEMM_TN, dt, m.UP, d, m.cap, m.UP, d, d) &&

@@ -222,8 +222,9 @@ struct GemmGroups {
   const int32_t* row_tiles = nullptr;    // dev [1 + row_tiles_cap]  (NT, NN): their number, then for each twice its first row block,
   int row_tiles_cap = 0;                 //   plus one where it holds the next block of the same group as well
   // Rows read where they lie instead of from a sorted copy (gemm_mfma_reads_source_rows): the source row, of src_rows, of each row of A
-  // (NT, NN) or of each k row of A (source_operand 0) or B (1) (TN, groups of at most MOE_SOURCE_ROWS).  Rows without one read
-  // some row of their group; what they are multiplied with has to be zero, or their results are never read.
+  // (NT, NN) or of each k row of A (source_operand 0) or B (1) (TN, src_rows at most MOE_SOURCE_ROWS).  A source row stands at
+  // most once in a group.  Rows without one stand at the end of a group: they read some row of it (NT, NN: results that are
+  // never read; TN: they add nothing).
   const int32_t* source = nullptr;
   int src_rows = 0, source_operand = 0;
   const float* row_scale = nullptr;      // dev [rows]: factor of every row of A, with the SwiGLU backward epilogue (its activation included)
@@ -264,8 +265,6 @@ bm_status gemm_grouped(int layout, int dtype, int M, int N, int K, const void* A
                        const void* B, int ldb, void* C, int ldc, const GemmGroups& g, hipStream_t st,
                        const GemmEpilogue* epi = nullptr);
 constexpr int MOE_SOURCE_ROWS = 8192;
-// the kernels reach a source row by a 32-bit byte offset from the first one
-inline bool source_rows_in_reach(long src_rows, int width) { return src_rows * width * (long)sizeof(bf16_t) <= (1L << 32); }
 bool gemm_mfma_reads_source_rows(int layout, int M, int N, const GemmEpilogue* epi);
 bool gemm_mfma_grouped_supported(int layout, int dtype, int M, int N, int K, int lda, int ldb, int ldc);
 bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int lda, const void* B,

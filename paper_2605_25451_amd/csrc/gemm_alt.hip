@@ -497,7 +497,7 @@ __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_tn_kernel(GemmParams p
 template <int SOURCE>
 __global__ __launch_bounds__(THREADS, 2) void gemm_alt256_tn_source_kernel(GemmParams p) {
   TileJob job = locate_tile<256, 256>(p, blockIdx.x);
-  job.kend = min(job.kend, job.kbeg + MOE_SOURCE_ROWS);
+  job.kend = min(job.kend, job.kbeg + MOE_SOURCE_ROWS);       // (no group of that many source rows is longer)
   alt256_tn_tile<EPI_ADD, false, SOURCE>(p, job);
 }
 

@@ -995,9 +995,14 @@ bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int 
   p.group_rows = layout == GEMM_TN ? g.group_rows : nullptr;
   p.row_tiles = layout == GEMM_TN ? nullptr : g.row_tiles;
   p.source = g.source; p.src_rows = g.src_rows; p.row_scale = g.row_scale; p.row_dot = g.row_dot;
-  if (g.source && !gemm_mfma_reads_source_rows(layout, M, N, epi)) {
-    set_error("grouped gemm: rows of this product are not read from their source");
-    return BM_ERR_UNSUPPORTED;
+  if (g.source) {
+    // a source row is reached by a 32-bit byte offset from the first one; the rows of a weight gradient's group fit a table in LDS
+    const long ld = layout == GEMM_TN && g.source_operand == 1 ? ldb : lda;
+    if (!gemm_mfma_reads_source_rows(layout, M, N, epi) || g.src_rows < 1 || g.src_rows * ld * (long)sizeof(bf16_t) > (1L << 32) ||
+        (layout == GEMM_TN && g.src_rows > MOE_SOURCE_ROWS)) {
+      set_error("grouped gemm: rows of this product are not read from their source");
+      return BM_ERR_UNSUPPORTED;
+    }
   }
   p.b_group_stride = g.b_stride; p.c_group_stride = g.c_stride;
   p.grid_groups = layout == GEMM_TN ? g.n_groups : 1;
