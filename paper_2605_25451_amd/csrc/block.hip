@@ -430,7 +430,7 @@ extern "C" bm_status bm_block_forward(const bm_block_desc* desc, const bm_block_
                         ws.gemm_ws, ws.gemm_ws_bytes, st));
     }
     GemmGroups g;
-    g.tile_group = sv.moe.tile_group; g.n_groups = m.E; g.routed_rows = (long)T * m.k;
+    g.tile_group = sv.moe.tile_group; g.routed_rows = (long)T * m.k;
     g.row_tiles = sv.moe.row_tiles; g.row_tiles_cap = moe_row_tiles_cap(m.cap, m.E);
     {
       ProfScope _p(PROF_ELEMENTWISE, 0.0, st);

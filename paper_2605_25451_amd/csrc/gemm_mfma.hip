@@ -1024,10 +1024,12 @@ bm_status gemm_mfma_grouped(int layout, int M, int N, int K, const void* A, int 
   }
   if (layout != GEMM_TN && N >= 256) {
     p.tiles_m = g.row_tiles_cap; p.tiles_n = cdiv(N, 256);
-    // Up to 512 rows an expert has two row tiles on average: walked two at a time, an XCD's CUs read the weights of half as many
-    // experts at once, and of more of each one's columns.  128 experts, a pass with two and with four: 512 rows each
-    // 4248 and 4274 us, 312 3491 and 3503, 16 to 156 level, eight at a time as four.  More rows share a weight panel among four.
-    p.walk_rows = g.n_groups > 0 && g.routed_rows <= 512L * g.n_groups ? 2 : 4;
+    // Walked two at a time, the row tiles of an XCD's CUs belong to half as many experts, of whose weights they read more columns;
+    // with more than 8 column tiles two rows of them are more panels than four rows of fewer.  A pass with four and with two, both
+    // products up to 2048 columns: 128 experts of 768, 512 rows each 4416 and 4390 us, 768 rows 6057 and 6014, 1024 rows 7485 and 7448, 64 experts
+    // of 2048 rows 6790 and 6751; up to 4096 columns: 16 experts of 512 rows 3568 and 3621, 750 rows 4687 and 4717.  With this line none
+    // of 18 (8 to 128 experts, 512 to 2048 rows each) is slower than by four or by two.
+    p.walk_rows = p.tiles_n <= 8 ? 2 : 4;
     return launch_gemm_alt_groups(layout, p, st);
   }
   if (layout != GEMM_TN) return launch_small(layout, p, st);

@@ -12,7 +12,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("E,k,lens,F", [(1, 1, [128], 256), (1, 1, [129], 256), (1, 1, [256], 264), (1, 1, [200, 57], 256),
                                         (1, 1, [300, 340], 136), (3, 2, [333, 167], 256), (4, 1, [260, 380], 264),
                                         # the most rows whose tokens a weight gradient looks up itself, and one pack that is sorted first
-                                        (1, 1, [512] * 16, 256), (2, 1, [500] * 16 + [193], 256)],
+                                        (1, 1, [512] * 16, 256), (2, 1, [500] * 16 + [193], 256),
+                                        # more than 8 column tiles: four row tiles side by side
+                                        (3, 2, [333, 467], 1288)],
                          ids=lambda v: str(v) if isinstance(v, int) else "%d_rows" % sum(v))
 def test_row_tiles(E, k, lens, F):
     cfg = moe.moe_cfg(synth.DTYPE_BF16, 512, 4, 2, 128, F, E, k, 0.2)
