@@ -11,16 +11,16 @@ pytestmark = pytest.mark.gpu
 TWO_HEIGHTS = (384, 256)
 
 
-@pytest.mark.parametrize("layout,M,N,K", [(0, 5477, 4104, 200), (0, 3301, 5376, 64), (0, 4300, 5384, 1024), (1, 5477, 4104, 200),
+@pytest.mark.parametrize("layout,M,N,K", [(0, 5121, 4496, 328), (0, 6204, 5256, 64), (0, 4300, 5384, 1024), (1, 3874, 3976, 216),
                                           (1, 4300, 4096, 520), (1, 3333, 5384, 1024)])
 def test_products(layout, M, N, K):
     gemm.test_gemm_tiles(layout, M, N, K, TWO_HEIGHTS, False, True)
 
 
 @pytest.mark.parametrize("hidden,mlp,T,product", [
-    (512, 2688, 3301, (0, "2F", "d")),          # SwiGLU forward
-    (512, 2688, 6203, (1, "F", "d")),           # SwiGLU backward
-    (1536, 512, 11003, (0, "d", "F")),          # residual
+    (384, 2688, 3929, (0, "2F", "d")),          # SwiGLU forward
+    (640, 3072, 5444, (1, "F", "d")),           # SwiGLU backward
+    (1536, 576, 11003, (0, "d", "F")),          # residual
 ])
 def test_fused_epilogues(hidden, mlp, T, product):
     from paper_2605_25451_amd import binding as bm
