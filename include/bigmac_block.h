@@ -288,8 +288,12 @@ bm_status bm_probe_attention_backward_plan(int32_t mask, int32_t Hq, int32_t Hkv
                                            int32_t* dkdv_wgs /* host */, int32_t* dq_wgs /* host */);
 /* The products of a dense block's backward that may share a launch (host only).  k_ranges[2 i], k_ranges[2 i + 1]: the k ranges of the
  * input gradient and of the weight gradient of pair i -- 0: up and down projection, 1: output and up, 2: QKV and output -- or
- * 0, 0 where they are launched apart. */
+ * 0, 0 where no launch holds both. */
 bm_status bm_probe_block_backward_plan(const bm_block_desc* desc, int32_t T, int32_t S, int32_t* k_ranges /* host [6] */);
+/* The weight gradients of a dense block's backward that share a launch with one another (host only): the k ranges of the down, up,
+ * output and QKV projection's, all four or the last two, 0 for one that shares none.  (Accumulators that overlap are
+ * added to by launches of their own.) */
+bm_status bm_probe_block_weight_gradients(const bm_block_desc* desc, int32_t T, int32_t S, int32_t* k_ranges /* host [4] */);
 
 /* ---- nested schedule (host only; Sec. 3.1 and the BuildSchedule figure) ------------ */
 

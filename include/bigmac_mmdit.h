@@ -64,6 +64,11 @@ bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit_params* w,
                             const bm_mmdit_params* grads, void* dcond,
                             void* scratch, size_t scratch_bytes, void* hip_stream);
 
+/* The weight gradients of the backward that share a launch with others of their stream (host only), as
+ * bm_probe_block_weight_gradients: four of the text stream, four of the image stream. */
+bm_status bm_probe_mmdit_weight_gradients(const bm_mmdit_desc* desc, int32_t T_text, int32_t T_img, int32_t S,
+                                          int32_t* k_ranges /* host [8] */);
+
 #ifdef __cplusplus
 }
 #endif

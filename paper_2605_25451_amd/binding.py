@@ -164,6 +164,8 @@ def lib() -> C.CDLL:
         l.bm_probe_attention_backward_plan.restype = C.c_int
         l.bm_probe_block_backward_plan.argtypes = [C.POINTER(BlockDesc), i32, i32, pi32]
         l.bm_probe_block_backward_plan.restype = C.c_int
+        l.bm_probe_block_weight_gradients.argtypes = l.bm_probe_block_backward_plan.argtypes
+        l.bm_probe_block_weight_gradients.restype = C.c_int
         l.bm_probe_read.restype = C.c_int
         l.bm_probe_fill.restype = C.c_int
         l.bm_probe_mfma.restype = C.c_int
@@ -205,7 +207,8 @@ def lib() -> C.CDLL:
         l.bm_mmdit_forward.argtypes = [pmd, pmp, vp, vp, vp, vp, vp, vp, i32, vp, vp, vp, vp, vp, sz, vp]
         l.bm_mmdit_backward.argtypes = [pmd, pmp, vp, vp, vp, vp, vp, vp, vp, vp, i32, vp, vp, vp, vp, pmp,
                                         vp, vp, sz, vp]
-        for name in ("bm_mmdit_sizes", "bm_mmdit_forward", "bm_mmdit_backward"):
+        l.bm_probe_mmdit_weight_gradients.argtypes = [pmd, i32, i32, i32, pi32]
+        for name in ("bm_mmdit_sizes", "bm_mmdit_forward", "bm_mmdit_backward", "bm_probe_mmdit_weight_gradients"):
             getattr(l, name).restype = C.c_int
         i64 = C.c_int64
         l.bm_cp_attention_forward.argtypes = [i32] * 5 + [vp, i32, vp, vp, i32, vp, vp, vp, vp, i32, vp, vp, vp]
@@ -530,10 +533,24 @@ def probe_attention_backward_plan(mask, Hq, Hkv, dh, cu_q_host, cu_k_host=None):
 
 
 def probe_block_backward_plan(desc: BlockDesc, T, S):
-    """Per pair of products that may share a launch: the k ranges of input and weight gradient, (0, 0) if launched apart."""
+    """Per pair of products that may share a launch: the k ranges of input and weight gradient, (0, 0) if no launch holds both."""
     out = (C.c_int32 * 6)()
     _check(lib().bm_probe_block_backward_plan(C.byref(desc), T, S, out))
     return [(out[i], out[i + 1]) for i in (0, 2, 4)]
+
+
+def probe_block_weight_gradients(desc: BlockDesc, T, S):
+    """The k ranges of the down, up, output and QKV projection's weight gradients that share a launch, 0 for one that shares none."""
+    out = (C.c_int32 * 4)()
+    _check(lib().bm_probe_block_weight_gradients(C.byref(desc), T, S, out))
+    return tuple(out)
+
+
+def probe_mmdit_weight_gradients(desc: MmditDesc, T_text, T_img, S):
+    """The same for the text and the image stream of a two-stream block."""
+    out = (C.c_int32 * 8)()
+    _check(lib().bm_probe_mmdit_weight_gradients(C.byref(desc), T_text, T_img, S, out))
+    return tuple(out[:4]), tuple(out[4:])
 
 
 def profile_begin():

@@ -729,3 +729,22 @@ extern "C" bm_status bm_probe_block_backward_plan(const bm_block_desc* desc, int
                       k_ranges + 5);
   return BM_OK;
 }
+
+extern "C" bm_status bm_probe_block_weight_gradients(const bm_block_desc* desc, int32_t T, int32_t S, int32_t* k_ranges) {
+  BM_RETURN_IF(check_desc(desc));
+  BM_ARG_CHECK(T >= 1 && S >= 1 && S <= T && k_ranges, "bm_probe_block_weight_gradients: bad T=%d S=%d or NULL output", T, S);
+  BM_RETURN_IF(check_extent(*desc, T, S));
+  if (desc->n_experts > 0) { set_error("bm_probe_block_weight_gradients: a block of experts"); return BM_ERR_UNSUPPORTED; }
+  const Dims m = make_dims(*desc, T, S);
+  const int dt = desc->dtype, d = m.d;
+  const size_t bytes = layout_bwd(m, dt, nullptr).gemm_ws_bytes;
+  for (int i = 0; i < 4; ++i) k_ranges[i] = 0;
+  void* const none = nullptr;
+  void* const some = (void*)256;                       // as above
+  if (weight_grads_last(m, dt, bytes))
+    gemm_mfma_tn_group_ranges(backward_gemms(m).tn, 4, bytes, k_ranges);
+  else if (gemm_tn_pair_shares_launch(dt, T, m.QKV, d, none, m.QKV, none, d, none, d, d, m.QD, none, d, none, m.QD, none, m.QD, some,
+                                      bytes, nullptr))
+    k_ranges[2] = k_ranges[3] = gemm_mfma_tn_pair_ranges(T, m.QKV, d, d, m.QD);
+  return BM_OK;
+}

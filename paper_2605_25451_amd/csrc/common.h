@@ -255,6 +255,9 @@ bool gemm_tn_group_pays(int dtype, const GemmCall nn[3], const GemmCall tn[4], s
 bool gemm_tn_group_pays(int dtype, const GemmCall* tn, int n, size_t scratch_bytes);
 bm_status gemm_tn_group(const GemmCall* tn, int n, void* scratch, size_t scratch_bytes, hipStream_t st);
 bm_status gemm_mfma_tn_group(const GemmCall* tn, int n, void* scratch, size_t scratch_bytes, hipStream_t st);
+// the k ranges of each where they share that launch (host only), and of either of a pair that shares one
+void gemm_mfma_tn_group_ranges(const GemmCall* tn, int n, size_t scratch_bytes, int32_t* k_ranges);
+int gemm_mfma_tn_pair_ranges(int K, int M0, int N0, int M1, int N1);
 // expected times in us; < 0: not supported or not the choice
 double gemm_mfma_tn_group_time(const GemmCall* tn, int n, size_t scratch_bytes);
 double gemm_mfma_nn_tn_time(const GemmCall& nn, const GemmCall& tn, size_t scratch_bytes);

@@ -474,7 +474,7 @@ int split_cap(int layout, int M, int N, int K) {
 // 8192x11008x4096 527 -> 516.  Of 260 products drawn from 384 to 16384 rows that it takes two are slower (NT 4509x12216x6160 by 3 %,
 // 8527x9608x4456 by 2 %), the mean is 8 % faster.  Where 128x128 is the best of the four it stays: on short contractions a
 // second workgroup on the CU hides the output, and the model prices that lower than it is (150 such products, K up to 976: 19 %
-// slower to 12 % faster with two heights, 5 % slower on average; NT 2566x13424x200 34 -> 43, 5430x3000x304 22.5 -> 27).
+// slower to 12 % faster with two heights, 4 % slower on average; NT 2566x13424x200 34 -> 43, 5430x3000x304 22.5 -> 27).
 void mixed_rows(int layout, int M, int N, int K, Plan* best, double* best_t) {
   const TileKind &big = TILE_KINDS[0], &low = TILE_KINDS[1];
   const int tiles_n = cdiv(N, 256), slices = cdiv(K, BK);
@@ -815,6 +815,14 @@ double gemm_mfma_tn_group_time(const GemmCall* w, int n, size_t scratch_bytes) {
   double t;
   return tn_group_plan(w, n, scratch_bytes, &plan, &t) ? t : -1.0;
 }
+
+void gemm_mfma_tn_group_ranges(const GemmCall* w, int n, size_t scratch_bytes, int32_t* k_ranges) {
+  TnGroupPlan plan;
+  const bool shared = tn_group_plan(w, n, scratch_bytes, &plan, nullptr);
+  for (int i = 0; i < n; ++i) k_ranges[i] = !shared ? 0 : plan.split_part == ALL_PARTS || plan.split_part == i ? plan.splits : 1;
+}
+
+int gemm_mfma_tn_pair_ranges(int K, int M0, int N0, int M1, int N1) { return pair_splits(K, M0, N0, M1, N1); }
 
 bm_status gemm_mfma_tn_group(const GemmCall* w, int n, void* scratch, size_t scratch_bytes, hipStream_t st) {
   TnGroupPlan plan;

@@ -478,6 +478,25 @@ AttnArgs joint_attn_args(const bm_block_desc& c, const MDims& m, const char* qkv
 
 using namespace bm;
 
+namespace {
+
+GemmCall weight_grad(int M, int N, int K, const void* A, const void* B, void* C) { return {M, N, K, A, M, B, N, C, N}; }
+
+// the weight gradients of a stream that may share a launch: down, up and output projection, of the second stream also QKV
+struct StreamGrads { GemmCall tn[4]; int n; };
+StreamGrads stream_grads(const MDims& m, int s) {
+  const int T = m.Ts[s], d = m.d;
+  void* const no = nullptr;
+  return {{weight_grad(d, m.F, T, no, no, no), weight_grad(m.F, d, T, no, no, no), weight_grad(d, m.QD, T, no, no, no),
+           weight_grad(m.QKV, d, T, no, no, no)}, s == 0 ? 3 : 4};
+}
+bool weight_grads_last(const MDims& m, int dtype, int s, size_t gemm_ws_bytes) {
+  const StreamGrads g = stream_grads(m, s);
+  return m.F >= 2 * m.d && gemm_tn_group_pays(dtype, g.tn, g.n, gemm_ws_bytes);
+}
+
+}  // namespace
+
 extern "C" bm_status bm_mmdit_sizes(const bm_mmdit_desc* desc, int32_t T_text, int32_t T_img, int32_t S,
                                     size_t* saved_bytes, size_t* scratch_bytes) {
   BM_RETURN_IF(check_mdesc(desc));
@@ -626,15 +645,8 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
   // Weight gradients of a stream in one launch where that pays: those of the MLP and the output projection, and for the stream that
   // is last in both halves also the QKV projection's, at its end.  Their operands then have to stay: the gradient of the
   // activation's output, spent early, takes the gated gradient of the attention branch and the output of norm 1.
-  auto weight_grad = [](int M, int N, int K, const void* A, const void* B, void* C) { return GemmCall{M, N, K, A, M, B, N, C, N}; };
   bool together[2];
-  for (int s = 0; s < 2; ++s) {
-    const int T = m.Ts[s];
-    void* const no = nullptr;
-    const GemmCall all[4] = {weight_grad(d, m.F, T, no, no, no), weight_grad(m.F, d, T, no, no, no), weight_grad(d, m.QD, T, no, no, no),
-                             weight_grad(m.QKV, d, T, no, no, no)};
-    together[s] = m.F >= 2 * d && gemm_tn_group_pays(dt, all, s == 0 ? 3 : 4, ws.gemm_ws_bytes);
-  }
+  for (int s = 0; s < 2; ++s) together[s] = weight_grads_last(m, dt, s, ws.gemm_ws_bytes);
   char* const gated1 = ws.da;
   char* const h1 = ws.da + (size_t)m.Tmax * d * m.es;
 
@@ -738,4 +750,22 @@ extern "C" bm_status bm_mmdit_backward(const bm_mmdit_desc* desc, const bm_mmdit
   BM_RETURN_IF(silu_backward_f32(dt, cond, ws.dsc[0], dcond, (long)S * d, st));
   ProfScope _p(PROF_ELEMENTWISE, 0.0, st);
   return flush_column_sums(&sums, st);
+}
+
+extern "C" bm_status bm_probe_mmdit_weight_gradients(const bm_mmdit_desc* desc, int32_t T_text, int32_t T_img, int32_t S,
+                                                     int32_t* k_ranges) {
+  BM_RETURN_IF(check_mdesc(desc));
+  BM_ARG_CHECK(S >= 1 && T_text >= S && T_img >= S && k_ranges,
+               "bm_probe_mmdit_weight_gradients: bad T_text=%d T_img=%d S=%d or NULL output", T_text, T_img, S);
+  BM_RETURN_IF(check_mextent(*desc, T_text, T_img));
+  const MDims m = make_mdims(*desc, T_text, T_img, S);
+  const int dt = desc->block.dtype;
+  const size_t bytes = layout_bwd(m, dt, nullptr).gemm_ws_bytes;
+  for (int i = 0; i < 8; ++i) k_ranges[i] = 0;
+  for (int s = 0; s < 2; ++s)
+    if (weight_grads_last(m, dt, s, bytes)) {
+      const StreamGrads g = stream_grads(m, s);
+      gemm_mfma_tn_group_ranges(g.tn, g.n, bytes, k_ranges + 4 * s);
+    }
+  return BM_OK;
 }

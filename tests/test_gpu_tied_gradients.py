@@ -41,13 +41,14 @@ def test_tied_gradients_add_up(cfg, lens):
 VIT_256 = synth.scaled(synth.vit_large(), hidden=256, n_q_heads=4, n_kv_heads=4, mlp_hidden=512)
 
 
-@pytest.mark.parametrize("lens", [[500, 268], [156, 100]], ids=["3_ranges", "1_range"])
-def test_tied_qkv_and_output_weights_add_up(lens):
+@pytest.mark.parametrize("lens,ranges", [([500, 268], 3), ([156, 100], 1)], ids=["3_ranges", "1_range"])
+def test_tied_qkv_and_output_weights_add_up(lens, ranges):
     """The weight gradients of the QKV and output projections share a launch; with accumulators that overlap, here the last
     rows of w_qkv's and the first ones of w_o's, they have one each."""
     import torch
     from paper_2605_25451_amd import binding as bm
     from paper_2605_25451_amd.runner import CaseOnDevice
+    assert bm.probe_block_weight_gradients(bm.make_desc(VIT_256), sum(lens), len(lens)) == (0, 0, ranges, ranges)
     dev = CaseOnDevice(synth.make_case(VIT_256, lens, 5, name="tied_qkv_o"))
     run = dev.runner
 

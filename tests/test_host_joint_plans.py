@@ -4,6 +4,7 @@ import pytest
 
 import test_gpu_joint_attention as attention
 import test_gpu_joint_gradients as gradients
+import test_gpu_weight_gradients as weights
 from paper_2605_25451_amd import binding as bm
 from paper_2605_25451_amd import synth
 
@@ -26,9 +27,23 @@ def test_every_variant_of_the_joint_products_has_a_case():
     assert len(seen) == 8
 
 
-def test_full_packs_are_launched_apart():
+def test_full_packs_share_no_launch_with_an_input_gradient():
     assert bm.probe_block_backward_plan(bm.make_desc(synth.vit_large()), 16384, 28) == [(0, 0)] * 3
     assert bm.probe_block_backward_plan(bm.make_desc(synth.decoder_7b()), 8192, 8) == [(0, 0)] * 3
+
+
+@pytest.mark.parametrize("cfg,T,ranges", [
+    (synth.vit_large(), 16384, (1, 1, 1, 1)), (synth.decoder_7b(), 8192, (1, 1, 1, 1)),
+    # past 16384 rows the QKV and output projection alone, or none; fewer than 1024 rows beside input gradients
+    (synth.vit_large(), 20000, (0, 0, 4, 4)), (synth.decoder_8b_gqa(), 32768, (0, 0, 0, 0)), (synth.decoder_7b(), 777, (0, 0, 0, 0)),
+    (synth.vit_tiny(), 40, (0, 0, 0, 0))])
+def test_weight_gradients_of_a_pack(cfg, T, ranges):
+    assert bm.probe_block_weight_gradients(bm.make_desc(cfg), T, 1) == ranges
+
+
+def test_weight_gradient_cases():
+    for name, (cfg, lens) in weights.CASES.items():
+        assert bm.probe_block_weight_gradients(bm.make_desc(cfg), sum(lens), len(lens)) == weights.RANGES[name], name
 
 
 @pytest.mark.parametrize("layout,M,N,K", [(0, 3301, 5376, 64), (0, 2566, 13424, 200), (1, 4631, 11600, 176), (0, 5430, 3000, 304),
@@ -43,8 +58,14 @@ def test_bad_arguments():
     for T, S in ((0, 1), (4, 5), (4, 0)):
         with pytest.raises(bm.BmError):
             bm.probe_block_backward_plan(desc, T, S)
+        with pytest.raises(bm.BmError):
+            bm.probe_block_weight_gradients(desc, T, S)
+        with pytest.raises(bm.BmError):
+            bm.probe_mmdit_weight_gradients(bm.make_mmdit_desc(synth.dit_block(), 1), T, 8, S)
     with pytest.raises(bm.BmError):
         bm.probe_block_backward_plan(bm.make_desc(synth.decoder_moe()), 64, 1)
+    with pytest.raises(bm.BmError):
+        bm.probe_block_weight_gradients(bm.make_desc(synth.decoder_moe()), 64, 1)
     with pytest.raises(bm.BmError):
         bm.probe_attention_backward_plan(2, 4, 4, 64, [0, 8])
     assert bm.probe_attention_backward_plan(0, 4, 4, 16, [0, 8]) == (0, 0, 0)
