@@ -124,15 +124,12 @@ static double tn_group_time(int dtype, const GemmCall* tn, int n, size_t scratch
   if (dtype != BM_DTYPE_BF16 || tn[0].K < 1024 || tn[0].K > 16384) return -1.0;
   const double together = gemm_mfma_tn_group_time(tn, n, scratch_bytes);
   if (together < 0.0) return -1.0;
-  // The model prices 256x256 tiles of weight gradients high (see TILE_KINDS), but not what a round of them that leaves CUs idle loses to
-  // the launches that input and weight gradients share.  Passes of 22 kinds of blocks, 256 to 3072 columns, at 1024 to 16384 rows,
-  // with this launch and without: from 160 tiles on 0.93 of the model is right (172 tiles and ratios of 0.95 to 1.0: 2 to 3 %
-  // faster; 776: 2 to 3 %; one of 200 measured loses more than 1.5 %: SwiGLU of 1024/2816 columns, 1301 rows, 322 -> 330 us).  Of 64 to
-  // 159 tiles, below 1.02 of it, more lost than gained (decoder of 640/1792 columns, 1500 rows 240 -> 253 us, 768/2048 columns, 3000
-  // rows 338 -> 353; the other way ViT of 768 columns, 4096 rows 425 -> 401).  Fewer tiles are mostly split and level near 1.
+  // The model prices 256x256 tiles of weight gradients high (see TILE_KINDS).  With 0.93 of it no block of 56 measured, 512 to
+  // 4096 columns and 1024 to 16384 rows, is slower than by separate launches, and what it turns down is level; the few
+  // tiles of narrow blocks leave CUs idle, where shared launches of 128x128 tiles are level for longer.
   long tiles = 0;
   for (int i = 0; i < n; ++i) tiles += (long)cdiv(tn[i].M, 256) * cdiv(tn[i].N, 256);
-  return (tiles < 64 ? 1.0 : tiles < 160 ? 1.02 : 0.93) * together;
+  return (tiles < 64 ? 1.0 : 0.93) * together;
 }
 
 bool gemm_tn_group_pays(int dtype, const GemmCall* tn, int n, size_t scratch_bytes) {

@@ -41,17 +41,6 @@ def test_weight_gradients_of_a_pack(cfg, T, ranges):
     assert bm.probe_block_weight_gradients(bm.make_desc(cfg), T, 1) == ranges
 
 
-@pytest.mark.parametrize("base,d,F,T,share", [
-    # 96, 108 and 144 tiles: a shared launch that the model sees level with the others is none; 172 and 192: it is one
-    (synth.decoder_7b(), 640, 1792, 1500, False), (synth.decoder_7b(), 768, 2048, 3000, False), (synth.vit_large(), 768, 3072, 1700, False),
-    (synth.decoder_7b(), 768, 3072, 2200, False), (synth.vit_large(), 768, 3072, 6000, True), (synth.vit_large(), 896, 3584, 1250, True),
-    (synth.vit_large(), 1024, 4096, 1555, True)])
-def test_shared_weight_gradients_by_tiles(base, d, F, T, share):
-    heads = d // base.head_dim
-    cfg = synth.scaled(base, hidden=d, n_q_heads=heads, n_kv_heads=heads, mlp_hidden=F)
-    assert all(bm.probe_block_weight_gradients(bm.make_desc(cfg), T, 1)) == share
-
-
 def test_weight_gradient_cases():
     for name, (cfg, lens) in weights.CASES.items():
         assert bm.probe_block_weight_gradients(bm.make_desc(cfg), sum(lens), len(lens)) == weights.RANGES[name], name
