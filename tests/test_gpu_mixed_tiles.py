@@ -18,9 +18,9 @@ def test_products(layout, M, N, K):
 
 
 @pytest.mark.parametrize("hidden,mlp,T,product", [
-    (384, 2688, 3929, (0, "2F", "d")),          # SwiGLU forward
-    (640, 3072, 5444, (1, "F", "d")),           # SwiGLU backward
-    (1536, 576, 11003, (0, "d", "F")),          # residual
+    (512, 2688, 3301, (0, "2F", "d")),          # SwiGLU forward
+    (512, 2688, 6203, (1, "F", "d")),           # SwiGLU backward
+    (1536, 512, 11003, (0, "d", "F")),          # residual
 ])
 def test_fused_epilogues(hidden, mlp, T, product):
     from paper_2605_25451_amd import binding as bm
