@@ -124,9 +124,12 @@ static double tn_group_time(int dtype, const GemmCall* tn, int n, size_t scratch
   if (dtype != BM_DTYPE_BF16 || tn[0].K < 1024 || tn[0].K > 16384) return -1.0;
   const double together = gemm_mfma_tn_group_time(tn, n, scratch_bytes);
   if (together < 0.0) return -1.0;
-  // The model prices 256x256 tiles of weight gradients high (see TILE_KINDS).  With 0.93 of it no block of 56 measured, 512 to
-  // 4096 columns and 1024 to 16384 rows, is slower than by separate launches, and what it turns down is level; the few
-  // tiles of narrow blocks leave CUs idle, where shared launches of 128x128 tiles are level for longer.
+  // The model prices 256x256 tiles of weight gradients high (see TILE_KINDS).  Passes over three states in turn, this launch against
+  // separate ones, 14 kinds of blocks of 512 to 1152 columns at 1024 to 5000 rows: where 0.93 of the model is below the others it is
+  // 4 % faster on average and at worst 3 % slower (ViT of 768 columns, 2200 rows; decoder of 768/2048 columns, 2600 to 3300 rows
+  // 2 %); the few tiles of narrow blocks leave CUs idle, where shared launches of 128x128 tiles are level for longer.
+  // The 192 tiles of a ViT of 1024 columns, one round that leaves CUs idle, differ by card over long packs: 12000 rows 1 to 2 % faster,
+  // 16384 rows 1 % slower (1622 -> 1643 us) on one and 1 to 3 % faster (1702 -> 1652) on others.
   long tiles = 0;
   for (int i = 0; i < n; ++i) tiles += (long)cdiv(tn[i].M, 256) * cdiv(tn[i].N, 256);
   return (tiles < 64 ? 1.0 : 0.93) * together;

@@ -33,7 +33,8 @@ def test_full_packs_share_no_launch_with_an_input_gradient():
 
 
 @pytest.mark.parametrize("cfg,T,ranges", [
-    (synth.vit_large(), 16384, (1, 1, 1, 1)), (synth.decoder_7b(), 8192, (1, 1, 1, 1)),
+    (synth.vit_large(), 16384, (1, 1, 1, 1)), (synth.decoder_7b(), 8192, (1, 1, 1, 1)), (synth.dit_block(), 16384, (1, 1, 8, 1)),
+    (synth.scaled(synth.vit_large(), hidden=512, n_q_heads=8, n_kv_heads=8, mlp_hidden=2048), 16384, (5, 5, 5, 5)),
     # past 16384 rows the QKV and output projection alone, or none; fewer than 1024 rows beside input gradients
     (synth.vit_large(), 20000, (0, 0, 4, 4)), (synth.decoder_8b_gqa(), 32768, (0, 0, 0, 0)), (synth.decoder_7b(), 777, (0, 0, 0, 0)),
     (synth.vit_tiny(), 40, (0, 0, 0, 0))])
