@@ -473,15 +473,16 @@ int split_cap(int layout, int M, int N, int K) {
 // 46 -> 40, 5477x4096x1024 51 -> 46, 777x22016x4096 161 -> 143, 8192x4608x1152 83 -> 76, 6352x6144x4096 244 -> 230, NN 1783x12288x3072 128 -> 110,
 // 8192x11008x4096 527 -> 516.  Of 260 products drawn from 384 to 16384 rows that it takes (operands out of the caches) four
 // are 3 % slower (NT 4509x12216x6160, 8527x9608x4456: ragged columns and a long contraction), the mean is 8 % faster.
-// Where 128x128 is the best of the four it competes only from four slices on and with columns that fill whole cache lines.  Below, a
-// second workgroup on the CU hides the output, which the model prices lower than it is: NN 1469x12288x128 12.7 -> 14.2, NT
-// 15816x1280x128 12.7 -> 14.1; 72 products of ragged columns took 6 % longer on average and up to 20 % (NT 2566x13424x200 34 -> 40,
-// NN 11265x4816x176 45 -> 55).  Beyond, 60 products took 14 % less to 5 % more (NT 2238x9216x400 29 -> 25, NN 13397x1280x296 20 -> 21).
+// Where 128x128 is the best of the four it competes only from six slices on and with columns that fill whole cache lines: below, a
+// second workgroup on the CU hides the output, which the model prices lower than it is.  72 products of ragged columns took 6 %
+// longer with two heights on average and up to 20 % (NT 2566x13424x200 34 -> 40, NN 11265x4816x176 45 -> 55); of 101 of four and five
+// slices 30 took 2 to 13 % longer (NT 8205x4096x224 31.4 -> 35.6), under four slices more did (NN 1469x12288x128 12.7 -> 14.2).  Of 99 of
+// six to nine slices five took up to 7 % longer, 94 up to 17 % less, 4 % on average (NT 2238x9216x400 29 -> 25).
 void mixed_rows(int layout, int M, int N, int K, Plan* best, double* best_t) {
   const TileKind &big = TILE_KINDS[0], &low = TILE_KINDS[1];
   const int tiles_n = cdiv(N, 256), slices = cdiv(K, BK);
   if (N < 256 || M < 256 + 128) return;
-  if (best->bm == 128 && best->bn == 128 && (slices < 4 || N % 64)) return;
+  if (best->bm == 128 && best->bn == 128 && (slices < 6 || N % 64)) return;
   const bool cut = K % BK;
   const double f = layout == GEMM_NT ? 1.0 : 1.05, fixed_cut = cut ? 1.0 : 0.0;
   const double t_big = slices * big.t_full * f + big.t_fixed + fixed_cut * big.t_cut;

@@ -48,13 +48,13 @@ def test_weight_gradient_cases():
 
 
 @pytest.mark.parametrize("layout,M,N,K", [(0, 3301, 5376, 64), (0, 2566, 13424, 200), (1, 4631, 11600, 176), (0, 5430, 3000, 304),
-                                          (1, 2186, 8552, 448), (1, 1469, 12288, 128)])
+                                          (1, 2186, 8552, 448), (1, 1469, 12288, 128), (0, 8205, 4096, 320)])
 def test_short_and_ragged_products_keep_the_smallest_tile(layout, M, N, K):
-    """Tiles of two heights give way to the 128x128 tile under four slices and where the columns end inside a cache line."""
+    """Tiles of two heights give way to the 128x128 tile under six slices and where the columns end inside a cache line."""
     assert bm.probe_gemm_plan(layout, M, N, K) == (128, 128, 1)
 
 
-@pytest.mark.parametrize("layout,M,N,K", [(0, 2238, 9216, 400), (1, 5376, 4096, 376), (1, 5615, 4096, 216), (0, 3301, 5376, 512)])
+@pytest.mark.parametrize("layout,M,N,K", [(0, 2238, 9216, 400), (1, 5376, 4096, 376), (0, 3301, 5376, 512)])
 def test_whole_lines_of_columns_take_two_heights(layout, M, N, K):
     assert bm.probe_gemm_plan(layout, M, N, K) == (384, 256, 1)
 
