@@ -48,7 +48,7 @@ def test_weight_gradient_cases():
 
 
 @pytest.mark.parametrize("layout,M,N,K", [(0, 3301, 5376, 64), (0, 2566, 13424, 200), (1, 4631, 11600, 176), (0, 5430, 3000, 304),
-                                          (1, 2186, 8552, 448), (1, 1469, 12288, 128), (0, 8205, 4096, 320)])
+                                          (1, 2186, 8552, 448), (1, 1469, 12288, 128), (0, 8205, 4096, 224), (1, 4429, 4096, 320)])
 def test_short_and_ragged_products_keep_the_smallest_tile(layout, M, N, K):
     """Tiles of two heights give way to the 128x128 tile under six slices and where the columns end inside a cache line."""
     assert bm.probe_gemm_plan(layout, M, N, K) == (128, 128, 1)
