@@ -427,8 +427,8 @@ bm_status gemm_generic_grouped(int layout, int dtype, int M, int N, int K, const
 }
 
 // GELU in the epilogue of 16x16 tiles with one k range, contiguous aligned rows: at these sizes a launch costs as much as a product
-// (fp32 block of 64 columns: 40 tokens 82 -> 76 us, 500 tokens 75 -> 69, 1000 tokens 90.5 -> 86; bf16 tiles of 128x128 gain nothing:
-// 300 to 1000 rows of 1024 columns within 0.5 %).
+// (fp32 block of 64 columns, two launches of 17 fewer: 70 -> 64 us of kernels at 40 tokens; a pass of 300 tokens 88 -> 84 us, 1000 tokens
+// 107 -> 102, 2000 tokens 141 -> 136; bf16 tiles of 128x128 gain nothing: 300 to 1000 rows of 1024 columns within 0.5 %).
 bool gemm_fuses_gelu(int layout, int dtype, int M, int N, int K) {
   return dtype == BM_DTYPE_FP32 && layout != GEMM_TN && generic_splits(M, N, K) == 1 && K % 4 == 0 &&
          choose_kernel(layout, M, N, K, 1, false, true) == 1;

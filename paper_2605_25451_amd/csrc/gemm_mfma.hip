@@ -471,13 +471,13 @@ int split_cap(int layout, int M, int N, int K) {
 // Rows on tiles of two heights: as many 256-row tiles as fill whole rounds (or all that the rows fill), the other rows on
 // 128-row tiles, which run beside the last of the former and behind them.  us against the best of the four tiles: NT 5477x3072x1024
 // 46 -> 40, 5477x4096x1024 51 -> 46, 777x22016x4096 161 -> 143, 8192x4608x1152 83 -> 76, 6352x6144x4096 244 -> 230, NN 1783x12288x3072 128 -> 110,
-// 8192x11008x4096 527 -> 516.  Of 260 products drawn from 384 to 16384 rows that it takes (operands out of the caches) four
-// are 3 % slower (NT 4509x12216x6160, 8527x9608x4456: ragged columns and a long contraction), the mean is 8 % faster.
+// 8192x11008x4096 527 -> 516.  Of 260 products of 384 to 16384 rows that it takes (operands out of the caches) five
+// are 2 to 3 % slower (NT 4509x12216x6160, 8527x9608x4456: ragged columns and a long contraction), the mean is 8 % faster.
 // Where 128x128 is the best of the four it competes only from six slices on and with columns that fill whole cache lines: below, a
-// second workgroup on the CU hides the output, which the model prices lower than it is.  72 products of ragged columns took 6 %
-// longer with two heights on average and up to 20 % (NT 2566x13424x200 34 -> 40, NN 11265x4816x176 45 -> 55); of 101 of four and five
-// slices 30 took 2 to 13 % longer (NT 8205x4096x224 31.4 -> 35.6), under four slices more did (NN 1469x12288x128 12.7 -> 14.2).  Of 99 of
-// six to nine slices five took up to 7 % longer, 94 up to 17 % less, 4 % on average (NT 2238x9216x400 29 -> 25).
+// second workgroup on the CU hides the output, which the model prices lower than it is.  71 products of ragged columns took 6 %
+// longer with two heights on average and up to 23 % (NT 2566x13424x200 34 -> 40, NN 11265x4816x176 45 -> 55); of 127 of four and five
+// slices 34 took 2 to 13 % longer (NT 8205x4096x224 31.4 -> 35.6), of 16 shorter ones twelve (NN 1469x12288x128 12.7 -> 14.2).  Of 135
+// from six slices on seven took 2 to 7 % longer, the mean is 4 % faster (NT 2238x9216x400 29 -> 25).
 void mixed_rows(int layout, int M, int N, int K, Plan* best, double* best_t) {
   const TileKind &big = TILE_KINDS[0], &low = TILE_KINDS[1];
   const int tiles_n = cdiv(N, 256), slices = cdiv(K, BK);
