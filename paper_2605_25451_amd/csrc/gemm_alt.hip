@@ -326,8 +326,8 @@ __device__ __forceinline__ void alt256_tile(const GemmParams& p, const TileJob& 
 // SOURCE: 1 or 2 where the k rows of A or B are read from their source rows (whole slices only).  The table of source rows costs a tile
 // about a microsecond in front of its first loads and four LDS reads a slice; a sorted copy costs its own pass and 268 MB to
 // be read back (65536 rows of 2048): up 1536x2048 with the pass 870 -> 755 us, down 2048x768 500 -> 405.
-// The rows that fill up a group stand at its end and read a row of a token: they are zeroed in the fragments, or an infinity of that
-// token would meet their zeros as a NaN.
+// The contraction ends at the last routed row: the rows that fill up a group read a row of a token, and an infinity of that token
+// would meet their zeros as a NaN (8192 tokens, 128 experts: 4268 us a pass with those rows masked in whole blocks, 4231 without them).
 template <int EPI, bool CUT, int SOURCE = 0>
 __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJob& job) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -337,8 +337,9 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 2, wn = wave & 3;                                   // wm is the group
   if (job.kbeg >= job.kend) return;
-  const int m0 = job.m0, n0 = job.n0, n = (job.kend - job.kbeg + BK - 1) / BK;
-  const int k_left = job.kend - job.kbeg - (n - 1) * BK;                     // of the last slice
+  const int m0 = job.m0, n0 = job.n0;
+  int n = (job.kend - job.kbeg + BK - 1) / BK;
+  int k_left = job.kend - job.kbeg - (n - 1) * BK;                           // of the last slice
 
   Reg ra, rb;
   ra.init(p.lda, 0, p.M - m0, wave, lane);
@@ -406,14 +407,13 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
 #pragma unroll
     for (int q = 0; q < 4; ++q) af[4 + q] = fa.read(smem, q, KS, buf + 128 * 2);
   };
-  auto cut = [&](int ks, int left) {
-    const u32x4 mask = cut_mask(ks, left, lane);
+  auto cut = [&](int ks) {
+    const u32x4 mask = cut_mask(ks, k_left, lane);
 #pragma unroll
     for (int q = 0; q < 4; ++q) cut_fragment(bf[q], mask);
 #pragma unroll
     for (int q = 0; q < 8; ++q) cut_fragment(af[q], mask);
   };
-  int routed = 0;                                           // SOURCE: k rows of the tile before those that fill up its group
   // COME: slices that follow this one (2: two or more, 0: this is the last).  A wait names the half slice that is read
   // next: everything older than the two halves requested since must have landed.
   auto slice = [&](auto come_t, int j) {
@@ -423,9 +423,7 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
     if (COME >= 1) load_half(Int<1>{}, j + 1, buf ^ BUF);
     if (COME >= 2) fetch_rows(Int<0>{}, j + 2);
     wait_fragments();
-    const int left = SOURCE ? routed - j * BK : k_left;     // (a group is filled up by less than two slices)
-    const bool ends = SOURCE ? COME <= 1 && left < BK : CUT && COME == 0 && k_left < BK;
-    if (ends) cut(0, left);
+    if ((CUT || SOURCE) && COME == 0 && k_left < BK) cut(0);
     wait_loads<COME >= 1 ? 2 * HL : 0>();
     end_phase();
     multiply();
@@ -434,7 +432,7 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
     read(Int<1>{}, buf);
     if (COME >= 2) { load_half(Int<0>{}, j + 2, buf); fetch_rows(Int<1>{}, j + 2); }
     wait_fragments();
-    if (ends) cut(1, left);
+    if ((CUT || SOURCE) && COME == 0 && k_left < BK) cut(1);
     if (COME == 0) { end_phase(); return; }                 // the last MFMAs belong to the epilogue
     wait_loads<COME >= 2 ? 2 * HL : HL>();
     end_phase();
@@ -447,10 +445,13 @@ __device__ __forceinline__ void alt256_tn_tile(const GemmParams& p, const TileJo
     if constexpr (SOURCE == 2) { load_a(Int<0>{}, 0, 0); load_a(Int<1>{}, 0, 0); }
     else { load_b(Int<0>{}, 0, 0); load_b(Int<1>{}, 0, 0); }
     for (int i = threadIdx.x; i < n * BK; i += THREADS) rows[i] = source_row(p.source + job.kbeg, i, p.src_rows);
-    routed = n * BK - MOE_PAD;
+    int routed = n * BK - MOE_PAD;
 #pragma unroll
     for (int i = 0; i < MOE_PAD; i += WAVE)
       routed += __popcll(__ballot((uint32_t)p.source[job.kend - MOE_PAD + i + lane] < (uint32_t)p.src_rows));
+    routed = __builtin_amdgcn_readfirstlane(max(routed, 1));
+    n = (routed + BK - 1) / BK;
+    k_left = routed - (n - 1) * BK;
     __syncthreads();
     fetch_rows(Int<0>{}, 0);
     fetch_rows(Int<1>{}, 0);

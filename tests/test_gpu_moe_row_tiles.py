@@ -13,6 +13,8 @@ pytestmark = pytest.mark.gpu
                                         (1, 1, [300, 340], 136), (3, 2, [333, 167], 256), (4, 1, [260, 380], 264),
                                         # the most rows whose tokens a weight gradient looks up itself, and one pack that is sorted first
                                         (1, 1, [512] * 16, 256), (2, 1, [500] * 16 + [193], 256),
+                                        # a weight gradient of one slice, whole and not
+                                        (1, 1, [64], 256), (4, 1, [40, 23], 256),
                                         # more than 8 column tiles: four row tiles side by side
                                         (3, 2, [333, 467], 1288)],
                          ids=lambda v: str(v) if isinstance(v, int) else "%d_rows" % sum(v))
